@@ -1,47 +1,15 @@
-// Grouped dense layer for jobs that bring many rows (M >= 128, or more than 64
-// when the round holds enough of them to give every CU a tile): the
-// compute-bound counterpart of the weight-streaming kernel.  Same contract (one
-// launch runs one layer of every scheduled job, Salus paper, Section 3.3), but
-// here a weight is used by 128 or 256 rows per workgroup, so operands are staged
-// through LDS.
-//
-// Workgroup tile BM x 256 (BM = 256 for jobs from 192 rows, else 128), k-slab 64,
-// eight wavefronts (4 x 2 of 64 x 128, or 2 x 4 of 64 x 64), v_mfma_f32_32x32x16_bf16.
-//   HBM -> registers : 16-byte loads, issued two slabs ahead of the multiply
-//   registers -> LDS : X rows as they are; W blocks of 4 k x 8 n are transposed in
-//                      registers first, so that both operands sit in LDS as
-//                      [row or column][64 k-values] = 128 bytes per line
-//   LDS -> registers : one ds_read_b128 per 32x16 operand fragment
-// LDS holds two slabs: the slab after the one being multiplied is written while
-// it is multiplied - a quarter of the writes after each quarter of the MFMAs, so
-// that they issue while the matrix pipe works through its queue - and the one
-// after that is on its way from memory; one barrier per slab.  One workgroup
-// fills a CU (registers at BM = 256, LDS at BM = 128), so this overlap has to
-// come from inside it.  Per multiply-add the 256-row tile moves a third less
-// through L2 than the 128-row one ((256 + 256) / (256 * 256) against
-// (128 + 256) / (128 * 256) operand bytes).
-// The 16-byte slot of k-chunk c in line r is c ^ swz(r), swz(r) = (r ^ r/8) % 8.
-// Fragment reads touch 32 consecutive lines at one k-chunk, the transposed W
-// writes touch lines 8 apart at one k-chunk, X writes fill whole lines: with
-// this swizzle each of them spreads every 8 lanes that the LDS serves together
-// over all 8 slots of the 128-byte bank row (measured: no bank conflicts).
+// Grouped dense layer for jobs that bring many rows: the compute-bound counterpart of the weight-streaming
+// kernels.  Same contract (one launch runs one layer of every scheduled job, Salus paper, Section 3.3), but
+// here a weight is used by 128 or 256 rows per workgroup, so operands go through LDS (tile_mfma.hpp).
 #include <algorithm>
 #include <vector>
 
-#include "group.hpp"
+#include "tile_mfma.hpp"
 
 namespace salus {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kBM = 128, kBN = 256, kBK = 64;
-constexpr int kLine = kBK * 2;                 // bytes per LDS line
-
-__device__ inline uint32_t swz(uint32_t line) { return (line ^ (line >> 3)) & 7u; }
-
-// Tiles of one job in bands of 8 row tiles, column tiles inside a band: the 64
-// tiles an XCD runs at a time then share 8 slabs of X and 8 slabs of W in its L2.
+// Tiles of one job in bands of 8 row tiles, column tiles inside a band: the tiles
+// an XCD runs at a time then share 8 slabs of X and 4 - 8 slabs of W in its L2.
 template <int BM, int BN>
 __device__ inline Tile find_tile_banded(const GroupArgs &a, uint32_t tile_id)
 {
@@ -62,306 +30,163 @@ __device__ inline Tile find_tile_banded(const GroupArgs &a, uint32_t tile_id)
     const uint32_t rows = min(8u, rt - band * 8u);
     Tile tile;
     tile.problem = __builtin_amdgcn_readfirstlane(g);
-    tile.m0 = (band * 8u + local % rows) * BM;
-    tile.n0 = (local / rows) * BN;
+    tile.m0 = __builtin_amdgcn_readfirstlane((band * 8u + local % rows) * BM);
+    tile.n0 = __builtin_amdgcn_readfirstlane((local / rows) * BN);
     return tile;
 }
 
-template <int ACT, int FM, int FN>
-__device__ inline void store_tile(const f32x16 (&acc)[FM][FN], const Problem &p, const Tile &tile,
-                                  uint32_t wm, uint32_t wn, uint32_t fl, uint32_t fh)
+// A wavefront's accumulators, whose first element is (m, n) of Y, to memory.  N is a multiple of 8, so a vector of 8
+// (bf16) or 4 (float) columns lies wholly inside or outside.
+template <int ACT, bool BF16, int FN, int FM, typename Landed>
+__device__ inline void store_dense(const Problem &p, uint32_t m, uint32_t n, const f32x16 (&acc)[FN][FM], int lane, Landed landed)
 {
-    const uint32_t M = p.M, N = p.N;
-    const bool out_bf16 = (p.flags & kOutBf16) != 0, mask = (p.flags & kMaskPositive) != 0;
+    constexpr int J = BF16 ? 2 : 1;              // blocks of a line
+    const uint32_t N = p.N, esz = BF16 ? 2 : 4, pitch = N * esz;
+    const uint32_t column = BF16 ? line_column_bf16(lane) : line_column_f32(lane);
+    char *Y = (char *)p.Y + ((uint64_t)m * N + n) * esz;
+    const char *aux = (const char *)p.aux + ((uint64_t)m * N + n) * 2;
+    const bool mask = BF16 && (p.flags & kMaskPositive);
+    const uint32_t rows = m < p.M ? p.M - m : 0, cols = n < N ? N - n : 0;
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-        const uint32_t col = tile.n0 + wn * (32u * FN) + 32u * j + fl;
-        if (col >= N) continue;
+    for (int i = 0; i < FM; ++i) {
 #pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            const uint32_t row0 = tile.m0 + wm * (32u * FM) + 32u * i + 4u * fh;
-            float v[16];
+        for (int j = 0; j < FN; j += J) {
+            __builtin_amdgcn_sched_barrier(0);       // one line at a time: the accumulators leave few registers
+            float v[J][16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float z = acc[i][j][r];
-                v[r] = ACT == 1 ? fmaxf(z, 0.0f) : ACT == 2 ? gelu_fast(z) : z;
-            }
-            if (mask) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const uint32_t row = row0 + 8u * (r >> 2) + (r & 3);
-                    if (row >= M) continue;
-                    const uint32_t bits = ((const uint16_t *)p.aux)[(size_t)row * N + col];
-                    if ((bits & 0x8000u) || !(bits & 0x7fffu)) v[r] = 0.0f;
-                }
-            }
-            if (out_bf16) {
+            for (int jj = 0; jj < J; ++jj)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const uint32_t row = row0 + 8u * (r >> 2) + (r & 3);
-                    if (row < M) ((uint16_t *)p.Y)[(size_t)row * N + col] = (uint16_t)bf16_bits(v[r]);
+                    const float z = acc[j + jj][i][r];
+                    v[jj][r] = ACT == 1 ? fmaxf(z, 0.0f) : ACT == 2 ? gelu_fast(z) : z;
                 }
+            __builtin_amdgcn_sched_barrier(0);
+            if (i == 0 && j == 0) landed();
+            const uint32_t c = 32u * j + column;
+            if constexpr (BF16) {
+                u32x4 o[2][2];
+                to_lines_bf16(v, o);
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        const uint32_t r_at = 32u * i + 16u * a + 8u * b + (lane & 7);
+                        if (!(r_at < rows && c < cols)) continue;
+                        const uint32_t at = r_at * pitch + c * 2u;
+                        u32x4 w = o[a][b];
+                        if (mask) {
+                            // ReLU derivative taken from the stored bf16 activation (sign bit clear, not zero)
+                            const u32x4 h = *(const u32x4 *)(aux + at);
+#pragma unroll
+                            for (int d = 0; d < 4; ++d) {
+                                const uint32_t lo = h[d] & 0xffffu, hi = h[d] >> 16;
+                                if ((lo & 0x8000u) || !lo) w[d] &= 0xffff0000u;
+                                if ((hi & 0x8000u) || !hi) w[d] &= 0x0000ffffu;
+                            }
+                        }
+                        *(u32x4 *)(Y + at) = w;
+                    }
             } else {
+                f32x4 o[2][2];
+                to_lines_f32(v[0], o);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const uint32_t row = row0 + 8u * (r >> 2) + (r & 3);
-                    if (row < M) ((float *)p.Y)[(size_t)row * N + col] = v[r];
-                }
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        const uint32_t r_at = 32u * i + 16u * a + 8u * b + (lane & 7);
+                        if (r_at < rows && c < cols) *(f32x4 *)(Y + (r_at * pitch + c * 4u)) = o[a][b];
+                    }
             }
         }
     }
 }
 
-// Epilogue of a tile that lies wholly inside its matrix (and whose matrix is
-// below 4 GiB): no bounds tests, 32-bit byte offsets from the uniform base
-// pointer, activation and output type fixed at compile time.  This is the
-// common case; the general routine above costs about twice the instructions.
-template <int ACT, bool BF16, int FM, int FN>
-__device__ inline void store_tile_full(const f32x16 (&acc)[FM][FN], const Problem &p, const Tile &tile,
-                                       uint32_t wm, uint32_t wn, uint32_t fl, uint32_t fh)
-{
-    constexpr uint32_t esz = BF16 ? 2u : 4u;
-    const uint32_t row_bytes = p.N * esz;
-    char *Y = (char *)p.Y;
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            const uint32_t row0 = tile.m0 + wm * (32u * FM) + 32u * i + 4u * fh;
-            const uint32_t col = tile.n0 + wn * (32u * FN) + 32u * j + fl;
-            const uint32_t off0 = row0 * row_bytes + col * esz;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float z = acc[i][j][r];
-                const float v = ACT == 1 ? fmaxf(z, 0.0f) : ACT == 2 ? gelu_fast(z) : z;
-                const uint32_t off = off0 + (8u * (r >> 2) + (r & 3)) * row_bytes;
-                if (BF16) *(uint16_t *)(Y + off) = (uint16_t)bf16_bits(v);
-                else *(float *)(Y + off) = v;
-            }
-        }
+// Y = act(X . W) (TW: Y = X . W^T, W stored N x K, masked by the ReLU derivative)
+template <int BM, int BN, bool TW>
+struct DenseWalk {
+    const GroupArgs &a;
+    struct Place { int problem; uint32_t m0, n0, depth; };
+    __device__ uint32_t tiles() const { return a.tiles; }
+    __device__ Place place(uint32_t id) const
+    {
+        const Tile t = find_tile_banded<BM, BN>(a, id);
+        return {t.problem, t.m0, t.n0, a.p[t.problem].K};
     }
-}
-
-// Requires K % 64 == 0 and N % 8 == 0 (the launcher routes other shapes to the
-// streaming kernel).  Rows >= M and columns >= N are loaded from clamped
-// addresses and never stored.  A thread owns BM / 64 16-byte k-chunks of X (rows
-// 64 apart) and a block of 4 k x 8 columns of W, which it transposes into eight
-// 8-byte half-chunks.
-constexpr int kBM2 = 256, kThreads2 = 512;
-
-// BM2 = 256: wavefronts 4 x 2, each 64 x 128.  BM2 = 128: 2 x 4, each 64 x 64.
-// The grid is one workgroup per CU; workgroup b runs tiles b, b + grid, ... and
-// requests the first slab of its next tile before the epilogue of the current
-// one, so that neither that latency nor a workgroup launch sits between tiles.
-template <int BM2>
-__global__ __launch_bounds__(kThreads2) void grouped_dense_bf16_tiled(GroupArgs a)
-{
-    constexpr uint32_t kStageBytes = (BM2 + kBN) * kLine;      // 64 KB or 48 KB
-    constexpr int WN = BM2 == 256 ? 2 : 4, FN = kBN / (32 * WN), XR = BM2 / 64;
-    __shared__ __attribute__((aligned(128))) unsigned char smem[2 * kStageBytes];
-    const uint32_t t = threadIdx.x, lane = t & 63u;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const uint32_t wm = wave / WN, wn = wave % WN;
-
-    // X: k-chunk ca of rows ra, ra+64, ... (lines 64 apart share their swizzle)
-    const uint32_t ca = t & 7u, ra = t >> 3;
-    const uint32_t xoff = ra * kLine + ((ca ^ swz(ra)) << 4);
-    // W: rows 4*kq .. 4*kq+3 of the slab, columns 8*nb .. 8*nb+7
-    const uint32_t kq = (lane >> 3) + 8u * (wave >> 2), nb = (lane & 7u) + 8u * (wave & 3u);
-    uint32_t woff[8];      // byte offset of this thread's half-chunk in column line 8*nb + i
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const uint32_t line = 8u * nb + i;
-        woff[i] = (BM2 + line) * kLine + (((kq >> 1) ^ swz(line)) << 4) + 8u * (kq & 1u);
+    __device__ Operand m(const Place &at) const
+    {
+        const Problem &p = a.p[at.problem];
+        return {p.X, p.K, p.M, p.K * 2u, false};
     }
-
-    struct Source {           // where this thread's part of a tile's operands comes from
-        Tile tile;
-        const uint16_t *x[XR];
-        const uint16_t *w;
-        uint32_t wpitch;
-    };
-    auto locate = [&](uint32_t id) {
-        Source src;
-        src.tile = find_tile_banded<BM2, kBN>(a, id);
-        const Problem &p = a.p[src.tile.problem];
-        const uint32_t M = p.M, K = p.K, N = p.N;
-        const uint16_t *W = (const uint16_t *)p.W;
-        const uint16_t *X = (const uint16_t *)p.X;
-#pragma unroll
-        for (int i = 0; i < XR; ++i) {
-            const uint32_t row = src.tile.m0 + ra + 64u * i;
-            src.x[i] = X + (size_t)(row < M ? row : M - 1) * K + 8u * ca;
-        }
-        const uint32_t ncol = src.tile.n0 + 8u * nb, ncol_c = ncol < N ? ncol : 0u;
+    __device__ Operand n(const Place &at) const
+    {
+        const Problem &p = a.p[at.problem];
+        if (TW) return {p.W, p.K, p.N, p.K * 2u, false};
         const bool strip = (p.flags & kStripW) != 0;
-        src.wpitch = strip ? 128u : N;
-        src.w = strip ? W + (size_t)(ncol_c & ~127u) * K + (4u * kq) * 128u + (ncol_c & 127u)
-                      : W + (size_t)(4u * kq) * N + ncol_c;
-        return src;
-    };
-
-    u32x4 xr[XR], wr[4];
-    auto load_slab = [&](const Source &src, uint32_t k0) {
-#pragma unroll
-        for (int i = 0; i < XR; ++i) xr[i] = *(const u32x4 *)(src.x[i] + k0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) wr[r] = *(const u32x4 *)(src.w + (size_t)(k0 + r) * src.wpitch);
-    };
-    auto store_x = [&](uint32_t stage) {
-        unsigned char *base = smem + stage;
-#pragma unroll
-        for (int i = 0; i < XR; ++i) *(u32x4 *)(base + xoff + 64 * i * kLine) = xr[i];
-    };
-    auto store_w = [&](uint32_t stage, int first) {      // columns first .. first+3 of the block
-        unsigned char *base = smem + stage;
-#pragma unroll
-        for (int i = first; i < first + 4; ++i) {
-            u32x2 b;       // column i of the block: dword j = (k 2j, k 2j+1)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                b[j] = __builtin_amdgcn_perm(wr[2 * j + 1][i >> 1], wr[2 * j][i >> 1],
-                                             (i & 1) ? 0x07060302u : 0x05040100u);
-            *(u32x2 *)(base + woff[i]) = b;
-        }
-    };
-
-    const uint32_t fl = lane & 31u, fh = lane >> 5, fs = swz(fl);
-    const uint32_t afrag = (wm * 64u + fl) * kLine;
-    const uint32_t bfrag = (BM2 + wn * (32u * FN) + fl) * kLine;
-
-    f32x16 acc[2][FN];
-    auto multiply = [&](const unsigned char *base, uint32_t ks) {
-        const uint32_t off = ((2u * ks + fh) ^ fs) << 4, off_odd = off ^ 64u;
-        bf16x8 av[2], bv[FN];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) av[i] = *(const bf16x8 *)(base + afrag + 32 * i * kLine + (i & 1 ? off_odd : off));
-#pragma unroll
-        for (int j = 0; j < FN; ++j) bv[j] = *(const bf16x8 *)(base + bfrag + 32 * j * kLine + (j & 1 ? off_odd : off));
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
-    };
-
-    const uint32_t tiles = a.tiles;
-    uint32_t id = blockIdx.x;
-    Source src = locate(id);
-    load_slab(src, 0);
-    for (;;) {
-        const Problem &p = a.p[src.tile.problem];
-        const uint32_t M = p.M, N = p.N, slabs = p.K / kBK;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-        // Slab s is multiplied out of one half of LDS while slab s+1 (already in
-        // registers) is written to the other half, a piece after each quarter of the
-        // multiplies so that the writes issue while the matrix pipe works through
-        // its queue, and slab s+2 is requested from memory.  The last slab has
-        // nothing to stage; the load past the end re-reads the last slab instead of
-        // branching.
-        uint32_t stage = 0;
-        __syncthreads();                     // the previous tile's last slab has been read
-        store_x(0);
-        store_w(0, 0);
-        store_w(0, 4);
-        load_slab(src, slabs > 1 ? kBK : 0);
-        __syncthreads();
-        for (uint32_t s = 0; s + 1 < slabs; ++s) {
-            const unsigned char *base = smem + stage;
-            const uint32_t other = stage ^ kStageBytes;      // everyone left it at the last barrier
-            multiply(base, 0);
-            store_x(other);
-            multiply(base, 1);
-            store_w(other, 0);
-            multiply(base, 2);
-            store_w(other, 4);
-            multiply(base, 3);
-            load_slab(src, (s + 2 < slabs ? s + 2 : slabs - 1) * kBK);
-            __syncthreads();
-            stage = other;
-        }
-        {
-            const unsigned char *base = smem + stage;
-#pragma unroll
-            for (uint32_t ks = 0; ks < 4; ++ks) multiply(base, ks);
-        }
-
-        // the next tile's first slab travels while this tile's epilogue runs
-        const Tile tile = src.tile;
-        const uint32_t next = id + gridDim.x;
-        const bool more = next < tiles;
-        if (more) {
-            src = locate(next);
-            load_slab(src, 0);
-        }
-
-        const uint32_t act = p.flags & 0xffu;
-        const bool full = tile.m0 + BM2 <= M && tile.n0 + kBN <= N && (uint64_t)M * N < (1ull << 30) &&
-                          !(p.flags & kMaskPositive);
-        if (full && (p.flags & kOutBf16)) {
-            if (act == 1) store_tile_full<1, true, 2, FN>(acc, p, tile, wm, wn, fl, fh);
-            else if (act == 2) store_tile_full<2, true, 2, FN>(acc, p, tile, wm, wn, fl, fh);
-            else store_tile_full<0, true, 2, FN>(acc, p, tile, wm, wn, fl, fh);
-        } else if (full) {
-            if (act == 1) store_tile_full<1, false, 2, FN>(acc, p, tile, wm, wn, fl, fh);
-            else if (act == 2) store_tile_full<2, false, 2, FN>(acc, p, tile, wm, wn, fl, fh);
-            else store_tile_full<0, false, 2, FN>(acc, p, tile, wm, wn, fl, fh);
-        } else if (act == 1) store_tile<1, 2, FN>(acc, p, tile, wm, wn, fl, fh);
-        else if (act == 2) store_tile<2, 2, FN>(acc, p, tile, wm, wn, fl, fh);
-        else store_tile<0, 2, FN>(acc, p, tile, wm, wn, fl, fh);
-        if (!more) break;
-        id = next;
+        return {p.W, p.K, p.N, strip ? 256u : p.N * 2u, strip};
     }
-}
+    template <int FN, int FM, typename Landed>
+    __device__ void finish(const Place &at, const f32x16 (&acc)[FN][FM], uint32_t m, uint32_t n, int lane, Landed landed) const
+    {
+        const Problem &p = a.p[at.problem];
+        const uint32_t act = p.flags & 0xffu;
+        m += at.m0;
+        n += at.n0;
+        if (p.flags & kOutBf16) {
+            if (act == 1) store_dense<1, true>(p, m, n, acc, lane, landed);
+            else if (act == 2) store_dense<2, true>(p, m, n, acc, lane, landed);
+            else store_dense<0, true>(p, m, n, acc, lane, landed);
+        } else {
+            if (act == 1) store_dense<1, false>(p, m, n, acc, lane, landed);
+            else if (act == 2) store_dense<2, false>(p, m, n, acc, lane, landed);
+            else store_dense<0, false>(p, m, n, acc, lane, landed);
+        }
+    }
+};
 
-bool tiled_shape_ok(const Problem &p) { return p.K != 0 && p.K % kBK == 0 && p.N % 8 == 0; }
-
-uint64_t tiled_tiles(const Problem &p)
+// The workgroups are resident (one per compute unit, two of the 128 x 128 tile): workgroup b runs tiles b, b + grid, ...
+// Bound: the power limit.  16 jobs x 4096 rows, 4096 -> 1024: 489 us (1.12 PFLOP/s; 529 us with operands staged through
+// registers and transposed on the way into LDS), matrix pipes busy 65 % of the cycles at the 1.66 GHz that the chip then
+// holds, no bank conflicts; with every request answered from L2 it takes 450 us.  1024 -> 4096 -> 1024 -> 1024 with GELU:
+// 1263 us (1421).
+template <int BM, int BN, int WM, int WN, bool TW>
+__global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled(GroupArgs a)
 {
-    return (uint64_t)((p.M + kBM - 1) / kBM) * ((p.N + kBN - 1) / kBN);
+    using T = TileMfma<BM, BN, WM, WN, false, !TW>;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
+    const DenseWalk<BM, BN, TW> walk{a};
+    T::run(walk, smem);
 }
 
-// Jobs of at least this many rows take the 256-row tile (at most a quarter of
-// their last row tile is padding); smaller ones the 128-row tile.
+// Jobs of at least this many rows (at most a quarter of the last of their 256-row tiles is padding) may take any of the
+// tiles; smaller ones take 128-row tiles in a launch of their own.
 constexpr uint32_t kTiled256MinM = 192;
 
-static uint32_t resident_grid()
+// A depth that is no multiple of a slab costs the padding of its last slab and, below three slabs, whole slabs of zeros: such
+// layers come here only from 192 rows and 192 deep (3 jobs x 300 - 700 rows, 520 -> 1000 -> 776: 54 us for the two layers).
+bool tiled_shape_ok(const Problem &p)
 {
-    static uint32_t cached = 0;
-    if (cached) return cached;
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
-        cus = 256;
-    cached = (uint32_t)cus & ~7u;
-    return cached;
+    const bool whole = p.K % kSlab == 0 || (p.M >= kTiled256MinM && p.K >= kMinSlabs * kSlab);
+    return p.K != 0 && whole && p.K % 8 == 0 && p.N % 8 == 0 && p.K < kTiledMaxWidth && p.N < kTiledMaxWidth;
 }
 
-template <int BM, typename Kernel>
-static hipError_t launch_tiled(Kernel kernel, int threads, const std::vector<Problem> &p, hipStream_t stream,
-                               uint64_t *launches)
+uint64_t tiled_tiles(const Problem &p) { return (uint64_t)((p.M + 127) / 128) * ((p.N + 255) / 256); }
+
+template <int BM, int BN, int PER_CU, typename Kernel>
+static hipError_t launch_tiled(Kernel kernel, int threads, const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
 {
-    const uint32_t n = (uint32_t)p.size();
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         GroupArgs a{};
         a.n = std::min(kMaxProblems, n - at);
         uint64_t tiles = 0;
         for (uint32_t i = 0; i < a.n; ++i) {
             a.p[i] = p[at + i];
-            tiles += (uint64_t)((a.p[i].M + BM - 1) / BM) * ((a.p[i].N + kBN - 1) / kBN);
+            tiles += (uint64_t)((a.p[i].M + BM - 1) / BM) * ((a.p[i].N + BN - 1) / BN);
         }
         if (tiles == 0) continue;
         if (tiles > 0x7fffffffull) return hipErrorInvalidValue;
         a.tiles = (uint32_t)tiles;
-        // one workgroup per CU (it fills the CU); a multiple of 8 so that the
-        // workgroups of an XCD keep to that XCD's range of tiles
-        const uint32_t grid = (uint32_t)std::min<uint64_t>(tiles, resident_grid());
+        // resident workgroups; a multiple of 8 so that the workgroups of an XCD keep to that XCD's range of tiles
+        const uint32_t grid = (uint32_t)std::min<uint64_t>(tiles, resident_grid() * PER_CU);
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, a);
         if (launches) *launches += 1;
         hipError_t e = hipGetLastError();
@@ -371,7 +196,7 @@ static hipError_t launch_tiled(Kernel kernel, int threads, const std::vector<Pro
 }
 
 // ---------------------------------------------------------------------------
-// Calibration: the multiply of grouped_dense_bf16_tiled<256> without its memory
+// Calibration: the multiply of a 256 x 256 tile without its memory
 // traffic.  One workgroup of eight wavefronts per CU runs `slabs` times the 32
 // MFMAs per wavefront of a 256 x 256 x 64 slab, either on fragments read once
 // (lds == 0: what the matrix pipes sustain) or on fragments read from LDS for
@@ -381,6 +206,10 @@ static hipError_t launch_tiled(Kernel kernel, int threads, const std::vector<Pro
 // what the multipliers toggle.  Wavefront 0 of workgroup 0 reports the shader
 // clocks and the 100 MHz ticks its loop took, so the clock under this load can
 // be read off: out[0] = s_memtime difference, out[1] = wall-clock difference.
+constexpr int kThreads2 = 512, kBK = 64, kBN = 256;
+constexpr int kLine = kBK * 2;                 // bytes per LDS line
+__device__ inline uint32_t swz(uint32_t line) { return (line ^ (line >> 3)) & 7u; }
+
 template <bool LDS>
 __global__ __launch_bounds__(kThreads2) void mfma_rate(uint64_t *out, uint32_t slabs)
 {
@@ -452,16 +281,47 @@ hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStre
     return hipGetLastError();
 }
 
+// Which tile a launch takes.  The grid walks its tiles in rounds of one (or two) per compute unit, so what counts is
+// rounds x time of a round; a large tile moves fewer operand bytes per multiply but leaves the last round emptier
+// and pads more.  Times of a round in nanoseconds, a slab and the rest (prologue and epilogue), fitted to launches of
+// 16 jobs x 4096 rows, 4096 -> 1024 and 1024 -> 1024 (measured 489 / 163 us with 256 x 256 tiles, 545 / 186 with 128 x
+// 256, 626 / 206 with 128 x 128); with at most one 128 x 128 tile per compute unit a slab takes half as long.  What the
+// rule is for: 4 jobs x 500 rows, 2048 -> 2048: 50 / 33 / 26 us; 32 jobs x 300 - 1000 rows, 4096 -> 1024: 212 / 205 /
+// 235, 1024 -> 4096: 237 / 254 / 277.
+struct TileKind { uint32_t bm, bn, per_cu, slab_ns, rest_ns; };
+constexpr TileKind kTile256 = {256, 256, 1, 1640, 12000}, kTile128x256 = {128, 256, 1, 935, 8000}, kTile128 = {128, 128, 2, 1090, 8000};
+
+static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n)
+{
+    uint64_t tiles = 0, work = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        const uint64_t count = (uint64_t)((p[i].M + t.bm - 1) / t.bm) * ((p[i].N + t.bn - 1) / t.bn);
+        tiles += count;
+        work += count * (((uint64_t)p[i].K + kSlab - 1) / kSlab * t.slab_ns + t.rest_ns);
+    }
+    if (tiles == 0) return 0;
+    const uint64_t cus = resident_grid(), rounds = (tiles + cus * t.per_cu - 1) / (cus * t.per_cu);
+    return rounds * (work / tiles) / (t.per_cu == 2 && tiles <= cus ? 2 : 1);
+}
+
 hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
 {
-    std::vector<Problem> big, small;
-    for (uint32_t i = 0; i < n; ++i) {
+    for (uint32_t i = 0; i < n; ++i)
         if (!tiled_shape_ok(p[i])) return hipErrorInvalidValue;
-        (p[i].M >= kTiled256MinM ? big : small).push_back(p[i]);
+    std::vector<Problem> big, small;
+    for (uint32_t i = 0; i < n; ++i) (p[i].M >= kTiled256MinM ? big : small).push_back(p[i]);
+    for (const std::vector<Problem> *group : {&big, &small}) {
+        const Problem *q = group->data();
+        const uint32_t count = (uint32_t)group->size();
+        if (count == 0) continue;
+        const uint64_t t0 = group == &big ? launch_ns(kTile256, q, count) : ~0ull;
+        const uint64_t t1 = launch_ns(kTile128x256, q, count), t2 = launch_ns(kTile128, q, count);
+        const hipError_t e = t0 <= t1 && t0 <= t2 ? launch_tiled<256, 256, 1>(grouped_dense_bf16_tiled<256, 256, 2, 4, false>, 512, q, count, stream, launches)
+                             : t1 <= t2           ? launch_tiled<128, 256, 1>(grouped_dense_bf16_tiled<128, 256, 2, 4, false>, 512, q, count, stream, launches)
+                                                  : launch_tiled<128, 128, 2>(grouped_dense_bf16_tiled<128, 128, 2, 2, false>, 256, q, count, stream, launches);
+        if (e != hipSuccess) return e;
     }
-    hipError_t e = launch_tiled<kBM2>(grouped_dense_bf16_tiled<kBM2>, kThreads2, big, stream, launches);
-    if (e != hipSuccess) return e;
-    return launch_tiled<kBM>(grouped_dense_bf16_tiled<kBM>, kThreads2, small, stream, launches);
+    return hipSuccess;
 }
 
 }  // namespace salus

@@ -1,0 +1,53 @@
+"""GPU parity of the LDS-tiled kernels at the edges of their tiles, slabs and dispatch rule, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import dense
+from paper_1902_04610_amd import salus, synth
+from gpu_util import DevicePool, mlp_layout, norm_rel_err
+from test_gpu_kernels import GELU, NONE, RELU, TOL_BF16_TIGHT, run_jobs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("jobs, M, K, N, strip", [
+    (20, 250, 200, 4104, False),      # 340 tiles of 256 x 256: workgroups walk two, the request stream crosses tile ends
+    (16, 193, 256, 4096, True),       # as many tiles as compute units
+    (8, 257, 264, 4096, False),       # 128 x 256
+    (33, 128, 64, 2176, True),        # 128 x 256 / 128 x 128, one slab of data in three
+    (1, 192, 192, 8, False), (1, 1024, 448, 136, False), (2, 385, 1096, 520, False),       # 128 x 128, tails everywhere
+    (80, 200, 128, 1032, False),      # 128 x 128 x 2 per compute unit or larger tiles, more than 64 problems
+])
+def test_tile_kinds_and_tails(jobs, M, K, N, strip):
+    specs = [dict(M=M - (i % 3 if M > 192 else 0), dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]], strip=strip) for i in range(jobs)]
+    outs, refs, _ = run_jobs(specs, salus.BF16)
+    for o, r, j in zip(outs, refs, specs):
+        assert np.isfinite(o).all(), j
+        assert norm_rel_err(o, r) < TOL_BF16_TIGHT, (j, norm_rel_err(o, r))
+
+
+def test_a_row_of_infinities_stays_in_its_row():
+    """The contraction (200) ends inside a slab: what is fetched beyond it - the next row of X, whatever follows W -
+    must not reach the sums, infinite or not."""
+    M, K, N = 200, 200, 264
+    dp = DevicePool(1 << 20, policy=salus.POLICY_PACK)
+    w_offs, P, x_off, y_off, h_off, E = mlp_layout((K, N), 2, M)
+    rng = np.random.default_rng(3)
+    W = synth.f32_to_bf16_bits((rng.standard_normal((K, N)) / np.sqrt(K)).astype(np.float32))
+    X = synth.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
+    ref = dense.mlp_forward_bf16(X, [W], [NONE])[-1]
+    X[7] = 0x7f80                                                  # a row of +inf; row 6 ends where it begins
+    st, job = dp.pool.lane_alloc(P + 4096, E, 0, 1)
+    q = dp.pool.job_query(job)
+    dp.write(q.persist_off, W)
+    dp.write(q.persist_off + W.nbytes, np.full(4096 // 2, 0x7fc0, np.uint16))      # NaN right behind the weights
+    dp.write(q.lane_off + x_off, X)
+    descs, keep = salus.Pool.make_descs([dict(job=job, M=M, dtype=salus.BF16, layers=[(K, N, 0, NONE)], x_off=x_off,
+                                              y_off=y_off, h_off=h_off)])
+    assert dp.pool.grouped_forward(descs, stream=dp.stream) == salus.OK
+    dp.sync()
+    Y = dp.read(q.lane_off + y_off, M * N * 4, np.float32).reshape(M, N)
+    rows = np.arange(M) != 7
+    assert not np.isfinite(Y[7]).any()
+    assert norm_rel_err(Y[rows], ref[rows]) < TOL_BF16_TIGHT
+    dp.close()
