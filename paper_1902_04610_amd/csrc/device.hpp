@@ -72,10 +72,14 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
 // Jobs with many rows: LDS-tiled compute-bound kernel (256 x 256, 128 x 256 or 128 x 128 tiles, by launch).
 // tiled_shape_ok says whether a problem may go there (K a multiple of 64, or many rows and K not small),
 // tiled_tiles how many workgroups it would occupy.
+bool tiled_shape_fits(const Problem &p);      // what the kernels can address at all
 bool tiled_shape_ok(const Problem &p);
 uint64_t tiled_tiles(const Problem &p);
 hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t stream,
                                      uint64_t *launches);
+// Jobs of 33 .. 128 rows, and transposed weights above: 64-row tiles fed through an LDS ring (tiled_shape_fits).
+hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream,
+                                      uint64_t *launches);
 // Calibration: the tiled kernel's multiply without its memory traffic (see kernels_gemm_tiled.hip).
 hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStream_t stream, uint64_t *flop);
 hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches);

@@ -14,7 +14,7 @@
 #include <algorithm>
 #include <vector>
 
-#include "dense_tile_n64.hpp"
+#include "dense_tile.hpp"
 
 namespace salus {
 
@@ -31,25 +31,14 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16(GroupArgs a)
     else dense_bf16_tile<MT, TW, NT>(p, tile, lds);
 }
 
-// 64-row tiles of 128 columns for deep layers of jobs with 33 .. 128 rows: every weight passes through a
+// 64-row tiles of 128 columns for deep layers of jobs with 33 .. 64 rows: every weight passes through a
 // compute unit once.  Two workgroups per compute unit (registers capped accordingly), so that one
 // workgroup's reduction and epilogue overlap the other's stream.
-template <bool NT>
 __global__ __launch_bounds__(kGemmThreads, 2) void grouped_dense_bf16_rows64(GroupArgs a)
 {
     __shared__ float lds[reduce_lds_floats<32>()];
     const Tile tile = find_tile<64, 128>(a);
-    dense_bf16_tile<4, false, NT>(a.p[tile.problem], tile, lds);
-}
-
-// Jobs of 33 .. 128 rows that do not go to the LDS-tiled kernel: row tiles of 64
-// rows, 64 columns wide (see dense_tile_n64.hpp).
-template <bool TW, bool NT>
-__global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_n64(GroupArgs a)
-{
-    __shared__ float lds[reduce_lds_floats<16>()];
-    const Tile tile = find_tile<64, 64>(a);
-    dense_bf16_tile_n64<4, TW, NT>(a.p[tile.problem], tile, lds);
+    dense_bf16_tile<4, false, true>(a.p[tile.problem], tile, lds);
 }
 
 template <int MT>
@@ -90,10 +79,7 @@ static hipError_t launch_groups(const Problem *p, uint32_t n, uint32_t tn, uint3
 }
 
 // Rows per job from which the LDS-tiled kernel is used: always from 128 rows; from
-// 65 rows (where the streaming kernel needs a third row tile) if the jobs routed
-// there make up at least one workgroup per CU (256).  Up to 64 rows the
-// streaming kernel's two row tiles run side by side and the second one finds the
-// weights in L2, which measured faster than a half-empty 128-row tile.
+// 65 rows if the jobs routed there make up at least one workgroup per CU (256).
 constexpr uint32_t kTiledAlways = 128, kTiledMaybe = 65;
 constexpr uint64_t kTiledMinGrid = 256;
 constexpr uint64_t kFullGrid = 256;      // one workgroup per compute unit
@@ -109,80 +95,65 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
         for (uint32_t i = 0; i < n; ++i)
             if (p[i].M >= kTiledMaybe && tiled_shape_ok(p[i])) grid += tiled_tiles(p[i]);
         const uint32_t min_m = grid >= kTiledMinGrid ? kTiledMaybe : kTiledAlways;
+        // Deep layers of a round that mixes jobs of 33 .. 64 and of 65 .. 128 rows and has enough of them to fill the chip: all
+        // in one launch (64 models x 33 - 128 rows, 4096 -> 1024 / 1024 -> 4096 / 1024 -> 1024: 112 / 134 / 39 us against
+        // 149 / 149 / 45 us with 64-row tiles, whose second row tile reads the weights again).
+        uint64_t mid_grid = 0;
+        bool above_64 = false;
+        auto deep_mid = [](const Problem &q) { return q.M > 32 && q.M <= 128 && q.K >= kDeepK && tiled_shape_fits(q); };
+        for (uint32_t i = 0; i < n; ++i)
+            if (deep_mid(p[i])) {
+                mid_grid += tiled_tiles(p[i]);
+                above_64 = above_64 || p[i].M > 64;
+            }
+        const bool take_mid = above_64 && mid_grid >= kTiledMinGrid;
         std::vector<Problem> tiled, streamed;
         for (uint32_t i = 0; i < n; ++i)
-            (p[i].M >= min_m && tiled_shape_ok(p[i]) ? tiled : streamed).push_back(p[i]);
+            ((p[i].M >= min_m && tiled_shape_ok(p[i])) || (take_mid && deep_mid(p[i])) ? tiled : streamed).push_back(p[i]);
         if (!tiled.empty()) {
             hipError_t e = launch_grouped_bf16_tiled(tiled.data(), (uint32_t)tiled.size(), stream, launches);
             if (e != hipSuccess || streamed.empty()) return e;
             return launch_grouped_bf16(streamed.data(), (uint32_t)streamed.size(), false, stream, launches);
         }
     }
-    // Up to 32 rows: one row tile of 16 or 32 rows per job, 128 columns, every weight
-    // read once (non-temporal).  33 .. 128 rows (those the tiled kernel did not take):
-    // when 64-row tiles of 128 columns would not even make one workgroup per compute
-    // unit (a few training jobs, say), row tiles of 64 rows and 64 columns: twice the
-    // workgroups, and the weights pass through a compute unit's memory path once per
-    // 64 rows (2048 x 2048 layers of 8 jobs at 64 rows: 21.0 us against 22.7 us
-    // forward, 21.4 against 28.2 us for the input gradient, whose rows are then read
-    // in whole cache lines).  With enough jobs to fill the chip: layers at least 1024 deep
-    // get one 64-row tile of 128 columns per workgroup, so that every weight passes through
-    // a compute unit once, with registers capped for two workgroups per compute unit (64
-    // models of the inference workload at 48 / 64 rows: 0.250 / 0.270 ms per round against
-    // 0.287 / 0.300 ms with two 32-row tiles, the second of which reads the weights from L2;
-    // the same 64-row tile uncapped, one workgroup per compute unit, had been 5 % slower
-    // than the two 32-row tiles on 1024-deep layers: nothing then overlaps a workgroup's
-    // reduction and epilogue); shallower layers, transposed weights and jobs above 128 rows
-    // keep 32-row tiles of 128 columns.
+    // Up to 32 rows: one row tile of 16 or 32 rows per job, 128 columns, every weight read once (non-temporal).
+    // 33 .. 128 rows (those the tiled kernel did not take): 64-row tiles fed through an LDS ring
+    // (launch_grouped_bf16_stream), except that deep layers of at least 1024 of jobs of up to 64 rows, with enough jobs
+    // to fill the chip, keep one 64-row tile of 128 columns straight from memory (64 models at 64 rows, 4096 -> 1024 /
+    // 1024 -> 4096 / 1024 -> 1024: 115 / 125 / 33 us against 117 / 130 / 34 us through the ring); registers are capped
+    // for two workgroups per compute unit there, without which it was slower.  Above 128 rows transposed weights take
+    // the ring as well (input gradients of 4 jobs x 500 rows, 2048 -> 2048: 40 us against 77 us with 32-row tiles; the
+    // 128 x 128 tiles of the compute-bound kernel are within 2 % at 500 and 1024 rows and slower below); other layers come
+    // here only if they are too shallow for the tiled kernel.
     std::vector<Problem> small, mid, large;
-    for (uint32_t i = 0; i < n; ++i)
-        (p[i].M <= 32 ? small : p[i].M <= 128 ? mid : large).push_back(p[i]);
+    for (uint32_t i = 0; i < n; ++i) {
+        const bool ring = tiled_shape_fits(p[i]);
+        (p[i].M <= 32 ? small : ring && (p[i].M <= 128 || trans_w) ? mid : large).push_back(p[i]);
+    }
     auto launch_wide = [&](int mt, const GroupArgs &a, uint32_t tiles) {
         const dim3 grid(tiles), block(kGemmThreads);
         bool one_row_tile = true;      // else several row tiles read the same weights: plain loads, L2 serves the others
         for (uint32_t i = 0; i < a.n; ++i) one_row_tile = one_row_tile && a.p[i].M <= 16u * mt;
-#define SALUS_WIDE(MT_)                                                                                        \
-        do {                                                                                                    \
-            if (trans_w && one_row_tile) hipLaunchKernelGGL((grouped_dense_bf16<MT_, true, true>), grid, block, 0, stream, a);   \
-            else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16<MT_, true, false>), grid, block, 0, stream, a);            \
-            else if (one_row_tile) hipLaunchKernelGGL((grouped_dense_bf16<MT_, false, true>), grid, block, 0, stream, a);       \
-            else hipLaunchKernelGGL((grouped_dense_bf16<MT_, false, false>), grid, block, 0, stream, a);                        \
-        } while (0)
-        if (mt == 4) {      // forward only (the launcher never asks for it with transposed weights)
-            if (one_row_tile) hipLaunchKernelGGL((grouped_dense_bf16_rows64<true>), grid, block, 0, stream, a);
-            else hipLaunchKernelGGL((grouped_dense_bf16_rows64<false>), grid, block, 0, stream, a);
-            return;
-        }
-        if (mt == 1) SALUS_WIDE(1);
-        else SALUS_WIDE(2);
-#undef SALUS_WIDE
-    };
-    auto launch_n64 = [&](int, const GroupArgs &a, uint32_t tiles) {
-        const dim3 grid(tiles), block(kGemmThreads);
-        bool one_row_tile = true;
-        for (uint32_t i = 0; i < a.n; ++i) one_row_tile = one_row_tile && a.p[i].M <= 64u;
-        if (trans_w && one_row_tile) hipLaunchKernelGGL((grouped_dense_bf16_n64<true, true>), grid, block, 0, stream, a);
-        else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16_n64<true, false>), grid, block, 0, stream, a);
-        else if (one_row_tile) hipLaunchKernelGGL((grouped_dense_bf16_n64<false, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((grouped_dense_bf16_n64<false, false>), grid, block, 0, stream, a);
+        if (mt == 4) hipLaunchKernelGGL(grouped_dense_bf16_rows64, grid, block, 0, stream, a);
+        else if (!one_row_tile && trans_w) hipLaunchKernelGGL((grouped_dense_bf16<2, true, false>), grid, block, 0, stream, a);
+        else if (!one_row_tile) hipLaunchKernelGGL((grouped_dense_bf16<2, false, false>), grid, block, 0, stream, a);
+        else if (mt == 2 && trans_w) hipLaunchKernelGGL((grouped_dense_bf16<2, true, true>), grid, block, 0, stream, a);
+        else if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16<2, false, true>), grid, block, 0, stream, a);
+        else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16<1, true, true>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((grouped_dense_bf16<1, false, true>), grid, block, 0, stream, a);
     };
     if (!small.empty())
         if (hipError_t e = launch_groups(small.data(), (uint32_t)small.size(), 128, 16, 32, launch_wide, launches)) return e;
     if (!mid.empty()) {
         uint64_t wide_tiles = 0;
         for (const Problem &q : mid) wide_tiles += (uint64_t)((q.M + 63) / 64) * ((q.N + 127) / 128);
-        hipError_t e = hipSuccess;
-        if (wide_tiles < kFullGrid) {
-            e = launch_groups(mid.data(), (uint32_t)mid.size(), 64, 0, 0, launch_n64, launches, 4);
-        } else {
-            std::vector<Problem> deep, shallow;
-            for (const Problem &q : mid) (!trans_w && q.K >= kDeepK ? deep : shallow).push_back(q);
-            if (!shallow.empty())
-                e = launch_groups(shallow.data(), (uint32_t)shallow.size(), 128, 0, 0, launch_wide, launches, 2);
-            if (e == hipSuccess && !deep.empty())
-                e = launch_groups(deep.data(), (uint32_t)deep.size(), 128, 0, 0, launch_wide, launches, 4);
-        }
-        if (e != hipSuccess) return e;
+        std::vector<Problem> deep, ring;
+        for (const Problem &q : mid)
+            (wide_tiles >= kFullGrid && !trans_w && q.K >= kDeepK && q.M <= 64 ? deep : ring).push_back(q);
+        if (!ring.empty())
+            if (hipError_t e = launch_grouped_bf16_stream(ring.data(), (uint32_t)ring.size(), trans_w, stream, launches)) return e;
+        if (!deep.empty())
+            if (hipError_t e = launch_groups(deep.data(), (uint32_t)deep.size(), 128, 0, 0, launch_wide, launches, 4)) return e;
     }
     if (!large.empty())
         if (hipError_t e = launch_groups(large.data(), (uint32_t)large.size(), 128, 0, 0, launch_wide, launches, 2)) return e;

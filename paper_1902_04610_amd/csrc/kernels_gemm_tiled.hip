@@ -148,10 +148,19 @@ struct DenseWalk {
 // registers and transposed on the way into LDS), matrix pipes busy 65 % of the cycles at the 1.66 GHz that the chip then
 // holds, no bank conflicts; with every request answered from L2 it takes 450 us.  1024 -> 4096 -> 1024 -> 1024 with GELU:
 // 1263 us (1421).
-template <int BM, int BN, int WM, int WN, bool TW>
+template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled(GroupArgs a)
 {
-    using T = TileMfma<BM, BN, WM, WN, false, !TW>;
+    using T = TileMfma<BM, BN, WM, WN, false, true>;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
+    const DenseWalk<BM, BN, false> walk{a};
+    T::run(walk, smem);
+}
+
+template <int BM, int BN, int WM, int WN, int KS, bool TW, int D>
+__global__ __launch_bounds__(64 * WM * WN * KS, WM * WN * KS / 2) void grouped_dense_bf16_stream(GroupArgs a)
+{
+    using T = TileStream<BM, BN, WM, WN, KS, !TW, D>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
     const DenseWalk<BM, BN, TW> walk{a};
     T::run(walk, smem);
@@ -165,8 +174,11 @@ constexpr uint32_t kTiled256MinM = 192;
 // layers come here only from 192 rows and 192 deep (3 jobs x 300 - 700 rows, 520 -> 1000 -> 776: 54 us for the two layers).
 bool tiled_shape_ok(const Problem &p)
 {
-    const bool whole = p.K % kSlab == 0 || (p.M >= kTiled256MinM && p.K >= kMinSlabs * kSlab);
-    return p.K != 0 && whole && p.K % 8 == 0 && p.N % 8 == 0 && p.K < kTiledMaxWidth && p.N < kTiledMaxWidth;
+    return tiled_shape_fits(p) && (p.K % kSlab == 0 || (p.M >= kTiled256MinM && p.K >= kMinSlabs * kSlab));
+}
+bool tiled_shape_fits(const Problem &p)
+{
+    return p.K != 0 && p.K % 8 == 0 && p.N % 8 == 0 && p.K < kTiledMaxWidth && p.N < kTiledMaxWidth;
 }
 
 uint64_t tiled_tiles(const Problem &p) { return (uint64_t)((p.M + 127) / 128) * ((p.N + 255) / 256); }
@@ -304,10 +316,29 @@ static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n)
     return rounds * (work / tiles) / (t.per_cu == 2 && tiles <= cus ? 2 : 1);
 }
 
+// Launches bound by the weight stream.  64 x 128 tiles, two workgroups per compute unit; when those would not even be one
+// per compute unit, 64 x 64: twice the workgroups.  8 jobs x 64 rows, 2048 -> 2048: 15.4 us (registers-only kernel with K
+// split over four wavefronts: 20.6; this tile without the split of the k-steps 17.5, with 64 x 128 tiles 19), input
+// gradients of the same layer 17 against 24; 8 jobs x 100 rows: 64 x 128 tiles, training step 386 us against 410 with 64
+// x 64.  Rings twice as deep with one workgroup per compute unit: 18.6.
+hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream, uint64_t *launches)
+{
+    uint64_t wide = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        if (!tiled_shape_fits(p[i])) return hipErrorInvalidValue;
+        wide += (uint64_t)((p[i].M + 63) / 64) * ((p[i].N + 127) / 128);
+    }
+    const bool few = wide < resident_grid();
+    if (few && trans_w) return launch_tiled<64, 64, 2>(grouped_dense_bf16_stream<64, 64, 2, 1, 2, true, 4>, 256, p, n, stream, launches);
+    if (few) return launch_tiled<64, 64, 2>(grouped_dense_bf16_stream<64, 64, 2, 1, 2, false, 4>, 256, p, n, stream, launches);
+    if (trans_w) return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 1, true, 3>, 256, p, n, stream, launches);
+    return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 1, false, 3>, 256, p, n, stream, launches);
+}
+
 hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
 {
     for (uint32_t i = 0; i < n; ++i)
-        if (!tiled_shape_ok(p[i])) return hipErrorInvalidValue;
+        if (!tiled_shape_fits(p[i])) return hipErrorInvalidValue;
     std::vector<Problem> big, small;
     for (uint32_t i = 0; i < n; ++i) (p[i].M >= kTiled256MinM ? big : small).push_back(p[i]);
     for (const std::vector<Problem> *group : {&big, &small}) {
@@ -316,9 +347,9 @@ hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t s
         if (count == 0) continue;
         const uint64_t t0 = group == &big ? launch_ns(kTile256, q, count) : ~0ull;
         const uint64_t t1 = launch_ns(kTile128x256, q, count), t2 = launch_ns(kTile128, q, count);
-        const hipError_t e = t0 <= t1 && t0 <= t2 ? launch_tiled<256, 256, 1>(grouped_dense_bf16_tiled<256, 256, 2, 4, false>, 512, q, count, stream, launches)
-                             : t1 <= t2           ? launch_tiled<128, 256, 1>(grouped_dense_bf16_tiled<128, 256, 2, 4, false>, 512, q, count, stream, launches)
-                                                  : launch_tiled<128, 128, 2>(grouped_dense_bf16_tiled<128, 128, 2, 2, false>, 256, q, count, stream, launches);
+        const hipError_t e = t0 <= t1 && t0 <= t2 ? launch_tiled<256, 256, 1>(grouped_dense_bf16_tiled<256, 256, 2, 4>, 512, q, count, stream, launches)
+                             : t1 <= t2           ? launch_tiled<128, 256, 1>(grouped_dense_bf16_tiled<128, 256, 2, 4>, 512, q, count, stream, launches)
+                                                  : launch_tiled<128, 128, 2>(grouped_dense_bf16_tiled<128, 128, 2, 2>, 256, q, count, stream, launches);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -23,12 +23,12 @@
 // LDS layout.  An operand with contiguous contraction index ("major"): line r = its row r, 64 k-values =
 // eight 16-byte chunks, chunk c at c ^ (r / 2 & 7): sixteen consecutive rows of a fragment read (256 bytes, what LDS
 // delivers per cycle) fall into different banks.  Transposed ("tr"): line r = k-row r of the slab, chunk c (8
-// columns) at c ^ 4 * (r & 3): the four k-rows x 64 bytes that 32 lanes of a transposing read touch fall into the
+// columns) at c ^ 4 * (r & 3), of 64-column tiles c ^ 4 * (r / 2 & 1): the four k-rows x 64 bytes that 32 lanes of a transposing read touch fall into the
 // four quarters of the 256-byte bank row.
 // The DMA writes LDS linearly, so the permutation is applied to the source address, inside a 128-byte line.
 //
-// Ragged shapes.  Rows and columns outside the matrices are fetched from clamped addresses and never
-// stored.  Chunks beyond the end of the contraction arrive as zeros, on both sides, so infinities and NaNs
+// Ragged shapes.  Rows and columns outside the matrices and chunks beyond the end of the contraction (on both sides) are
+// requested outside the buffer's range: they arrive as zeros without a memory access, and infinities and NaNs
 // elsewhere in the operands cannot leak into the sums.
 #pragma once
 #include "group.hpp"
@@ -81,15 +81,20 @@ struct Operand {
     bool strip;           // tr only: columns in strips of 128, each depth x 128 contiguous
 };
 
+// tr: what is xored to the chunks of k-row `row` (64 columns: two k-rows share a 256-byte bank row)
+template <int B>
+__device__ inline uint32_t tr_swizzle(uint32_t row) { return B >= 128 ? 4u * (row & 3u) : 4u * ((row >> 1) & 1u); }
+
 // One operand's request stream: where it is in the walk and what this wavefront's share of it is, I instructions of
 // 1 KB per slab.  Requests are issued in k-steps 3, 0, 1, 2 (major: a slab, three slabs ahead) or 1, 2 and 3, 0 (tr: the
 // first and the second half of a slab, two slabs ahead) of the slab being multiplied.
-template <int B, bool TR, int WAVES>
+template <int B, bool TR, int WAVES, int STAGES = TR ? 2 : 3>
 struct OperandStream {
     static constexpr int kBytes = B * (int)kSlab * 2, I = kBytes / 1024 / WAVES;
-    static constexpr int kStages = TR ? 2 : 3, kRing = kStages * kBytes;
+    static constexpr int kStages = STAGES, kRing = kStages * kBytes;
+    static constexpr int kHalf = I > 1 ? I / 2 : 1;
     static constexpr int kChunks = B / 8, kRowsPer = TR ? 64 / kChunks : 8;      // tr: 16-byte chunks of a k-row
-    static_assert(I >= 1 && kBytes == I * 1024 * WAVES && (!TR || I % 2 == 0), "whole instructions per wavefront");
+    static_assert(I >= 1 && kBytes == I * 1024 * WAVES && (!TR || STAGES != 2 || I % 2 == 0), "whole instructions per wavefront");
     uint64_t base;        // scalar: of the slab under the cursor
     uint64_t stride;      // bytes per slab
     uint32_t off[I];      // per lane
@@ -101,23 +106,23 @@ struct OperandStream {
         at = 0;
         lane_k = TR ? lane / kChunks : (int)(8u * chunk_of((uint32_t)lane / 8u, lane));
     }
-    // k-row (tr) or row (major) of the slab that instruction i fetches into: tr instructions 0 .. I/2 - 1 cover k-rows
-    // below 32, the others the rest
-    __device__ static uint32_t piece(int wave, int i) { return TR ? (uint32_t)((i / (I / 2)) * (WAVES * (I / 2)) + wave * (I / 2) + i % (I / 2)) : (uint32_t)(wave * I + i); }
+    // The KB of the slab that instruction i fetches: where a tr ring has two stages, instructions 0 .. I/2 - 1 cover the
+    // k-rows below 32, the others the rest.
+    __device__ static uint32_t piece(int wave, int i) { return TR && STAGES == 2 ? (uint32_t)((i / kHalf) * (WAVES * kHalf) + wave * kHalf + i % kHalf) : (uint32_t)(wave * I + i); }
     __device__ static uint32_t row_of(int wave, int i, int lane)
     {
         return kRowsPer * piece(wave, i) + (uint32_t)(TR ? lane / kChunks : lane / 8);
     }
     __device__ static uint32_t chunk_of(uint32_t row, int lane)
     {
-        return TR ? ((uint32_t)(lane % kChunks) ^ (4u * (row & 3u))) : ((uint32_t)(lane & 7) ^ ((row >> 1) & 7u));
+        return TR ? ((uint32_t)(lane % kChunks) ^ tr_swizzle<B>(row)) : ((uint32_t)(lane & 7) ^ ((row >> 1) & 7u));
     }
     __device__ void locate(const Operand &o, uint32_t first, int wave)
     {
         const int lane = fresh_lane();
         uint64_t from;
         if (TR) {
-            from = o.strip ? (uint64_t)(first >> 7) * o.depth * 256u : (uint64_t)first * 2u;
+            from = o.strip ? (uint64_t)(first >> 7) * o.depth * 256u + (first & 127u) * 2u : (uint64_t)first * 2u;
             stride = (uint64_t)kSlab * o.pitch;
         } else {
             from = (uint64_t)first * o.pitch;
@@ -132,10 +137,10 @@ struct OperandStream {
         for (int i = 0; i < I; ++i) {
             const uint32_t r = row_of(wave, i, lane), c = chunk_of(r, lane);
             if (TR) {
-                const uint32_t cc = first + 8u * c < o.extent ? c : 0u;
-                off[i] = r * o.pitch + (o.strip ? (cc >> 4) * (uint32_t)(o.depth * 256u) + (cc & 15u) * 16u : cc * 16u);
+                off[i] = r * o.pitch + (o.strip ? (c >> 4) * (uint32_t)(o.depth * 256u) + (c & 15u) * 16u : c * 16u);
+                if (first + 8u * c >= o.extent) off[i] = kOutside;
             } else {
-                off[i] = (first + r < o.extent ? r : o.extent - 1 - first) * o.pitch + c * 16u;
+                off[i] = first + r < o.extent ? r * o.pitch + c * 16u : kOutside;
             }
         }
     }
@@ -185,12 +190,17 @@ struct Fragments {
             const uint32_t i = lane & 15u, rr = i >> 2, row = 8u * (lane >> 5) + rr;
             const uint32_t c = (first >> 3) + 2u * ((lane >> 4) & 1u) + ((i & 3u) >> 1);
 #pragma unroll
-            for (uint32_t j = 0; j < (uint32_t)F; ++j) at[j] = row * (B * 2u) + (((c + 4u * j) ^ (4u * rr)) << 4) + 8u * (i & 1u);
+            for (uint32_t j = 0; j < (uint32_t)F; ++j) at[j] = row * (B * 2u) + (((c + 4u * j) ^ tr_swizzle<B>(rr)) << 4) + 8u * (i & 1u);
         } else {
             const uint32_t r = first + (lane & 31u);
 #pragma unroll
             for (uint32_t ks = 0; ks < 4; ++ks) at[ks] = r * 128u + (((2u * ks + (lane >> 5)) ^ ((r >> 1) & 7u)) << 4);
         }
+    }
+    __device__ void skip(uint32_t ks)        // k-steps are counted from here on (ks 0 or 2)
+    {
+#pragma unroll
+        for (uint32_t &v : at) v = TR ? v + ks * 16u * (B * 2u) : v ^ (ks << 5);
     }
     __device__ bf16x8 read(const unsigned char *base, int ks, int block) const
     {
@@ -365,6 +375,142 @@ struct TileMfma {
                 break;
             }
             cur = ahead;         // crossed into by the request cursor at least one slab ago, and no further
+        }
+    }
+};
+
+// The same tiles for launches that are bound by the weight stream (few rows per job): what counts is bytes in flight per
+// compute unit, so LDS is one ring of D whole slabs per operand, D - 1 of them on their way, and the walk across
+// tiles keeps it full through the epilogues.  One barrier per slab: after it slab s has landed for everyone
+// and everyone has left the stage of slab s - 1, which is requested into at once.  KS groups of wavefronts share the
+// k-steps of a slab (and the last one the sums, through LDS): with few tiles a slab's reads and multiplies are a chain.
+template <int BM, int BN, int WM, int WN, int KS, bool TRN, int D>
+struct TileStream {
+    static constexpr int kWavesT = WM * WN * KS, kThreads = 64 * kWavesT;
+    static constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
+    using SM = OperandStream<BM, false, kWavesT, D>;
+    using SN = OperandStream<BN, TRN, kWavesT, D>;
+    static constexpr uint32_t kRings = SM::kRing + SN::kRing, kLds = kRings + (KS - 1) * BM * BN * 4;
+    static constexpr int kBehind = (D - 2) * (SM::I + SN::I);
+    static_assert(kLds <= 160 * 1024 && kBehind <= 63, "LDS of a compute unit, largest count of s_waitcnt");
+    typedef f32x16 Acc[FN][FM];
+
+    template <typename Walk>
+    __device__ static void run(const Walk &walk, unsigned char *smem)
+    {
+        const int lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t kg = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+        const uint32_t lds_m = lds_address(smem), lds_n = lds_m + SM::kRing;
+        Fragments<BM, false, FM> fm;
+        Fragments<BN, TRN, FN> fn;
+        fm.init(wm * (32u * FM), lane);
+        fn.init(wn * (32u * FN), lane);
+        fm.skip(kg * (4 / KS));
+        fn.skip(kg * (4 / KS));
+        const uint32_t tiles = walk.tiles();
+        uint32_t id = blockIdx.x, cur_id = id;
+        typename Walk::Place ahead = walk.place(id), cur = ahead;
+        SM sm;
+        SN sn;
+        sm.start(lane);
+        sn.start(lane);
+        sm.locate(walk.m(ahead), ahead.m0, wave);
+        sn.locate(walk.n(ahead), ahead.n0, wave);
+        // part of four of the requests of the slab under the cursors; the last one moves on
+        auto request = [&](int part) {
+#pragma unroll
+            for (int i = 0; i < SN::I + SM::I; ++i) {
+                if (i * 4 / (SN::I + SM::I) != part) continue;
+                if (i < SN::I) sn.fetch(i, lds_n, wave);
+                else sm.fetch(i - SN::I, lds_m, wave);
+            }
+            if (part != 3) return;
+            sm.advance();
+            sn.advance();
+            if (sm.slabs_left != 0) return;
+            id += gridDim.x;
+            if (id < tiles) {
+                ahead = walk.place(id);
+                sm.locate(walk.m(ahead), ahead.m0, wave);
+                sn.locate(walk.n(ahead), ahead.n0, wave);
+            } else {
+                sm.stop();
+                sn.stop();
+            }
+        };
+#pragma clang loop unroll(disable)
+        for (int d = 0; d < D - 1; ++d)
+#pragma unroll
+            for (int part = 0; part < 4; ++part) request(part);
+
+        Acc acc;
+        uint32_t stage = 0;
+        for (;;) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+            uint32_t left = __builtin_amdgcn_readfirstlane(max((cur.depth + kSlab - 1) / kSlab, kMinSlabs));
+#pragma clang loop unroll(disable)
+            do {
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kBehind) : "memory");
+                const unsigned char *base_m = smem + stage * SM::kBytes, *base_n = smem + SM::kRing + stage * SN::kBytes;
+                bf16x8 a[4 / KS][FN], b[4 / KS][FM];
+#pragma unroll
+                for (int ks = 0; ks < 4 / KS; ++ks) {
+#pragma unroll
+                    for (int i = 0; i < FM; ++i) b[ks][i] = fm.read(base_m, ks, i);
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) a[ks][j] = fn.read(base_n, ks, j);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    request(ks);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (ks >= 4 / KS) continue;
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int i = 0; i < FM; ++i)
+                            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][j], b[ks][i], acc[j][i], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                stage = stage + 1 == (uint32_t)D ? 0u : stage + 1;
+            } while (--left != 0);
+            if (KS > 1) {
+                // the first group of wavefronts collects the others' sums, in order
+                float *sums = (float *)(smem + kRings) + (size_t)(wave % (WM * WN)) * FM * FN * 16 * 64 + lane;
+                constexpr size_t kGroup = (size_t)BM * BN;
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (kg) sums[(kg - 1) * kGroup + ((j * FM + i) * 16 + r) * 64] = acc[j][i][r];
+                __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
+                __builtin_amdgcn_s_barrier();
+#pragma unroll
+                for (int g = 1; g < KS; ++g)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int i = 0; i < FM; ++i)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r)
+                                if (!kg) acc[j][i][r] += sums[(g - 1) * kGroup + ((j * FM + i) * 16 + r) * 64];
+            }
+            if (kg == 0) walk.finish(cur, acc, wm * (32u * FM), wn * (32u * FN), fresh_lane(), []() {});
+            cur_id += gridDim.x;
+            if (cur_id >= tiles) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may arrive in LDS after this workgroup
+                break;
+            }
+            cur = walk.place(cur_id);          // the requests may be more than one tile ahead
         }
     }
 };

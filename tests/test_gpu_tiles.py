@@ -6,6 +6,7 @@ from oracle import dense
 from paper_1902_04610_amd import salus, synth
 from gpu_util import DevicePool, mlp_layout, norm_rel_err
 from test_gpu_kernels import GELU, NONE, RELU, TOL_BF16_TIGHT, run_jobs
+from test_gpu_train import run as run_training
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +52,25 @@ def test_a_row_of_infinities_stays_in_its_row():
     assert not np.isfinite(Y[7]).any()
     assert norm_rel_err(Y[rows], ref[rows]) < TOL_BF16_TIGHT
     dp.close()
+
+
+@pytest.mark.parametrize("jobs, M, K, N, strip", [
+    (1, 33, 8, 8, False), (2, 64, 72, 128, True), (3, 65, 1096, 264, False), (1, 128, 520, 1024, True),
+    (4, 50, 256, 384, True),          # 64 x 64 tiles: some begin in the middle of a strip of 128 columns
+    (40, 100, 72, 1032, False),       # 64 x 128 tiles, 720 of them: workgroups walk two, fewer slabs than the ring has stages
+    (30, 128, 264, 1152, True),
+    (36, 70, 1032, 2056, False),      # deep, more than 64 rows, fills the chip: the compute-bound kernel takes them all
+])
+def test_rows_33_to_128_through_the_ring(jobs, M, K, N, strip):
+    specs = [dict(M=max(33, M - (i % 5) * 7), dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]], strip=strip) for i in range(jobs)]
+    outs, refs, launches = run_jobs(specs, salus.BF16)
+    assert launches == 1
+    for o, r, j in zip(outs, refs, specs):
+        assert np.isfinite(o).all(), j
+        assert norm_rel_err(o, r) < TOL_BF16_TIGHT, (j, norm_rel_err(o, r))
+
+
+@pytest.mark.parametrize("dims, M", [((72, 136, 8), 33), ((520, 264, 40), 64), ((264, 1032, 72), 130), ((192, 200, 1000), 300)])
+def test_input_gradients_through_the_ring(dims, M):
+    """The transposed product, masked by the ReLU derivative, at ragged widths."""
+    run_training([(dims, M, 0.05)], steps=1, seed=4)
