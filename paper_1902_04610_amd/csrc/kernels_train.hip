@@ -8,11 +8,9 @@
 // every launch here, as in the forward pass.
 #include <algorithm>
 
-#include "group.hpp"
+#include "tile_mfma.hpp"
 
 namespace salus {
-
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ inline uint32_t bf16_rne(float f) { return bf16_bits(f); }
 
@@ -33,11 +31,12 @@ __device__ inline float wave_sum(float v)
 // ---------------------------------------------------------------------------
 // Mean softmax cross-entropy over the M rows of each job and its gradient
 // (softmax - onehot) / M, written as bf16 for the backward products.  A
-// workgroup of 16 wavefronts takes 64 rows of one job (the job is found with the
-// scan + ballot used everywhere else), one wavefront four rows.  Rows of up to
-// 1024 classes are read once and kept in registers (all four rows' loads are in
-// flight together); wider rows are re-read from memory for each of the three
-// passes.  Row losses are added in row order by one thread, so the result does
+// workgroup of 16 wavefronts takes 16 rows of one job (the job is found with the
+// scan + ballot used everywhere else), one wavefront one row: the rows are spread over as many
+// compute units as there are, since one unit's memory path is what bounds it (8 jobs x 64 rows x 1000 classes:
+// 5.3 us, with 64 rows per workgroup 13 us).  Rows of up to
+// 1024 classes are read once and kept in registers; wider rows are re-read from memory for each of the three
+// passes.  Row losses are added in row order, so the result does
 // not depend on how the rows were scheduled: inside the workgroup when it holds
 // the whole job, else by a second, tiny kernel over the scratch array.
 // ---------------------------------------------------------------------------
@@ -47,7 +46,7 @@ struct LossArgs {
     LossProblem p[kMaxProblems];
 };
 
-constexpr int kLossRows = 64, kLossWaves = 16, kLossPerWave = kLossRows / kLossWaves, kLossRegs = 16;
+constexpr int kLossRows = 16, kLossWaves = 16, kLossPerWave = kLossRows / kLossWaves, kLossRegs = 16;
 
 __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
 {
@@ -153,14 +152,28 @@ __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
     }
 }
 
-// Jobs of more than 64 rows: add the row losses of each in row order.
+// Jobs of more than 16 rows: add the row losses of each in row order: 512 of them are loaded at a time and added lane by
+// lane (500 rows: 5 us; a load per row took 23 us).
 __global__ __launch_bounds__(64) void loss_mean(LossArgs a)
 {
     const LossProblem &p = a.p[blockIdx.x];
-    if (threadIdx.x != 0 || p.M <= (uint32_t)kLossRows) return;
+    if (p.M <= (uint32_t)kLossRows) return;
     float sum = 0.0f;
-    for (uint32_t r = 0; r < p.M; ++r) sum += p.row_loss[r];
-    *p.loss = sum / (float)p.M;
+    for (uint32_t r0 = 0; r0 < p.M; r0 += 512) {
+        float v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const uint32_t r = r0 + 64u * c + threadIdx.x;
+            v[c] = r < p.M ? p.row_loss[r] : 0.0f;
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            if (r0 + 64u * c >= p.M) break;
+#pragma unroll
+            for (int i = 0; i < 64; ++i) sum += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[c]), i));
+        }
+    }
+    if (threadIdx.x == 0) *p.loss = sum / (float)p.M;
 }
 
 hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
@@ -203,11 +216,13 @@ hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, hipStream_t str
 // ---------------------------------------------------------------------------
 struct UpdateArgs {
     uint32_t n;
-    uint32_t pad;
+    uint32_t tiles;      // all tiles of the launch (the kernel whose workgroups loop over tiles)
     UpdateProblem p[kMaxProblems];
 };
 
 constexpr int kUpdK = 64, kUpdN = 256;      // workgroup tile
+constexpr double kDwTiledRows = 256;
+constexpr int kDwTile = 128;                // tile of the many-row kernel
 
 // Which update problem and tile workgroup `id` owns: lane i holds job i's tile count.
 __device__ inline int find_update(const UpdateProblem *p, uint32_t n, uint32_t id, uint32_t *t, uint32_t *kt)
@@ -308,9 +323,125 @@ __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
     dw_sgd_tile(a.p[job], t, kt);
 }
 
+// Many rows per job (the contraction is long): the product goes through the LDS tiles of tile_mfma.hpp, both operands
+// transposed on the way out of LDS.  M side: H (rows of W), N side: G (columns of W).
+struct UpdateWalk {
+    const UpdateArgs &a;
+    uint32_t count;
+    struct Place { int problem; uint32_t m0, n0, depth; };
+    __device__ uint32_t tiles() const { return count; }
+    __device__ Place place(uint32_t tile_id) const
+    {
+        const int lane = threadIdx.x & 63;
+        const bool valid = lane < (int)a.n;
+        uint32_t kt = 0, nt = 0;
+        if (valid) {
+            kt = (a.p[lane].K + kDwTile - 1) / kDwTile;
+            nt = (a.p[lane].N + kDwTile - 1) / kDwTile;
+        }
+        const uint32_t first = wave_excl_scan_u32(kt * nt, nullptr);
+        const uint32_t id = xcd_remap(tile_id, count);
+        const int g = __builtin_amdgcn_readfirstlane(wave_find_range(first, id, valid));
+        const uint32_t t = id - __shfl(first, g, 64), k = __shfl(kt, g, 64);
+        return {g, (uint32_t)__builtin_amdgcn_readfirstlane((t % k) * kDwTile), (uint32_t)__builtin_amdgcn_readfirstlane((t / k) * kDwTile), a.p[g].M};
+    }
+    __device__ Operand m(const Place &at) const { const UpdateProblem &p = a.p[at.problem]; return {p.H, p.M, p.K, p.K * 2u, false}; }
+    __device__ Operand n(const Place &at) const { const UpdateProblem &p = a.p[at.problem]; return {p.G, p.M, p.N, p.N * 2u, false}; }
+    template <int FN, int FM, typename Landed>
+    __device__ void finish(const Place &at, const f32x16 (&acc)[FN][FM], uint32_t m, uint32_t n, int lane, Landed landed) const
+    {
+        const UpdateProblem &p = a.p[at.problem];
+        const uint32_t N = p.N;
+        m += at.m0;
+        n += at.n0;
+        float *Wm = p.Wm + ((uint64_t)m * N + n);
+        uint16_t *Wb = (uint16_t *)p.Wb + ((uint64_t)m * N + n);
+        const uint32_t rows = m < p.K ? p.K - m : 0, cols = n < N ? N - n : 0, column = line_column_f32(lane);
+        const float lr = p.lr;
+        // all master weights of the wavefront's part are requested before the first is used
+        f32x4 w[FN][FM][2][2];
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t r = 32u * i + 8u * q + (lane & 7), c = 32u * j + column;
+                    w[j][i][q >> 1][q & 1] = r < rows && c < cols ? __builtin_nontemporal_load((const f32x4 *)(Wm + (size_t)r * N + c))
+                                                                  : f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        landed();
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                float v[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = acc[j][i][r];
+                f32x4 o[2][2];
+                to_lines_f32(v, o);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t r = 32u * i + 8u * q + (lane & 7), c = 32u * j + column;
+                    if (!(r < rows && c < cols)) continue;
+                    f32x4 x = w[j][i][q >> 1][q & 1];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)      // one rounded multiply, one rounded subtract
+                        x[e] = __fsub_rn(x[e], __fmul_rn(lr, o[q >> 1][q & 1][e]));
+                    __builtin_nontemporal_store(x, (f32x4 *)(Wm + (size_t)r * N + c));
+                    *(u32x2 *)(Wb + (size_t)r * N + c) = u32x2{bf16_pack(x[0], x[1]), bf16_pack(x[2], x[3])};
+                }
+            }
+    }
+};
+
+// Bound by the master weights' traffic, in bursts: two workgroups per compute unit, so that one updates while the other
+// multiplies.  4 jobs x 500 rows (588 MB): 169 us against 204 us for the register kernel, whose wavefronts read H and G
+// from L2 once per 64 x 64 block; 64 x 128 tiles, two or three per compute unit: step 11 - 17 us longer.
+__global__ __launch_bounds__(256, 2) void grouped_dw_sgd_tiled(UpdateArgs a)
+{
+    using T = TileMfma<kDwTile, kDwTile, 2, 2, true, true>;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
+    const UpdateWalk walk{a, a.tiles};
+    T::run(walk, smem);
+}
+
+static hipError_t launch_dw_tiled(const UpdateProblem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
+{
+    for (uint32_t at = 0; at < n; at += kMaxProblems) {
+        UpdateArgs a{};
+        a.n = std::min(kMaxProblems, n - at);
+        uint64_t tiles = 0;
+        for (uint32_t i = 0; i < a.n; ++i) {
+            a.p[i] = p[at + i];
+            tiles += (uint64_t)((a.p[i].K + kDwTile - 1) / kDwTile) * ((a.p[i].N + kDwTile - 1) / kDwTile);
+        }
+        if (tiles == 0) continue;
+        if (tiles > 0x7fffffffull) return hipErrorInvalidValue;
+        a.tiles = (uint32_t)tiles;
+        hipLaunchKernelGGL(grouped_dw_sgd_tiled, dim3((uint32_t)std::min<uint64_t>(tiles, 2 * resident_grid())), dim3(256), 0, stream, a);
+        if (launches) *launches += 1;
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, hipStream_t stream,
                                  uint64_t *launches)
 {
+    // One kernel for all updates of a step (two would each ramp up and drain): the tiled one if a weight's rows, on
+    // average over the weights, are at least 256.  Step of 8 jobs of 2048-wide layers at 130 / 256 rows: 419 / 493 us
+    // without, 438 / 486 us with it; 4 jobs x 500 rows 394 / 360, 2 jobs x 1024 rows 344 / 292.
+    double rows = 0, weights = 0;
+    bool fits = true;
+    for (uint32_t i = 0; i < n; ++i) {
+        const double w = (double)p[i].K * p[i].N;
+        weights += w;
+        rows += w * p[i].M;
+        fits = fits && p[i].K < kTiledMaxWidth && p[i].N < kTiledMaxWidth;
+    }
+    if (fits && rows >= kDwTiledRows * weights) return launch_dw_tiled(p, n, stream, launches);
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         UpdateArgs a{};
         a.n = std::min(kMaxProblems, n - at);

@@ -230,6 +230,7 @@ struct TileMfma {
     using SN = OperandStream<BN, TRN, kWavesT>;
     static constexpr uint32_t kLds = SM::kRing + SN::kRing;
     static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
+    static_assert(FM * FN > 1, "a k-step places its reads between its multiplies");
     static_assert(!TRM || TRN, "the M side meets the end of a tile no later than the N side");
     typedef f32x16 Acc[FN][FM];
 

@@ -74,3 +74,13 @@ def test_rows_33_to_128_through_the_ring(jobs, M, K, N, strip):
 def test_input_gradients_through_the_ring(dims, M):
     """The transposed product, masked by the ReLU derivative, at ragged widths."""
     run_training([(dims, M, 0.05)], steps=1, seed=4)
+
+
+@pytest.mark.parametrize("configs", [
+    [((136, 520, 40), 257, 0.05)], [((64, 72), 256, 0.05), ((264, 128, 136), 333, 0.01)],
+    [((200, 1096, 264), 600, 0.02)],          # several slabs of batch, more tiles than compute units would need
+    [((72, 40), 16, 0.1), ((72, 40), 17, 0.1), ((40, 1032), 18, 0.1)],      # rows of one and of two workgroups of the loss
+])
+def test_updates_of_many_rows_and_loss_rows(configs):
+    """The weight gradient through the LDS tiles (256 rows on average and more), and jobs around the loss kernel's 16 rows."""
+    run_training(configs, steps=2, seed=12)
