@@ -51,7 +51,7 @@ struct HipOps : DeviceOps {
             if (e != hipSuccess) return fail(e, "hipHostGetDevicePointer");
             CopySeg seg = kind == hipMemcpyDeviceToHost ? CopySeg{src, mapped, n}
                                                         : CopySeg{mapped, dst, n};
-            e = launch_copy(&seg, 1, stream);
+            e = launch_copy(&seg, 1, stream, true);
             copy_launches += 1;
         } else {
             e = hipMemcpyAsync(dst, src, n, kind, stream);

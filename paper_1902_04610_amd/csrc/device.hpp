@@ -17,14 +17,17 @@ constexpr uint32_t kCopyChunk = 8 * 1024;   // bytes one workgroup moves per gri
 
 // Copies n mutually independent segments (no destination may overlap another
 // segment's source); more than kMaxSeg segments are split over launches.
-hipError_t launch_copy(const CopySeg *segs, uint32_t n, hipStream_t stream);
+// host_link: one side of every segment is host memory.
+hipError_t launch_copy(const CopySeg *segs, uint32_t n, hipStream_t stream, bool host_link = false);
 
-// Device state of the in-place slide kernel: one progress counter per resident
-// workgroup and a failure word (16 KB of device memory, allocated once).
+// State of the in-place slide kernel: one progress counter per resident workgroup (16 KB of device memory) and a
+// failure word in mapped host memory (allocated with the first in-place move).
 constexpr uint32_t kSlideMaxGrid = 4032;
 struct SlideState {
     uint32_t *progress = nullptr;   // kSlideMaxGrid counters
-    uint32_t *failed = nullptr;     // set to 1 by a workgroup whose bounded wait ran out
+    uint32_t epoch = 0;             // no counter is above it between launches
+    uint32_t *failed = nullptr;     // set to 1 by a workgroup whose bounded wait ran out (host address)
+    uint32_t *failed_dev = nullptr; // the same word as the kernel sees it
     uint32_t max_grid = 0;          // resident workgroups a launch may use (found at the first launch)
     uint32_t spin_limit = 1u << 22; // polls (a microsecond or two each) before a wait gives up: seconds
 };

@@ -66,8 +66,12 @@ __global__ __launch_bounds__(kCopyThreads) void copy_segments(CopyArgs a, uint64
     }
 }
 
-static uint32_t copy_grid(uint64_t chunks)
+static uint32_t copy_grid(uint64_t chunks, bool host_link)
 {
+    // Across the host link a few workgroups that loop keep the transfers in order: 256 MB out / in with one workgroup per
+    // chunk 54.2 / 54.3 GB/s, with 512 54.4 / 56.0, 128 55.4 / 57.4, 64 55.5 / 56.4, 32 55.3 / 57.4, 16 48.9 / 52.1; 4 MB
+    // 45.2 / 35.7 GB/s with one per chunk, 46.3 / 46.8 with 64.
+    if (host_link) return (uint32_t)std::min<uint64_t>(chunks, 64);
     // measured on MI355X, 8 GiB copied: one workgroup per 8 KiB chunk gives the best
     // read+write rate, 6.07 TB/s (chunks of 4 / 16 / 32 KiB: 5.61 / 5.74 / 5.47; 16 KiB
     // chunks with 8 passes over a smaller grid: 5.27).  The cap keeps grid x block
@@ -76,7 +80,7 @@ static uint32_t copy_grid(uint64_t chunks)
     return (uint32_t)std::min<uint64_t>(chunks, cap);
 }
 
-hipError_t launch_copy(const CopySeg *segs, uint32_t n, hipStream_t stream)
+hipError_t launch_copy(const CopySeg *segs, uint32_t n, hipStream_t stream, bool host_link)
 {
     for (uint32_t at = 0; at < n; at += kMaxSeg) {
         CopyArgs a{};
@@ -87,7 +91,7 @@ hipError_t launch_copy(const CopySeg *segs, uint32_t n, hipStream_t stream)
             chunks += (a.seg[i].len + kCopyChunk - 1) / kCopyChunk;
         }
         if (chunks == 0) continue;
-        hipLaunchKernelGGL(copy_segments, dim3(copy_grid(chunks)), dim3(kCopyThreads), 0, stream, a,
+        hipLaunchKernelGGL(copy_segments, dim3(copy_grid(chunks, host_link)), dim3(kCopyThreads), 0, stream, a,
                            chunks);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -129,14 +133,8 @@ hipError_t launch_copy(const CopySeg *segs, uint32_t n, hipStream_t stream)
 constexpr uint32_t kSlideChunk = 192 * 1024;
 constexpr int kSlideVec = kSlideChunk / (kCopyThreads * 16);
 
-__global__ void slide_reset(uint32_t *progress, uint32_t n, uint32_t *failed)
-{
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) progress[i] = 0;
-    if (failed && threadIdx.x == 0) *failed = 0;      // null: keep what an earlier launch of this plan reported
-}
-
 __global__ __launch_bounds__(kCopyThreads) void slide_down(char *dst, const char *src, uint64_t len,
-                                                           uint32_t *progress, uint32_t *failed,
+                                                           uint32_t *progress, uint32_t epoch, uint32_t *failed,
                                                            uint32_t spin_limit)
 {
     const uint64_t shift = (uint64_t)(src - dst);
@@ -145,7 +143,7 @@ __global__ __launch_bounds__(kCopyThreads) void slide_down(char *dst, const char
     const bool straddles = shift % kSlideChunk != 0;
     const uint32_t G = gridDim.x, w = blockIdx.x;
     __shared__ uint32_t give_up;
-    uint32_t round = 0;
+    uint32_t round = epoch;
     for (uint64_t chunk = w; chunk < chunks; chunk += G, ++round) {
         const uint64_t off = chunk * kSlideChunk;
         const uint64_t left = len - off;
@@ -169,14 +167,14 @@ __global__ __launch_bounds__(kCopyThreads) void slide_down(char *dst, const char
             const bool want[2] = {straddles && chunk >= q + 1, q > 0 && chunk >= q};
             for (int k = 0; k < 2 && !bad; ++k) {
                 if (!want[k]) continue;
-                const uint32_t owner = (uint32_t)(need[k] % G), target = (uint32_t)(need[k] / G) + 1;
+                const uint32_t owner = (uint32_t)(need[k] % G), target = epoch + (uint32_t)(need[k] / G) + 1;
                 uint32_t spins = 0;
-                while (__hip_atomic_load(progress + owner, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+                while ((int32_t)(__hip_atomic_load(progress + owner, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
                     if (++spins > spin_limit) { bad = 1; break; }
                     __builtin_amdgcn_s_sleep(4);
                 }
             }
-            if (bad) __hip_atomic_store(failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (bad) __hip_atomic_store(failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             give_up = bad;
         }
         __syncthreads();
@@ -191,8 +189,7 @@ __global__ __launch_bounds__(kCopyThreads) void slide_down(char *dst, const char
     }
 }
 
-static hipError_t launch_slide_down(char *dst, const char *src, uint64_t len, SlideState *st, bool clear_failed,
-                                    hipStream_t stream)
+static hipError_t launch_slide_down(char *dst, const char *src, uint64_t len, SlideState *st, hipStream_t stream)
 {
     if (!st || !st->progress) return hipErrorInvalidValue;
     const uint64_t chunks = (len + kSlideChunk - 1) / kSlideChunk;
@@ -201,60 +198,70 @@ static hipError_t launch_slide_down(char *dst, const char *src, uint64_t len, Sl
         hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, slide_down, kCopyThreads, 0);
         if (e == hipSuccess) e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess && !st->failed) {
+            e = hipHostMalloc((void **)&st->failed, 64, hipHostMallocMapped | hipHostMallocPortable);
+            if (e == hipSuccess) *st->failed = 0;
+        }
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&st->failed_dev, st->failed, 0);
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // the counters are cleared, also for streams that do not wait
         if (e != hipSuccess) return e;
         if (per_cu < 1 || cus < 1) return hipErrorInvalidValue;
         // two workgroups per compute unit keep 256 KB per unit in flight; more changes nothing
         st->max_grid = (uint32_t)std::min<int64_t>((int64_t)std::min(per_cu, 2) * cus, kSlideMaxGrid);
     }
-    uint32_t grid = (uint32_t)std::min<uint64_t>(chunks, st->max_grid);
-    hipLaunchKernelGGL(slide_reset, dim3(1), dim3(256), 0, stream, st->progress, grid,
-                       clear_failed ? st->failed : (uint32_t *)nullptr);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const uint32_t grid = (uint32_t)std::min<uint64_t>(chunks, st->max_grid);
     hipLaunchKernelGGL(slide_down, dim3(grid), dim3(kCopyThreads), 0, stream, dst, (const char *)src, len,
-                       st->progress, st->failed, st->spin_limit);
+                       st->progress, st->epoch, st->failed_dev, st->spin_limit);
+    // Counters run on from launch to launch: every counter is at most `epoch` when a launch begins (launches of one
+    // SlideState are ordered), so nothing has to be cleared in a launch of its own.
+    st->epoch += (uint32_t)((chunks + grid - 1) / grid);
     return hipGetLastError();
 }
 
 hipError_t slide_state_create(SlideState *st)
 {
-    st->max_grid = 0;
-    hipError_t e = hipMalloc((void **)&st->progress, (kSlideMaxGrid + 64) * sizeof(uint32_t));
+    *st = SlideState{};
+    hipError_t e = hipMalloc((void **)&st->progress, kSlideMaxGrid * sizeof(uint32_t));
     if (e != hipSuccess) { st->progress = nullptr; return e; }
-    st->failed = st->progress + kSlideMaxGrid;
-    return hipMemset(st->progress, 0, (kSlideMaxGrid + 64) * sizeof(uint32_t));
+    return hipMemset(st->progress, 0, kSlideMaxGrid * sizeof(uint32_t));
 }
 
 void slide_state_destroy(SlideState *st)
 {
     if (st->progress) (void)hipFree(st->progress);
-    st->progress = st->failed = nullptr;
+    if (st->failed) (void)hipHostFree(st->failed);
+    st->progress = st->failed = st->failed_dev = nullptr;
 }
 
-// 1 if a slide launched since the last call gave up a wait (the caller has synchronized).
+// 1 if a slide launched since the last call gave up a wait: reported once, a later plan must not see it again.
+// Waits for the stream.
 hipError_t slide_state_failed(SlideState *st, hipStream_t stream, uint32_t *out)
 {
     *out = 0;
-    if (!st->progress) return hipSuccess;
-    hipError_t e = hipMemcpyAsync(out, st->failed, 4, hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    // reported once: a later plan without an in-place move must not see it again
-    if (e == hipSuccess && *out) e = hipMemsetAsync(st->failed, 0, 4, stream);
-    return e;
+    hipError_t e = hipStreamSynchronize(stream);
+    if (!st->failed || e != hipSuccess) return e;
+    *out = *(volatile uint32_t *)st->failed;
+    *(volatile uint32_t *)st->failed = 0;
+    return hipSuccess;
 }
 
+// From this shift on an overlapping move is cheaper as a chain of plain copies of `shift` bytes each (every piece is
+// written where the one before it was read) than in place.  4 GiB moved, read + write, in place / in pieces: 64 MiB 5.62 /
+// 5.42 TB/s, 96 MiB 5.33 / 5.74, 128 MiB 5.55 / 5.91, 256 MiB 5.48 / 6.18, 1000 MiB 5.37 / 6.22 (8 MiB 5.91 / 3.09).
+constexpr uint64_t kSlidePiece = 80ull << 20;
+
 // Sliding compaction.  Moves are listed in ascending address order and every
-// destination lies below its source.  A move whose shift (src - dst) is at
+// destination lies below its source.  Blocks that lie side by side and move by the same distance - all blocks above
+// the only hole, say - are one move.  A move whose shift (src - dst) is at
 // least its length is an independent segment; consecutive ones share a launch as
 // long as none of them writes what an earlier one of the same launch still reads.
-// A move that overlaps its own destination runs as one in-place slide_down launch.
+// A move that overlaps its own destination runs as one in-place slide_down launch, or in pieces.
 // Launches run in stream order.
 hipError_t launch_slide(char *base, const uint64_t *src, const uint64_t *dst, const uint64_t *len,
                         uint32_t n, SlideState *st, hipStream_t stream, uint64_t *launches)
 {
     std::vector<CopySeg> phase;
     uint64_t phase_first_src = 0;
-    bool first_slide = true;        // the plan's first in-place move clears the "gave up" flag, later ones keep it
     auto flush = [&]() -> hipError_t {
         if (phase.empty()) return hipSuccess;
         hipError_t e = launch_copy(phase.data(), (uint32_t)phase.size(), stream);
@@ -262,21 +269,29 @@ hipError_t launch_slide(char *base, const uint64_t *src, const uint64_t *dst, co
         phase.clear();
         return e;
     };
-    for (uint32_t i = 0; i < n; ++i) {
-        if (len[i] == 0) continue;
-        const uint64_t shift = src[i] - dst[i];
-        if (shift >= len[i]) {
+    for (uint32_t i = 0; i < n;) {
+        const uint64_t from = src[i], to = dst[i], shift = from - to;
+        uint64_t bytes = len[i++];
+        while (i < n && src[i] == from + bytes && dst[i] == to + bytes) bytes += len[i++];
+        if (bytes == 0) continue;
+        if (shift >= bytes) {
             // joins the current launch only if it writes nothing that launch still reads
-            if (!phase.empty() && dst[i] + len[i] > phase_first_src)
+            if (!phase.empty() && to + bytes > phase_first_src)
                 if (hipError_t e = flush()) return e;
-            if (phase.empty()) phase_first_src = src[i];
-            phase.push_back({base + src[i], base + dst[i], len[i]});
+            if (phase.empty()) phase_first_src = from;
+            phase.push_back({base + from, base + to, bytes});
             continue;
         }
         if (hipError_t e = flush()) return e;
-        if (hipError_t e = launch_slide_down(base + dst[i], base + src[i], len[i], st, first_slide, stream))
-            return e;
-        first_slide = false;
+        if (shift >= kSlidePiece) {
+            for (uint64_t at = 0; at < bytes; at += shift) {
+                const CopySeg piece{base + from + at, base + to + at, std::min(shift, bytes - at)};
+                if (hipError_t e = launch_copy(&piece, 1, stream)) return e;
+                if (launches) *launches += 1;
+            }
+            continue;
+        }
+        if (hipError_t e = launch_slide_down(base + to, base + from, bytes, st, stream)) return e;
         if (launches) *launches += 1;
     }
     return flush();

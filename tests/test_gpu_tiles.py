@@ -1,6 +1,7 @@
 """GPU parity of the LDS-tiled kernels at the edges of their tiles, slabs and dispatch rule, against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import dense
 from paper_1902_04610_amd import salus, synth
@@ -84,3 +85,26 @@ def test_input_gradients_through_the_ring(dims, M):
 def test_updates_of_many_rows_and_loss_rows(configs):
     """The weight gradient through the LDS tiles (256 rows on average and more), and jobs around the loss kernel's 16 rows."""
     run_training(configs, steps=2, seed=12)
+
+
+@pytest.mark.parametrize("shift_mb, blocks", [(79, 3), (80, 3), (81, 2), (96, 4)])
+def test_equal_shifts_move_as_one(shift_mb, blocks):
+    """All blocks above the only hole move by its size: one move, in place below 80 MiB and in pieces of the shift
+    from there on (the last piece is a remainder)."""
+    MiB = 1 << 20
+    sizes = [shift_mb * MiB] + [90 * MiB + 4096 * (i + 1) for i in range(blocks)]
+    dp = DevicePool(sum(sizes) + 16 * MiB, max_lanes=1)
+    scratch = torch.zeros(8, dtype=torch.uint8, device="cuda")
+    for i, s in enumerate(sizes):
+        st, job = dp.pool.lane_alloc(s, 4096, 0, 1)
+        assert st == salus.OK
+        salus.fill_pattern(dp.buf.data_ptr() + dp.pool.job_query(job).persist_off, s, 100 + i)
+    for again in range(2):                        # the counters of the in-place kernel run on from move to move
+        assert dp.pool.lane_free(again) == salus.OK
+        plan = dp.pool.compact()
+        assert len(plan) == len(sizes) - 1 - again and len({src - dst for src, dst, _ in plan}) == 1
+        for i in range(again + 1, len(sizes)):
+            q = dp.pool.job_query(i)
+            assert q.persist_off == sum(sizes[again + 1:i])
+            assert salus.check_pattern(dp.buf.data_ptr() + q.persist_off, sizes[i], 100 + i, scratch.data_ptr()) == 0
+    dp.close()
