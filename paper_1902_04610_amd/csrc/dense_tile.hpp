@@ -60,14 +60,18 @@ constexpr int reduce_lds_floats() { return kWaves * 3 * (NACC < 16 ? NACC : 16) 
 // so the loads carry the non-temporal hint and do not displace activations in
 // L2.  With several row tiles per column tile the neighbours read the same
 // weights at about the same time and a plain load lets the second one hit in L2.
-template <int MT, bool TW, bool NT>
+// CPL: columns per lane, 8, 4 or 2; the tile is 16 * CPL columns wide.  An output's products are summed in the same order
+// whatever the width, so the result is the same to the bit.  D: k-steps in flight per wavefront; a narrow tile has fewer
+// bytes per step and needs more of them to cover the latency.
+template <int MT, bool TW, bool NT, int CPL = 8, int D = 2>
 __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float *lds)
 {
-    constexpr int NACC = MT * 8;
+    constexpr int NACC = MT * CPL, NROW = TW ? CPL : 8;      // weight vectors per lane and k-step
+    typedef unsigned int wvec __attribute__((ext_vector_type(TW ? 4 : CPL / 2)));
     const uint32_t M = p.M, K = p.K, N = p.N;
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t ncol = tile.n0 + 8 * c;
+    const uint32_t ncol = tile.n0 + CPL * c;
     const bool col_ok = ncol < N;
     const uint16_t *W = (const uint16_t *)p.W;
     const uint16_t *X = (const uint16_t *)p.X;
@@ -92,15 +96,15 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
     const uint32_t xtiles = (M + 15) / 16;
     const bool strip = !TW && (p.flags & kStripW);
     const uint32_t wpitch = strip ? 128u : N;
-    const uint16_t *Wc = strip ? W + (size_t)tile.n0 * K + 8 * c : W + ncol_c;
-    auto load = [&](int s, u32x4 (&w)[8], u32x4 (&x)[MT], bool &k_ok) {
+    const uint16_t *Wc = strip ? W + (size_t)(tile.n0 & ~127u) * K + (tile.n0 & 127u) + CPL * c : W + ncol_c;
+    auto load = [&](int s, wvec (&w)[NROW], u32x4 (&x)[MT], bool &k_ok) {
         const uint32_t kb = 32u * (uint32_t)s + 8u * (uint32_t)g;
         k_ok = kb < K;
         const uint32_t kc = k_ok ? kb : 0u;
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
+        for (int r = 0; r < NROW; ++r) {
             const uint16_t *at = TW ? W + (size_t)(ncol_c + r) * K + kc : Wc + (size_t)(kc + r) * wpitch;
-            w[r] = NT ? __builtin_nontemporal_load((const u32x4 *)at) : *(const u32x4 *)at;
+            w[r] = NT ? __builtin_nontemporal_load((const wvec *)at) : *(const wvec *)at;
         }
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
@@ -115,15 +119,15 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
             }
         }
     };
-    auto compute = [&](const u32x4 (&w)[8], const u32x4 (&xr)[MT], bool k_ok) {
+    auto compute = [&](const wvec (&w)[NROW], const u32x4 (&xr)[MT], bool k_ok) {
         u32x4 x[MT];
 #pragma unroll
         for (int t = 0; t < MT; ++t) x[t] = k_ok ? xr[t] : zero;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            // column i of the 8x8 block: dword j = (row 2j, row 2j+1)
+        for (int i = 0; i < CPL; ++i) {
+            // column i of the 8 x CPL block: dword j = (row 2j, row 2j+1)
             u32x4 b;
-            if (TW) {
+            if constexpr (TW) {
                 b = w[i];
             } else {
 #pragma unroll
@@ -133,39 +137,43 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
             }
 #pragma unroll
             for (int t = 0; t < MT; ++t)
-                acc[t * 8 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8, x[t]), __builtin_bit_cast(bf16x8, b), acc[t * 8 + i],
+                acc[t * CPL + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8, x[t]), __builtin_bit_cast(bf16x8, b), acc[t * CPL + i],
                     0, 0, 0);
         }
     };
 
     // The four wavefronts take k-steps wave, wave+4, ...: this wavefront owns
-    // `mine` steps.  Two steps are in flight at any time; the last (up to three)
+    // `mine` steps.  D steps are in flight at any time; the last (fewer than 2 D)
     // steps are peeled so that the main loop never loads past the end.
-    u32x4 w0[8], w1[8], x0[MT], x1[MT];
-    bool ok0, ok1;
+    wvec w[D][NROW];
+    u32x4 x[D][MT];
+    bool ok[D];
     const int mine = nsteps > wave ? (nsteps - wave + kWaves - 1) / kWaves : 0;
     auto step = [&](int i) { return wave + kWaves * i; };
-    load(step(0), w0, x0, ok0);
-    load(step(1), w1, x1, ok1);
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(step(d), w[d], x[d], ok[d]);
     int i = 0;
-    for (; i + 3 < mine; i += 2) {
+    for (; i + 2 * D <= mine; i += D) {
         // keep the instruction scheduler from sinking the loads below the next
         // multiply phase: each phase must stay where it is written
-        compute(w0, x0, ok0);
-        __builtin_amdgcn_sched_barrier(0);
-        load(step(i + 2), w0, x0, ok0);
-        __builtin_amdgcn_sched_barrier(0);
-        compute(w1, x1, ok1);
-        __builtin_amdgcn_sched_barrier(0);
-        load(step(i + 3), w1, x1, ok1);
-        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            compute(w[d], x[d], ok[d]);
+            __builtin_amdgcn_sched_barrier(0);
+            load(step(i + d + D), w[d], x[d], ok[d]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     const int left = mine - i;
-    if (left >= 1) compute(w0, x0, ok0);
-    if (left == 3) load(step(i + 2), w0, x0, ok0);
-    if (left >= 2) compute(w1, x1, ok1);
-    if (left == 3) compute(w0, x0, ok0);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        if (d < left) compute(w[d], x[d], ok[d]);
+        if (d + D < left) load(step(i + d + D), w[d], x[d], ok[d]);
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (d + D < left) compute(w[d], x[d], ok[d]);
 
     float own[NACC];
     reduce_scatter<NACC>(acc, own, lds);
@@ -175,34 +183,40 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
     for (int t = 0; t < MT; ++t) {
         const uint32_t row = tile.m0 + 16 * t + 4 * g + wave;
         if (row >= M || !col_ok) continue;
-        float v[8];
+        float v[CPL];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = activate(own[t * 8 + i], act);
+        for (int i = 0; i < CPL; ++i) v[i] = activate(own[t * CPL + i], act);
+        typedef unsigned int out_vec __attribute__((ext_vector_type(CPL / 2)));
         if (p.flags & kMaskPositive) {
             // ReLU derivative taken from the stored bf16 activation (sign bit clear, not zero)
-            const u32x4 h = *(const u32x4 *)((const uint16_t *)p.aux + (size_t)row * N + ncol);
+            const out_vec h = *(const out_vec *)((const uint16_t *)p.aux + (size_t)row * N + ncol);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < CPL; ++i) {
                 const uint32_t bits = (h[i >> 1] >> ((i & 1) * 16)) & 0xffffu;
                 if ((bits & 0x8000u) || !(bits & 0x7fffu)) v[i] = 0.0f;
             }
         }
         if (p.flags & kOutBf16) {
-            u32x4 o;
+            out_vec o;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] = bf16_pack(v[2 * j], v[2 * j + 1]);
+            for (int j = 0; j < CPL / 2; ++j) o[j] = bf16_pack(v[2 * j], v[2 * j + 1]);
             if (p.flags & kOutBlocked) {
-                // these 8 columns are k-group (ncol / 8) % 4 of k-step ncol / 32 of the next layer
+                // these columns are in k-group (ncol / 8) % 4 of k-step ncol / 32 of the next layer
                 const size_t unit = (((size_t)(ncol >> 5) * xtiles + (row >> 4)) * 4 + ((ncol >> 3) & 3)) * 16 +
                                     (row & 15);
-                *(u32x4 *)((uint16_t *)p.Y + unit * 8) = o;
+                *(out_vec *)((uint16_t *)p.Y + unit * 8 + (ncol & 7u)) = o;
             } else {
-                *(u32x4 *)((uint16_t *)p.Y + (size_t)row * N + ncol) = o;
+                *(out_vec *)((uint16_t *)p.Y + (size_t)row * N + ncol) = o;
             }
         } else {
             float *y = (float *)p.Y + (size_t)row * N + ncol;
-            *(f32x4 *)y = f32x4{v[0], v[1], v[2], v[3]};
-            *(f32x4 *)(y + 4) = f32x4{v[4], v[5], v[6], v[7]};
+            if constexpr (CPL == 2) {
+                typedef float f32x2 __attribute__((ext_vector_type(2)));
+                *(f32x2 *)y = f32x2{v[0], v[1]};
+            } else {
+#pragma unroll
+                for (int j = 0; j < CPL; j += 4) *(f32x4 *)(y + j) = f32x4{v[j], v[j + 1], v[j + 2], v[j + 3]};
+            }
         }
     }
 }

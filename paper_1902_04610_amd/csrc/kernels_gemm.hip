@@ -31,6 +31,26 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16(GroupArgs a)
     else dense_bf16_tile<MT, TW, NT>(p, tile, lds);
 }
 
+// 16 * CPL columns per workgroup, for launches with few jobs of up to 32 rows: what a launch lasts is then how long one
+// compute unit streams one tile, so the tile is narrow and there are more of them.  A wavefront's k-step is only CPL / 8
+// of 8 KB: deep layers keep DEEP of them in flight instead of two.
+constexpr uint32_t kNarrowDeepK = 2048;
+template <int MT, bool TW, int CPL, int DEEP>
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(GroupArgs a)
+{
+    __shared__ float lds[reduce_lds_floats<MT * CPL>()];
+    const Tile tile = find_tile<16 * MT, 16 * CPL>(a);
+    const Problem &p = a.p[tile.problem];
+    const bool one = MT == 2 && p.M <= 16;
+    if (p.K > kNarrowDeepK) {
+        if (one) dense_bf16_tile<1, TW, true, CPL, DEEP>(p, tile, lds);
+        else dense_bf16_tile<MT, TW, true, CPL, DEEP>(p, tile, lds);
+    } else {
+        if (one) dense_bf16_tile<1, TW, true, CPL>(p, tile, lds);
+        else dense_bf16_tile<MT, TW, true, CPL>(p, tile, lds);
+    }
+}
+
 // 64-row tiles of 128 columns for deep layers of jobs with 33 .. 64 rows: every weight passes through a
 // compute unit once.  Two workgroups per compute unit (registers capped accordingly), so that one
 // workgroup's reduction and epilogue overlap the other's stream.
@@ -130,6 +150,17 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
         const bool ring = tiled_shape_fits(p[i]);
         (p[i].M <= 32 ? small : ring && (p[i].M <= 128 || trans_w) ? mid : large).push_back(p[i]);
     }
+    uint64_t small_tiles = 0;
+    for (const Problem &q : small) small_tiles += (q.N + 127) / 128;
+    if (trans_w && small_tiles * 4 > kFullGrid) {
+        // Input gradients of 17 .. 32 rows take the ring too, unless 32-column tiles do (below).  Training step, 8 jobs x 32
+        // rows, 2048-wide layers: 360 us against 375; 2 jobs x 24 rows: 146 against 140, so not there.
+        std::vector<Problem> rest;
+        for (const Problem &q : small) (q.M > 16 && tiled_shape_fits(q) ? mid : rest).push_back(q);
+        small.swap(rest);
+        small_tiles = 0;
+        for (const Problem &q : small) small_tiles += (q.N + 127) / 128;
+    }
     auto launch_wide = [&](int mt, const GroupArgs &a, uint32_t tiles) {
         const dim3 grid(tiles), block(kGemmThreads);
         bool one_row_tile = true;      // else several row tiles read the same weights: plain loads, L2 serves the others
@@ -142,8 +173,32 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
         else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16<1, true, true>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((grouped_dense_bf16<1, false, true>), grid, block, 0, stream, a);
     };
-    if (!small.empty())
-        if (hipError_t e = launch_groups(small.data(), (uint32_t)small.size(), 128, 16, 32, launch_wide, launches)) return e;
+    if (!small.empty()) {
+        // As many workgroups as compute units, not more: a narrower tile streams less efficiently.  128 / 64 / 32 columns:
+        // one job, 4096 -> 1024: 21.4 / 16.3 / 12.7 us (8 / 16 / 32 workgroups; with two k-steps in flight 18.3 / 15.3),
+        // 1024 -> 4096 8.8 / 7.4 / 6.6; 2048 -> 2048 of 4 jobs 20.3 / 16.2 / 14.5, of 8 jobs 18.3 / 15.5 / 20.9, of 16 jobs
+        // 25.6 / 28.8 / 43.6.
+        auto launch_64 = [&](int mt, const GroupArgs &a, uint32_t tiles) {
+            const dim3 grid(tiles), block(kGemmThreads);
+            if (mt == 2 && trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, true, 4, 4>), grid, block, 0, stream, a);
+            else if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 4, 4>), grid, block, 0, stream, a);
+            else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, true, 4, 4>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 4, 4>), grid, block, 0, stream, a);
+        };
+        auto launch_32 = [&](int mt, const GroupArgs &a, uint32_t tiles) {
+            const dim3 grid(tiles), block(kGemmThreads);
+            if (mt == 2 && trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, true, 2, 8>), grid, block, 0, stream, a);
+            else if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 8>), grid, block, 0, stream, a);
+            else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, true, 2, 8>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 2, 8>), grid, block, 0, stream, a);
+        };
+        const Problem *q = small.data();
+        const uint32_t count = (uint32_t)small.size();
+        const hipError_t e = small_tiles * 4 <= kFullGrid   ? launch_groups(q, count, 32, 16, 32, launch_32, launches)
+                             : small_tiles * 2 <= kFullGrid ? launch_groups(q, count, 64, 16, 32, launch_64, launches)
+                                                            : launch_groups(q, count, 128, 16, 32, launch_wide, launches);
+        if (e != hipSuccess) return e;
+    }
     if (!mid.empty()) {
         uint64_t wide_tiles = 0;
         for (const Problem &q : mid) wide_tiles += (uint64_t)((q.M + 63) / 64) * ((q.N + 127) / 128);

@@ -108,3 +108,20 @@ def test_equal_shifts_move_as_one(shift_mb, blocks):
             assert q.persist_off == sum(sizes[again + 1:i])
             assert salus.check_pattern(dp.buf.data_ptr() + q.persist_off, sizes[i], 100 + i, scratch.data_ptr()) == 0
     dp.close()
+
+
+@pytest.mark.parametrize("M", [1, 16, 17, 32])
+@pytest.mark.parametrize("copies", [1, 9, 17])
+def test_few_jobs_take_narrow_tiles(M, copies):
+    """1, 9, 17 copies of three shapes: 32-, 64- and 128-column tiles in the wider layers."""
+    shapes = [((8, 8), False), ((2120, 1000), False), ((136, 512, 384, 72), True)]
+    specs = [dict(M=M, dims=d, acts=[GELU] * (len(d) - 2) + [RELU], strip=s) for d, s in shapes]
+    outs, refs, _ = run_jobs(specs * copies, salus.BF16)
+    for o, r, j in zip(outs, refs, specs * copies):
+        assert np.isfinite(o).all() and norm_rel_err(o, r) < TOL_BF16_TIGHT, (j, norm_rel_err(o, r))
+
+
+@pytest.mark.parametrize("configs", [[((136, 520, 264, 72), 20, 0.05)], [((264, 1032, 72), 24, 0.05)] * 9, [((2104, 136, 40), 9, 0.05)]])
+def test_input_gradients_of_few_rows(configs):
+    """Narrow tiles of the transposed product, and the ring from 17 rows with enough jobs."""
+    run_training(configs, steps=1, seed=5)
