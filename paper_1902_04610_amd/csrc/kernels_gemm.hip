@@ -61,12 +61,18 @@ __global__ __launch_bounds__(kGemmThreads, 2) void grouped_dense_bf16_rows64(Gro
     dense_bf16_tile<4, false, true>(a.p[tile.problem], tile, lds);
 }
 
+// Row tiles of 16 * MT rows; the last one of a job computes only as many 16-row blocks as it needs (the sums of a row do not
+// depend on how many there are).
 template <int MT>
 __global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(GroupArgs a)
 {
     __shared__ float lds[reduce_lds_floats<MT * 4>()];
     const Tile tile = find_tile<16 * MT, 64>(a);
-    dense_f32_tile<MT>(a.p[tile.problem], tile, lds);
+    const Problem &p = a.p[tile.problem];
+    const uint32_t rows = p.M - tile.m0;
+    if (MT > 1 && rows <= 16) dense_f32_tile<1>(p, tile, lds);
+    else if (MT > 2 && rows <= 32) dense_f32_tile<2>(p, tile, lds);
+    else dense_f32_tile<MT>(p, tile, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -225,7 +231,21 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
         else
             hipLaunchKernelGGL(grouped_dense_f32<4>, dim3(tiles), dim3(kGemmThreads), 0, stream, a);
     };
-    return launch_groups(p, n, 64, 16, 32, launch, launches);
+    // Float multiplies are what a 64-row tile takes long for (16 x 16 x 4 per instruction), so rows are spread over
+    // workgroups as long as two per compute unit hold them: 16-row tiles, else 64-row tiles while those leave compute
+    // units idle, else 32-row tiles.  16 / 32 / 64 rows per tile: 12 jobs x 1 - 128 rows, 516 -> 1204 -> 780 -> 388: 50 / 50 /
+    // 70 us; one job x 64 rows, 1024 -> 1024 8.8 / 12.7 / 21.3; 12 jobs x 128 rows, 1536 -> 1536 88 / 80 / 89, 4 jobs 33 /
+    // 33 / 32.
+    uint64_t tiles_16 = 0, tiles_64 = 0;
+    uint32_t max_m = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        const uint64_t cols = (p[i].N + 63) / 64;
+        tiles_16 += (p[i].M + 15) / 16 * cols;
+        tiles_64 += (p[i].M + 63) / 64 * cols;
+        max_m = std::max(max_m, p[i].M);
+    }
+    const int mt = tiles_16 <= 2 * kFullGrid ? 1 : max_m > 128 || tiles_64 <= kFullGrid ? 0 : max_m > 16 ? 2 : 1;
+    return launch_groups(p, n, 64, 16, 32, launch, launches, mt);
 }
 
 }  // namespace salus

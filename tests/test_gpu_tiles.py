@@ -6,7 +6,7 @@ import torch
 from oracle import dense
 from paper_1902_04610_amd import salus, synth
 from gpu_util import DevicePool, mlp_layout, norm_rel_err
-from test_gpu_kernels import GELU, NONE, RELU, TOL_BF16_TIGHT, run_jobs
+from test_gpu_kernels import GELU, NONE, RELU, TOL_BF16_TIGHT, TOL_F32, run_jobs
 from test_gpu_train import run as run_training
 
 pytestmark = pytest.mark.gpu
@@ -125,3 +125,12 @@ def test_few_jobs_take_narrow_tiles(M, copies):
 def test_input_gradients_of_few_rows(configs):
     """Narrow tiles of the transposed product, and the ring from 17 rows with enough jobs."""
     run_training(configs, steps=1, seed=5)
+
+
+@pytest.mark.parametrize("jobs, M", [(1, 16), (1, 17), (3, 64), (3, 65), (40, 33), (40, 66), (2, 200)])
+def test_float_row_tiles(jobs, M):
+    """16-, 32- and 64-row tiles, and last tiles that compute only the 16-row blocks they need."""
+    specs = [dict(M=max(1, M - 15 * (i % 4)), dims=(132, 68 + 260 * (i % 3), 64), acts=[GELU, RELU]) for i in range(jobs)]
+    outs, refs, _ = run_jobs(specs, salus.F32)
+    for o, r, j in zip(outs, refs, specs):
+        assert np.isfinite(o).all() and norm_rel_err(o, r) < TOL_F32, (j, norm_rel_err(o, r))
