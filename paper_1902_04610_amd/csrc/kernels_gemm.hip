@@ -5,8 +5,8 @@
 // its job with a wavefront scan over the per-job tile counts.
 //
 // Shape of the work: per job Y[M x N] = act(X[M x K] . W[K x N]) with M small
-// (1..64 rows) and W read straight out of the job's persistent block.  Every
-// weight is used once per launch, so the kernel is a weight-streaming kernel:
+// (1..32 rows, 64 for deep layers; larger ones go to kernels_gemm_tiled.hip) and
+// W read straight out of the job's persistent block.  Every weight is used once per launch, so the kernel is a weight-streaming kernel:
 // W goes HBM -> registers with 16-byte loads (no LDS staging: nothing would be
 // reused), each wavefront keeps two k-steps of loads in flight, the 8x8 bf16
 // sub-blocks are transposed in registers into MFMA operand order, and the four

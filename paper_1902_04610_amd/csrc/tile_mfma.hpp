@@ -2,7 +2,7 @@
 // operands, float sums, v_mfma_f32_32x32x16_bf16, operands streamed HBM -> LDS -> registers.
 //
 // What bounds it: the matrix pipes, if everything else stays out of their way.  So
-//   - operands go from memory straight into LDS (global_load_lds_dwordx4): no staging registers, no LDS
+//   - operands go from memory straight into LDS (buffer_load_dwordx4 .. lds): no staging registers, no LDS
 //     stores, no address arithmetic in the loop (a scalar base that advances per slab + fixed 32-bit offsets, which the launcher keeps below 2 GB);
 //   - an operand whose contraction index is not its contiguous one (the K x N weights of a forward pass;
 //     both operands of H^T . G) is stored in LDS as it lies in memory and transposed on the way to the
