@@ -108,6 +108,7 @@ static hipError_t launch_groups(const Problem *p, uint32_t n, uint32_t tn, uint3
 // 65 rows if the jobs routed there make up at least one workgroup per CU (256).
 constexpr uint32_t kTiledAlways = 128, kTiledMaybe = 65;
 constexpr uint64_t kTiledMinGrid = 256;
+constexpr uint64_t kMixedMinGrid = 96;   // 128 x 256 tiles
 constexpr uint64_t kFullGrid = 256;      // one workgroup per compute unit
 constexpr uint32_t kDeepK = 1024;
 
@@ -121,8 +122,11 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
         for (uint32_t i = 0; i < n; ++i)
             if (p[i].M >= kTiledMaybe && tiled_shape_ok(p[i])) grid += tiled_tiles(p[i]);
         const uint32_t min_m = grid >= kTiledMinGrid ? kTiledMaybe : kTiledAlways;
-        // Deep layers of a round that mixes jobs of 33 .. 64 and of 65 .. 128 rows and has enough of them to fill the chip: all
-        // in one launch (64 models x 33 - 128 rows, 4096 -> 1024 / 1024 -> 4096 / 1024 -> 1024: 112 / 134 / 39 us against
+        // Deep layers of a round that mixes jobs of 33 .. 64 and of 65 .. 128 rows: all in one launch of the tiled kernel from
+        // 96 tiles of 128 x 256 (the 128 x 128 ones it may take instead then hold most compute units), below that through
+        // the ring.  Tiled / ring, 30 jobs x 33 - 87 rows, 3584 -> 1536 (180 tiles): 77 / 92 us, 1584 -> 776 (120): 28 / 36,
+        // 1536 -> 768 (90): 27 / 25; 20 jobs x 33 - 128 rows, 4096 -> 1024 (80): 55 / 47.  Two launches, one for each range
+        // of rows, never: 116, 52 and 47 us for the first three.  (64 models x 33 - 128 rows, 4096 -> 1024 / 1024 -> 4096 / 1024 -> 1024: 112 / 134 / 39 us against
         // 149 / 149 / 45 us with 64-row tiles, whose second row tile reads the weights again).
         uint64_t mid_grid = 0;
         bool above_64 = false;
@@ -132,7 +136,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
                 mid_grid += tiled_tiles(p[i]);
                 above_64 = above_64 || p[i].M > 64;
             }
-        const bool take_mid = above_64 && mid_grid >= kTiledMinGrid;
+        const bool take_mid = above_64 && mid_grid >= kMixedMinGrid;
         std::vector<Problem> tiled, streamed;
         for (uint32_t i = 0; i < n; ++i)
             ((p[i].M >= min_m && tiled_shape_ok(p[i])) || (take_mid && deep_mid(p[i])) ? tiled : streamed).push_back(p[i]);
@@ -207,10 +211,14 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
     }
     if (!mid.empty()) {
         uint64_t wide_tiles = 0;
-        for (const Problem &q : mid) wide_tiles += (uint64_t)((q.M + 63) / 64) * ((q.N + 127) / 128);
+        bool mixed = false;      // one launch for jobs below and above 64 rows
+        for (const Problem &q : mid) {
+            wide_tiles += (uint64_t)((q.M + 63) / 64) * ((q.N + 127) / 128);
+            mixed = mixed || q.M > 64;
+        }
         std::vector<Problem> deep, ring;
         for (const Problem &q : mid)
-            (wide_tiles >= kFullGrid && !trans_w && q.K >= kDeepK && q.M <= 64 ? deep : ring).push_back(q);
+            (wide_tiles >= kFullGrid && !trans_w && !mixed && q.K >= kDeepK ? deep : ring).push_back(q);
         if (!ring.empty())
             if (hipError_t e = launch_grouped_bf16_stream(ring.data(), (uint32_t)ring.size(), trans_w, stream, launches)) return e;
         if (!deep.empty())

@@ -316,19 +316,22 @@ static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n)
     return rounds * (work / tiles) / (t.per_cu == 2 && tiles <= cus ? 2 : 1);
 }
 
-// Launches bound by the weight stream.  64 x 128 tiles, two workgroups per compute unit; when those would not even be one
-// per compute unit, 64 x 64: twice the workgroups.  8 jobs x 64 rows, 2048 -> 2048: 15.4 us (registers-only kernel with K
+// Launches bound by the weight stream.  64 x 128 tiles, two workgroups per compute unit; 64 x 64, twice the workgroups,
+// while there is at most one of them per compute unit (transposed weights: while 64 x 128 would be fewer than one).  64 x
+// 128 / 64 x 64: 12 jobs x 64 rows, 2048 -> 1536 26 / 33 us, 20 jobs x 33 - 128 rows, 4096 -> 1024 47 / 56, 16 jobs x 33 -
+// 100 rows, 1536 -> 768 19 / 21, 8 jobs x 64 rows, 2048 -> 2048 with weights from memory 27 / 22.5.  8 jobs x 64 rows, 2048 -> 2048: 15.4 us (registers-only kernel with K
 // split over four wavefronts: 20.6; this tile without the split of the k-steps 17.5, with 64 x 128 tiles 19), input
 // gradients of the same layer 17 against 24; 8 jobs x 100 rows: 64 x 128 tiles, training step 386 us against 410 with 64
 // x 64.  Rings twice as deep with one workgroup per compute unit: 18.6.
 hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream, uint64_t *launches)
 {
-    uint64_t wide = 0;
+    uint64_t wide = 0, narrow = 0;
     for (uint32_t i = 0; i < n; ++i) {
         if (!tiled_shape_fits(p[i])) return hipErrorInvalidValue;
         wide += (uint64_t)((p[i].M + 63) / 64) * ((p[i].N + 127) / 128);
+        narrow += (uint64_t)((p[i].M + 63) / 64) * ((p[i].N + 63) / 64);
     }
-    const bool few = wide < resident_grid();
+    const bool few = trans_w ? wide < resident_grid() : narrow <= resident_grid();
     if (few && trans_w) return launch_tiled<64, 64, 2>(grouped_dense_bf16_stream<64, 64, 2, 1, 2, true, 4>, 256, p, n, stream, launches);
     if (few) return launch_tiled<64, 64, 2>(grouped_dense_bf16_stream<64, 64, 2, 1, 2, false, 4>, 256, p, n, stream, launches);
     if (trans_w) return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 1, true, 3>, 256, p, n, stream, launches);

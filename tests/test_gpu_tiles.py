@@ -61,6 +61,9 @@ def test_a_row_of_infinities_stays_in_its_row():
     (40, 100, 72, 1032, False),       # 64 x 128 tiles, 720 of them: workgroups walk two, fewer slabs than the ring has stages
     (30, 128, 264, 1152, True),
     (36, 70, 1032, 2056, False),      # deep, more than 64 rows, fills the chip: the compute-bound kernel takes them all
+    (16, 66, 1096, 1544, False),      # 112 tiles of 128 x 256, not enough to fill the chip: the same
+    (30, 87, 1096, 768, True),        # 90: one launch through the ring, of jobs on either side of 64 rows
+    (13, 64, 1032, 1288, False),      # 64 x 64 tiles would be 273, more than one per compute unit: 64 x 128
 ])
 def test_rows_33_to_128_through_the_ring(jobs, M, K, N, strip):
     specs = [dict(M=max(33, M - (i % 5) * 7), dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]], strip=strip) for i in range(jobs)]
