@@ -493,8 +493,8 @@ struct TileStream {
 #pragma unroll
                         for (int r = 0; r < 16; ++r)
                             if (kg) sums[(kg - 1) * kGroup + ((j * FM + i) * 16 + r) * 64] = acc[j][i][r];
-                __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
-                __builtin_amdgcn_s_barrier();
+                // clobbers memory, so that neither the stores above nor the loads below cross it
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
                 for (int g = 1; g < KS; ++g)
 #pragma unroll
