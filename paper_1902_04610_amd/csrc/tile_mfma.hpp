@@ -63,7 +63,7 @@ constexpr uint32_t kOutside = 0x80000000u;
 __device__ inline void dma16(uint32_t to, uint64_t base, uint32_t off)
 {
     const u32x4 buffer = {(uint32_t)base, (uint32_t)(base >> 32) & 0xffffu, kOutside, 0x00027000u};
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(buffer) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(buffer) : "m0", "memory");
 }
 
 __device__ inline uint64_t uniform64(uint64_t v)

@@ -44,3 +44,10 @@ def test_a_barrier_orders_memory_for_the_compiler(ir):
                 seen += 1
                 assert "~{memory}" in line, (f, line)
     assert seen > 10
+
+
+def test_direct_to_lds_loads_declare_m0(ir):
+    """The LDS address of such a load is passed in m0, which the compiler may be using for something else."""
+    asm = [line for lines in ir.values() for line in lines if "asm sideeffect" in line and " lds" in line]
+    assert len(asm) > 50
+    assert all("~{m0}" in line for line in asm if "m0" in line.split("~{")[0])
