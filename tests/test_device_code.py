@@ -22,6 +22,28 @@ def compile_device(source, out, *flags):
 
 
 @pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    """Kernels of each file: name -> instructions [(opcode, operands, text)], label -> index."""
+    d = tmp_path_factory.mktemp("asm")
+    with concurrent.futures.ThreadPoolExecutor(4) as pool:
+        list(pool.map(lambda f: compile_device(f, d / f), FILES))
+    kernels = {}
+    for f in FILES:
+        code, labels = None, None
+        for line in (d / f).read_text().splitlines():
+            line = line.split(";")[0].strip()
+            if m := re.match(r"(_Z\w+):$", line):
+                kernels[m.group(1)] = code, labels = [], {}
+            elif m := re.match(r"([.\w]+):$", line):
+                if labels is not None:
+                    labels[m.group(1)] = len(code)
+            elif line and code is not None and not line.startswith("."):
+                op, *rest = line.split(None, 1)
+                code.append((op, [a.split()[0] for a in rest[0].split(",")] if rest else [], line))
+    return kernels
+
+
+@pytest.fixture(scope="module")
 def ir(tmp_path_factory):
     """LLVM IR of each kernel file, as lines."""
     d = tmp_path_factory.mktemp("ir")
@@ -51,3 +73,40 @@ def test_direct_to_lds_loads_declare_m0(ir):
     asm = [line for lines in ir.values() for line in lines if "asm sideeffect" in line and " lds" in line]
     assert len(asm) > 50
     assert all("~{m0}" in line for line in asm if "m0" in line.split("~{")[0])
+
+
+def scalar_registers(operand):
+    if m := re.fullmatch(r"s\[(\d+):(\d+)\]", operand):
+        return set(range(int(m.group(1)), int(m.group(2)) + 1))
+    m = re.fullmatch(r"s(\d+)", operand)
+    return {int(m.group(1))} if m else set()
+
+
+def test_direct_to_lds_loads_keep_their_distance(assembly):
+    """A vector memory instruction may read a scalar register at the earliest five wait states after a vector instruction
+    (a lane read of an address or of a spilled register) wrote it.  The compiler inserts waits in its own code, but
+    not in front of an asm statement: every path into one is looked at here (s_nop n is n + 1 wait states)."""
+    loads = 0
+    for name, (code, labels) in assembly.items():
+        before = [[] for _ in code]
+        for i, (op, args, _) in enumerate(code):
+            if op.startswith(("s_branch", "s_cbranch")) and labels.get(args[0], len(code)) < len(code):
+                before[labels[args[0]]].append(i)
+            if op not in ("s_branch", "s_endpgm") and i + 1 < len(code):
+                before[i + 1].append(i)
+        for i, (op, args, text) in enumerate(code):
+            if not (op.startswith("buffer_load") and text.endswith("lds")):
+                continue
+            loads += 1
+            reads = scalar_registers(args[1])
+            assert len(reads) == 4, text
+            walk, nearest = [(j, 0) for j in before[i]], {}
+            while walk:
+                j, waits = walk.pop()
+                if waits >= 5 or nearest.get(j, 5) <= waits:
+                    continue
+                nearest[j] = waits
+                op_j, args_j, text_j = code[j]
+                assert not (op_j.startswith("v_") and args_j and scalar_registers(args_j[0]) & reads), (name, text_j, text, waits)
+                walk += [(k, waits + (int(args_j[0], 0) + 1 if op_j == "s_nop" else 1)) for k in before[j]]
+    assert loads > 50
