@@ -60,11 +60,16 @@ __device__ inline int fresh_lane()
 // 16 bytes per lane from base + off to LDS at `to` + 16 * lane; zeros where off is kOutside.  A raw buffer descriptor of
 // 2 GB: the hardware's range check is the mask of the contraction's tail.
 constexpr uint32_t kOutside = 0x80000000u;
+// m0 (the LDS address) is reserved: the compiler sets it where it needs it and keeps nothing there, but it may take two
+// equal settings for one unless it knows that the register changes in between.  It warns about any reserved register.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ inline void dma16(uint32_t to, uint64_t base, uint32_t off)
 {
     const u32x4 buffer = {(uint32_t)base, (uint32_t)(base >> 32) & 0xffffu, kOutside, 0x00027000u};
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(buffer) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 
 __device__ inline uint64_t uniform64(uint64_t v)
 {
