@@ -146,34 +146,61 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
     // The four wavefronts take k-steps wave, wave+4, ...: this wavefront owns
     // `mine` steps.  D steps are in flight at any time; the last (fewer than 2 D)
     // steps are peeled so that the main loop never loads past the end.
-    wvec w[D][NROW];
-    u32x4 x[D][MT];
-    bool ok[D];
     const int mine = nsteps > wave ? (nsteps - wave + kWaves - 1) / kWaves : 0;
     auto step = [&](int i) { return wave + kWaves * i; };
-#pragma unroll
-    for (int d = 0; d < D; ++d) load(step(d), w[d], x[d], ok[d]);
-    int i = 0;
-    for (; i + 2 * D <= mine; i += D) {
-        // keep the instruction scheduler from sinking the loads below the next
-        // multiply phase: each phase must stay where it is written
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            compute(w[d], x[d], ok[d]);
+    if constexpr (D == 2) {
+        // Not the loop below with D = 2: in that form the 64-row tile (MT = 4, capped at 256 registers) spills 11 of them, and a reload
+        // inside the loop waits for all weights in flight (64 models x 48 / 64 rows of 1024 - 4096 - 1024 - 1024: 292 / 308 us
+        // a round against 251 / 270 us in this form, which just fits).
+        wvec w0[NROW], w1[NROW];
+        u32x4 x0[MT], x1[MT];
+        bool ok0, ok1;
+        load(step(0), w0, x0, ok0);
+        load(step(1), w1, x1, ok1);
+        int i = 0;
+        for (; i + 3 < mine; i += 2) {
+            // keep the instruction scheduler from sinking the loads below the next
+            // multiply phase: each phase must stay where it is written
+            compute(w0, x0, ok0);
             __builtin_amdgcn_sched_barrier(0);
-            load(step(i + d + D), w[d], x[d], ok[d]);
+            load(step(i + 2), w0, x0, ok0);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(w1, x1, ok1);
+            __builtin_amdgcn_sched_barrier(0);
+            load(step(i + 3), w1, x1, ok1);
             __builtin_amdgcn_sched_barrier(0);
         }
-    }
-    const int left = mine - i;
+        const int left = mine - i;
+        if (left >= 1) compute(w0, x0, ok0);
+        if (left == 3) load(step(i + 2), w0, x0, ok0);
+        if (left >= 2) compute(w1, x1, ok1);
+        if (left == 3) compute(w0, x0, ok0);
+    } else {
+        wvec w[D][NROW];
+        u32x4 x[D][MT];
+        bool ok[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        if (d < left) compute(w[d], x[d], ok[d]);
-        if (d + D < left) load(step(i + d + D), w[d], x[d], ok[d]);
-    }
+        for (int d = 0; d < D; ++d) load(step(d), w[d], x[d], ok[d]);
+        int i = 0;
+        for (; i + 2 * D <= mine; i += D) {
 #pragma unroll
-    for (int d = 0; d < D; ++d)
-        if (d + D < left) compute(w[d], x[d], ok[d]);
+            for (int d = 0; d < D; ++d) {
+                compute(w[d], x[d], ok[d]);
+                __builtin_amdgcn_sched_barrier(0);
+                load(step(i + d + D), w[d], x[d], ok[d]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const int left = mine - i;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            if (d < left) compute(w[d], x[d], ok[d]);
+            if (d + D < left) load(step(i + d + D), w[d], x[d], ok[d]);
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d + D < left) compute(w[d], x[d], ok[d]);
+    }
 
     float own[NACC];
     reduce_scatter<NACC>(acc, own, lds);

@@ -23,11 +23,11 @@ def compile_device(source, out, *flags):
 
 @pytest.fixture(scope="module")
 def assembly(tmp_path_factory):
-    """Kernels of each file: name -> instructions [(opcode, operands, text)], label -> index."""
+    """Kernels of all files: name -> instructions [(opcode, operands, text)], label -> index; "remarks": what they use."""
     d = tmp_path_factory.mktemp("asm")
     with concurrent.futures.ThreadPoolExecutor(4) as pool:
-        list(pool.map(lambda f: compile_device(f, d / f), FILES))
-    kernels = {}
+        remarks = list(pool.map(lambda f: compile_device(f, d / f, "-Rpass-analysis=kernel-resource-usage"), FILES))
+    kernels = {"remarks": "".join(remarks)}
     for f in FILES:
         code, labels = None, None
         for line in (d / f).read_text().splitlines():
@@ -87,7 +87,7 @@ def test_direct_to_lds_loads_keep_their_distance(assembly):
     (a lane read of an address or of a spilled register) wrote it.  The compiler inserts waits in its own code, but
     not in front of an asm statement: every path into one is looked at here (s_nop n is n + 1 wait states)."""
     loads = 0
-    for name, (code, labels) in assembly.items():
+    for name, (code, labels) in ((n, k) for n, k in assembly.items() if n != "remarks"):
         before = [[] for _ in code]
         for i, (op, args, _) in enumerate(code):
             if op.startswith(("s_branch", "s_cbranch")) and labels.get(args[0], len(code)) < len(code):
@@ -110,3 +110,12 @@ def test_direct_to_lds_loads_keep_their_distance(assembly):
                 assert not (op_j.startswith("v_") and args_j and scalar_registers(args_j[0]) & reads), (name, text_j, text, waits)
                 walk += [(k, waits + (int(args_j[0], 0) + 1 if op_j == "s_nop" else 1)) for k in before[j]]
     assert loads > 50
+
+
+def test_no_kernel_spills_vector_registers(assembly):
+    """A reload from scratch memory waits for every load in flight: in a loop that streams weights it empties the pipe."""
+    names = re.findall(r"Function Name: (\S+)", assembly["remarks"])
+    scratch = re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", assembly["remarks"])
+    spills = re.findall(r"VGPRs Spill: (\d+)", assembly["remarks"])
+    assert len(names) == len(scratch) == len(spills) > 30
+    assert not [t for t in zip(names, scratch, spills) if t[1:] != ("0", "0")]
