@@ -167,14 +167,15 @@ __global__ __launch_bounds__(64 * WM * WN * KS, WM * WN * KS / 2) void grouped_d
 }
 
 // Jobs of at least this many rows (at most a quarter of the last of their 256-row tiles is padding) may take any of the
-// tiles; smaller ones take 128-row tiles in a launch of their own.
+// tiles; smaller ones take 128-row tiles.
 constexpr uint32_t kTiled256MinM = 192;
 
-// A depth that is no multiple of a slab costs the padding of its last slab and, below three slabs, whole slabs of zeros: such
-// layers come here only from 192 rows and 192 deep (3 jobs x 300 - 700 rows, 520 -> 1000 -> 776: 54 us for the two layers).
-bool tiled_shape_ok(const Problem &p)
+bool tiled_shape_ok(const Problem &p) { return tiled_shape_fits(p) && p.K % kSlab == 0; }
+// A depth that is no multiple of a slab costs the padding of the last slab and, below three slabs, whole slabs of zeros:
+// such layers come here only if they are three slabs deep and the round has enough of them (launch_grouped_bf16).
+bool tiled_shape_ragged(const Problem &p)
 {
-    return tiled_shape_fits(p) && (p.K % kSlab == 0 || (p.M >= kTiled256MinM && p.K >= kMinSlabs * kSlab));
+    return tiled_shape_fits(p) && p.M > 128 && p.K % kSlab != 0 && p.K >= kMinSlabs * kSlab;
 }
 bool tiled_shape_fits(const Problem &p)
 {
@@ -338,21 +339,46 @@ hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w
     return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 1, false, 3>, 256, p, n, stream, launches);
 }
 
+// The tile for these jobs (256 rows only if all have the rows for it) and the time it takes.
+struct TileChoice { const TileKind *kind; uint64_t ns; };
+static TileChoice choose_tile(const std::vector<Problem> &p, bool tall)
+{
+    TileChoice best{nullptr, ~0ull};
+    for (const TileKind *t : {&kTile256, &kTile128x256, &kTile128}) {
+        if (t == &kTile256 && !tall) continue;
+        const uint64_t ns = launch_ns(*t, p.data(), (uint32_t)p.size());
+        if (ns < best.ns) best = {t, ns};
+    }
+    return best;
+}
+
 hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
 {
     for (uint32_t i = 0; i < n; ++i)
         if (!tiled_shape_fits(p[i])) return hipErrorInvalidValue;
     std::vector<Problem> big, small;
     for (uint32_t i = 0; i < n; ++i) (p[i].M >= kTiled256MinM ? big : small).push_back(p[i]);
+    TileChoice tall = choose_tile(big, true);
+    const TileChoice low = choose_tile(small, false);
+    if (!big.empty() && !small.empty()) {
+        // Jobs on either side of 192 rows: one launch of 128-row tiles, unless two launches are quicker even though each
+        // ends with a round of its own.  16 jobs x 129 - 260 rows, 2056 -> 520: 21 us, in two launches 42.
+        const std::vector<Problem> all(p, p + n);
+        const TileChoice one = choose_tile(all, false);
+        if (one.ns <= tall.ns + low.ns) {
+            big = all;
+            small.clear();
+            tall = one;
+        }
+    }
     for (const std::vector<Problem> *group : {&big, &small}) {
+        if (group->empty()) continue;
         const Problem *q = group->data();
         const uint32_t count = (uint32_t)group->size();
-        if (count == 0) continue;
-        const uint64_t t0 = group == &big ? launch_ns(kTile256, q, count) : ~0ull;
-        const uint64_t t1 = launch_ns(kTile128x256, q, count), t2 = launch_ns(kTile128, q, count);
-        const hipError_t e = t0 <= t1 && t0 <= t2 ? launch_tiled<256, 256, 1>(grouped_dense_bf16_tiled<256, 256, 2, 4>, 512, q, count, stream, launches)
-                             : t1 <= t2           ? launch_tiled<128, 256, 1>(grouped_dense_bf16_tiled<128, 256, 2, 4>, 512, q, count, stream, launches)
-                                                  : launch_tiled<128, 128, 2>(grouped_dense_bf16_tiled<128, 128, 2, 2>, 256, q, count, stream, launches);
+        const TileKind *kind = group == &big ? tall.kind : low.kind;
+        const hipError_t e = kind == &kTile256       ? launch_tiled<256, 256, 1>(grouped_dense_bf16_tiled<256, 256, 2, 4>, 512, q, count, stream, launches)
+                             : kind == &kTile128x256 ? launch_tiled<128, 256, 1>(grouped_dense_bf16_tiled<128, 256, 2, 4>, 512, q, count, stream, launches)
+                                                     : launch_tiled<128, 128, 2>(grouped_dense_bf16_tiled<128, 128, 2, 2>, 256, q, count, stream, launches);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
