@@ -360,10 +360,11 @@ hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t s
     for (uint32_t i = 0; i < n; ++i) (p[i].M >= kTiled256MinM ? big : small).push_back(p[i]);
     TileChoice tall = choose_tile(big, true);
     const TileChoice low = choose_tile(small, false);
-    if (!big.empty() && !small.empty()) {
-        // Jobs on either side of 192 rows: one launch of 128-row tiles, unless two launches are quicker even though each
-        // ends with a round of its own.  16 jobs x 129 - 260 rows, 2056 -> 520: 21 us, in two launches 42.
-        const std::vector<Problem> all(p, p + n);
+    const std::vector<Problem> all(p, p + n);
+    if (!big.empty() && !small.empty() && std::any_of(all.begin(), all.end(), tiled_shape_ragged)) {
+        // Jobs on either side of 192 rows, ragged ones among them (whose alternative, register tiles, is one launch): one
+        // launch of 128-row tiles, unless two are quicker even though each ends with a round of its own.  16 jobs x
+        // 129 - 260 rows, 2056 -> 520: 21 us, in two launches 42.
         const TileChoice one = choose_tile(all, false);
         if (one.ns <= tall.ns + low.ns) {
             big = all;
