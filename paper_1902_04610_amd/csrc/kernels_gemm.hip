@@ -31,11 +31,11 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16(GroupArgs a)
     else dense_bf16_tile<MT, TW, NT>(p, tile, lds);
 }
 
-// 16 * CPL columns per workgroup, for launches with few jobs of up to 32 rows: what a launch lasts is then how long one
+// 16 * CPL columns per workgroup, for launches with few jobs: what a launch lasts is then how long one
 // compute unit streams one tile, so the tile is narrow and there are more of them.  A wavefront's k-step is only CPL / 8
 // of 8 KB: deep layers keep DEEP of them in flight instead of two.
 constexpr uint32_t kNarrowDeepK = 2048;
-template <int MT, bool TW, int CPL, int DEEP>
+template <int MT, bool TW, int CPL, int DEEP, bool NT = true>
 __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(GroupArgs a)
 {
     __shared__ float lds[reduce_lds_floats<MT * CPL>()];
@@ -43,11 +43,11 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(GroupA
     const Problem &p = a.p[tile.problem];
     const bool one = MT == 2 && p.M <= 16;
     if (p.K > kNarrowDeepK) {
-        if (one) dense_bf16_tile<1, TW, true, CPL, DEEP>(p, tile, lds);
-        else dense_bf16_tile<MT, TW, true, CPL, DEEP>(p, tile, lds);
+        if (one) dense_bf16_tile<1, TW, NT, CPL, DEEP>(p, tile, lds);
+        else dense_bf16_tile<MT, TW, NT, CPL, DEEP>(p, tile, lds);
     } else {
-        if (one) dense_bf16_tile<1, TW, true, CPL>(p, tile, lds);
-        else dense_bf16_tile<MT, TW, true, CPL>(p, tile, lds);
+        if (one) dense_bf16_tile<1, TW, NT, CPL>(p, tile, lds);
+        else dense_bf16_tile<MT, TW, NT, CPL>(p, tile, lds);
     }
 }
 
@@ -226,6 +226,28 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
                              : small_tiles * 2 <= kFullGrid ? launch_groups(q, count, 64, 16, 32, launch_64, launches)
                                                             : launch_groups(q, count, 128, 16, 32, launch_wide, launches);
         if (e != hipSuccess) return e;
+    }
+    if (!mid.empty() && !trans_w) {
+        // Too few for the ring, whose workgroup walks all of K in a row of slabs: narrow 32-row tiles as above, K split over
+        // the wavefronts, as many workgroups as compute units.  Ring / narrow, one job x 33 rows, 1024 -> 64: 8.5 / 5.2 us
+        // (the 64 x 64 register tile that the ring replaced: 7.1), 4096 -> 1024 20.4 / 11.9 (16.5); 16 jobs x 33 rows,
+        // 128 -> 512, 64 columns: 6.1 / 4.5 (5.7); 10 jobs x 33 rows, 1024 -> 512 9.0 / 7.3 (7.8); beyond one per compute unit,
+        // 24 jobs x 65 rows, 1024 -> 512: 11.0 / 14.1.
+        uint64_t tiles_32 = 0, tiles_64 = 0;
+        for (const Problem &q : mid) {
+            tiles_32 += (uint64_t)((q.M + 31) / 32) * ((q.N + 31) / 32);
+            tiles_64 += (uint64_t)((q.M + 31) / 32) * ((q.N + 63) / 64);
+        }
+        if (tiles_64 <= kFullGrid) {
+            const bool narrowest = tiles_32 <= kFullGrid;
+            auto launch = [&](int, const GroupArgs &a, uint32_t tiles) {
+                const dim3 grid(tiles), block(kGemmThreads);
+                if (narrowest) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 8, false>), grid, block, 0, stream, a);
+                else hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 4, 4, false>), grid, block, 0, stream, a);
+            };
+            if (hipError_t e = launch_groups(mid.data(), (uint32_t)mid.size(), narrowest ? 32 : 64, 0, 0, launch, launches, 2)) return e;
+            mid.clear();
+        }
     }
     if (!mid.empty()) {
         uint64_t wide_tiles = 0;

@@ -96,3 +96,15 @@ def test_ragged_depth_many_tiles(record, many):
     """With enough of them, or beside jobs of other shapes: one launch of the tiled kernel, whatever the rows."""
     (log,) = record([many])
     assert len(kernels(log)) == 1 and kernels(log)[0].startswith("grouped_dense_bf16_tiled<")
+
+
+@pytest.mark.parametrize("rows, K, N, kernel", [
+    ([33], 1024, 64, "narrow<2, false, 2, 8, false>"), ([48] * 4, 64, 1024, "narrow<2, false, 2, 8, false>"),       # 32-column tiles
+    ([33, 127, 64], 4096, 1032, "narrow<2, false, 4, 4, false>"), ([33] * 16, 128, 512, "narrow<2, false, 4, 4, false>"),     # 64-column tiles
+    ([33] * 24, 1024, 512, "stream<64, 64, 2, 1, 2, false, 4>"), ([33] * 17, 128, 512, "stream<64, 64, 2, 1, 2, false, 4>"),
+    ([64] * 40, 520, 1032, "stream<64, 128, 2, 2, 1, false, 3>"), ([48] * 64, 1024, 4096, "rows64"),
+])
+def test_rows_33_to_128(record, rows, K, N, kernel):
+    """Narrow register tiles while there is at most one per compute unit, the ring or (deep, full) 64-row tiles beyond."""
+    (log,) = record([case(rows, K, N)])
+    assert kernels(log) == ["grouped_dense_bf16_" + kernel]

@@ -60,3 +60,20 @@ def test_a_row_of_infinities_stays_in_its_row_of_a_large_tile():
         assert not np.isfinite(Y[7]).any()
         assert norm_rel_err(Y[rows], ref[rows]) < TOL_BF16_TIGHT
     dp.close()
+
+
+@pytest.mark.parametrize("jobs, M, K, N, strip", [
+    (1, 33, 8, 8, False), (1, 128, 2056, 264, False), (3, 65, 1096, 264, True), (4, 64, 136, 1024, True),       # 32 columns, the last two to the tile
+    (1, 97, 2056, 2056, False), (16, 64, 128, 512, True), (3, 50, 520, 2056, False),        # 64 columns, deep and not
+    (17, 64, 128, 512, True), (8, 128, 264, 520, False), (16, 40, 72, 1000, False), (70, 33, 200, 136, False),       # the ring, 64 x 64 tiles
+    (9, 128, 72, 1032, True),                                                                # the ring, 64 x 128
+])
+def test_rows_33_to_128_around_the_ring(jobs, M, K, N, strip):
+    """Rows of a job's second tile read the same weights; some tiles begin in the middle of a strip of 128 columns."""
+    check([dict(M=max(33, M - 7 * (i % 4)), dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]], strip=strip) for i in range(jobs)],
+          1 if jobs <= 64 else 2)
+
+
+def test_hidden_layers_of_33_to_128_rows_in_narrow_tiles():
+    """bf16 hidden activations, written and read by narrow tiles."""
+    check([dict(M=m, dims=(136, 264, 72, 520), acts=[GELU, RELU, NONE], strip=False) for m in (33, 63, 64, 90, 127)], 3)
