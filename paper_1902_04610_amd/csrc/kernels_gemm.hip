@@ -117,7 +117,10 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
 {
     // Jobs with many rows reuse every weight often enough to pay for LDS staging:
     // they go to the tiled kernel, the rest of the round to the streaming kernel.
-    if (!trans_w) {
+    // (A round of small jobs takes less time on the device than on the host: no lists are built that it does not need.)
+    uint32_t max_m = 0;
+    for (uint32_t i = 0; i < n; ++i) max_m = std::max(max_m, p[i].M);
+    if (!trans_w && max_m > 32) {
         uint64_t grid = 0;
         for (uint32_t i = 0; i < n; ++i)
             if (p[i].M >= kTiledMaybe && tiled_shape_ok(p[i])) grid += tiled_tiles(p[i]);
@@ -154,11 +157,12 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
                 ragged_deep = ragged_deep && p[i].K > kNarrowDeepK;
             }
         const bool take_ragged = tiled_anyway || ragged_tiles > (ragged_deep ? kFullGrid * 5 / 4 : kFullGrid * 2);
-        std::vector<Problem> tiled, streamed;
-        for (uint32_t i = 0; i < n; ++i)
-            ((p[i].M >= min_m && tiled_shape_ok(p[i])) || (take_mid && deep_mid(p[i])) || (take_ragged && tiled_shape_ragged(p[i]))
-                 ? tiled : streamed).push_back(p[i]);
-        if (!tiled.empty()) {
+        auto takes_tiled = [&](const Problem &q) {
+            return (q.M >= min_m && tiled_shape_ok(q)) || (take_mid && deep_mid(q)) || (take_ragged && tiled_shape_ragged(q));
+        };
+        if (std::any_of(p, p + n, takes_tiled)) {
+            std::vector<Problem> tiled, streamed;
+            for (uint32_t i = 0; i < n; ++i) (takes_tiled(p[i]) ? tiled : streamed).push_back(p[i]);
             hipError_t e = launch_grouped_bf16_tiled(tiled.data(), (uint32_t)tiled.size(), stream, launches);
             if (e != hipSuccess || streamed.empty()) return e;
             return launch_grouped_bf16(streamed.data(), (uint32_t)streamed.size(), false, stream, launches);
@@ -174,6 +178,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
     // 128 x 128 tiles of the compute-bound kernel are within 2 % at 500 and 1024 rows and slower below); forward layers come
     // here only if K is no multiple of 64 and they are too few or too shallow for the tiled kernel, and get 32-row tiles.
     std::vector<Problem> small, mid, large;
+    (max_m <= 32 ? small : mid).reserve(n);
     for (uint32_t i = 0; i < n; ++i) {
         const bool ring = tiled_shape_fits(p[i]);
         (p[i].M <= 32 ? small : ring && (p[i].M <= 128 || trans_w) ? mid : large).push_back(p[i]);
@@ -256,9 +261,11 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
             wide_tiles += (uint64_t)((q.M + 63) / 64) * ((q.N + 127) / 128);
             mixed = mixed || q.M > 64;
         }
+        const bool full = wide_tiles >= kFullGrid && !trans_w && !mixed;
         std::vector<Problem> deep, ring;
-        for (const Problem &q : mid)
-            (wide_tiles >= kFullGrid && !trans_w && !mixed && q.K >= kDeepK ? deep : ring).push_back(q);
+        if (full)
+            for (const Problem &q : mid) (q.K >= kDeepK ? deep : ring).push_back(q);
+        else ring.swap(mid);
         if (!ring.empty())
             if (hipError_t e = launch_grouped_bf16_stream(ring.data(), (uint32_t)ring.size(), trans_w, stream, launches)) return e;
         if (!deep.empty())

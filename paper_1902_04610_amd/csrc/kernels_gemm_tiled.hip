@@ -344,6 +344,7 @@ struct TileChoice { const TileKind *kind; uint64_t ns; };
 static TileChoice choose_tile(const std::vector<Problem> &p, bool tall)
 {
     TileChoice best{nullptr, ~0ull};
+    if (p.empty()) return best;
     for (const TileKind *t : {&kTile256, &kTile128x256, &kTile128}) {
         if (t == &kTile256 && !tall) continue;
         const uint64_t ns = launch_ns(*t, p.data(), (uint32_t)p.size());
@@ -354,17 +355,21 @@ static TileChoice choose_tile(const std::vector<Problem> &p, bool tall)
 
 hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
 {
-    for (uint32_t i = 0; i < n; ++i)
-        if (!tiled_shape_fits(p[i])) return hipErrorInvalidValue;
     std::vector<Problem> big, small;
+    bool ragged = false;
+    for (uint32_t i = 0; i < n; ++i) {
+        if (!tiled_shape_fits(p[i])) return hipErrorInvalidValue;
+        ragged = ragged || tiled_shape_ragged(p[i]);
+    }
+    big.reserve(n);
     for (uint32_t i = 0; i < n; ++i) (p[i].M >= kTiled256MinM ? big : small).push_back(p[i]);
     TileChoice tall = choose_tile(big, true);
     const TileChoice low = choose_tile(small, false);
-    const std::vector<Problem> all(p, p + n);
-    if (!big.empty() && !small.empty() && std::any_of(all.begin(), all.end(), tiled_shape_ragged)) {
+    if (ragged && !big.empty() && !small.empty()) {
         // Jobs on either side of 192 rows, ragged ones among them (whose alternative, register tiles, is one launch): one
         // launch of 128-row tiles, unless two are quicker even though each ends with a round of its own.  16 jobs x
         // 129 - 260 rows, 2056 -> 520: 21 us, in two launches 42.
+        const std::vector<Problem> all(p, p + n);
         const TileChoice one = choose_tile(all, false);
         if (one.ns <= tall.ns + low.ns) {
             big = all;
