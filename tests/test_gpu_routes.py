@@ -5,7 +5,7 @@ import pytest
 from oracle import dense
 from paper_1902_04610_amd import salus, synth
 from gpu_util import DevicePool, mlp_layout, norm_rel_err
-from test_gpu_kernels import GELU, NONE, RELU, TOL_BF16_TIGHT, run_jobs
+from test_gpu_kernels import GELU, NONE, RELU, TOL_BF16_TIGHT, TOL_F32, run_jobs
 
 pytestmark = pytest.mark.gpu
 
@@ -77,3 +77,13 @@ def test_rows_33_to_128_around_the_ring(jobs, M, K, N, strip):
 def test_hidden_layers_of_33_to_128_rows_in_narrow_tiles():
     """bf16 hidden activations, written and read by narrow tiles."""
     check([dict(M=m, dims=(136, 264, 72, 520), acts=[GELU, RELU, NONE], strip=False) for m in (33, 63, 64, 90, 127)], 3)
+
+
+@pytest.mark.parametrize("jobs, M, K, N", [(12, 32, 132, 780), (60, 17, 68, 388), (26, 40, 1028, 964), (17, 64, 1032, 1536)])
+def test_float_rows_around_the_lines(jobs, M, K, N):
+    """32-row tiles of 17 .. 32 rows, and 64-row tiles of deep layers that fill the chip with one each."""
+    specs = [dict(M=max(17 if M <= 32 else 33, M - 5 * (i % 3)), dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]]) for i in range(jobs)]
+    outs, refs, n = run_jobs(specs, salus.F32)
+    assert n == 1
+    for o, r, j in zip(outs, refs, specs):
+        assert np.isfinite(o).all() and norm_rel_err(o, r) < TOL_F32, (j, norm_rel_err(o, r))
