@@ -21,11 +21,12 @@ constexpr uint32_t kCopyChunk = 8 * 1024;   // bytes one workgroup moves per gri
 hipError_t launch_copy(const CopySeg *segs, uint32_t n, hipStream_t stream, bool host_link = false);
 
 // State of the in-place slide kernel: one progress counter per resident workgroup (16 KB of device memory) and a
-// failure word in mapped host memory (allocated with the first in-place move).
+// failure word in mapped host memory (from a page that the process keeps).
 constexpr uint32_t kSlideMaxGrid = 4032;
+constexpr uint32_t kSlideEpochs = 1u << 30;     // from this epoch on the counters are cleared before the next launch
 struct SlideState {
     uint32_t *progress = nullptr;   // kSlideMaxGrid counters
-    uint32_t epoch = 0;             // no counter is above it between launches
+    uint32_t epoch = kSlideEpochs;  // no counter is above it between launches (at first: not cleared yet)
     uint32_t *failed = nullptr;     // set to 1 by a workgroup whose bounded wait ran out (host address)
     uint32_t *failed_dev = nullptr; // the same word as the kernel sees it
     uint32_t max_grid = 0;          // resident workgroups a launch may use (found at the first launch)

@@ -12,6 +12,7 @@
 // chunk (kCopyChunk bytes) per step, and all addressing is 64-bit (pools are far
 // larger than 4 GiB).
 #include <algorithm>
+#include <mutex>
 #include <vector>
 
 #include "device.hpp"
@@ -189,47 +190,97 @@ __global__ __launch_bounds__(kCopyThreads) void slide_down(char *dst, const char
     }
 }
 
+__global__ __launch_bounds__(kCopyThreads) void slide_clear(uint32_t *progress, uint32_t n)
+{
+    for (uint32_t i = threadIdx.x; i < n; i += kCopyThreads) progress[i] = 0;
+}
+
 static hipError_t launch_slide_down(char *dst, const char *src, uint64_t len, SlideState *st, hipStream_t stream)
 {
-    if (!st || !st->progress) return hipErrorInvalidValue;
+    if (!st || !st->progress || !st->failed) return hipErrorInvalidValue;
     const uint64_t chunks = (len + kSlideChunk - 1) / kSlideChunk;
     if (st->max_grid == 0) {
         int per_cu = 0, dev = 0, cus = 0;
         hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, slide_down, kCopyThreads, 0);
         if (e == hipSuccess) e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess && !st->failed) {
-            e = hipHostMalloc((void **)&st->failed, 64, hipHostMallocMapped | hipHostMallocPortable);
-            if (e == hipSuccess) *st->failed = 0;
-        }
-        if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&st->failed_dev, st->failed, 0);
-        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // the counters are cleared, also for streams that do not wait
         if (e != hipSuccess) return e;
         if (per_cu < 1 || cus < 1) return hipErrorInvalidValue;
         // two workgroups per compute unit keep 256 KB per unit in flight; more changes nothing
         st->max_grid = (uint32_t)std::min<int64_t>((int64_t)std::min(per_cu, 2) * cus, kSlideMaxGrid);
     }
+    // Counters run on from launch to launch: every counter is at most `epoch` when a launch begins (launches of one
+    // SlideState are ordered), so nothing has to be cleared in a launch of its own (5 us) except before the first one and
+    // long before the difference of a counter that rested and the epoch leaves 31 bits.
+    if (st->epoch >= kSlideEpochs) {
+        hipLaunchKernelGGL(slide_clear, dim3(1), dim3(kCopyThreads), 0, stream, st->progress, kSlideMaxGrid);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        st->epoch = 0;
+    }
     const uint32_t grid = (uint32_t)std::min<uint64_t>(chunks, st->max_grid);
     hipLaunchKernelGGL(slide_down, dim3(grid), dim3(kCopyThreads), 0, stream, dst, (const char *)src, len,
                        st->progress, st->epoch, st->failed_dev, st->spin_limit);
-    // Counters run on from launch to launch: every counter is at most `epoch` when a launch begins (launches of one
-    // SlideState are ordered), so nothing has to be cleared in a launch of its own.
     st->epoch += (uint32_t)((chunks + grid - 1) / grid);
     return hipGetLastError();
 }
+
+// Failure words in mapped host memory, which costs some 50 us to allocate: one page per process, kept, that pools take a word (a
+// 64-byte line) from and give it back to; further pages while more pools than it has lines exist.
+namespace {
+struct WordPage { char *host; uint64_t taken; };
+constexpr uint32_t kWordPage = 4096, kWordLine = kWordPage / 64;
+std::mutex &word_mutex = *new std::mutex;       // not destroyed at exit: a pool may be closed later than that
+std::vector<WordPage> &word_pages = *new std::vector<WordPage>;
+
+hipError_t take_word(uint32_t **out)
+{
+    std::lock_guard<std::mutex> lock(word_mutex);
+    auto page = std::find_if(word_pages.begin(), word_pages.end(), [](const WordPage &w) { return ~w.taken != 0; });
+    if (page == word_pages.end()) {
+        WordPage fresh{nullptr, 0};
+        const hipError_t e = hipHostMalloc((void **)&fresh.host, kWordPage, hipHostMallocMapped | hipHostMallocPortable);
+        if (e != hipSuccess) return e;
+        page = word_pages.insert(word_pages.end(), fresh);
+    }
+    const int line = __builtin_ctzll(~page->taken);
+    page->taken |= 1ull << line;
+    *out = (uint32_t *)(page->host + line * kWordLine);
+    **out = 0;
+    return hipSuccess;
+}
+
+void give_word(uint32_t *word)
+{
+    std::lock_guard<std::mutex> lock(word_mutex);
+    for (size_t i = 0; i < word_pages.size(); ++i) {
+        const ptrdiff_t at = (char *)word - word_pages[i].host;
+        if (at < 0 || at >= (ptrdiff_t)kWordPage) continue;
+        word_pages[i].taken &= ~(1ull << (at / kWordLine));
+        if (i > 0 && word_pages[i].taken == 0) {
+            (void)hipHostFree(word_pages[i].host);
+            word_pages.erase(word_pages.begin() + i);
+        }
+        return;
+    }
+}
+}  // namespace
 
 hipError_t slide_state_create(SlideState *st)
 {
     *st = SlideState{};
     hipError_t e = hipMalloc((void **)&st->progress, kSlideMaxGrid * sizeof(uint32_t));
-    if (e != hipSuccess) { st->progress = nullptr; return e; }
-    return hipMemset(st->progress, 0, kSlideMaxGrid * sizeof(uint32_t));
+    if (e != hipSuccess) st->progress = nullptr;
+    else e = take_word(&st->failed);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&st->failed_dev, st->failed, 0);
+    if (e != hipSuccess) slide_state_destroy(st);
+    return e;
 }
 
 void slide_state_destroy(SlideState *st)
 {
     if (st->progress) (void)hipFree(st->progress);
-    if (st->failed) (void)hipHostFree(st->failed);
+    if (st->failed) give_word(st->failed);
     st->progress = st->failed = st->failed_dev = nullptr;
 }
 

@@ -44,6 +44,40 @@ def forward(case):
     p.close()
     return out
 
+def compaction(case):
+    # two blocks above a hole smaller than either: one in-place move; then the same again above the next hole
+    p = pool(1 << 30, max_lanes=1)
+    created = take().decode()
+    for size in (1 << 20, 8 << 20, 2 << 20, 16 << 20):
+        assert p.lane_alloc(size, 4096, 0, 0)[0] == salus.OK
+    out = [created]
+    for job in (0, 2):
+        assert p.lane_free(job) >= 0
+        take()
+        assert len(p.compact()) >= 1
+        out.append(take().decode())
+    p.close()
+    return "====\n".join(out)
+
+class SlideState(ctypes.Structure):
+    _fields_ = [("progress", ctypes.c_void_p), ("epoch", ctypes.c_uint32), ("failed", ctypes.c_void_p), ("failed_dev", ctypes.c_void_p),
+                ("max_grid", ctypes.c_uint32), ("spin_limit", ctypes.c_uint32)]
+
+def slides(case):
+    lib = salus.lib()
+    state = SlideState()
+    assert lib._ZN5salus18slide_state_createEPNS_10SlideStateE(ctypes.byref(state)) == 0
+    one = lambda v: ctypes.byref(ctypes.c_uint64(v))
+    take()
+    out = []
+    for epoch in case["epochs"]:
+        if epoch is not None:
+            state.epoch = epoch
+        assert lib._ZN5salus12launch_slideEPcPKmS2_S2_jPNS_10SlideStateEP12ihipStream_tPm(
+            ctypes.c_void_p(BASE), one(4096), one(0), one(300 << 20), 1, ctypes.byref(state), ctypes.c_void_p(STREAM), None) == 0
+        out.append("%%d\n" %% state.epoch + take().decode())
+    return "====\n".join(out)
+
 CASES = json.load(sys.stdin)
 print(json.dumps([globals()[c["do"]](c) for c in CASES]))
 """ % STREAM
@@ -120,3 +154,26 @@ def test_float_row_tiles(record):
         ([40] * 20, 1536, 1536, 4), ([64] * 40, 1536, 1536, 4), ([128] * 40, 1024, 1024, 4), ([33] * 30, 1024, 1024, 4),     # whole rounds
         ([200] * 12, 516, 1204, 4),
     )])
+
+
+def test_a_compaction_allocates_nothing_and_waits_for_its_own_stream(record):
+    """The first in-place move of a pool like every other: what it needs was there when the pool was created."""
+    (log,) = record([dict(do="compaction")])
+    created, first, second = "\n".join(log).split("====\n")
+    assert "hipMalloc" in created
+    for lines in (first, second):
+        assert re.findall(r"^hip(?:Host)?(?:Malloc|Free).*", lines, re.M) == []
+        assert set(re.findall(r"^hip(?:Stream|Device)Synchronize.*", lines, re.M)) == {"hipStreamSynchronize %#x" % STREAM}
+    # counters are cleared by a launch on that stream, once
+    assert re.findall(r"launch (slide_\w+)", first) == ["slide_clear", "slide_down"]
+    assert re.findall(r"launch (slide_\w+)", second) == ["slide_down"]
+
+
+def test_counters_of_the_in_place_move_never_wrap(record):
+    """A workgroup's counter may rest for any number of launches; the difference to the epoch is taken in 32 bits with a sign."""
+    (log,) = record([dict(do="slides", epochs=[None, None, (1 << 30) - 1, None, None, (1 << 31) - 2, None])])
+    runs = [r.split("\n", 1) for r in "\n".join(log).split("====\n")]
+    assert all(0 < int(epoch) <= (1 << 30) + 16 for epoch, _ in runs)
+    assert [re.findall(r"launch (slide_\w+)", lines) for _, lines in runs] == \
+        [["slide_clear", "slide_down"], ["slide_down"], ["slide_down"], ["slide_clear", "slide_down"], ["slide_down"],
+         ["slide_clear", "slide_down"], ["slide_down"]]
