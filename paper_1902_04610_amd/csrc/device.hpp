@@ -75,10 +75,11 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
                                uint64_t *launches);
 // Jobs with many rows: LDS-tiled compute-bound kernel (256 x 256, 128 x 256 or 128 x 128 tiles, by launch).
 // tiled_shape_ok says whether a problem may go there (K a multiple of 64), tiled_shape_ragged whether it may in a round
-// with many such (other K), tiled_tiles how many workgroups it would occupy.
+// with many such (other K), tiled_shape_shallow whether the former needs many as well; tiled_tiles: workgroups it would occupy.
 bool tiled_shape_fits(const Problem &p);      // what the kernels can address at all
 bool tiled_shape_ok(const Problem &p);
 bool tiled_shape_ragged(const Problem &p);
+bool tiled_shape_shallow(const Problem &p);
 uint64_t tiled_tiles(const Problem &p);
 hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t stream,
                                      uint64_t *launches);

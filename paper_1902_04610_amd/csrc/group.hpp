@@ -11,6 +11,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 struct GroupArgs {
     uint32_t n;
     uint32_t tiles;      // all tiles of the launch (kernels whose workgroups loop over tiles)
+    uint32_t past_l2;    // the same kernels: float outputs whose rows begin on a line are stored past L2
+    uint32_t pad;
     Problem p[kMaxProblems];
 };
 

@@ -140,26 +140,28 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
                 above_64 = above_64 || p[i].M > 64;
             }
         const bool take_mid = above_64 && mid_grid >= kMixedMinGrid;
-        // Jobs of more than 128 rows whose K is no multiple of a slab: all of them in the tiled kernel if they hold more than two
-        // 32-row register tiles per compute unit (deeper than 2048: 1.25), else all in register tiles, which split
-        // K over wavefronts where a compute unit would walk a large tile alone.  Register / tiled, 1 job x 256 rows, 3080 -> 776
-        // (56 register tiles): 17.6 / 27.9 us, 1032 -> 72 8.0 / 12.4; 8 jobs x 129 rows, 776 -> 1016 (320) 10.9 / 11.6; 16 jobs (640)
-        // 17.4 / 13.0; 4 jobs x 600 rows, 3080 -> 776 (532) 46.6 / 31.1.  The rows do not matter beside that, and one rule for
-        // all of them keeps a round in one launch: 8 jobs x 100 - 400 rows, 1000 -> 3080 -> 776, 81 us against 111 us when
-        // those from 192 rows went to the tiled kernel and the others did not.  Beside jobs that take the tiled kernel
-        // anyway they join those, again for one launch.
-        uint64_t ragged_tiles = 0;
-        bool ragged_deep = true, tiled_anyway = false;
-        for (uint32_t i = 0; i < n; ++i)
-            if (p[i].M >= min_m && tiled_shape_ok(p[i])) tiled_anyway = true;
-            else if (tiled_shape_ragged(p[i])) {
-                ragged_tiles += (uint64_t)((p[i].M + 31) / 32) * ((p[i].N + 127) / 128);
-                ragged_deep = ragged_deep && p[i].K > kNarrowDeepK;
-            }
-        const bool take_ragged = tiled_anyway || ragged_tiles > (ragged_deep ? kFullGrid * 5 / 4 : kFullGrid * 2);
-        auto takes_tiled = [&](const Problem &q) {
-            return (q.M >= min_m && tiled_shape_ok(q)) || (take_mid && deep_mid(q)) || (take_ragged && tiled_shape_ragged(q));
+        // Jobs whose K is no multiple of a slab or at most 256: all of them in the tiled kernel if they hold more than two
+        // 32-row register tiles per compute unit (deeper than 2048: 1.25), else none: register tiles split K over wavefronts
+        // where a compute unit would walk a large tile alone.  Register / tiled, 1 job x 256 rows, 3080 -> 776 (56 register
+        // tiles): 17.6 / 27.9 us, 1032 -> 72 8.0 / 12.4; 8 jobs x 129 rows, 776 -> 1016 (320) 10.9 / 11.6, 16 jobs (640) 17.4 / 13.0; 4 jobs x
+        // 600 rows, 3080 -> 776 (532) 46.6 / 31.1; depths of 64 - 256, up to 512 tiles 0.36 - 1.00 of tiled, from 640 1.2 - 3.
+        // The rows do not matter beside that, and one rule for all of them keeps a round in one launch: 8 jobs x 100 - 400 rows,
+        // 1000 -> 3080 -> 776, 81 us against 111 us when those from 192 rows went to the tiled kernel and the others did not.
+        // Beside jobs that take the tiled kernel anyway they join those, again for one launch.
+        auto always = [&](const Problem &q) { return q.M >= min_m && tiled_shape_ok(q) && !tiled_shape_shallow(q); };
+        auto if_many = [&](const Problem &q) {
+            return tiled_shape_ragged(q) || (q.M >= min_m && tiled_shape_ok(q) && tiled_shape_shallow(q));
         };
+        uint64_t many_tiles = 0;
+        bool many_deep = true, tiled_anyway = false;
+        for (uint32_t i = 0; i < n; ++i)
+            if (always(p[i])) tiled_anyway = true;
+            else if (if_many(p[i])) {
+                many_tiles += (uint64_t)((p[i].M + 31) / 32) * ((p[i].N + 127) / 128);
+                many_deep = many_deep && p[i].K > kNarrowDeepK;
+            }
+        const bool many = tiled_anyway || many_tiles > (many_deep ? kFullGrid * 5 / 4 : kFullGrid * 2);
+        auto takes_tiled = [&](const Problem &q) { return always(q) || (take_mid && deep_mid(q)) || (many && if_many(q)); };
         if (std::any_of(p, p + n, takes_tiled)) {
             std::vector<Problem> tiled, streamed;
             for (uint32_t i = 0; i < n; ++i) (takes_tiled(p[i]) ? tiled : streamed).push_back(p[i]);
@@ -176,7 +178,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
     // for two workgroups per compute unit there, without which it was slower.  Above 128 rows transposed weights take
     // the ring as well (input gradients of 4 jobs x 500 rows, 2048 -> 2048: 40 us against 77 us with 32-row tiles; the
     // 128 x 128 tiles of the compute-bound kernel are within 2 % at 500 and 1024 rows and slower below); forward layers come
-    // here only if K is no multiple of 64 and they are too few or too shallow for the tiled kernel, and get 32-row tiles.
+    // here only if they are too few or too shallow for the tiled kernel, and get 32-row tiles.
     std::vector<Problem> small, mid, large;
     (max_m <= 32 ? small : mid).reserve(n);
     for (uint32_t i = 0; i < n; ++i) {

@@ -2,6 +2,7 @@
 // kernels.  Same contract (one launch runs one layer of every scheduled job, Salus paper, Section 3.3), but
 // here a weight is used by 128 or 256 rows per workgroup, so operands go through LDS (tile_mfma.hpp).
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "tile_mfma.hpp"
@@ -37,7 +38,7 @@ __device__ inline Tile find_tile_banded(const GroupArgs &a, uint32_t tile_id)
 
 // A wavefront's accumulators, whose first element is (m, n) of Y, to memory.  N is a multiple of 8, so a vector of 8
 // (bf16) or 4 (float) columns lies wholly inside or outside.
-template <int ACT, bool BF16, int FN, int FM, typename Landed>
+template <int ACT, bool BF16, bool PAST_L2, int FN, int FM, typename Landed>
 __device__ inline void store_dense(const Problem &p, uint32_t m, uint32_t n, const f32x16 (&acc)[FN][FM], int lane, Landed landed)
 {
     constexpr int J = BF16 ? 2 : 1;              // blocks of a line
@@ -94,7 +95,10 @@ __device__ inline void store_dense(const Problem &p, uint32_t m, uint32_t n, con
 #pragma unroll
                     for (int b = 0; b < 2; ++b) {
                         const uint32_t r_at = 32u * i + 16u * a + 8u * b + (lane & 7);
-                        if (r_at < rows && c < cols) *(f32x4 *)(Y + (r_at * pitch + c * 4u)) = o[a][b];
+                        if (!(r_at < rows && c < cols)) continue;
+                        f32x4 *y = (f32x4 *)(Y + (r_at * pitch + c * 4u));
+                        if constexpr (PAST_L2) __builtin_nontemporal_store(o[a][b], y);
+                        else *y = o[a][b];
                     }
             }
         }
@@ -131,15 +135,15 @@ struct DenseWalk {
         const uint32_t act = p.flags & 0xffu;
         m += at.m0;
         n += at.n0;
-        if (p.flags & kOutBf16) {
-            if (act == 1) store_dense<1, true>(p, m, n, acc, lane, landed);
-            else if (act == 2) store_dense<2, true>(p, m, n, acc, lane, landed);
-            else store_dense<0, true>(p, m, n, acc, lane, landed);
-        } else {
-            if (act == 1) store_dense<1, false>(p, m, n, acc, lane, landed);
-            else if (act == 2) store_dense<2, false>(p, m, n, acc, lane, landed);
-            else store_dense<0, false>(p, m, n, acc, lane, landed);
-        }
+        auto store = [&](auto bf16, auto past_l2) {
+            constexpr bool BF16 = decltype(bf16)::value, PAST = decltype(past_l2)::value;
+            if (act == 1) store_dense<1, BF16, PAST>(p, m, n, acc, lane, landed);
+            else if (act == 2) store_dense<2, BF16, PAST>(p, m, n, acc, lane, landed);
+            else store_dense<0, BF16, PAST>(p, m, n, acc, lane, landed);
+        };
+        if (p.flags & kOutBf16) store(std::true_type{}, std::false_type{});
+        else if (a.past_l2 && p.N % 32u == 0 && (uintptr_t)p.Y % 128u == 0) store(std::false_type{}, std::true_type{});
+        else store(std::false_type{}, std::false_type{});
     }
 };
 
@@ -171,12 +175,14 @@ __global__ __launch_bounds__(64 * WM * WN * KS, WM * WN * KS / 2) void grouped_d
 constexpr uint32_t kTiled256MinM = 192;
 
 bool tiled_shape_ok(const Problem &p) { return tiled_shape_fits(p) && p.K % kSlab == 0; }
-// A depth that is no multiple of a slab costs the padding of the last slab and, below three slabs, whole slabs of zeros:
-// such layers come here only if they are three slabs deep and the round has enough of them (launch_grouped_bf16).
+// A depth that is no multiple of a slab costs the padding of the last slab, and one of up to four slabs leaves prologue and
+// epilogue uncovered (below three there are whole slabs of zeros): such layers come here only if the round has enough
+// of them (launch_grouped_bf16), ragged ones only from three slabs.
 bool tiled_shape_ragged(const Problem &p)
 {
     return tiled_shape_fits(p) && p.M > 128 && p.K % kSlab != 0 && p.K >= kMinSlabs * kSlab;
 }
+bool tiled_shape_shallow(const Problem &p) { return p.K <= 4 * kSlab; }
 bool tiled_shape_fits(const Problem &p)
 {
     return p.K != 0 && p.K % 8 == 0 && p.N % 8 == 0 && p.K < kTiledMaxWidth && p.N < kTiledMaxWidth;
@@ -200,6 +206,13 @@ static hipError_t launch_tiled(Kernel kernel, int threads, const Problem *p, uin
         a.tiles = (uint32_t)tiles;
         // resident workgroups; a multiple of 8 so that the workgroups of an XCD keep to that XCD's range of tiles
         const uint32_t grid = (uint32_t)std::min<uint64_t>(tiles, resident_grid() * PER_CU);
+        // Float outputs are a model's results, not read again here: whole lines of them go past L2 (non-temporal), which
+        // bounds wide shallow layers.  16 jobs x 4096 rows, 1024 -> 4096: 578 us, with plain stores 644; 32 jobs x 1000
+        // rows, 256 -> 4096 131 / 174.  Not where rows do not begin on a line, whose pieces have to meet in L2 (256 -> 1000:
+        // 68 / 38, see finish), nor with one workgroup per compute unit in one to three rounds, where its next tile waits for
+        // the stores of the one before and nothing else covers that: 6 jobs x 1000 rows, 512 -> 4096, 1.09 of plain.  900
+        // launches of 200 - 4096 rows: 6 % less on average.
+        a.past_l2 = PER_CU == 2 || tiles < resident_grid() || tiles > 3 * (uint64_t)resident_grid();
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, a);
         if (launches) *launches += 1;
         hipError_t e = hipGetLastError();
@@ -298,11 +311,13 @@ hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStre
 // rounds x time of a round; a large tile moves fewer operand bytes per multiply but leaves the last round emptier
 // and pads more.  Times of a round in nanoseconds, a slab and the rest (prologue and epilogue), fitted to launches of
 // 16 jobs x 4096 rows, 4096 -> 1024 and 1024 -> 1024 (measured 489 / 163 us with 256 x 256 tiles, 545 / 186 with 128 x
-// 256, 626 / 206 with 128 x 128); with at most one 128 x 128 tile per compute unit a slab takes half as long.  What the
-// rule is for: 4 jobs x 500 rows, 2048 -> 2048: 50 / 33 / 26 us; 32 jobs x 300 - 1000 rows, 4096 -> 1024: 212 / 205 /
-// 235, 1024 -> 4096: 237 / 254 / 277.
+// 256, 626 / 206 with 128 x 128); of two 128 x 128 tiles on a compute unit one ends while the other multiplies, so their rest counts
+// less (fitted to 2300 launches of 64 - 4096 -> 256 - 4096, where the choice is then 1.2 % off the best kind on average); with at
+// most one 128 x 128 tile per compute unit a slab takes half as long.  What the rule is for: 4 jobs x 500 rows, 2048 ->
+// 2048: 50 / 33 / 26 us; 24 jobs x 300 rows, 256 -> 4096: 45 / 42 / 36; 32 jobs x 300 - 1000 rows, 4096 -> 1024: 212 /
+// 205 / 235, 1024 -> 4096: 237 / 254 / 277.
 struct TileKind { uint32_t bm, bn, per_cu, slab_ns, rest_ns; };
-constexpr TileKind kTile256 = {256, 256, 1, 1640, 12000}, kTile128x256 = {128, 256, 1, 935, 8000}, kTile128 = {128, 128, 2, 1090, 8000};
+constexpr TileKind kTile256 = {256, 256, 1, 1640, 12000}, kTile128x256 = {128, 256, 1, 935, 8000}, kTile128 = {128, 128, 2, 1090, 6000};
 
 static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n)
 {
@@ -339,14 +354,17 @@ hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w
     return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 1, false, 3>, 256, p, n, stream, launches);
 }
 
-// The tile for these jobs (256 rows only if all have the rows for it) and the time it takes.
+// The tile for these jobs (256 rows only if all have the rows for it) and the time it takes.  Shallow layers are all
+// epilogue, which only two tiles on a compute unit overlap: 128 x 128 (160 launches of 256 -> 1024 and 4096, 192 - 4096 rows:
+// 1 % off the best kind on average, 128 x 256 11 %, 256 x 256 28 %).
 struct TileChoice { const TileKind *kind; uint64_t ns; };
 static TileChoice choose_tile(const std::vector<Problem> &p, bool tall)
 {
     TileChoice best{nullptr, ~0ull};
     if (p.empty()) return best;
+    const bool shallow = std::all_of(p.begin(), p.end(), tiled_shape_shallow);
     for (const TileKind *t : {&kTile256, &kTile128x256, &kTile128}) {
-        if (t == &kTile256 && !tall) continue;
+        if ((t == &kTile256 && !tall) || (t != &kTile128 && shallow)) continue;
         const uint64_t ns = launch_ns(*t, p.data(), (uint32_t)p.size());
         if (ns < best.ns) best = {t, ns};
     }

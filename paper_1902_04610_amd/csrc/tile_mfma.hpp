@@ -225,7 +225,7 @@ struct Fragments {
 // contraction.  Walk: tile id -> place, operands and epilogue:
 //   uint32_t tiles(); Place place(id); Operand m(Place), n(Place);
 //   finish(Place, acc, m, n, lane, landed): (m, n) is the wavefront's corner in the tile; calls landed() before its
-//   first memory access.
+//   first store.
 // Place has m0, n0 and depth.  The grid has at most tiles() workgroups.
 template <int BM, int BN, int WM, int WN, bool TRM, bool TRN>
 struct TileMfma {

@@ -130,10 +130,20 @@ def test_ragged_depth_many_tiles(record):
     """With enough of them, or beside jobs of other shapes: one launch of the tiled kernel, whatever the rows."""
     many = [
         case([150, 191, 192, 260] * 5, 1000, 1016), case([129] * 30, 200, 1000), case([200] * 10, 3080, 776),
-        case([256, 333], [64, 264], 72),                                   # few, but beside a job that takes it anyway
+        case([256, 333], [320, 264], 72),                                   # few, but beside a job that takes it anyway
     ]
     for c, log in zip(many, record(many)):
         assert len(kernels(log)) == 1 and kernels(log)[0].startswith("grouped_dense_bf16_tiled<"), (c, kernels(log))
+
+
+def test_shallow_layers_above_128_rows(record):
+    """K of up to 256, a multiple of 64: the same rule; 128 rows take the kernels of smaller jobs when there are few."""
+    check(record, [(case(rows, K, N), ["grouped_dense_bf16" + kernel]) for rows, K, N, kernel in (
+        ([256], 64, 4096, "<2, false, false>"), ([160] * 8, 128, 1024, "<2, false, false>"), ([700], 256, 2048, "<2, false, false>"),
+        ([128], 64, 1024, "_narrow<2, false, 2, 8, false>"), ([128] * 8, 256, 1024, "_stream<64, 64, 2, 1, 2, false, 4>"),
+        ([128] * 32, 64, 1024, "_tiled<128, 128, 2, 2>"), ([300] * 8, 256, 4096, "_tiled<128, 128, 2, 2>"),
+        ([256], 320, 4096, "_tiled<128, 128, 2, 2>"),
+    )])
 
 
 def test_rows_33_to_128(record):

@@ -87,3 +87,18 @@ def test_float_rows_around_the_lines(jobs, M, K, N):
     assert n == 1
     for o, r, j in zip(outs, refs, specs):
         assert np.isfinite(o).all() and norm_rel_err(o, r) < TOL_F32, (j, norm_rel_err(o, r))
+
+
+@pytest.mark.parametrize("jobs, M, K, N, strip, launches", [
+    (2, 300, 64, 1024, True, 1), (8, 160, 128, 1032, False, 1), (1, 700, 256, 2056, False, 1),      # register tiles
+    (3, 128, 64, 1024, False, 1),                                        # 128 rows: the narrow tiles of fewer rows
+    (40, 200, 64, 1024, True, 1), (6, 700, 256, 2056, False, 1),         # tiled: float rows that begin on a line and that do not
+])
+def test_shallow_depth_from_128_rows(jobs, M, K, N, strip, launches):
+    check([dict(M=M, dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]], strip=strip) for i in range(jobs)], launches)
+
+
+@pytest.mark.parametrize("jobs, M, K, N", [(20, 250, 320, 4096), (70, 256, 320, 4096), (40, 40, 520, 4096), (3, 300, 576, 520)])
+def test_float_outputs_past_l2(jobs, M, K, N):
+    """Results stored past L2 (rows that begin on a line; 256 x 256 tiles below one round and above three) and not."""
+    check([dict(M=M - (i % 2), dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]], strip=False) for i in range(jobs)], 1 if jobs <= 64 else 2)
