@@ -76,6 +76,9 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
 // Jobs with many rows: LDS-tiled compute-bound kernel (256 x 256, 128 x 256 or 128 x 128 tiles, by launch).
 // tiled_shape_ok says whether a problem may go there (K a multiple of 64), tiled_shape_ragged whether it may in a round
 // with many such (other K), tiled_shape_shallow whether the former needs many as well; tiled_tiles: workgroups it would occupy.
+// Jobs of at least this many rows (at most a quarter of the last of their 256-row tiles is padding) may take any of the
+// tiles; smaller ones take 128-row tiles, in a launch of their own.
+constexpr uint32_t kTiled256MinM = 192;
 bool tiled_shape_fits(const Problem &p);      // what the kernels can address at all
 bool tiled_shape_ok(const Problem &p);
 bool tiled_shape_ragged(const Problem &p);

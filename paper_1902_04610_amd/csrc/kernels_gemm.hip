@@ -5,7 +5,7 @@
 // its job with a wavefront scan over the per-job tile counts.
 //
 // Shape of the work: per job Y[M x N] = act(X[M x K] . W[K x N]) with M small
-// (1..32 rows, 64 for deep layers; larger ones go to kernels_gemm_tiled.hip) and
+// (1..32 rows, more where the round is small, 64 for deep layers; the others go to kernels_gemm_tiled.hip) and
 // W read straight out of the job's persistent block.  Every weight is used once per launch, so the kernel is a weight-streaming kernel:
 // W goes HBM -> registers with 16-byte loads (no LDS staging: nothing would be
 // reused), each wavefront keeps two k-steps of loads in flight, the 8x8 bf16
@@ -147,10 +147,16 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
         // 600 rows, 3080 -> 776 (532) 46.6 / 31.1; depths of 64 - 256, up to 512 tiles 0.36 - 1.00 of tiled, from 640 1.2 - 3.
         // The rows do not matter beside that, and one rule for all of them keeps a round in one launch: 8 jobs x 100 - 400 rows,
         // 1000 -> 3080 -> 776, 81 us against 111 us when those from 192 rows went to the tiled kernel and the others did not.
-        // Beside jobs that take the tiled kernel anyway they join those, again for one launch.
-        auto always = [&](const Problem &q) { return q.M >= min_m && tiled_shape_ok(q) && !tiled_shape_shallow(q); };
+        // Beside jobs that take the tiled kernel anyway they join those, again for one launch; so do shallow ones with rows on
+        // either side of 192, which have a launch for each tile height.
+        bool shallow_low = false, shallow_high = false;
+        for (uint32_t i = 0; i < n; ++i)
+            if (p[i].M >= min_m && tiled_shape_ok(p[i]) && tiled_shape_shallow(p[i]))
+                (p[i].M >= kTiled256MinM ? shallow_high : shallow_low) = true;
+        const bool both = shallow_low && shallow_high;
+        auto always = [&](const Problem &q) { return q.M >= min_m && tiled_shape_ok(q) && (both || !tiled_shape_shallow(q)); };
         auto if_many = [&](const Problem &q) {
-            return tiled_shape_ragged(q) || (q.M >= min_m && tiled_shape_ok(q) && tiled_shape_shallow(q));
+            return tiled_shape_ragged(q) || (!both && q.M >= min_m && tiled_shape_ok(q) && tiled_shape_shallow(q));
         };
         uint64_t many_tiles = 0;
         bool many_deep = true, tiled_anyway = false;
@@ -201,6 +207,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
         bool one_row_tile = true;      // else several row tiles read the same weights: plain loads, L2 serves the others
         for (uint32_t i = 0; i < a.n; ++i) one_row_tile = one_row_tile && a.p[i].M <= 16u * mt;
         if (mt == 4) hipLaunchKernelGGL(grouped_dense_bf16_rows64, grid, block, 0, stream, a);
+        // (transposed weights with several row tiles: only widths from 2^22, which the ring cannot address)
         else if (!one_row_tile && trans_w) hipLaunchKernelGGL((grouped_dense_bf16<2, true, false>), grid, block, 0, stream, a);
         else if (!one_row_tile) hipLaunchKernelGGL((grouped_dense_bf16<2, false, false>), grid, block, 0, stream, a);
         else if (mt == 2 && trans_w) hipLaunchKernelGGL((grouped_dense_bf16<2, true, true>), grid, block, 0, stream, a);

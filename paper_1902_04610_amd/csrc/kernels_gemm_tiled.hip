@@ -148,10 +148,11 @@ struct DenseWalk {
 };
 
 // The workgroups are resident (one per compute unit, two of the 128 x 128 tile): workgroup b runs tiles b, b + grid, ...
-// Bound: the power limit.  16 jobs x 4096 rows, 4096 -> 1024: 489 us (1.12 PFLOP/s; 529 us with operands staged through
-// registers and transposed on the way into LDS), matrix pipes busy 65 % of the cycles at the 1.66 GHz that the chip then
-// holds, no bank conflicts; with every request answered from L2 it takes 450 us.  1024 -> 4096 -> 1024 -> 1024 with GELU:
-// 1263 us (1421).
+// Bound, deep layers: the power limit.  16 jobs x 4096 rows, 4096 -> 1024: 489 us (1.12 PFLOP/s; 529 us with operands staged
+// through registers and transposed on the way into LDS); 64 jobs: matrix pipes busy 64 % of the cycles at the 1.8 GHz that the
+// chip then holds, no bank conflicts.  Layers of 16 slabs: the epilogue, which the one workgroup of a compute unit does with
+// all its wavefronts at once, 128 outputs per lane (pipes 42 % at 1.95 GHz).  1024 -> 4096 -> 1024 -> 1024 with GELU, 16 jobs x
+// 4096 rows: 1270 - 1290 us (1421).
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled(GroupArgs a)
 {
@@ -169,10 +170,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS, WM * WN * KS / 2) void grouped_d
     const DenseWalk<BM, BN, TW> walk{a};
     T::run(walk, smem);
 }
-
-// Jobs of at least this many rows (at most a quarter of the last of their 256-row tiles is padding) may take any of the
-// tiles; smaller ones take 128-row tiles.
-constexpr uint32_t kTiled256MinM = 192;
 
 bool tiled_shape_ok(const Problem &p) { return tiled_shape_fits(p) && p.K % kSlab == 0; }
 // A depth that is no multiple of a slab costs the padding of the last slab, and one of up to four slabs leaves prologue and
@@ -206,8 +203,8 @@ static hipError_t launch_tiled(Kernel kernel, int threads, const Problem *p, uin
         a.tiles = (uint32_t)tiles;
         // resident workgroups; a multiple of 8 so that the workgroups of an XCD keep to that XCD's range of tiles
         const uint32_t grid = (uint32_t)std::min<uint64_t>(tiles, resident_grid() * PER_CU);
-        // Float outputs are a model's results, not read again here: whole lines of them go past L2 (non-temporal), which
-        // bounds wide shallow layers.  16 jobs x 4096 rows, 1024 -> 4096: 578 us, with plain stores 644; 32 jobs x 1000
+        // Float outputs are a model's results, not read again here (a training step's logits are, without a difference): whole lines
+        // of them go past L2 (non-temporal), as these stores bound wide shallow layers.  16 jobs x 4096 rows, 1024 -> 4096: 578 us, with plain stores 644; 32 jobs x 1000
         // rows, 256 -> 4096 131 / 174.  Not where rows do not begin on a line, whose pieces have to meet in L2 (256 -> 1000:
         // 68 / 38, see finish), nor with one workgroup per compute unit in one to three rounds, where its next tile waits for
         // the stores of the one before and nothing else covers that: 6 jobs x 1000 rows, 512 -> 4096, 1.09 of plain.  900
@@ -335,8 +332,8 @@ static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n)
 // Launches bound by the weight stream.  64 x 128 tiles, two workgroups per compute unit; 64 x 64, twice the workgroups,
 // while there is at most one of them per compute unit (transposed weights: while 64 x 128 would be fewer than one).  64 x
 // 128 / 64 x 64: 12 jobs x 64 rows, 2048 -> 1536 26 / 33 us, 20 jobs x 33 - 128 rows, 4096 -> 1024 47 / 56, 16 jobs x 33 -
-// 100 rows, 1536 -> 768 19 / 21, 8 jobs x 64 rows, 2048 -> 2048 with weights from memory 27 / 22.5.  8 jobs x 64 rows, 2048 -> 2048: 15.4 us (registers-only kernel with K
-// split over four wavefronts: 20.6; this tile without the split of the k-steps 17.5, with 64 x 128 tiles 19), input
+// 100 rows, 1536 -> 768 19 / 21, 8 jobs x 64 rows, 2048 -> 2048 with weights from memory 27 / 22.5.  The same launched over and over (weights
+// in L2): 15.4 us (registers-only kernel with K split over four wavefronts: 20.6; this tile without the split of the k-steps 17.5, with 64 x 128 tiles 19), input
 // gradients of the same layer 17 against 24; 8 jobs x 100 rows: 64 x 128 tiles, training step 386 us against 410 with 64
 // x 64.  Rings twice as deep with one workgroup per compute unit: 18.6.
 hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream, uint64_t *launches)
