@@ -297,22 +297,23 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
     };
     // Float multiplies are what a 64-row tile takes long for (16 x 16 x 4 per instruction), so rows are spread over
     // workgroups.  16-row tiles as long as two per compute unit hold them, except that jobs most of which have 17 .. 32 rows take one
-    // 32-row tile each where compute units are left for all of them.  Else 64-row tiles while those leave compute units idle,
+    // 32-row tile each, in layers deeper than 512, where compute units are left for all of them.  Else 64-row tiles while those leave compute units idle,
     // or if they fill whole rounds of the chip and every job has the rows for them (a weight is then read half as often); else
     // 32-row tiles.  16 / 32 / 64 rows per tile: 12 jobs x 1 - 128 rows, 516 -> 1204 -> 780 -> 388: 50 / 50 / 70 us; one job x
-    // 64 rows, 1024 -> 1024 8.8 / 12.7 / 21.3; 12 jobs x 32 rows, 1204 -> 780 (312 16-row tiles) 16.9 / 15.3; 12 jobs x 128
+    // 64 rows, 1024 -> 1024 8.8 / 12.7 / 21.3; 12 jobs x 32 rows, 1204 -> 780 (312 16-row tiles) 16.9 / 15.3, 40 jobs, 256 -> 256 (320) 5.9 / 6.0; 12 jobs x 128
     // rows, 1536 -> 1536 88 / 80 / 89, 4 jobs 33 / 33 / 32; 40 jobs x 33 rows, 1536 -> 1536 (960 64-row tiles, 3.75 rounds), 32 / 64 rows:
     // 121 / 113; 40 jobs x 128 rows, 1024 -> 1024 -> 1024 (5 rounds) 213 / 202, 40 rows (2.5) 110 / 122.
     uint64_t tiles_16 = 0, tiles_32 = 0, tiles_64 = 0;
-    uint32_t max_m = 0;
+    uint32_t max_m = 0, min_k = ~0u;
     for (uint32_t i = 0; i < n; ++i) {
         const uint64_t cols = (p[i].N + 63) / 64;
         tiles_16 += (p[i].M + 15) / 16 * cols;
         tiles_32 += (p[i].M + 31) / 32 * cols;
         tiles_64 += (p[i].M + 63) / 64 * cols;
         max_m = std::max(max_m, p[i].M);
+        min_k = std::min(min_k, p[i].K);
     }
-    const bool one_32 = max_m > 16 && max_m <= 32 && tiles_16 > kFullGrid && tiles_32 <= kFullGrid && tiles_16 * 4 > tiles_32 * 7;
+    const bool one_32 = min_k > 512 && max_m > 16 && max_m <= 32 && tiles_16 > kFullGrid && tiles_32 <= kFullGrid && tiles_16 * 4 > tiles_32 * 7;
     const uint64_t rounds_64 = (tiles_64 + kFullGrid - 1) / kFullGrid;
     const bool whole_64 = tiles_32 == 2 * tiles_64 && tiles_64 * 16 >= rounds_64 * kFullGrid * 15;
     const int mt = one_32                                          ? 2

@@ -159,7 +159,7 @@ def test_rows_33_to_128(record):
 def test_float_row_tiles(record):
     check(record, [(case(rows, K, N, "f32"), ["grouped_dense_f32<%d>" % tile]) for rows, K, N, tile in (
         ([32] * 12, 1204, 780, 2), ([17] * 30, 1536, 384, 2),       # 312 and 360 16-row tiles: 32-row ones, each on a compute unit of its own
-        ([32] * 4, 1204, 780, 1), ([64] * 8, 512, 512, 1), ([16] * 40, 516, 1204, 1), ([8] * 8 + [32] * 4, 1536, 1536, 1),
+        ([32] * 4, 1204, 780, 1), ([32] * 40, 256, 256, 1), ([64] * 8, 512, 512, 1), ([16] * 40, 516, 1204, 1), ([8] * 8 + [32] * 4, 1536, 1536, 1),
         ([128] * 12, 1536, 1536, 2), ([40] * 12, 1536, 1536, 2), ([33, 80] * 20, 1536, 1536, 2), ([40] * 40, 1024, 1024, 2),
         ([40] * 20, 1536, 1536, 4), ([64] * 40, 1536, 1536, 4), ([128] * 40, 1024, 1024, 4), ([33] * 30, 1024, 1024, 4),     # whole rounds
         ([200] * 12, 516, 1204, 4),

@@ -79,7 +79,7 @@ def test_hidden_layers_of_33_to_128_rows_in_narrow_tiles():
     check([dict(M=m, dims=(136, 264, 72, 520), acts=[GELU, RELU, NONE], strip=False) for m in (33, 63, 64, 90, 127)], 3)
 
 
-@pytest.mark.parametrize("jobs, M, K, N", [(12, 32, 132, 780), (60, 17, 68, 388), (26, 40, 1028, 964), (17, 64, 1032, 1536)])
+@pytest.mark.parametrize("jobs, M, K, N", [(12, 32, 516, 780), (12, 32, 132, 780), (60, 17, 68, 388), (26, 40, 1028, 964), (17, 64, 1032, 1536)])
 def test_float_rows_around_the_lines(jobs, M, K, N):
     """32-row tiles of 17 .. 32 rows, and 64-row tiles of deep layers that fill the chip with one each."""
     specs = [dict(M=max(17 if M <= 32 else 33, M - 5 * (i % 3)), dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]]) for i in range(jobs)]
