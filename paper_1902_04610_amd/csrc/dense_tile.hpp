@@ -73,8 +73,8 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t ncol = tile.n0 + CPL * c;
     const bool col_ok = ncol < N;
-    const uint16_t *W = (const uint16_t *)p.W;
-    const uint16_t *X = (const uint16_t *)p.X;
+    const Global<uint16_t> *W = (const Global<uint16_t> *)p.W;
+    const Global<uint16_t> *X = (const Global<uint16_t> *)p.X;
 
     f32x4 acc[NACC];
 #pragma unroll
@@ -96,15 +96,15 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
     const uint32_t xtiles = (M + 15) / 16;
     const bool strip = !TW && (p.flags & kStripW);
     const uint32_t wpitch = strip ? 128u : N;
-    const uint16_t *Wc = strip ? W + (size_t)(tile.n0 & ~127u) * K + (tile.n0 & 127u) + CPL * c : W + ncol_c;
+    const Global<uint16_t> *Wc = strip ? W + (size_t)(tile.n0 & ~127u) * K + (tile.n0 & 127u) + CPL * c : W + ncol_c;
     auto load = [&](int s, wvec (&w)[NROW], u32x4 (&x)[MT], bool &k_ok) {
         const uint32_t kb = 32u * (uint32_t)s + 8u * (uint32_t)g;
         k_ok = kb < K;
         const uint32_t kc = k_ok ? kb : 0u;
 #pragma unroll
         for (int r = 0; r < NROW; ++r) {
-            const uint16_t *at = TW ? W + (size_t)(ncol_c + r) * K + kc : Wc + (size_t)(kc + r) * wpitch;
-            w[r] = NT ? __builtin_nontemporal_load((const wvec *)at) : *(const wvec *)at;
+            const Global<uint16_t> *at = TW ? W + (size_t)(ncol_c + r) * K + kc : Wc + (size_t)(kc + r) * wpitch;
+            w[r] = NT ? __builtin_nontemporal_load((const Global<wvec> *)at) : *(const Global<wvec> *)at;
         }
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
@@ -112,10 +112,10 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
                 // one contiguous kilobyte per wavefront; a row tile the job does not
                 // have (its rows are never stored) reads the job's last one instead
                 const uint32_t tt = (uint32_t)t < xtiles ? (uint32_t)t : xtiles - 1;
-                x[t] = *(const u32x4 *)(X + (((size_t)(kc >> 5) * xtiles + tt) * 64 + lane) * 8);
+                x[t] = *(const Global<u32x4> *)(X + (((size_t)(kc >> 5) * xtiles + tt) * 64 + lane) * 8);
             } else {
                 const uint32_t row = tile.m0 + 16 * t + c;
-                x[t] = *(const u32x4 *)(X + (size_t)(row < M ? row : M - 1) * K + kc);
+                x[t] = *(const Global<u32x4> *)(X + (size_t)(row < M ? row : M - 1) * K + kc);
             }
         }
     };
@@ -216,7 +216,7 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
         typedef unsigned int out_vec __attribute__((ext_vector_type(CPL / 2)));
         if (p.flags & kMaskPositive) {
             // ReLU derivative taken from the stored bf16 activation (sign bit clear, not zero)
-            const out_vec h = *(const out_vec *)((const uint16_t *)p.aux + (size_t)row * N + ncol);
+            const out_vec h = *(const Global<out_vec> *)((const Global<uint16_t> *)p.aux + (size_t)row * N + ncol);
 #pragma unroll
             for (int i = 0; i < CPL; ++i) {
                 const uint32_t bits = (h[i >> 1] >> ((i & 1) * 16)) & 0xffffu;
@@ -231,18 +231,18 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
                 // these columns are in k-group (ncol / 8) % 4 of k-step ncol / 32 of the next layer
                 const size_t unit = (((size_t)(ncol >> 5) * xtiles + (row >> 4)) * 4 + ((ncol >> 3) & 3)) * 16 +
                                     (row & 15);
-                *(out_vec *)((uint16_t *)p.Y + unit * 8 + (ncol & 7u)) = o;
+                *(Global<out_vec> *)((Global<uint16_t> *)p.Y + unit * 8 + (ncol & 7u)) = o;
             } else {
-                *(out_vec *)((uint16_t *)p.Y + (size_t)row * N + ncol) = o;
+                *(Global<out_vec> *)((Global<uint16_t> *)p.Y + (size_t)row * N + ncol) = o;
             }
         } else {
-            float *y = (float *)p.Y + (size_t)row * N + ncol;
+            Global<float> *y = (Global<float> *)p.Y + (size_t)row * N + ncol;
             if constexpr (CPL == 2) {
                 typedef float f32x2 __attribute__((ext_vector_type(2)));
-                *(f32x2 *)y = f32x2{v[0], v[1]};
+                *(Global<f32x2> *)y = f32x2{v[0], v[1]};
             } else {
 #pragma unroll
-                for (int j = 0; j < CPL; j += 4) *(f32x4 *)(y + j) = f32x4{v[j], v[j + 1], v[j + 2], v[j + 3]};
+                for (int j = 0; j < CPL; j += 4) *(Global<f32x4> *)(y + j) = f32x4{v[j], v[j + 1], v[j + 2], v[j + 3]};
             }
         }
     }
@@ -255,7 +255,8 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
 // (q, i) multiplies component q of X with component i of W row q, so lane
 // group g contributes k = k0+4g+q in step q and output column n0+4c+i.
 // ---------------------------------------------------------------------------
-template <int MT>
+// D: k-steps in flight per wavefront, as above.
+template <int MT, int D = 2>
 __device__ inline void dense_f32_tile(const Problem &p, const Tile tile, float *lds)
 {
     constexpr int NACC = MT * 4;
@@ -264,8 +265,8 @@ __device__ inline void dense_f32_tile(const Problem &p, const Tile tile, float *
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t ncol = tile.n0 + 4 * c;
     const bool col_ok = ncol < N;
-    const float *W = (const float *)p.W;
-    const float *X = (const float *)p.X;
+    const Global<float> *W = (const Global<float> *)p.W;
+    const Global<float> *X = (const Global<float> *)p.X;
 
     f32x4 acc[NACC];
 #pragma unroll
@@ -281,11 +282,11 @@ __device__ inline void dense_f32_tile(const Problem &p, const Tile tile, float *
         k_ok = kb < K;
         const uint32_t kc = k_ok ? kb : 0u;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) w[q] = *(const f32x4 *)(W + (size_t)(kc + q) * N + ncol_c);
+        for (int q = 0; q < 4; ++q) w[q] = *(const Global<f32x4> *)(W + (size_t)(kc + q) * N + ncol_c);
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
             const uint32_t row = tile.m0 + 16 * t + c;
-            x[t] = *(const f32x4 *)(X + (size_t)(row < M ? row : M - 1) * K + kc);
+            x[t] = *(const Global<f32x4> *)(X + (size_t)(row < M ? row : M - 1) * K + kc);
         }
     };
     auto compute = [&](const f32x4 (&w)[4], const f32x4 (&xr)[MT], bool k_ok) {
@@ -302,30 +303,58 @@ __device__ inline void dense_f32_tile(const Problem &p, const Tile tile, float *
                                                                           acc[t * 4 + i], 0, 0, 0);
     };
 
-    f32x4 w0[4], w1[4], x0[MT], x1[MT];
-    bool ok0, ok1;
     const int mine = nsteps > wave ? (nsteps - wave + kWaves - 1) / kWaves : 0;
     auto step = [&](int i) { return wave + kWaves * i; };
-    load(step(0), w0, x0, ok0);
-    load(step(1), w1, x1, ok1);
-    int i = 0;
-    for (; i + 3 < mine; i += 2) {
-        // keep the instruction scheduler from sinking the loads below the next
-        // multiply phase: each phase must stay where it is written
-        compute(w0, x0, ok0);
-        __builtin_amdgcn_sched_barrier(0);
-        load(step(i + 2), w0, x0, ok0);
-        __builtin_amdgcn_sched_barrier(0);
-        compute(w1, x1, ok1);
-        __builtin_amdgcn_sched_barrier(0);
-        load(step(i + 3), w1, x1, ok1);
-        __builtin_amdgcn_sched_barrier(0);
+    if constexpr (D == 2) {
+        f32x4 w0[4], w1[4], x0[MT], x1[MT];
+        bool ok0, ok1;
+        load(step(0), w0, x0, ok0);
+        load(step(1), w1, x1, ok1);
+        int i = 0;
+        for (; i + 3 < mine; i += 2) {
+            // keep the instruction scheduler from sinking the loads below the next
+            // multiply phase: each phase must stay where it is written
+            compute(w0, x0, ok0);
+            __builtin_amdgcn_sched_barrier(0);
+            load(step(i + 2), w0, x0, ok0);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(w1, x1, ok1);
+            __builtin_amdgcn_sched_barrier(0);
+            load(step(i + 3), w1, x1, ok1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const int left = mine - i;
+        if (left >= 1) compute(w0, x0, ok0);
+        if (left == 3) load(step(i + 2), w0, x0, ok0);
+        if (left >= 2) compute(w1, x1, ok1);
+        if (left == 3) compute(w0, x0, ok0);
+    } else {
+        f32x4 w[D][4], x[D][MT];
+        bool ok[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(step(d), w[d], x[d], ok[d]);
+        int i = 0;
+        for (; i + 2 * D <= mine; i += D) {
+            // keep the instruction scheduler from sinking the loads below the next
+            // multiply phase: each phase must stay where it is written
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                compute(w[d], x[d], ok[d]);
+                __builtin_amdgcn_sched_barrier(0);
+                load(step(i + d + D), w[d], x[d], ok[d]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const int left = mine - i;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            if (d < left) compute(w[d], x[d], ok[d]);
+            if (d + D < left) load(step(i + d + D), w[d], x[d], ok[d]);
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d + D < left) compute(w[d], x[d], ok[d]);
     }
-    const int left = mine - i;
-    if (left >= 1) compute(w0, x0, ok0);
-    if (left == 3) load(step(i + 2), w0, x0, ok0);
-    if (left >= 2) compute(w1, x1, ok1);
-    if (left == 3) compute(w0, x0, ok0);
 
     float own[NACC];
     reduce_scatter<NACC>(acc, own, lds);
@@ -338,7 +367,7 @@ __device__ inline void dense_f32_tile(const Problem &p, const Tile tile, float *
         f32x4 o;
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[i] = activate_f32(own[t * 4 + i], act);
-        *(f32x4 *)((float *)p.Y + (size_t)row * N + ncol) = o;
+        *(Global<f32x4> *)((Global<float> *)p.Y + (size_t)row * N + ncol) = o;
     }
 }
 

@@ -10,11 +10,30 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 struct GroupArgs {
     uint32_t n;
-    uint32_t tiles;      // all tiles of the launch (kernels whose workgroups loop over tiles)
-    uint32_t past_l2;    // the same kernels: float outputs whose rows begin on a line are stored past L2
+    uint32_t tiles;      // all tiles of the launch
+    uint32_t past_l2;    // kernels whose workgroups loop over tiles: float outputs whose rows begin on a line are stored past L2
     uint32_t pad;
+    uint32_t first[kMaxProblems];      // first tile of problem i; kNoTile from n on
     Problem p[kMaxProblems];
 };
+constexpr uint32_t kNoTile = ~0u;
+static_assert(sizeof(GroupArgs) <= 4096, "kernel arguments are limited to 4 KB");
+
+// Fills in a launch of at most kMaxProblems problems whose i-th has tiles(problem) tiles; returns how many there are in all.
+template <typename Args, typename P, typename Tiles>
+inline uint64_t fill_group(Args &a, const P *p, uint32_t n, Tiles tiles)
+{
+    uint64_t total = 0;
+    a.n = n;
+    for (uint32_t i = 0; i < n; ++i) {
+        a.p[i] = p[i];
+        a.first[i] = (uint32_t)total;
+        total += tiles(p[i]);
+    }
+    for (uint32_t i = n; i < kMaxProblems; ++i) a.first[i] = kNoTile;
+    a.tiles = (uint32_t)total;
+    return total;
+}
 
 constexpr int kGemmThreads = 256;
 constexpr int kWaves = 4;
@@ -87,34 +106,37 @@ __device__ inline uint32_t xcd_remap(uint32_t b, uint32_t total)
     return x * q + (x < r ? x : r) + slot;
 }
 
+// Which problem of a launch the tile `id` belongs to: copied to `owner`; returns the tile's number among that problem's.
+// Nothing can begin before this answer, so it is one trip to memory: lane i loads problem i and its first tile, a ballot
+// finds the last one that begins at or before `id`, and that lane is read out.  0.6 us from a workgroup's start; scanning
+// tile counts and then reading the problem by its number, three dependent trips, took 1.6: one request against a 1024 -
+// 4096 - 1024 - 1024 model, three launches, 26.1 / 24.1 us, 64 such models 174.5 / 172.5.
+template <typename P>
+__device__ inline uint32_t find_owner(const uint32_t (&first)[kMaxProblems], const P (&p)[kMaxProblems], uint32_t id, P &owner)
+{
+    constexpr int kWords = sizeof(P) / 4;
+    struct Words { uint32_t w[kWords]; };
+    const int lane = threadIdx.x & 63;
+    const uint32_t from = first[lane];
+    const Words mine = __builtin_bit_cast(Words, p[lane]);
+    const int g = __builtin_amdgcn_readfirstlane(wave_find_range(from, id, true));
+    Words words;
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) words.w[i] = __builtin_amdgcn_readlane(mine.w[i], g);
+    owner = __builtin_bit_cast(P, words);
+    return id - __builtin_amdgcn_readlane(from, g);
+}
+
 struct Tile {
-    int problem;
     uint32_t m0, n0;
 };
 
-// Which (job, row tile, column tile) this workgroup owns: lane i of every
-// wavefront holds job i's tile count; an exclusive scan gives each job's first
-// tile; a ballot finds the job whose range contains this workgroup's index.
+// Which (job, row tile, column tile) this workgroup owns, and that job's problem.
 template <int TM, int TN>
-__device__ inline Tile find_tile(const GroupArgs &a)
+__device__ inline Tile find_tile(const GroupArgs &a, Problem &p)
 {
-    const int lane = threadIdx.x & 63;
-    const bool valid = lane < (int)a.n;
-    uint32_t row_tiles = 0, count = 0;
-    if (valid) {
-        row_tiles = (a.p[lane].M + TM - 1) / TM;
-        count = row_tiles * ((a.p[lane].N + TN - 1) / TN);
-    }
-    const uint32_t first = wave_excl_scan_u32(count, nullptr);
-    const uint32_t id = xcd_remap(blockIdx.x, gridDim.x);
-    const int g = wave_find_range(first, id, valid);
-    const uint32_t t = id - __shfl(first, g, 64);
-    const uint32_t rt = __shfl(row_tiles, g, 64);
-    Tile tile;
-    tile.problem = __builtin_amdgcn_readfirstlane(g);
-    tile.m0 = (t % rt) * TM;      // row tiles of one column tile are neighbours: they share W
-    tile.n0 = (t / rt) * TN;
-    return tile;
+    const uint32_t t = find_owner(a.first, a.p, xcd_remap(blockIdx.x, a.tiles), p), rt = (p.M + TM - 1) / TM;
+    return {(t % rt) * TM, (t / rt) * TN};      // row tiles of one column tile are neighbours: they share W
 }
 
 }  // namespace salus

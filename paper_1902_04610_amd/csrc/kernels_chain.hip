@@ -95,7 +95,6 @@ __device__ inline bool chain_find(const ChainArgs &a, ChainWork &w)
     w.p.N = d[10];
     w.p.flags = d[11];
     const uint32_t t = id - start, rt = (w.p.M + TM - 1) / TM;
-    w.tile.problem = (int)pair;
     w.tile.m0 = (t % rt) * TM;
     w.tile.n0 = (t / rt) * TN;
     w.pair = pair;

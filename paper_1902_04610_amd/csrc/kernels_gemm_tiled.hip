@@ -9,33 +9,6 @@
 
 namespace salus {
 
-// Tiles of one job in bands of 8 row tiles, column tiles inside a band: the tiles
-// an XCD runs at a time then share 8 slabs of X and 4 - 8 slabs of W in its L2.
-template <int BM, int BN>
-__device__ inline Tile find_tile_banded(const GroupArgs &a, uint32_t tile_id)
-{
-    const int lane = threadIdx.x & 63;
-    const bool valid = lane < (int)a.n;
-    uint32_t row_tiles = 0, col_tiles = 0;
-    if (valid) {
-        row_tiles = (a.p[lane].M + BM - 1) / BM;
-        col_tiles = (a.p[lane].N + BN - 1) / BN;
-    }
-    const uint32_t first = wave_excl_scan_u32(row_tiles * col_tiles, nullptr);
-    // the grid is a multiple of 8, so a workgroup's tiles all map to its own XCD's range
-    const uint32_t id = xcd_remap(tile_id, a.tiles);
-    const int g = wave_find_range(first, id, valid);
-    const uint32_t t = id - __shfl(first, g, 64);
-    const uint32_t rt = __shfl(row_tiles, g, 64), ct = __shfl(col_tiles, g, 64);
-    const uint32_t band = t / (8u * ct), local = t - band * 8u * ct;
-    const uint32_t rows = min(8u, rt - band * 8u);
-    Tile tile;
-    tile.problem = __builtin_amdgcn_readfirstlane(g);
-    tile.m0 = __builtin_amdgcn_readfirstlane((band * 8u + local % rows) * BM);
-    tile.n0 = __builtin_amdgcn_readfirstlane((local / rows) * BN);
-    return tile;
-}
-
 // A wavefront's accumulators, whose first element is (m, n) of Y, to memory.  N is a multiple of 8, so a vector of 8
 // (bf16) or 4 (float) columns lies wholly inside or outside.
 template <int ACT, bool BF16, bool PAST_L2, int FN, int FM, typename Landed>
@@ -109,12 +82,21 @@ __device__ inline void store_dense(const Problem &p, uint32_t m, uint32_t n, con
 template <int BM, int BN, bool TW>
 struct DenseWalk {
     const GroupArgs &a;
+    const uint32_t first;      // lane i: the first tile of problem i
     struct Place { int problem; uint32_t m0, n0, depth; };
+    __device__ explicit DenseWalk(const GroupArgs &args) : a(args), first(args.first[threadIdx.x & 63]) {}
     __device__ uint32_t tiles() const { return a.tiles; }
-    __device__ Place place(uint32_t id) const
+    // Tiles of one job in bands of 8 row tiles, column tiles inside a band: the tiles an XCD runs at a time then share 8
+    // slabs of X and 4 - 8 slabs of W in its L2.
+    __device__ Place place(uint32_t tile_id) const
     {
-        const Tile t = find_tile_banded<BM, BN>(a, id);
-        return {t.problem, t.m0, t.n0, a.p[t.problem].K};
+        // the grid is a multiple of 8, so a workgroup's tiles all map to its own XCD's range
+        const uint32_t id = xcd_remap(tile_id, a.tiles);
+        const int g = __builtin_amdgcn_readfirstlane(wave_find_range(first, id, true));
+        const Problem &p = a.p[g];
+        const uint32_t t = id - __builtin_amdgcn_readlane(first, g), rt = (p.M + BM - 1) / BM, ct = (p.N + BN - 1) / BN;
+        const uint32_t band = t / (8u * ct), local = t - band * 8u * ct, rows = min(8u, rt - band * 8u);
+        return {g, (band * 8u + local % rows) * BM, (local / rows) * BN, p.K};
     }
     __device__ Operand m(const Place &at) const
     {
@@ -158,7 +140,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled(Grou
 {
     using T = TileMfma<BM, BN, WM, WN, false, true>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
-    const DenseWalk<BM, BN, false> walk{a};
+    const DenseWalk<BM, BN, false> walk(a);
     T::run(walk, smem);
 }
 
@@ -167,7 +149,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, WM * WN * KS / 2) void grouped_d
 {
     using T = TileStream<BM, BN, WM, WN, KS, !TW, D>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
-    const DenseWalk<BM, BN, TW> walk{a};
+    const DenseWalk<BM, BN, TW> walk(a);
     T::run(walk, smem);
 }
 
@@ -192,15 +174,10 @@ static hipError_t launch_tiled(Kernel kernel, int threads, const Problem *p, uin
 {
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         GroupArgs a{};
-        a.n = std::min(kMaxProblems, n - at);
-        uint64_t tiles = 0;
-        for (uint32_t i = 0; i < a.n; ++i) {
-            a.p[i] = p[at + i];
-            tiles += (uint64_t)((a.p[i].M + BM - 1) / BM) * ((a.p[i].N + BN - 1) / BN);
-        }
+        const uint64_t tiles = fill_group(a, p + at, std::min(kMaxProblems, n - at),
+                                          [](const Problem &q) { return (uint64_t)((q.M + BM - 1) / BM) * ((q.N + BN - 1) / BN); });
         if (tiles == 0) continue;
         if (tiles > 0x7fffffffull) return hipErrorInvalidValue;
-        a.tiles = (uint32_t)tiles;
         // resident workgroups; a multiple of 8 so that the workgroups of an XCD keep to that XCD's range of tiles
         const uint32_t grid = (uint32_t)std::min<uint64_t>(tiles, resident_grid() * PER_CU);
         // Float outputs are a model's results, not read again here (a training step's logits are, without a difference): whole lines

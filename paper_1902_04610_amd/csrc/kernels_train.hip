@@ -32,7 +32,7 @@ __device__ inline float wave_sum(float v)
 // Mean softmax cross-entropy over the M rows of each job and its gradient
 // (softmax - onehot) / M, written as bf16 for the backward products.  A
 // workgroup of 16 wavefronts takes 16 rows of one job (the job is found with the
-// scan + ballot used everywhere else), one wavefront one row: the rows are spread over as many
+// lookup used everywhere else), one wavefront one row: the rows are spread over as many
 // compute units as there are, since one unit's memory path is what bounds it (8 jobs x 64 rows x 1000 classes:
 // 5.3 us, with 64 rows per workgroup 13 us).  Rows of up to
 // 1024 classes are read once and kept in registers; wider rows are re-read from memory for each of the three
@@ -42,7 +42,8 @@ __device__ inline float wave_sum(float v)
 // ---------------------------------------------------------------------------
 struct LossArgs {
     uint32_t n;
-    uint32_t pad;
+    uint32_t tiles;      // blocks of kLossRows rows
+    uint32_t first[kMaxProblems];      // first block of job i; kNoTile from n on
     LossProblem p[kMaxProblems];
 };
 
@@ -52,13 +53,11 @@ __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
 {
     __shared__ float row_loss[kLossRows];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool valid = lane < (int)a.n;
-    const uint32_t blocks = valid ? (a.p[lane].M + kLossRows - 1) / kLossRows : 0;
-    const uint32_t first = wave_excl_scan_u32(blocks, nullptr);
-    const int job = __builtin_amdgcn_readfirstlane(wave_find_range(first, blockIdx.x, valid));
-    const LossProblem &p = a.p[job];
-    const uint32_t row0 = (blockIdx.x - __shfl(first, job, 64)) * kLossRows;
+    LossProblem p;
+    const uint32_t row0 = find_owner(a.first, a.p, blockIdx.x, p) * kLossRows;
     const uint32_t M = p.M, N = p.N;
+    const Global<float> *logits = (const Global<float> *)p.logits;
+    Global<float> *row_losses = (Global<float> *)p.row_loss;
     const float inv_m = 1.0f / (float)M;
     // register path: lane owns classes 256 i + 4 lane .. + 3 of a row (16-byte loads, 8-byte stores)
     const bool in_regs = N <= 64u * kLossRegs && N % 4 == 0;
@@ -68,18 +67,18 @@ __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
 #pragma unroll
     for (int q = 0; q < kLossPerWave; ++q) {
         const uint32_t row = row0 + wave * kLossPerWave + q;
-        const int l = p.labels[row < M ? row : M - 1];
+        const int l = ((const Global<int32_t> *)p.labels)[row < M ? row : M - 1];
         labels[q] = l < 0 ? 0 : (l >= (int)N ? (int)N - 1 : l);          // never read outside the row
     }
     if (in_regs) {
 #pragma unroll
         for (int q = 0; q < kLossPerWave; ++q) {
             const uint32_t row = row0 + wave * kLossPerWave + q;
-            const float *z = p.logits + (size_t)(row < M ? row : M - 1) * N;
+            const Global<float> *z = logits + (size_t)(row < M ? row : M - 1) * N;
 #pragma unroll
             for (int i = 0; i < kLossRegs / 4; ++i) {
                 const uint32_t n = 256u * i + 4u * lane;
-                zr[q][i] = *(const f32x4 *)(z + (n < N ? n : N - 4));
+                zr[q][i] = *(const Global<f32x4> *)(z + (n < N ? n : N - 4));
             }
         }
     }
@@ -87,8 +86,8 @@ __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
     for (int q = 0; q < kLossPerWave; ++q) {
         const uint32_t row = row0 + wave * kLossPerWave + q;
         if (row >= M) continue;                              // uniform per wavefront
-        const float *z = p.logits + (size_t)row * N;
-        uint16_t *g = (uint16_t *)p.grad + (size_t)row * N;
+        const Global<float> *z = logits + (size_t)row * N;
+        Global<uint16_t> *g = (Global<uint16_t> *)p.grad + (size_t)row * N;
         const int label = labels[q];
         float zmax = -INFINITY, denom = 0.0f, zlabel = 0.0f;
         if (in_regs) {
@@ -118,7 +117,7 @@ __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
                     if (hit) zlabel = zr[q][i][j];
                     h[j] = (e[i][j] * inv_d - (hit ? 1.0f : 0.0f)) * inv_m;
                 }
-                *(u32x2 *)(g + n) = u32x2{bf16_pack(h[0], h[1]), bf16_pack(h[2], h[3])};
+                *(Global<u32x2> *)(g + n) = u32x2{bf16_pack(h[0], h[1]), bf16_pack(h[2], h[3])};
             }
             // the lane that holds the label's class hands its logit to lane 0
             zlabel = __shfl(zlabel, (label & 255) >> 2, 64);
@@ -137,7 +136,7 @@ __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
         if (lane == 0) {
             const float loss = -(zlabel - zmax - logf(denom));
             row_loss[row - row0] = loss;
-            if (M > (uint32_t)kLossRows) p.row_loss[row] = loss;
+            if (M > (uint32_t)kLossRows) row_losses[row] = loss;
         }
     }
     __syncthreads();
@@ -148,7 +147,7 @@ __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
             const float v = row_loss[r < M ? r : 0];
             if (r < M) sum += v;
         }
-        *p.loss = sum / (float)M;
+        *(Global<float> *)p.loss = sum / (float)M;
     }
 }
 
@@ -180,14 +179,9 @@ hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, hipStream_t str
 {
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         LossArgs a{};
-        a.n = std::min(kMaxProblems, n - at);
-        uint64_t blocks = 0;
-        bool big = false;
-        for (uint32_t i = 0; i < a.n; ++i) {
-            a.p[i] = p[at + i];
-            blocks += (a.p[i].M + kLossRows - 1) / kLossRows;
-            big = big || a.p[i].M > (uint32_t)kLossRows;
-        }
+        const uint32_t count = std::min(kMaxProblems, n - at);
+        const uint64_t blocks = fill_group(a, p + at, count, [](const LossProblem &q) { return (uint64_t)((q.M + kLossRows - 1) / kLossRows); });
+        const bool big = std::any_of(p + at, p + at + count, [](const LossProblem &q) { return q.M > (uint32_t)kLossRows; });
         if (blocks == 0) continue;
         if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
         hipLaunchKernelGGL(softmax_xent_rows, dim3((uint32_t)blocks), dim3(64 * kLossWaves), 0, stream, a);
@@ -216,7 +210,8 @@ hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, hipStream_t str
 // ---------------------------------------------------------------------------
 struct UpdateArgs {
     uint32_t n;
-    uint32_t tiles;      // all tiles of the launch (the kernel whose workgroups loop over tiles)
+    uint32_t tiles;      // all tiles of the launch
+    uint32_t first[kMaxProblems];      // first tile of update i; kNoTile from n on
     UpdateProblem p[kMaxProblems];
 };
 
@@ -224,35 +219,20 @@ constexpr int kUpdK = 64, kUpdN = 256;      // workgroup tile
 constexpr double kDwTiledRows = 256;
 constexpr int kDwTile = 128;                // tile of the many-row kernel
 
-// Which update problem and tile workgroup `id` owns: lane i holds job i's tile count.
-__device__ inline int find_update(const UpdateProblem *p, uint32_t n, uint32_t id, uint32_t *t, uint32_t *kt)
-{
-    const int lane = threadIdx.x & 63;
-    const bool valid = lane < (int)n;
-    uint32_t k_tiles = 0, count = 0;
-    if (valid) {
-        k_tiles = (p[lane].K + kUpdK - 1) / kUpdK;
-        count = k_tiles * ((p[lane].N + kUpdN - 1) / kUpdN);
-    }
-    const uint32_t first = wave_excl_scan_u32(count, nullptr);
-    const int job = __builtin_amdgcn_readfirstlane(wave_find_range(first, id, valid));
-    *t = id - __shfl(first, job, 64);
-    *kt = __shfl(k_tiles, job, 64);
-    return job;
-}
-
-// Tile t of one job's update (kt = its number of 64-row tiles).
-__device__ inline void dw_sgd_tile(const UpdateProblem &p, uint32_t t, uint32_t kt)
+// Tile t of one job's update.
+__device__ inline void dw_sgd_tile(const UpdateProblem &p, uint32_t t)
 {
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t M = p.M, K = p.K, N = p.N;
+    const uint32_t M = p.M, K = p.K, N = p.N, kt = (K + kUpdK - 1) / kUpdK;
     const uint32_t k0 = (t % kt) * kUpdK;                  // neighbours share the G columns
     const uint32_t n0 = (t / kt) * kUpdN + 64 * wave;
     const uint32_t ncol = n0 + 4 * c;
     const bool col_ok = ncol < N;
-    const uint16_t *H = (const uint16_t *)p.H;
-    const uint16_t *G = (const uint16_t *)p.G;
+    const Global<uint16_t> *H = (const Global<uint16_t> *)p.H;
+    const Global<uint16_t> *G = (const Global<uint16_t> *)p.G;
+    Global<float> *Wm = (Global<float> *)p.Wm;
+    Global<uint16_t> *Wb = (Global<uint16_t> *)p.Wb;
 
     // master weights of this lane: rows k0 + 16g + 4r + i, columns ncol .. ncol+3
     f32x4 wm[16];
@@ -262,7 +242,7 @@ __device__ inline void dw_sgd_tile(const UpdateProblem &p, uint32_t t, uint32_t 
         for (int i = 0; i < 4; ++i) {
             const uint32_t krow = k0 + 16 * g + 4 * r + i;
             wm[r * 4 + i] = (krow < K && col_ok)
-                                ? __builtin_nontemporal_load((const f32x4 *)(p.Wm + (size_t)krow * N + ncol))
+                                ? __builtin_nontemporal_load((const Global<f32x4> *)(Wm + (size_t)krow * N + ncol))
                                 : f32x4{0.f, 0.f, 0.f, 0.f};
         }
 
@@ -276,8 +256,8 @@ __device__ inline void dw_sgd_tile(const UpdateProblem &p, uint32_t t, uint32_t 
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const uint32_t m = m0 + 8 * g + r;
-            h[r] = (m < M && kcol_ok) ? *(const u32x2 *)(H + (size_t)m * K + kcol) : u32x2{0u, 0u};
-            d[r] = (m < M && col_ok) ? *(const u32x2 *)(G + (size_t)m * N + ncol) : u32x2{0u, 0u};
+            h[r] = (m < M && kcol_ok) ? *(const Global<u32x2> *)(H + (size_t)m * K + kcol) : u32x2{0u, 0u};
+            d[r] = (m < M && col_ok) ? *(const Global<u32x2> *)(G + (size_t)m * N + ncol) : u32x2{0u, 0u};
         }
         u32x4 A[4], B[4];
 #pragma unroll
@@ -308,42 +288,35 @@ __device__ inline void dw_sgd_tile(const UpdateProblem &p, uint32_t t, uint32_t 
 #pragma unroll
             for (int j = 0; j < 4; ++j)      // one rounded multiply, one rounded subtract
                 w[j] = __fsub_rn(w[j], __fmul_rn(lr, acc[i * 4 + j][r]));
-            __builtin_nontemporal_store(w, (f32x4 *)(p.Wm + (size_t)krow * N + ncol));
+            __builtin_nontemporal_store(w, (Global<f32x4> *)(Wm + (size_t)krow * N + ncol));
             u32x2 b;
             b[0] = bf16_pack(w[0], w[1]);
             b[1] = bf16_pack(w[2], w[3]);
-            *(u32x2 *)((uint16_t *)p.Wb + (size_t)krow * N + ncol) = b;
+            *(Global<u32x2> *)(Wb + (size_t)krow * N + ncol) = b;
         }
 }
 
 __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
 {
-    uint32_t t, kt;
-    const int job = find_update(a.p, a.n, blockIdx.x, &t, &kt);
-    dw_sgd_tile(a.p[job], t, kt);
+    UpdateProblem p;
+    const uint32_t t = find_owner(a.first, a.p, blockIdx.x, p);
+    dw_sgd_tile(p, t);
 }
 
 // Many rows per job (the contraction is long): the product goes through the LDS tiles of tile_mfma.hpp, both operands
 // transposed on the way out of LDS.  M side: H (rows of W), N side: G (columns of W).
 struct UpdateWalk {
     const UpdateArgs &a;
-    uint32_t count;
+    const uint32_t first;      // lane i: the first tile of update i
     struct Place { int problem; uint32_t m0, n0, depth; };
-    __device__ uint32_t tiles() const { return count; }
+    __device__ explicit UpdateWalk(const UpdateArgs &args) : a(args), first(args.first[threadIdx.x & 63]) {}
+    __device__ uint32_t tiles() const { return a.tiles; }
     __device__ Place place(uint32_t tile_id) const
     {
-        const int lane = threadIdx.x & 63;
-        const bool valid = lane < (int)a.n;
-        uint32_t kt = 0, nt = 0;
-        if (valid) {
-            kt = (a.p[lane].K + kDwTile - 1) / kDwTile;
-            nt = (a.p[lane].N + kDwTile - 1) / kDwTile;
-        }
-        const uint32_t first = wave_excl_scan_u32(kt * nt, nullptr);
-        const uint32_t id = xcd_remap(tile_id, count);
-        const int g = __builtin_amdgcn_readfirstlane(wave_find_range(first, id, valid));
-        const uint32_t t = id - __shfl(first, g, 64), k = __shfl(kt, g, 64);
-        return {g, (uint32_t)__builtin_amdgcn_readfirstlane((t % k) * kDwTile), (uint32_t)__builtin_amdgcn_readfirstlane((t / k) * kDwTile), a.p[g].M};
+        const uint32_t id = xcd_remap(tile_id, a.tiles);
+        const int g = __builtin_amdgcn_readfirstlane(wave_find_range(first, id, true));
+        const uint32_t t = id - __builtin_amdgcn_readlane(first, g), kt = (a.p[g].K + kDwTile - 1) / kDwTile;
+        return {g, (t % kt) * kDwTile, (t / kt) * kDwTile, a.p[g].M};
     }
     __device__ Operand m(const Place &at) const { const UpdateProblem &p = a.p[at.problem]; return {p.H, p.M, p.K, p.K * 2u, false}; }
     __device__ Operand n(const Place &at) const { const UpdateProblem &p = a.p[at.problem]; return {p.G, p.M, p.N, p.N * 2u, false}; }
@@ -402,7 +375,7 @@ __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_tiled(UpdateArgs a)
 {
     using T = TileMfma<kDwTile, kDwTile, 2, 2, true, true>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
-    const UpdateWalk walk{a, a.tiles};
+    const UpdateWalk walk(a);
     T::run(walk, smem);
 }
 
@@ -410,15 +383,11 @@ static hipError_t launch_dw_tiled(const UpdateProblem *p, uint32_t n, hipStream_
 {
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         UpdateArgs a{};
-        a.n = std::min(kMaxProblems, n - at);
-        uint64_t tiles = 0;
-        for (uint32_t i = 0; i < a.n; ++i) {
-            a.p[i] = p[at + i];
-            tiles += (uint64_t)((a.p[i].K + kDwTile - 1) / kDwTile) * ((a.p[i].N + kDwTile - 1) / kDwTile);
-        }
+        const uint64_t tiles = fill_group(a, p + at, std::min(kMaxProblems, n - at), [](const UpdateProblem &q) {
+            return (uint64_t)((q.K + kDwTile - 1) / kDwTile) * ((q.N + kDwTile - 1) / kDwTile);
+        });
         if (tiles == 0) continue;
         if (tiles > 0x7fffffffull) return hipErrorInvalidValue;
-        a.tiles = (uint32_t)tiles;
         hipLaunchKernelGGL(grouped_dw_sgd_tiled, dim3((uint32_t)std::min<uint64_t>(tiles, 2 * resident_grid())), dim3(256), 0, stream, a);
         if (launches) *launches += 1;
         hipError_t e = hipGetLastError();
@@ -444,12 +413,9 @@ hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, hipStream_t
     if (fits && rows >= kDwTiledRows * weights) return launch_dw_tiled(p, n, stream, launches);
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         UpdateArgs a{};
-        a.n = std::min(kMaxProblems, n - at);
-        uint64_t tiles = 0;
-        for (uint32_t i = 0; i < a.n; ++i) {
-            a.p[i] = p[at + i];
-            tiles += (uint64_t)((a.p[i].K + kUpdK - 1) / kUpdK) * ((a.p[i].N + kUpdN - 1) / kUpdN);
-        }
+        const uint64_t tiles = fill_group(a, p + at, std::min(kMaxProblems, n - at), [](const UpdateProblem &q) {
+            return (uint64_t)((q.K + kUpdK - 1) / kUpdK) * ((q.N + kUpdN - 1) / kUpdN);
+        });
         if (tiles == 0) continue;
         if (tiles > 0x7fffffffull) return hipErrorInvalidValue;
         hipLaunchKernelGGL(grouped_dw_sgd, dim3((uint32_t)tiles), dim3(256), 0, stream, a);

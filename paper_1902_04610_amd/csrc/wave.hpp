@@ -9,6 +9,11 @@ namespace salus {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// A T in device memory, for addresses the compiler cannot trace to a kernel argument (it would use flat accesses,
+// which count as LDS accesses too and are waited for in order).
+template <typename T>
+using Global = T __attribute__((address_space(1)));
+
 // Exclusive prefix sum across the 64 lanes of a wavefront (Hillis-Steele over
 // cross-lane shuffles).  *total receives the sum over all lanes.
 __device__ inline uint64_t wave_excl_scan_u64(uint64_t v, uint64_t *total)
@@ -21,19 +26,6 @@ __device__ inline uint64_t wave_excl_scan_u64(uint64_t v, uint64_t *total)
         if (lane >= d) incl += up;
     }
     if (total) *total = __shfl((unsigned long long)incl, 63, 64);
-    return incl - v;
-}
-
-__device__ inline uint32_t wave_excl_scan_u32(uint32_t v, uint32_t *total)
-{
-    const int lane = threadIdx.x & 63;
-    uint32_t incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t up = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += up;
-    }
-    if (total) *total = __shfl(incl, 63, 64);
     return incl - v;
 }
 
