@@ -38,31 +38,26 @@ inline uint64_t fill_group(Args &a, const P *p, uint32_t n, Tiles tiles)
 constexpr int kGemmThreads = 256;
 constexpr int kWaves = 4;
 
-// bf16 kernels: GELU(z) = z / 2 + |z| (1/2 - Q(|z|)) with the upper tail Q(x) = erfc(x / sqrt 2) / 2
-// taken from approximation 7.1.28 of Abramowitz & Stegun, erfc(y) = (1 + a1 y + ... + a6 y^6)^-16
-// (absolute error below 3e-7, far inside half a bf16 step): the factors 1 / sqrt 2 of y and 2^(1/16) of
-// the 1/2 are folded into the coefficients, so it is six multiply-adds, one reciprocal, four squarings
-// and three more operations, no exponential and no branch (in float arithmetic over [-9, 9]: |error| of
-// the result below 8e-7).  The error is *absolute* in Q, so for z < -3.5, where Q itself falls below
-// 5e-4, the relative error of a single output grows - such outputs are below 1e-3 in magnitude and only
-// decide a comparison when a whole matrix consists of them (then the error relative to the largest
-// output is up to 2.3e-3, still inside the 2e-2 bound of the bf16 path).  Large |z| overflow the polynomial to
-// infinity, whose reciprocal is the right Q = 0; a NaN stays a NaN.
+// bf16 kernels: GELU(z) = z / 2 + |z| (1/2 - Q(|z|)) with the upper tail Q(x) = erfc(x / sqrt 2) / 2 = 2^p(x), p the
+// polynomial of degree 6 that minimizes the largest |x (2^p - Q)| over [0, 5.5] (fitted by linear programming: 9.4e-8),
+// evaluated up to 9, from where on Q is below 2^-62 and 1/2 - Q is 1/2.  Fourteen operations, counting the exponential
+// (v_exp_f32) as four: the epilogues of wide layers are bound by them, and where the power limit sets the clock they cost
+// what multiplies could use (16 jobs x 4096 rows, 1024 - 4096 - 1024 - 1024: 1186 us, 1264 with the rational
+// approximation of erfc before it).  In float arithmetic over [-40, 40]: |error| of the result below 3.8e-7 (7.6e-7).  The error is *absolute* in Q,
+// so for z < -3.5, where Q itself falls below 5e-4, the relative error of a single output grows; such outputs are below
+// 1e-3 in magnitude and only decide a comparison when a whole matrix consists of them.  Infinities give what the sum
+// of z / 2 and |z| / 2 gives, a NaN stays a NaN.
 __device__ inline float gelu_fast(float z)
 {
-    const float x = fabsf(z);
-    float p = fmaf(5.62129980608006e-06f, x, 5.105520904180594e-05f);
-    p = fmaf(p, x, 3.9686136005911976e-05f);
-    p = fmaf(p, x, 0.003422739217057824f);
-    p = fmaf(p, x, 0.02207699790596962f);
-    p = fmaf(p, x, 0.052075162529945374f);
-    p = fmaf(p, x, 1.0442737340927124f);
-    float r = __frcp_rn(p);
-    r *= r;
-    r *= r;
-    r *= r;
-    r *= r;                                   // Q(|z|)
-    return fmaf(x, 0.5f - r, 0.5f * z);
+    const float x = fabsf(z), c = __builtin_amdgcn_fmed3f(x, 0.0f, 9.0f);
+    float p = fmaf(2.90425268758554e-05f, c, -0.0007323235622607172f);
+    p = fmaf(p, c, 0.007953787222504616f);
+    p = fmaf(p, c, -0.05320511385798454f);
+    p = fmaf(p, c, -0.45893481373786926f);
+    p = fmaf(p, c, -1.1511449813842773f);
+    p = fmaf(p, c, -0.9999991059303284f);
+    const float q = __builtin_amdgcn_exp2f(p);
+    return fmaf(x, 0.5f - q, 0.5f * z);
 }
 
 __device__ inline float activate(float z, uint32_t act)
