@@ -135,10 +135,11 @@ struct DenseWalk {
 // chip then holds, no bank conflicts.  Layers of 16 slabs: the epilogue, which the one workgroup of a compute unit does with
 // all its wavefronts at once, 128 outputs per lane (pipes 42 % at 1.95 GHz).  1024 -> 4096 -> 1024 -> 1024 with GELU, 16 jobs x
 // 4096 rows: 1270 - 1290 us (1421).
+// <128, 256, 1, 4>: the tile of two workgroups per compute unit.
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled(GroupArgs a)
 {
-    using T = TileMfma<BM, BN, WM, WN, false, true>;
+    using T = std::conditional_t<BM * BN == 128 * 256 && WM * WN == 4, TilePair<BM, BN, WM, WN>, TileMfma<BM, BN, WM, WN, false, true>>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
     const DenseWalk<BM, BN, false> walk(a);
     T::run(walk, smem);
@@ -284,26 +285,35 @@ hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStre
 // Which tile a launch takes.  The grid walks its tiles in rounds of one (or two) per compute unit, so what counts is
 // rounds x time of a round; a large tile moves fewer operand bytes per multiply but leaves the last round emptier
 // and pads more.  Times of a round in nanoseconds, a slab and the rest (prologue and epilogue), fitted to launches of
-// 16 jobs x 4096 rows, 4096 -> 1024 and 1024 -> 1024 (measured 489 / 163 us with 256 x 256 tiles, 545 / 186 with 128 x
-// 256, 626 / 206 with 128 x 128); of two 128 x 128 tiles on a compute unit one ends while the other multiplies, so their rest counts
-// less (fitted to 2300 launches of 64 - 4096 -> 256 - 4096, where the choice is then 1.2 % off the best kind on average); with at
-// most one 128 x 128 tile per compute unit a slab takes half as long.  What the rule is for: 4 jobs x 500 rows, 2048 ->
-// 2048: 50 / 33 / 26 us; 24 jobs x 300 rows, 256 -> 4096: 45 / 42 / 36; 32 jobs x 300 - 1000 rows, 4096 -> 1024: 212 /
-// 205 / 235, 1024 -> 4096: 237 / 254 / 277.
+// 16 jobs x 4096 rows, 4096 -> 1024 and 1024 -> 1024 (measured 480 / 161 us with 256 x 256 tiles, 536 / 175 with 128 x
+// 256, 515 / 171 with two of those per compute unit, 612 / 201 with 128 x 128); of two tiles on a compute unit one ends
+// while the other multiplies, so their rest counts less, and in a last round with at most one per compute unit a tile takes
+// 0.6 of the time.  Two 128 x 256 tiles per compute unit also cover each other's waits for weights: where every weight
+// is used by one row tile (up to 128 rows) and most compute units have one, half (64 jobs x 100 rows, 1024 -> 1024: 28 us,
+// one per compute unit with twice the wavefronts 38; 24 jobs 20 / 18, so not there).  Over 528 launches of 33 - 4096 rows,
+// 512 - 4096 -> 512 - 4096, the choice is 1.0 % off the best kind on average; without that kind it was 2.4 % slower.  What the rule is
+// for: 4 jobs x 500 rows, 2048 -> 2048, 256 x 256 / 128 x 256 / 128 x 128 / two 128 x 256: 48 / 30 / 25 / 33 us; 32 jobs x
+// 300 - 1000 rows, 4096 -> 1024 207 / 200 / 222 / 195, 1024 -> 1024 70 / 69 / 61 / 55; 32 jobs x 500 rows, 1024 -> 4096 167 /
+// 190 / 222 / 181.
 struct TileKind { uint32_t bm, bn, per_cu, slab_ns, rest_ns; };
-constexpr TileKind kTile256 = {256, 256, 1, 1640, 12000}, kTile128x256 = {128, 256, 1, 935, 8000}, kTile128 = {128, 128, 2, 1090, 6000};
+constexpr TileKind kTile256 = {256, 256, 1, 1640, 12000}, kTile128x256 = {128, 256, 1, 935, 8000}, kTile128 = {128, 128, 2, 1090, 6000},
+                   kTilePair = {128, 256, 2, 1720, 12000};
 
 static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n)
 {
     uint64_t tiles = 0, work = 0;
+    bool weight_bound = true;
     for (uint32_t i = 0; i < n; ++i) {
         const uint64_t count = (uint64_t)((p[i].M + t.bm - 1) / t.bm) * ((p[i].N + t.bn - 1) / t.bn);
         tiles += count;
         work += count * (((uint64_t)p[i].K + kSlab - 1) / kSlab * t.slab_ns + t.rest_ns);
+        weight_bound = weight_bound && p[i].M <= 128;
     }
     if (tiles == 0) return 0;
-    const uint64_t cus = resident_grid(), rounds = (tiles + cus * t.per_cu - 1) / (cus * t.per_cu);
-    return rounds * (work / tiles) / (t.per_cu == 2 && tiles <= cus ? 2 : 1);
+    const uint64_t cus = resident_grid(), grid = cus * t.per_cu, last = tiles % grid;
+    uint64_t tenths = tiles / grid * 10;       // of a round
+    if (last) tenths += t.per_cu == 1 || last > cus ? 10 : &t == &kTilePair && weight_bound && last * 4 > cus * 3 ? 5 : 6;
+    return tenths * (work / tiles) / 10;
 }
 
 // Launches bound by the weight stream.  64 x 128 tiles, two workgroups per compute unit; 64 x 64, twice the workgroups,
@@ -337,7 +347,7 @@ static TileChoice choose_tile(const std::vector<Problem> &p, bool tall)
     TileChoice best{nullptr, ~0ull};
     if (p.empty()) return best;
     const bool shallow = std::all_of(p.begin(), p.end(), tiled_shape_shallow);
-    for (const TileKind *t : {&kTile256, &kTile128x256, &kTile128}) {
+    for (const TileKind *t : {&kTile256, &kTile128x256, &kTile128, &kTilePair}) {
         if ((t == &kTile256 && !tall) || (t != &kTile128 && shallow)) continue;
         const uint64_t ns = launch_ns(*t, p.data(), (uint32_t)p.size());
         if (ns < best.ns) best = {t, ns};
@@ -375,6 +385,7 @@ hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t s
         const uint32_t count = (uint32_t)group->size();
         const TileKind *kind = group == &big ? tall.kind : low.kind;
         const hipError_t e = kind == &kTile256       ? launch_tiled<256, 256, 1>(grouped_dense_bf16_tiled<256, 256, 2, 4>, 512, q, count, stream, launches)
+                             : kind == &kTilePair    ? launch_tiled<128, 256, 2>(grouped_dense_bf16_tiled<128, 256, 1, 4>, 256, q, count, stream, launches)
                              : kind == &kTile128x256 ? launch_tiled<128, 256, 1>(grouped_dense_bf16_tiled<128, 256, 2, 4>, 512, q, count, stream, launches)
                                                      : launch_tiled<128, 128, 2>(grouped_dense_bf16_tiled<128, 128, 2, 2>, 256, q, count, stream, launches);
         if (e != hipSuccess) return e;

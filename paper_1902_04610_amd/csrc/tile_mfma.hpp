@@ -93,17 +93,19 @@ __device__ inline uint32_t tr_swizzle(uint32_t row) { return B >= 128 ? 4u * (ro
 // One operand's request stream: where it is in the walk and what this wavefront's share of it is, I instructions of
 // 1 KB per slab.  Requests are issued in k-steps 3, 0, 1, 2 (major: a slab, three slabs ahead) or 1, 2 and 3, 0 (tr: the
 // first and the second half of a slab, two slabs ahead) of the slab being multiplied.
-template <int B, bool TR, int WAVES, int STAGES = TR ? 2 : 3>
+// UNIT: k-values of a stage (a major operand's is a whole slab, the 128 bytes of a line).
+template <int B, bool TR, int WAVES, int STAGES = TR ? 2 : 3, uint32_t UNIT = kSlab>
 struct OperandStream {
-    static constexpr int kBytes = B * (int)kSlab * 2, I = kBytes / 1024 / WAVES;
+    static constexpr int kBytes = B * (int)UNIT * 2, I = kBytes / 1024 / WAVES;
     static constexpr int kStages = STAGES, kRing = kStages * kBytes;
     static constexpr int kHalf = I > 1 ? I / 2 : 1;
     static constexpr int kChunks = B / 8, kRowsPer = TR ? 64 / kChunks : 8;      // tr: 16-byte chunks of a k-row
     static_assert(I >= 1 && kBytes == I * 1024 * WAVES && (!TR || STAGES != 2 || I % 2 == 0), "whole instructions per wavefront");
-    uint64_t base;        // scalar: of the slab under the cursor
-    uint64_t stride;      // bytes per slab
+    static_assert(UNIT == kSlab || (TR && STAGES != 2), "parts of a slab");
+    uint64_t base;        // scalar: of the slab (unit) under the cursor
+    uint64_t stride;      // bytes per slab (unit)
     uint32_t off[I];      // per lane
-    uint32_t k, depth, slabs_left, at;      // at: offset in the ring of the stage it goes to
+    uint32_t k, depth, slabs_left, at;      // at: offset in the ring of the stage it goes to; slabs_left: in units
     int lane_k;           // this lane's k-row (tr) or first k-value (major) in a request of piece 0
 
     __device__ void start(int lane)
@@ -128,7 +130,7 @@ struct OperandStream {
         uint64_t from;
         if (TR) {
             from = o.strip ? (uint64_t)(first >> 7) * o.depth * 256u + (first & 127u) * 2u : (uint64_t)first * 2u;
-            stride = (uint64_t)kSlab * o.pitch;
+            stride = (uint64_t)UNIT * o.pitch;
         } else {
             from = (uint64_t)first * o.pitch;
             stride = kSlab * 2;
@@ -137,7 +139,7 @@ struct OperandStream {
         stride = uniform64(stride);
         k = 0;
         depth = __builtin_amdgcn_readfirstlane((uint32_t)o.depth);
-        slabs_left = __builtin_amdgcn_readfirstlane(max((depth + kSlab - 1) / kSlab, kMinSlabs));
+        slabs_left = __builtin_amdgcn_readfirstlane(max((depth + kSlab - 1) / kSlab, kMinSlabs) * (kSlab / UNIT));
 #pragma unroll
         for (int i = 0; i < I; ++i) {
             const uint32_t r = row_of(wave, i, lane), c = chunk_of(r, lane);
@@ -170,7 +172,7 @@ struct OperandStream {
     __device__ void advance()
     {
         base += stride;
-        k += kSlab;
+        k += UNIT;
         --slabs_left;
         at = at + kBytes == (uint32_t)kRing ? 0u : at + kBytes;
     }
@@ -381,6 +383,156 @@ struct TileMfma {
                 break;
             }
             cur = ahead;         // crossed into by the request cursor at least one slab ago, and no further
+        }
+    }
+};
+
+// The same product with two workgroups per compute unit (M side major, N side tr): while one is in its epilogue, or waits,
+// the other multiplies.  Half the LDS each: the M side has two slabs, the N side three half slabs of 32 k-rows.  Per
+// slab two barriers, before k-steps 1 and 3.  After the first, the slab's first half of N has been read and its stage is
+// requested into (second half of the next slab); after the other, its second half and the M slab (first half and M slab two
+// ahead).  Requests have the three k-steps to the barrier that needs them.
+template <int BM, int BN, int WM, int WN>
+struct TilePair {
+    static constexpr int kWavesT = WM * WN, kThreads = 64 * kWavesT;
+    static constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
+    using SM = OperandStream<BM, false, kWavesT, 2>;
+    using SN = OperandStream<BN, true, kWavesT, 3, kSlab / 2>;
+    static constexpr uint32_t kLds = SM::kRing + SN::kRing;
+    static_assert(kLds <= 80 * 1024, "half the LDS of a compute unit");
+    typedef f32x16 Acc[FN][FM];
+
+    template <typename Walk>
+    __device__ static void run(const Walk &walk, unsigned char *smem)
+    {
+        const int lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t wm = wave / WN, wn = wave % WN;
+        const uint32_t lds_m = lds_address(smem), lds_n = lds_m + SM::kRing;
+        Fragments<BM, false, FM> fm;
+        Fragments<BN, true, FN> fn;
+        fm.init(wm * (32u * FM), lane);
+        fn.init(wn * (32u * FN), lane);
+
+        const uint32_t tiles = walk.tiles();
+        uint32_t id = blockIdx.x;                // of the tile that the M stream walks towards
+        typename Walk::Place ahead = walk.place(id), cur = ahead;
+        uint32_t cur_id = id;
+        SM sm;
+        SN sn;
+        sm.start(lane);
+        sn.start(lane);
+        sm.locate(walk.m(ahead), ahead.m0, wave);
+        sn.locate(walk.n(ahead), ahead.n0, wave);
+        // Crossed into right before the first request of the next tile, the M side first (k-step 3 of the last but one slab).
+        auto cross_m = [&]() {
+            if (sm.slabs_left != 0) return;
+            id += gridDim.x;
+            if (id < tiles) {
+                ahead = walk.place(id);
+                sm.locate(walk.m(ahead), ahead.m0, wave);
+            } else sm.stop();
+        };
+        auto cross_n = [&]() {
+            if (sn.slabs_left != 0) return;
+            if (id < tiles) sn.locate(walk.n(ahead), ahead.n0, wave);
+            else sn.stop();
+        };
+        auto fetch_m = [&]() {
+#pragma unroll
+            for (int i = 0; i < SM::I; ++i) sm.fetch(i, lds_m, wave);
+            sm.advance();
+        };
+        auto fetch_n = [&]() {
+#pragma unroll
+            for (int i = 0; i < SN::I; ++i) sn.fetch(i, lds_n, wave);
+            sn.advance();
+        };
+        // what steady state has requested before k-step 0 of slab 0, of which the first reads need the first two
+        fetch_m();
+        fetch_n();
+        fetch_n();
+        fetch_m();
+        fetch_n();
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(SM::I + 2 * SN::I) : "memory");
+
+        Acc acc;
+        bf16x8 a[2][FN], b[2][FM];
+        uint32_t at_m = 0, at_n = 0;             // ring offsets of what is read
+        auto read = [&](int r, int ks, int set) {
+            const unsigned char *base_m = smem + at_m, *base_n = smem + SM::kRing + at_n;
+            if (r == 0) b[set][0] = fm.read(base_m, ks, 0);
+            else if (r == 1) a[set][0] = fn.read(base_n, ks & 1, 0);
+            else if (r < FM + 1) b[set][r - 1] = fm.read(base_m, ks, r - 1);
+            else if (r < FM + FN) a[set][r - FM] = fn.read(base_n, ks & 1, r - FM);
+        };
+        // k-step q: its multiplies, with the reads of the next one and the requests of q between them
+        auto step = [&](int q) {
+            const int set = q & 1;
+            int r = 0, f = 0;
+            const int requests = q == 1 ? SN::I : q == 3 ? SN::I + SM::I : 0;
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int i = 0; i < FM; ++i) {
+                    acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[set][j], b[set][i], acc[j][i], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const int n = j * FM + i + 1;
+                    const int until = (n * (FM + FN) + FM * FN - 2) / (FM * FN - 1);
+#pragma unroll
+                    for (; r < until && r < FM + FN; ++r) read(r, (q + 1) & 3, set ^ 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const int upto = n * requests / (FM * FN);
+#pragma unroll
+                    for (; f < upto; ++f) {
+                        if (q == 3 && f < SM::I) sm.fetch(f, lds_m, wave);
+                        else sn.fetch(f - (q == 3 ? SM::I : 0), lds_n, wave);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            if (q == 3) sm.advance();
+            if (q & 1) sn.advance();
+        };
+        bool landed = false;                     // everything requested up to the last epilogue
+        auto next_n = [&]() { at_n = at_n + SN::kBytes == (uint32_t)SN::kRing ? 0u : at_n + SN::kBytes; };
+
+#pragma unroll
+        for (int r = 0; r < FM + FN; ++r) read(r, 0, 0);
+        for (;;) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+            uint32_t left = __builtin_amdgcn_readfirstlane(max((cur.depth + kSlab - 1) / kSlab, kMinSlabs));
+#pragma clang loop unroll(disable)
+            do {
+                step(0);
+                if (landed) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(SM::I + SN::I) : "memory");
+                next_n();
+                step(1);
+                step(2);
+                if (landed) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(SN::I) : "memory");
+                landed = false;
+                cross_m();
+                cross_n();
+                next_n();
+                at_m = at_m + SM::kBytes == (uint32_t)SM::kRing ? 0u : at_m + SM::kBytes;
+                step(3);
+            } while (--left != 0);
+            walk.finish(cur, acc, wm * (32u * FM), wn * (32u * FN), fresh_lane(), [&]() {
+                if (!landed) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                landed = true;
+            });
+            cur_id += gridDim.x;
+            if (cur_id >= tiles) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may arrive in LDS after this workgroup
+                break;
+            }
+            cur = ahead;
         }
     }
 };

@@ -187,3 +187,14 @@ def test_counters_of_the_in_place_move_never_wrap(record):
     assert [re.findall(r"launch (slide_\w+)", lines) for _, lines in runs] == \
         [["slide_clear", "slide_down"], ["slide_down"], ["slide_down"], ["slide_clear", "slide_down"], ["slide_down"],
          ["slide_clear", "slide_down"], ["slide_down"]]
+
+
+def test_two_tiles_of_128_by_256_per_compute_unit(record):
+    """Where they leave less of the last round empty than 256 x 256 or waste less of it than 128 x 128; 256 of them only if the
+    launch is bound by weights (up to 128 rows)."""
+    check(record, [(case(rows, K, N), ["grouped_dense_bf16_tiled" + kernel]) for rows, K, N, kernel in (
+        ([65] * 64, 320, 1024, "<128, 256, 1, 4>"), ([100] * 64, 1024, 1024, "<128, 256, 1, 4>"),
+        ([293, 300, 299] * 11, [320, 320, 328] * 11, 1544, "<128, 256, 1, 4>"), ([100] * 64, 384, 1544, "<128, 256, 1, 4>"),
+        ([100] * 48, 1024, 1024, "<128, 256, 2, 4>"), ([200] * 24, 1024, 1024, "<128, 256, 2, 4>"),
+        ([500] * 4, 2048, 2048, "<128, 128, 2, 2>"), ([4096] * 4, 1024, 4096, "<256, 256, 2, 4>"),
+    )])

@@ -102,3 +102,17 @@ def test_shallow_depth_from_128_rows(jobs, M, K, N, strip, launches):
 def test_float_outputs_past_l2(jobs, M, K, N):
     """Results stored past L2 (rows that begin on a line; 256 x 256 tiles below one round and above three) and not."""
     check([dict(M=M - (i % 2), dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]], strip=False) for i in range(jobs)], 1 if jobs <= 64 else 2)
+
+
+@pytest.mark.parametrize("jobs, M, Ks, N, strip", [
+    (64, 65, [320], 1024, True),                    # one tile for every workgroup
+    (33, 300, [320, 320, 328], 1544, False),        # more tiles than workgroups, the walk crosses from one depth to another
+    (33, 299, [448, 320], 1024, True), (64, 100, [384], 1544, False),
+])
+def test_two_tiles_of_128_by_256_per_compute_unit(jobs, M, Ks, N, strip):
+    check([dict(M=max(65, M - 7 * (i % 3)), dims=(Ks[i % len(Ks)], N), acts=[[GELU, RELU, NONE][i % 3]], strip=strip) for i in range(jobs)], 1)
+
+
+def test_hidden_layers_in_two_tiles_of_128_by_256_per_compute_unit():
+    """bf16 outputs of such tiles, and their use as inputs; rows end inside a tile."""
+    check([dict(M=293 + i % 8, dims=(328, 1544, 136), acts=[GELU if i % 2 else RELU, NONE], strip=False) for i in range(33)], 2)
