@@ -14,7 +14,7 @@
 #include <algorithm>
 #include <vector>
 
-#include "dense_tile.hpp"
+#include "narrow_tile.hpp"
 
 namespace salus {
 
@@ -32,22 +32,33 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16(GroupArgs a)
 }
 
 // 16 * CPL columns per workgroup, for launches with few jobs: what a launch lasts is then how long one
-// compute unit streams one tile, so the tile is narrow and there are more of them.  A wavefront's k-step is only CPL / 8
-// of 8 KB: deep layers keep DEEP of them in flight instead of two.
+// compute unit streams one tile, so the tile is narrow and there are more of them.  Where every weight is read by one row
+// tile (NT) its operands go straight into LDS (narrow_tile.hpp).  Transposed weights, whose lanes load 16 bytes as it
+// is, and several row tiles above one another (4 jobs x 64 rows, 2048 -> 512: 7.6 us, through LDS 7.9; 16 jobs x 33 rows,
+// 128 -> 512 4.0 / 4.4) keep registers.  A wavefront's k-step is only CPL / 8 of 8 KB there: deep layers keep DEEP of them
+// in flight instead of two.
 constexpr uint32_t kNarrowDeepK = 2048;
 template <int MT, bool TW, int CPL, int DEEP, bool NT = true>
 __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(GroupArgs a)
 {
-    __shared__ float lds[reduce_lds_floats<MT * CPL>()];
     Problem p;
-    const Tile tile = find_tile<16 * MT, 16 * CPL>(a, p);
-    const bool one = MT == 2 && p.M <= 16;
-    if (p.K > kNarrowDeepK) {
-        if (one) dense_bf16_tile<1, TW, NT, CPL, DEEP>(p, tile, lds);
-        else dense_bf16_tile<MT, TW, NT, CPL, DEEP>(p, tile, lds);
+    if constexpr (TW || !NT) {
+        __shared__ float lds[reduce_lds_floats<MT * CPL>()];
+        const Tile tile = find_tile<16 * MT, 16 * CPL>(a, p);
+        const bool one = MT == 2 && p.M <= 16;
+        if (p.K > kNarrowDeepK) {
+            if (one) dense_bf16_tile<1, TW, NT, CPL, DEEP>(p, tile, lds);
+            else dense_bf16_tile<MT, TW, NT, CPL, DEEP>(p, tile, lds);
+        } else {
+            if (one) dense_bf16_tile<1, TW, NT, CPL>(p, tile, lds);
+            else dense_bf16_tile<MT, TW, NT, CPL>(p, tile, lds);
+        }
     } else {
-        if (one) dense_bf16_tile<1, TW, NT, CPL>(p, tile, lds);
-        else dense_bf16_tile<MT, TW, NT, CPL>(p, tile, lds);
+        constexpr uint32_t kOne = NarrowTile<1, CPL>::kLds, kAll = NarrowTile<MT, CPL>::kLds;
+        __shared__ __attribute__((aligned(1024))) unsigned char smem[kOne > kAll ? kOne : kAll];
+        const Tile tile = find_tile<16 * MT, 16 * CPL>(a, p);
+        if (MT == 2 && p.M <= 16) NarrowTile<1, CPL>::run(p, tile, smem);
+        else NarrowTile<MT, CPL>::run(p, tile, smem);
     }
 }
 
@@ -213,29 +224,37 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
         else hipLaunchKernelGGL((grouped_dense_bf16<1, false, true>), grid, block, 0, stream, a);
     };
     if (!small.empty()) {
-        // As many workgroups as compute units, not more: a narrower tile streams less efficiently.  128 / 64 / 32 columns:
-        // one job, 4096 -> 1024: 21.4 / 16.3 / 12.7 us (8 / 16 / 32 workgroups; with two k-steps in flight 18.3 / 15.3),
-        // 1024 -> 4096 8.8 / 7.4 / 6.6; 2048 -> 2048 of 4 jobs 20.3 / 16.2 / 14.5, of 8 jobs 18.3 / 15.5 / 20.9, of 16 jobs
-        // 25.6 / 28.8 / 43.6.
+        // As many workgroups as compute units, not more: a narrower tile streams less efficiently.  32 / 16 columns, one job x
+        // 1 row: 2048 -> 1024 4.9 / 4.0 us (32 / 64 workgroups; 32 columns through registers 9.2), 1024 -> 1024 3.6 / 3.2, x 32 rows
+        // 5.1 / 4.8, 4 jobs x 32 rows 5.3 / 5.0.  Transposed weights, 128 / 64 / 32 columns: 2048 -> 2048 of 4 jobs 20.3 /
+        // 16.2 / 14.5, of 8 jobs 18.3 / 15.5 / 20.9, of 16 jobs 25.6 / 28.8 / 43.6.  (Widths from 2^22, which the direct-to-LDS
+        // loads cannot address, keep 128.)
+        auto launch_16 = [&](int mt, const GroupArgs &a, uint32_t tiles) {
+            const dim3 grid(tiles), block(kGemmThreads);
+            if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 1, 0>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 1, 0>), grid, block, 0, stream, a);
+        };
         auto launch_64 = [&](int mt, const GroupArgs &a, uint32_t tiles) {
             const dim3 grid(tiles), block(kGemmThreads);
             if (mt == 2 && trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, true, 4, 4>), grid, block, 0, stream, a);
-            else if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 4, 4>), grid, block, 0, stream, a);
+            else if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 4, 0>), grid, block, 0, stream, a);
             else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, true, 4, 4>), grid, block, 0, stream, a);
-            else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 4, 4>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 4, 0>), grid, block, 0, stream, a);
         };
         auto launch_32 = [&](int mt, const GroupArgs &a, uint32_t tiles) {
             const dim3 grid(tiles), block(kGemmThreads);
             if (mt == 2 && trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, true, 2, 8>), grid, block, 0, stream, a);
-            else if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 8>), grid, block, 0, stream, a);
+            else if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 0>), grid, block, 0, stream, a);
             else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, true, 2, 8>), grid, block, 0, stream, a);
-            else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 2, 8>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 2, 0>), grid, block, 0, stream, a);
         };
         const Problem *q = small.data();
         const uint32_t count = (uint32_t)small.size();
-        const hipError_t e = small_tiles * 4 <= kFullGrid   ? launch_groups(q, count, 32, 16, 32, launch_32, launches)
-                             : small_tiles * 2 <= kFullGrid ? launch_groups(q, count, 64, 16, 32, launch_64, launches)
-                                                            : launch_groups(q, count, 128, 16, 32, launch_wide, launches);
+        const bool narrow = small_tiles * 2 <= kFullGrid && (trans_w || std::all_of(small.begin(), small.end(), tiled_shape_fits));
+        const hipError_t e = !narrow                                      ? launch_groups(q, count, 128, 16, 32, launch_wide, launches)
+                             : !trans_w && small_tiles * 8 <= kFullGrid   ? launch_groups(q, count, 16, 16, 32, launch_16, launches)
+                             : small_tiles * 4 <= kFullGrid               ? launch_groups(q, count, 32, 16, 32, launch_32, launches)
+                                                                          : launch_groups(q, count, 64, 16, 32, launch_64, launches);
         if (e != hipSuccess) return e;
     }
     if (!mid.empty() && !trans_w) {

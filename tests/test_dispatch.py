@@ -198,3 +198,13 @@ def test_two_tiles_of_128_by_256_per_compute_unit(record):
         ([100] * 48, 1024, 1024, "<128, 256, 2, 4>"), ([200] * 24, 1024, 1024, "<128, 256, 2, 4>"),
         ([500] * 4, 2048, 2048, "<128, 128, 2, 2>"), ([4096] * 4, 1024, 4096, "<256, 256, 2, 4>"),
     )])
+
+
+def test_narrow_tiles_up_to_32_rows(record):
+    """The fewest columns that leave at most one tile per compute unit, 16 at least; 128 once 64 leave more."""
+    check(record, [(case(rows, K, N), ["grouped_dense_bf16" + kernel]) for rows, K, N, kernel in (
+        ([1], 4096, 4096, "_narrow<1, false, 1, 0, true>"), ([17] * 4, 1024, 1024, "_narrow<2, false, 1, 0, true>"),
+        ([16] * 5, 1024, 1024, "_narrow<1, false, 2, 0, true>"), ([17] * 8, 1024, 1024, "_narrow<2, false, 2, 0, true>"),
+        ([32] * 9, 1024, 1024, "_narrow<2, false, 4, 0, true>"), ([8] * 16, 1024, 1024, "_narrow<1, false, 4, 0, true>"),
+        ([8] * 17, 1024, 1024, "<1, false, true>"), ([1], 8, 1 << 22, "<1, false, true>"),
+    )])

@@ -116,3 +116,46 @@ def test_two_tiles_of_128_by_256_per_compute_unit(jobs, M, Ks, N, strip):
 def test_hidden_layers_in_two_tiles_of_128_by_256_per_compute_unit():
     """bf16 outputs of such tiles, and their use as inputs; rows end inside a tile."""
     check([dict(M=293 + i % 8, dims=(328, 1544, 136), acts=[GELU if i % 2 else RELU, NONE], strip=False) for i in range(33)], 2)
+
+
+@pytest.mark.parametrize("jobs, dims, strip", [
+    (1, (8, 8), False), (1, (24, 16, 40, 8), False), (3, (4104, 24), False), (2, (1000, 2056, 264, 520), False), (2, (512, 1024, 128), True),      # 16 columns
+    (5, (264, 1032, 136), False), (7, (1032, 1024, 32), True),                               # 32 (layers of 1024 columns)
+    (12, (520, 1032, 8), False), (14, (136, 1024, 1032), True),                              # 64
+])
+def test_narrow_tiles_up_to_32_rows(jobs, dims, strip):
+    """Depths that end inside a k-step, a pair of them or the ring; widths that end inside a tile; 1 - 32 rows, one row tile and two
+    in a launch.  The order of the sums is that of the wide tiles: the depth-fused launch gives the same bits."""
+    specs = [dict(M=[1, 16, 17, 32, 7][i % 5], dims=dims, acts=([GELU, RELU] * 2)[:len(dims) - 2] + [NONE], strip=strip) for i in range(jobs)]
+    outs, refs, n = run_jobs(specs, salus.BF16)
+    assert n == len(dims) - 1
+    fused, _, _ = run_jobs(specs, salus.BF16, fuse=True)
+    for o, r, f, j in zip(outs, refs, fused, specs):
+        assert np.isfinite(o).all(), j
+        assert norm_rel_err(o, r) < TOL_BF16_TIGHT, (j, norm_rel_err(o, r))
+        assert np.array_equal(o.view(np.uint32), f.view(np.uint32)), j
+
+
+def test_rows_of_infinities_stay_in_their_rows_of_a_narrow_tile():
+    """K ends inside a k-step: what follows a row of X and the last row of W does not reach the sums."""
+    M, K, N = 3, 40, 24
+    w_offs, P, x_off, y_off, h_off, E = mlp_layout((K, N), 2, M)
+    dp = DevicePool(P + 4096 + E, policy=salus.POLICY_PACK)
+    rng = np.random.default_rng(3)
+    W = synth.f32_to_bf16_bits((rng.standard_normal((K, N)) / np.sqrt(K)).astype(np.float32))
+    X = synth.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
+    ref = dense.mlp_forward_bf16(X, [W], [NONE])[-1]
+    X[1] = 0x7f80
+    st, job = dp.pool.lane_alloc(P + 4096, E, 0, 1)
+    assert st == salus.OK
+    q = dp.pool.job_query(job)
+    dp.write(q.persist_off, W)
+    dp.write(q.persist_off + W.nbytes, np.full(4096 // 2, 0x7fc0, np.uint16))      # NaN right behind the weights
+    dp.write(q.lane_off + x_off, X)
+    descs, keep = salus.Pool.make_descs([dict(job=job, M=M, dtype=salus.BF16, layers=[(K, N, 0, NONE)], x_off=x_off, y_off=y_off, h_off=h_off)])
+    assert dp.pool.grouped_forward(descs, stream=dp.stream) == salus.OK
+    dp.sync()
+    Y = dp.read(q.lane_off + y_off, M * N * 4, np.float32).reshape(M, N)
+    assert not np.isfinite(Y[1]).any()
+    assert norm_rel_err(Y[[0, 2]], ref[[0, 2]]) < TOL_BF16_TIGHT
+    dp.close()
