@@ -110,8 +110,10 @@ struct DenseWalk {
         const bool strip = (p.flags & kStripW) != 0;
         return {p.W, p.K, p.N, strip ? 256u : p.N * 2u, strip};
     }
+    struct Held {};            // nothing of the output is read
+    __device__ void begin(const Place &, Held &, uint32_t, uint32_t, int) const {}
     template <int FN, int FM, typename Landed>
-    __device__ void finish(const Place &at, const f32x16 (&acc)[FN][FM], uint32_t m, uint32_t n, int lane, Landed landed) const
+    __device__ void finish(const Place &at, const f32x16 (&acc)[FN][FM], const Held &, uint32_t m, uint32_t n, int lane, Landed landed) const
     {
         const Problem &p = a.p[at.problem];
         const uint32_t act = p.flags & 0xffu;

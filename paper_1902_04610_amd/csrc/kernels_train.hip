@@ -216,7 +216,7 @@ struct UpdateArgs {
 };
 
 constexpr int kUpdK = 64, kUpdN = 256;      // workgroup tile
-constexpr double kDwTiledRows = 256;
+constexpr double kDwTiledRows = 192;
 constexpr int kDwTile = 128;                // tile of the many-row kernel
 
 // Tile t of one job's update.
@@ -311,38 +311,53 @@ struct UpdateWalk {
     struct Place { int problem; uint32_t m0, n0, depth; };
     __device__ explicit UpdateWalk(const UpdateArgs &args) : a(args), first(args.first[threadIdx.x & 63]) {}
     __device__ uint32_t tiles() const { return a.tiles; }
+    // Columns first: the tiles under way at a time touch whole rows of the master weights (8 jobs x 256 rows: 454 us a step, rows
+    // first 470).
     __device__ Place place(uint32_t tile_id) const
     {
         const uint32_t id = xcd_remap(tile_id, a.tiles);
         const int g = __builtin_amdgcn_readfirstlane(wave_find_range(first, id, true));
-        const uint32_t t = id - __builtin_amdgcn_readlane(first, g), kt = (a.p[g].K + kDwTile - 1) / kDwTile;
-        return {g, (t % kt) * kDwTile, (t / kt) * kDwTile, a.p[g].M};
+        const uint32_t t = id - __builtin_amdgcn_readlane(first, g), nt = (a.p[g].N + kDwTile - 1) / kDwTile;
+        return {g, (t / nt) * kDwTile, (t % nt) * kDwTile, a.p[g].M};
     }
     __device__ Operand m(const Place &at) const { const UpdateProblem &p = a.p[at.problem]; return {p.H, p.M, p.K, p.K * 2u, false}; }
     __device__ Operand n(const Place &at) const { const UpdateProblem &p = a.p[at.problem]; return {p.G, p.M, p.N, p.N * 2u, false}; }
-    template <int FN, int FM, typename Landed>
-    __device__ void finish(const Place &at, const f32x16 (&acc)[FN][FM], uint32_t m, uint32_t n, int lane, Landed landed) const
+    // The master weights of a wavefront's part of a tile, requested in front of its multiplies: the second slab waits for them
+    // (loads complete in order), the update does not.
+    static constexpr int kF = kDwTile / 2 / 32;      // blocks of 32 rows or columns in it
+    struct Held { f32x4 w[kF][kF][2][2]; };
+    struct Part { float *Wm; uint16_t *Wb; uint32_t N, rows, cols; };
+    __device__ Part part(const Place &at, uint32_t m, uint32_t n) const
     {
         const UpdateProblem &p = a.p[at.problem];
-        const uint32_t N = p.N;
         m += at.m0;
         n += at.n0;
-        float *Wm = p.Wm + ((uint64_t)m * N + n);
-        uint16_t *Wb = (uint16_t *)p.Wb + ((uint64_t)m * N + n);
-        const uint32_t rows = m < p.K ? p.K - m : 0, cols = n < N ? N - n : 0, column = line_column_f32(lane);
-        const float lr = p.lr;
-        // all master weights of the wavefront's part are requested before the first is used
-        f32x4 w[FN][FM][2][2];
+        const uint64_t corner = (uint64_t)m * p.N + n;
+        return {p.Wm + corner, (uint16_t *)p.Wb + corner, p.N, m < p.K ? p.K - m : 0, n < p.N ? p.N - n : 0};
+    }
+    __device__ void begin(const Place &at, Held &held, uint32_t m, uint32_t n, int lane) const
+    {
+        const Part p = part(at, m, n);
+        const uint32_t column = line_column_f32(lane);
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < kF; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
+            for (int j = 0; j < kF; ++j)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const uint32_t r = 32u * i + 8u * q + (lane & 7), c = 32u * j + column;
-                    w[j][i][q >> 1][q & 1] = r < rows && c < cols ? __builtin_nontemporal_load((const f32x4 *)(Wm + (size_t)r * N + c))
-                                                                  : f32x4{0.f, 0.f, 0.f, 0.f};
+                    held.w[j][i][q >> 1][q & 1] = r < p.rows && c < p.cols ? __builtin_nontemporal_load((const f32x4 *)(p.Wm + (size_t)r * p.N + c))
+                                                                           : f32x4{0.f, 0.f, 0.f, 0.f};
                 }
+    }
+    template <int FN, int FM, typename Landed>
+    __device__ void finish(const Place &at, const f32x16 (&acc)[FN][FM], const Held &held, uint32_t m, uint32_t n, int lane, Landed landed) const
+    {
+        const Part p = part(at, m, n);
+        const uint32_t N = p.N, rows = p.rows, cols = p.cols, column = line_column_f32(lane);
+        float *Wm = p.Wm;
+        uint16_t *Wb = p.Wb;
+        const float lr = a.p[at.problem].lr;
         landed();
 #pragma unroll
         for (int i = 0; i < FM; ++i)
@@ -357,7 +372,7 @@ struct UpdateWalk {
                 for (int q = 0; q < 4; ++q) {
                     const uint32_t r = 32u * i + 8u * q + (lane & 7), c = 32u * j + column;
                     if (!(r < rows && c < cols)) continue;
-                    f32x4 x = w[j][i][q >> 1][q & 1];
+                    f32x4 x = held.w[j][i][q >> 1][q & 1];
 #pragma unroll
                     for (int e = 0; e < 4; ++e)      // one rounded multiply, one rounded subtract
                         x[e] = __fsub_rn(x[e], __fmul_rn(lr, o[q >> 1][q & 1][e]));
@@ -368,9 +383,12 @@ struct UpdateWalk {
     }
 };
 
-// Bound by the master weights' traffic, in bursts: two workgroups per compute unit, so that one updates while the other
-// multiplies.  4 jobs x 500 rows (588 MB): 169 us against 204 us for the register kernel, whose wavefronts read H and G
-// from L2 once per 64 x 64 block; 64 x 128 tiles, two or three per compute unit: step 11 - 17 us longer.
+// Bound by a compute unit's vector memory path, which the slabs (32 KB each, from L2) and the master weights (160 KB a tile, read
+// and written) pass one after the other: two workgroups per compute unit take 15.1 us and 1.04 us per slab for a tile each, while the
+// traffic of the weights alone takes 13.5 at the copy rate.  4 jobs x 500 rows (588 MB): 164 us; master weights requested behind the multiplies 177; the
+// register kernel, whose wavefronts read H and G from L2 once per 64 x 64 block, 204.  Four wavefronts that multiply and four that
+// update, the sums handed over in LDS: 176 us (98 without the weights' traffic, 119 with the stores only, 110 with the loads
+// only).  64 x 128 tiles, two or three per compute unit: step 11 - 17 us longer.
 __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_tiled(UpdateArgs a)
 {
     using T = TileMfma<kDwTile, kDwTile, 2, 2, true, true>;
@@ -400,8 +418,8 @@ hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, hipStream_t
                                  uint64_t *launches)
 {
     // One kernel for all updates of a step (two would each ramp up and drain): the tiled one if a weight's rows, on
-    // average over the weights, are at least 256.  Step of 8 jobs of 2048-wide layers at 130 / 256 rows: 419 / 493 us
-    // without, 438 / 486 us with it; 4 jobs x 500 rows 394 / 360, 2 jobs x 1024 rows 344 / 292.
+    // average over the weights, are at least 192.  Register / tiled, step of 8 jobs of 2048-wide layers at 130 / 160 / 192 / 224 rows: 408 /
+    // 428 / 445 / 466 us, 412 / 420 / 431 / 442 us; 4 jobs of 1024 - 1536 - 776 at 130 / 160 / 200 rows: 79 / 80 / 85, 81 / 82 / 83.
     double rows = 0, weights = 0;
     bool fits = true;
     for (uint32_t i = 0; i < n; ++i) {

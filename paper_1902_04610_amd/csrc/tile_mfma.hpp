@@ -226,8 +226,8 @@ struct Fragments {
 // BM x BN tile by WM x WN wavefronts; TRM / TRN: the M / N side is stored with its rows along the
 // contraction.  Walk: tile id -> place, operands and epilogue:
 //   uint32_t tiles(); Place place(id); Operand m(Place), n(Place);
-//   finish(Place, acc, m, n, lane, landed): (m, n) is the wavefront's corner in the tile; calls landed() before its
-//   first store.
+//   begin(Place, Held, m, n, lane): before the first multiply; (m, n) is the wavefront's corner in the tile;
+//   finish(Place, acc, Held, m, n, lane, landed): calls landed() before its first store.
 // Place has m0, n0 and depth.  The grid has at most tiles() workgroups.
 template <int BM, int BN, int WM, int WN, bool TRM, bool TRN>
 struct TileMfma {
@@ -355,6 +355,8 @@ struct TileMfma {
                 for (int i = 0; i < FM; ++i)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+            typename Walk::Held held;
+            walk.begin(cur, held, wm * (32u * FM), wn * (32u * FN), fresh_lane());
             uint32_t left = __builtin_amdgcn_readfirstlane(max((cur.depth + kSlab - 1) / kSlab, kMinSlabs));
 #pragma clang loop unroll(disable)
             do {
@@ -373,7 +375,7 @@ struct TileMfma {
                 at_n = at_n + SN::kBytes == (uint32_t)SN::kRing ? 0u : at_n + SN::kBytes;
                 step(3);
             } while (--left != 0);
-            walk.finish(cur, acc, wm * (32u * FM), wn * (32u * FN), fresh_lane(), [&]() {
+            walk.finish(cur, acc, held, wm * (32u * FM), wn * (32u * FN), fresh_lane(), [&]() {
                 if (!landed) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 landed = true;
             });
@@ -523,7 +525,7 @@ struct TilePair {
                 at_m = at_m + SM::kBytes == (uint32_t)SM::kRing ? 0u : at_m + SM::kBytes;
                 step(3);
             } while (--left != 0);
-            walk.finish(cur, acc, wm * (32u * FM), wn * (32u * FN), fresh_lane(), [&]() {
+            walk.finish(cur, acc, typename Walk::Held{}, wm * (32u * FM), wn * (32u * FN), fresh_lane(), [&]() {
                 if (!landed) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 landed = true;
             });
@@ -662,7 +664,7 @@ struct TileStream {
                             for (int r = 0; r < 16; ++r)
                                 if (!kg) acc[j][i][r] += sums[(g - 1) * kGroup + ((j * FM + i) * 16 + r) * 64];
             }
-            if (kg == 0) walk.finish(cur, acc, wm * (32u * FM), wn * (32u * FN), fresh_lane(), []() {});
+            if (kg == 0) walk.finish(cur, acc, typename Walk::Held{}, wm * (32u * FM), wn * (32u * FN), fresh_lane(), []() {});
             cur_id += gridDim.x;
             if (cur_id >= tiles) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may arrive in LDS after this workgroup

@@ -90,6 +90,13 @@ def test_updates_of_many_rows_and_loss_rows(configs):
     run_training(configs, steps=2, seed=12)
 
 
+@pytest.mark.parametrize("configs", [[((136, 264, 72), 191, 0.05)], [((136, 264, 72), 192, 0.05)], [((2056, 4232), 193, 0.05)]])
+def test_updates_around_192_rows(configs):
+    """The register kernel below 192 rows, LDS tiles from there; the last one has more tiles than workgroups: master weights of the
+    next tile are requested while those of the last are stored."""
+    run_training(configs, steps=1, seed=13)
+
+
 @pytest.mark.parametrize("shift_mb, blocks", [(79, 3), (80, 3), (81, 2), (96, 4)])
 def test_equal_shifts_move_as_one(shift_mb, blocks):
     """All blocks above the only hole move by its size: one move, in place below 80 MiB and in pieces of the shift
