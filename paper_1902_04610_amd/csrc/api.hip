@@ -465,13 +465,17 @@ static int32_t forward_impl(salus_pool_t *pool, const salus_gemm_desc *descs, ui
             }
         }
         // one grouped launch per layer depth over all jobs that have that layer
+        uint64_t weights = 0;
+        for (uint32_t i = 0; i < n; ++i)
+            for (uint32_t l = 0; l < descs[i].n_layers; ++l)
+                weights += (uint64_t)descs[i].layers[l].K * descs[i].layers[l].N * (descs[i].dtype == SALUS_BF16 ? 2 : 4);
         for (uint32_t l = 0; l < depth; ++l) {
             probs.clear();
             for (uint32_t i = 0; i < n; ++i)
                 if (descs[i].dtype == dt && l < descs[i].n_layers) probs.push_back(problem(i, l));
             if (probs.empty()) continue;
             hipError_t e = dt == SALUS_BF16
-                               ? launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), false, s, &pool->gemm_launches)
+                               ? launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), false, weights <= kCachedBytes, s, &pool->gemm_launches)
                                : launch_grouped_f32(probs.data(), (uint32_t)probs.size(), s, &pool->gemm_launches);
             if (e != hipSuccess) return set_error(pool, SALUS_EHIP, hipGetErrorString(e));
         }
@@ -614,6 +618,10 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
     uint64_t *count = &pool->gemm_launches;
     // forward, one launch per layer depth
     std::vector<Problem> probs;
+    uint64_t weights = 0;      // master and working copies
+    for (uint32_t i = 0; i < n; ++i)
+        for (uint32_t l = 0; l < descs[i].n_layers; ++l) weights += (uint64_t)descs[i].layers[l].K * descs[i].layers[l].N * 6;
+    const bool cached = weights <= kCachedBytes;
     for (uint32_t l = 0; l < depth && e == hipSuccess; ++l) {
         probs.clear();
         for (uint32_t i = 0; i < n; ++i) {
@@ -630,7 +638,7 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
             pr.flags = last ? (uint32_t)SALUS_ACT_NONE : ((uint32_t)SALUS_ACT_RELU | kOutBf16);
             probs.push_back(pr);
         }
-        e = launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), false, stream, count);
+        e = launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), false, cached, stream, count);
     }
     // loss and its gradient
     if (e == hipSuccess) {
@@ -690,7 +698,7 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
             up.lr = d.lr;
             ups.push_back(up);
         }
-        if (!probs.empty()) e = launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), true, stream, count);
+        if (!probs.empty()) e = launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), true, cached, stream, count);
     }
     if (e == hipSuccess) e = launch_grouped_dw_sgd(ups.data(), (uint32_t)ups.size(), stream, count);
     if (e != hipSuccess) return set_error(pool, SALUS_EHIP, hipGetErrorString(e));

@@ -70,8 +70,10 @@ constexpr uint32_t kOutBlocked = 1u << 12;  // Y (bf16) is written in that order
 constexpr uint32_t kBlockedMaxM = 32;
 constexpr uint32_t kStripW = 1u << 10;      // W is stored in strips of 128 columns: (k, n) at (n/128 * K + k) * 128 + n % 128
 
-// One launch (or several when n > kMaxProblems): Y_g = act(X_g . W_g) for all g.
-hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream,
+// One launch (or several when n > kMaxProblems): Y_g = act(X_g . W_g) for all g.  cached: what the whole round (all layers of
+// all jobs) reads and writes of its weights is at most kCachedBytes, so that a repeated round finds them in the memory-side cache.
+constexpr uint64_t kCachedBytes = 224ull << 20;      // of 256 MB
+hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool cached, hipStream_t stream,
                                uint64_t *launches);
 // Jobs with many rows: LDS-tiled compute-bound kernel (256 x 256, 128 x 256 or 128 x 128 tiles, by launch).
 // tiled_shape_ok says whether a problem may go there (K a multiple of 64), tiled_shape_ragged whether it may in a round

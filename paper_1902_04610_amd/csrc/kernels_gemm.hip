@@ -62,6 +62,21 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(GroupA
     }
 }
 
+// Tiles of 64, 80, 96 or 128 columns, operands through LDS, two workgroups per compute unit: for launches of too many jobs for narrow
+// tiles whose 128-column tiles would leave compute units unevenly loaded (even_columns).  48 jobs x 1 - 32 rows,
+// 3080 -> 776, weights from HBM: 48.9 us with 80 columns (480 tiles), 58.6 with 128 through registers (336).
+template <int MT, int NB>
+__global__ __launch_bounds__(kGemmThreads, 2) void grouped_dense_bf16_even(GroupArgs a)
+{
+    using One = NarrowTile<1, NB, 1, 80 * 1024>;
+    using All = NarrowTile<MT, NB, 1, 80 * 1024>;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[One::kLds > All::kLds ? One::kLds : All::kLds];
+    Problem p;
+    const Tile tile = find_tile<16 * MT, 16 * NB>(a, p);
+    if (MT == 2 && p.M <= 16) One::run(p, tile, smem);
+    else All::run(p, tile, smem);
+}
+
 // 64-row tiles of 128 columns for deep layers of jobs with 33 .. 64 rows: every weight passes through a
 // compute unit once.  Two workgroups per compute unit (registers capped accordingly), so that one
 // workgroup's reduction and epilogue overlap the other's stream.
@@ -120,7 +135,41 @@ constexpr uint64_t kMixedMinGrid = 96;   // 128 x 256 tiles
 constexpr uint64_t kFullGrid = 256;      // one workgroup per compute unit
 constexpr uint32_t kDeepK = 1024;
 
-hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream,
+// Tile width (in 16 columns) with which the busiest compute unit streams least, its weights and the activations beside them; 0: 128
+// columns through registers.  A width that is no whole lines, where the rows of the weights are, costs a fifth (80) or a
+// third (96) more: 8 jobs, 3072 -> 2688, 96 columns 1.3 of 128.  Weights that come from HBM leave less to gain: whole lines
+// stream faster through registers (20 jobs x 1 - 32 rows, 2048 -> 2048 -> 2048 -> 2048, strips: 102 us, 64 columns 111), others are worth
+// the change only where the load falls by a tenth (registers / this, 40 jobs, 776 wide, nine layers 156 / 140 us, 16 jobs,
+// 3080 -> 1496 -> 3080 -> 1496 101 / 88; without: 24 jobs, 1160 wide, 107 / 122).  Where they come from the cache (256 MB), also with one
+// tile of 128 per compute unit, but for whole lines in shallow layers (40 jobs, 768 wide, three layers 30 / 32): 15 jobs, 2136 -> 1144 23.1 / 13.3, 20 jobs x 32 rows, 2048 -> 2048 39.7 / 29.1, 33 jobs,
+// 2832 -> 928 45 / 28, 12 jobs, 512 -> 1792 -> 2816, strips, 34 / 27.
+static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
+{
+    uint64_t two = 0, wide_tiles = 0;
+    bool lines = true, deep = true;
+    for (const Problem &q : p) {
+        two += q.M > 16;
+        deep = deep && q.K > kDeepK;
+        lines = lines && ((q.flags & kStripW) || q.N % 64 == 0);
+        wide_tiles += (q.N + 127) / 128;
+    }
+    if (lines && (!cached || (!deep && wide_tiles <= kFullGrid))) return 0;
+    const uint64_t x = two * 2 > p.size() ? 20 : two ? 15 : 10;      // tenths of what 16 columns of weights are
+    auto cost = [&](uint64_t tiles, uint32_t nb) { return (tiles + kFullGrid - 1) / kFullGrid * (10 * nb + x) * (lines && nb == 5 ? 24 : lines && nb == 6 ? 27 : 20); };
+    uint64_t least = cached && wide_tiles <= kFullGrid ? ~0ull : cost(wide_tiles, 8) * 9 / 10;
+    uint32_t best = 0;
+    for (const uint32_t nb : {8u, 4u, 5u, 6u}) {
+        uint64_t tiles = 0;
+        for (const Problem &q : p) tiles += (q.N + 16 * nb - 1) / (16 * nb);
+        const uint64_t c = cost(tiles, nb);
+        if (c > least || (c == least && best)) continue;
+        least = c;
+        best = nb;
+    }
+    return best;
+}
+
+hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool cached, hipStream_t stream,
                                uint64_t *launches)
 {
     // Jobs with many rows reuse every weight often enough to pay for LDS staging:
@@ -181,7 +230,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
             for (uint32_t i = 0; i < n; ++i) (takes_tiled(p[i]) ? tiled : streamed).push_back(p[i]);
             hipError_t e = launch_grouped_bf16_tiled(tiled.data(), (uint32_t)tiled.size(), stream, launches);
             if (e != hipSuccess || streamed.empty()) return e;
-            return launch_grouped_bf16(streamed.data(), (uint32_t)streamed.size(), false, stream, launches);
+            return launch_grouped_bf16(streamed.data(), (uint32_t)streamed.size(), false, cached, stream, launches);
         }
     }
     // Up to 32 rows: one row tile of 16 or 32 rows per job, 128 columns, every weight read once (non-temporal).
@@ -223,6 +272,20 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
         else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16<1, true, true>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((grouped_dense_bf16<1, false, true>), grid, block, 0, stream, a);
     };
+    const bool narrow = small_tiles * 2 <= kFullGrid && (trans_w || std::all_of(small.begin(), small.end(), tiled_shape_fits));
+    if (!small.empty() && !trans_w && !narrow && std::all_of(small.begin(), small.end(), tiled_shape_fits)) {
+        if (const uint32_t nb = even_columns(small, cached)) {
+            auto launch_even = [&](int mt, const GroupArgs &a, uint32_t tiles) {
+                auto go = [&](auto one, auto two) { hipLaunchKernelGGL(mt == 2 ? two : one, dim3(tiles), dim3(kGemmThreads), 0, stream, a); };
+                if (nb == 4) go(grouped_dense_bf16_even<1, 4>, grouped_dense_bf16_even<2, 4>);
+                else if (nb == 5) go(grouped_dense_bf16_even<1, 5>, grouped_dense_bf16_even<2, 5>);
+                else if (nb == 6) go(grouped_dense_bf16_even<1, 6>, grouped_dense_bf16_even<2, 6>);
+                else go(grouped_dense_bf16_even<1, 8>, grouped_dense_bf16_even<2, 8>);
+            };
+            if (hipError_t e = launch_groups(small.data(), (uint32_t)small.size(), 16 * nb, 16, 32, launch_even, launches)) return e;
+            small.clear();
+        }
+    }
     if (!small.empty()) {
         // As many workgroups as compute units, not more: a narrower tile streams less efficiently.  32 / 16 columns, one job x
         // 1 row: 2048 -> 1024 4.9 / 4.0 us (32 / 64 workgroups; 32 columns through registers 9.2), 1024 -> 1024 3.6 / 3.2, x 32 rows
@@ -250,7 +313,6 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, hipSt
         };
         const Problem *q = small.data();
         const uint32_t count = (uint32_t)small.size();
-        const bool narrow = small_tiles * 2 <= kFullGrid && (trans_w || std::all_of(small.begin(), small.end(), tiled_shape_fits));
         const hipError_t e = !narrow                                      ? launch_groups(q, count, 128, 16, 32, launch_wide, launches)
                              : !trans_w && small_tiles * 8 <= kFullGrid   ? launch_groups(q, count, 16, 16, 32, launch_16, launches)
                              : small_tiles * 4 <= kFullGrid               ? launch_groups(q, count, 32, 16, 32, launch_32, launches)

@@ -1,5 +1,6 @@
-// Narrow tiles of a dense layer (16, 32 or 64 columns) for launches with fewer tiles of 128 columns than compute units:
-// the arithmetic of dense_bf16_tile, in the same order, with its operands fetched straight into LDS.
+// Tiles of a dense layer for launches with fewer tiles of 128 columns than compute units (16, 32 or 64 columns), or with so few that
+// their number does not divide evenly (64 - 128): the arithmetic of dense_bf16_tile, in the same order, with its operands fetched straight
+// into LDS.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -15,31 +16,36 @@ namespace salus {
 // the order in which they lie in memory, a kilobyte an instruction, into an LDS ring that each wavefront has to itself (no
 // barrier in the loop), and ds_read_b64_tr_b16 hands each lane its column.  One job, one row,
 // 1024 -> 4096 -> 1024 -> 1024: 15.7 us, 24.0 with loads into registers; 2048 -> 1024 4.0 / 9.2; 3 jobs x 32 rows, 4096 -> 1024 14.8 / 22.
-// 16 * NB columns, 16 * MT rows; D k-steps of 32 in flight per wavefront.
-template <int MT, int NB>
+// 16 * NB columns, 16 * MT rows; D k-steps of 32 in flight per wavefront, as many as BUDGET bytes of LDS hold, STEP of which share a
+// wait.  STEP == 1 is for half the LDS, two workgroups per compute unit: the sums take the ring's place there.
+template <int MT, int NB, int STEP = 2, uint32_t BUDGET = 160 * 1024>
 struct NarrowTile {
     static constexpr uint32_t kRequests = NB + MT, kSlot = kRequests * 1024;       // instructions and bytes of a k-step
     static constexpr int kNacc = MT * NB;
     static constexpr uint32_t kSums = reduce_lds_floats<kNacc>() * 4;
-    static constexpr uint32_t kWant = NB + MT <= 2 ? 16 : 8;
-    static constexpr uint32_t D = kWant * kSlot * kWaves + kSums <= 160 * 1024 ? kWant : (160 * 1024 - kSums) / (kSlot * kWaves) & ~1u;
-    static constexpr uint32_t kRing = D * kSlot, kLds = kWaves * kRing + kSums;
-    static_assert(D >= 4 && D % 2 == 0 && (D - 2) * kRequests <= 63, "largest count of s_waitcnt");
+    static constexpr bool kAlias = STEP == 1;
+    static constexpr uint32_t kWant = NB + MT <= 2 ? 16 : 8, kRoom = BUDGET - (kAlias ? 0 : kSums);
+    static constexpr uint32_t D = kWant * kSlot * kWaves <= kRoom ? kWant : kRoom / (kSlot * kWaves) / STEP * STEP;
+    static constexpr uint32_t kRing = D * kSlot, kSumsAt = kAlias ? 0 : kWaves * kRing, kLds = kAlias ? (kSums > kWaves * kRing ? kSums : kWaves * kRing) : kWaves * kRing + kSums;
+    static_assert(D >= 2 * STEP && (D - STEP) * kRequests <= 63, "largest count of s_waitcnt");
 
     // Where the transposing reads find a k-row: its row in the slot (an involution), and what is xored to the number of its
     // 16-byte chunks.  Such a read touches rows 8 g .. 8 g + 3 of all four g, 32 bytes each, which are spread evenly over
     // the 256 bytes that LDS delivers at a time.
     __device__ static uint32_t row_at(uint32_t r) { return NB == 1 ? r ^ ((r >> 3 & 1u) << 2) : r; }
-    __device__ static uint32_t chunk_swizzle(uint32_t r) { return NB == 1 ? 0u : NB == 2 ? (r >> 3 & 1u) << 1 : (r >> 1 & 1u) << 1 | (r >> 3 & 1u) << 2; }
+    __device__ static uint32_t chunk_swizzle(uint32_t r)
+    {
+        return NB == 2 ? (r >> 3 & 1u) << 1 : NB == 4 ? (r >> 1 & 1u) << 1 | (r >> 3 & 1u) << 2 : NB == 8 ? (r & 3u) << 1 | (r >> 3 & 1u) << 3 : 0u;
+    }
 
-    // LEFT .. 1 pairs of k-steps, of which `pairs` are there
+    // The last D / STEP groups of k-steps, of which `groups` are there.
     template <size_t... I, typename Multiply>
-    __device__ static void drain(std::index_sequence<I...>, uint32_t pairs, Multiply &multiply)
+    __device__ static void drain(std::index_sequence<I...>, uint32_t groups, Multiply &multiply)
     {
         auto one = [&](auto behind) {
             constexpr uint32_t kBehind = decltype(behind)::value;
-            if (pairs <= kBehind) return;
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kBehind * 2 * kRequests) : "memory");
+            if (groups <= kBehind) return;
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kBehind * STEP * kRequests) : "memory");
             multiply(false);
         };
         (one(std::integral_constant<uint32_t, sizeof...(I) - 1 - I>{}), ...);
@@ -54,14 +60,16 @@ struct NarrowTile {
         const uint32_t xtiles = (M + 15) / 16;
 
         // Requests of a k-step: NB kilobytes of weights, 32 / NB rows each, then a kilobyte of activations per row tile.
-        constexpr uint32_t kLanes = 2 * NB, kRows = 64 / kLanes;      // lanes of a k-row, k-rows of an instruction
-        const uint32_t pitch = strip ? 256u : N * 2u, krow = row_at(lane / kLanes);
+        constexpr uint32_t kLanes = 2 * NB;      // lanes of a k-row
+        const uint32_t pitch = strip ? 256u : N * 2u;
         const uint32_t first_col = strip ? (tile.n0 & 127u) : tile.n0;
-        uint32_t w_off[2];                       // of even and odd instructions
+        uint32_t w_off[NB], krow[NB];
 #pragma unroll
-        for (uint32_t i = 0; i < 2; ++i) {
-            const uint32_t col = 8u * ((lane % kLanes) ^ chunk_swizzle(krow + i * kRows));
-            w_off[i] = tile.n0 + col < N ? krow * pitch + (first_col + col) * 2u : kOutside;
+        for (uint32_t i = 0; i < (uint32_t)NB; ++i) {
+            const uint32_t at = 64u * i + lane;
+            krow[i] = row_at(at / kLanes);
+            const uint32_t col = 8u * ((at % kLanes) ^ chunk_swizzle(krow[i]));
+            w_off[i] = tile.n0 + col < N ? krow[i] * pitch + (first_col + col) * 2u + (strip && first_col + col >= 128u ? (K - 1) * 256u : 0u) : kOutside;
         }
         uint64_t w_base = (uint64_t)(uintptr_t)p.W + (strip ? (uint64_t)(tile.n0 & ~127u) * K * 2u : 0);
         uint64_t x_base = (uint64_t)(uintptr_t)p.X;
@@ -84,7 +92,7 @@ struct NarrowTile {
             const int left = (int)K - (int)k;
 #pragma unroll
             for (uint32_t i = 0; i < (uint32_t)NB; ++i)
-                dma16(ring + to + i * 1024u, w_base + (uint64_t)(i * kRows) * pitch, (int)(krow + i * kRows) < left ? w_off[i & 1] : kOutside);
+                dma16(ring + to + i * 1024u, w_base, (int)krow[i] < left ? w_off[i] : kOutside);
 #pragma unroll
             for (int t = 0; t < MT; ++t) dma16(ring + to + (NB + t) * 1024u, x_base, 8 * g < left ? x_off[t] : kOutside);
             k += 32u * kWaves;
@@ -93,12 +101,11 @@ struct NarrowTile {
             to = to + kSlot == kRing ? 0u : to + kSlot;
         };
         const uint32_t mine = nsteps > (uint32_t)wave ? (nsteps - wave + kWaves - 1) / kWaves : 0;
-        uint32_t pairs = (mine + 1) / 2;         // two k-steps at a time, which share the waits; one past the last is all zeros
+        uint32_t groups = (mine + STEP - 1) / STEP;        // of k-steps that share a wait; one past the last is all zeros
 #pragma unroll 1
-        for (uint32_t d = 0; d < min(pairs, D / 2); ++d) {
-            request();
-            request();
-        }
+        for (uint32_t d = 0; d < min(groups, D / STEP); ++d)
+#pragma unroll
+            for (int s = 0; s < STEP; ++s) request();
 
         f32x4 acc[kNacc];
 #pragma unroll
@@ -115,9 +122,9 @@ struct NarrowTile {
             }
         uint32_t at = 0;
         auto multiply = [&](bool more) {
-            bf16x8 x[2][MT], w[2][NB];
+            bf16x8 x[STEP][MT], w[STEP][NB];
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
+            for (int s = 0; s < STEP; ++s) {
                 const unsigned char *slot = from + at + s * kSlot;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
@@ -133,27 +140,28 @@ struct NarrowTile {
             if (more) {
                 // the slots have been read before they are requested into
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                request();
-                request();
+#pragma unroll
+                for (int s = 0; s < STEP; ++s) request();
             }
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
+            for (int s = 0; s < STEP; ++s)
 #pragma unroll
                 for (int j = 0; j < NB; ++j)
 #pragma unroll
                     for (int t = 0; t < MT; ++t) acc[t * NB + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[s][t], w[s][j], acc[t * NB + j], 0, 0, 0);
-            at = at + 2 * kSlot == kRing ? 0u : at + 2 * kSlot;
+            at = at + STEP * kSlot == kRing ? 0u : at + STEP * kSlot;
         };
 #pragma unroll 1
-        for (; pairs > D / 2; --pairs) {
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * kRequests) : "memory");
+        for (; groups > D / STEP; --groups) {
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - STEP) * kRequests) : "memory");
             multiply(true);
         }
         // the last ones, all requested: nothing is left in flight after them
-        drain(std::make_index_sequence<D / 2>{}, pairs, multiply);
+        drain(std::make_index_sequence<D / STEP>{}, groups, multiply);
 
         float own[kNacc];
-        reduce_scatter<kNacc>(acc, own, (float *)(smem + kWaves * kRing));
+        if (kAlias) __syncthreads();
+        reduce_scatter<kNacc>(acc, own, (float *)(smem + kSumsAt));
         const uint32_t act = p.flags & 0xffu;
 #pragma unroll
         for (int t = 0; t < MT; ++t)

@@ -208,3 +208,14 @@ def test_narrow_tiles_up_to_32_rows(record):
         ([32] * 9, 1024, 1024, "_narrow<2, false, 4, 0, true>"), ([8] * 16, 1024, 1024, "_narrow<1, false, 4, 0, true>"),
         ([8] * 17, 1024, 1024, "<1, false, true>"), ([1], 8, 1 << 22, "<1, false, true>"),
     )])
+
+
+def test_columns_spread_evenly_up_to_32_rows(record):
+    """Tiles of 64 - 128 columns where 128 load compute units unevenly; registers where they do not, and for whole lines from HBM."""
+    even = "_even<%d, %d>"
+    check(record, [(case(rows, K, N), ["grouped_dense_bf16" + kernel]) for rows, K, N, kernel in (
+        ([8] * 48, 512, 1016, even % (1, 4)), ([17] * 48, 1000, 776, even % (2, 5)), ([8] * 20, 264, 1000, even % (1, 6)),
+        ([8] * 23, 520, 1272, even % (1, 8)), ([32] * 20, 1032, 2048, even % (2, 4)), ([8] * 64, 128, 640, even % (1, 5)),
+        ([8] * 64, 4096, 1024, "<1, false, true>"), ([32] * 64, 1000, 3080, "<2, false, true>"), ([8] * 24, 8000, 1160, "<1, false, true>"),
+        ([8] * 40, 4096, 1024, "<1, false, true>"),
+    )])

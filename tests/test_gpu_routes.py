@@ -136,6 +136,24 @@ def test_narrow_tiles_up_to_32_rows(jobs, dims, strip):
         assert np.array_equal(o.view(np.uint32), f.view(np.uint32)), j
 
 
+@pytest.mark.parametrize("jobs, dims, strip", [
+    (48, (40, 1016), False), (48, (8, 776, 1016), False),                            # 64 columns, 80
+    (20, (264, 1000), False), (23, (520, 1272), False), (48, (136, 776), False),     # 96, 128, 80
+    (64, (72, 640), True), (40, (136, 1024, 8), True),                               # strips: 80 columns, across their borders; 64
+])
+def test_evenly_spread_columns_up_to_32_rows(jobs, dims, strip):
+    """Widths that end inside a tile, depths of less than a k-step and of less than the ring, 1 - 32 rows; the depth-fused launch gives
+    the same bits."""
+    specs = [dict(M=[1, 16, 17, 32, 7][i % 5], dims=dims, acts=([GELU, RELU] * 2)[:len(dims) - 2] + [NONE], strip=strip) for i in range(jobs)]
+    outs, refs, n = run_jobs(specs, salus.BF16)
+    assert n == len(dims) - 1
+    fused, _, _ = run_jobs(specs, salus.BF16, fuse=True)
+    for o, r, f, j in zip(outs, refs, fused, specs):
+        assert np.isfinite(o).all(), j
+        assert norm_rel_err(o, r) < TOL_BF16_TIGHT, (j, norm_rel_err(o, r))
+        assert np.array_equal(o.view(np.uint32), f.view(np.uint32)), j
+
+
 def test_rows_of_infinities_stay_in_their_rows_of_a_narrow_tile():
     """K ends inside a k-step: what follows a row of X and the last row of W does not reach the sums."""
     M, K, N = 3, 40, 24
