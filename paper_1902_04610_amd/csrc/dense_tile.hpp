@@ -255,15 +255,16 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
 // (q, i) multiplies component q of X with component i of W row q, so lane
 // group g contributes k = k0+4g+q in step q and output column n0+4c+i.
 // ---------------------------------------------------------------------------
-// D: k-steps in flight per wavefront, as above.
-template <int MT, int D = 2>
+// D: k-steps in flight per wavefront, CPL: columns per lane (4 or 1; the tile is 16 * CPL wide), as above.
+template <int MT, int D = 2, int CPL = 4>
 __device__ inline void dense_f32_tile(const Problem &p, const Tile tile, float *lds)
 {
-    constexpr int NACC = MT * 4;
+    constexpr int NACC = MT * CPL;
+    typedef float wvec __attribute__((ext_vector_type(CPL)));
     const uint32_t M = p.M, K = p.K, N = p.N;
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t ncol = tile.n0 + 4 * c;
+    const uint32_t ncol = tile.n0 + CPL * c;
     const bool col_ok = ncol < N;
     const Global<float> *W = (const Global<float> *)p.W;
     const Global<float> *X = (const Global<float> *)p.X;
@@ -277,36 +278,36 @@ __device__ inline void dense_f32_tile(const Problem &p, const Tile tile, float *
 
     // unpredicated loads from clamped addresses, as in the bf16 kernel
     const uint32_t ncol_c = col_ok ? ncol : 0u;
-    auto load = [&](int s, f32x4 (&w)[4], f32x4 (&x)[MT], bool &k_ok) {
+    auto load = [&](int s, wvec (&w)[4], f32x4 (&x)[MT], bool &k_ok) {
         const uint32_t kb = 16u * (uint32_t)s + 4u * (uint32_t)g;
         k_ok = kb < K;
         const uint32_t kc = k_ok ? kb : 0u;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) w[q] = *(const Global<f32x4> *)(W + (size_t)(kc + q) * N + ncol_c);
+        for (int q = 0; q < 4; ++q) w[q] = *(const Global<wvec> *)(W + (size_t)(kc + q) * N + ncol_c);
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
             const uint32_t row = tile.m0 + 16 * t + c;
             x[t] = *(const Global<f32x4> *)(X + (size_t)(row < M ? row : M - 1) * K + kc);
         }
     };
-    auto compute = [&](const f32x4 (&w)[4], const f32x4 (&xr)[MT], bool k_ok) {
+    auto compute = [&](const wvec (&w)[4], const f32x4 (&xr)[MT], bool k_ok) {
         f32x4 x[MT];
 #pragma unroll
         for (int t = 0; t < MT; ++t) x[t] = k_ok ? xr[t] : zero;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < CPL; ++i)
 #pragma unroll
                 for (int t = 0; t < MT; ++t)
-                    acc[t * 4 + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][q], w[q][i],
-                                                                          acc[t * 4 + i], 0, 0, 0);
+                    acc[t * CPL + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][q], w[q][i], acc[t * CPL + i], 0, 0, 0);
     };
 
     const int mine = nsteps > wave ? (nsteps - wave + kWaves - 1) / kWaves : 0;
     auto step = [&](int i) { return wave + kWaves * i; };
     if constexpr (D == 2) {
-        f32x4 w0[4], w1[4], x0[MT], x1[MT];
+        wvec w0[4], w1[4];
+        f32x4 x0[MT], x1[MT];
         bool ok0, ok1;
         load(step(0), w0, x0, ok0);
         load(step(1), w1, x1, ok1);
@@ -329,7 +330,8 @@ __device__ inline void dense_f32_tile(const Problem &p, const Tile tile, float *
         if (left >= 2) compute(w1, x1, ok1);
         if (left == 3) compute(w0, x0, ok0);
     } else {
-        f32x4 w[D][4], x[D][MT];
+        wvec w[D][4];
+        f32x4 x[D][MT];
         bool ok[D];
 #pragma unroll
         for (int d = 0; d < D; ++d) load(step(d), w[d], x[d], ok[d]);
@@ -364,10 +366,10 @@ __device__ inline void dense_f32_tile(const Problem &p, const Tile tile, float *
     for (int t = 0; t < MT; ++t) {
         const uint32_t row = tile.m0 + 16 * t + 4 * g + wave;
         if (row >= M || !col_ok) continue;
-        f32x4 o;
+        wvec o;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = activate_f32(own[t * 4 + i], act);
-        *(Global<f32x4> *)((Global<float> *)p.Y + (size_t)row * N + ncol) = o;
+        for (int i = 0; i < CPL; ++i) o[i] = activate_f32(own[t * CPL + i], act);
+        *(Global<wvec> *)((Global<float> *)p.Y + (size_t)row * N + ncol) = o;
     }
 }
 

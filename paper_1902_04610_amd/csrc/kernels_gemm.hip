@@ -103,6 +103,17 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(GroupArgs a)
     else dense_f32_tile<MT>(p, tile, lds);
 }
 
+// 16 columns and 16 rows per workgroup, for launches of few tiles: a launch lasts as long as one wavefront's chain of
+// multiplies and loads over its quarter of K, and this tile has a quarter of the multiplies.  16 columns / 64, 4 jobs x 16 rows, 1536 ->
+// 1000: 6.7 / 10.7 us, 1024 -> 1000 5.5 / 8.0, 384 -> 1000 4.1 / 5.2 on the device, 2 jobs x 8 rows, 256 -> 256 3.4 / 4.4.
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32_narrow(GroupArgs a)
+{
+    __shared__ float lds[reduce_lds_floats<1>()];
+    Problem p;
+    const Tile tile = find_tile<16, 16>(a, p);
+    dense_f32_tile<1, 4, 1>(p, tile, lds);
+}
+
 // ---------------------------------------------------------------------------
 // force_mt != 0: row tiles of 16 * force_mt rows whatever the jobs' sizes
 template <typename Launch>
@@ -381,15 +392,24 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
     // 64 rows, 1024 -> 1024 8.8 / 12.7 / 21.3; 12 jobs x 32 rows, 1204 -> 780 (312 16-row tiles) 16.9 / 15.3, 40 jobs, 256 -> 256 (320) 5.9 / 6.0; 12 jobs x 128
     // rows, 1536 -> 1536 88 / 80 / 89, 4 jobs 33 / 33 / 32; 40 jobs x 33 rows, 1536 -> 1536 (960 64-row tiles, 3.75 rounds), 32 / 64 rows:
     // 121 / 113; 40 jobs x 128 rows, 1024 -> 1024 -> 1024 (5 rounds) 213 / 202, 40 rows (2.5) 110 / 122.
-    uint64_t tiles_16 = 0, tiles_32 = 0, tiles_64 = 0;
+    uint64_t tiles_16 = 0, tiles_32 = 0, tiles_64 = 0, columns_16 = 0;
     uint32_t max_m = 0, min_k = ~0u;
     for (uint32_t i = 0; i < n; ++i) {
         const uint64_t cols = (p[i].N + 63) / 64;
         tiles_16 += (p[i].M + 15) / 16 * cols;
         tiles_32 += (p[i].M + 31) / 32 * cols;
         tiles_64 += (p[i].M + 63) / 64 * cols;
+        columns_16 += (uint64_t)((p[i].M + 15) / 16) * ((p[i].N + 15) / 16);
         max_m = std::max(max_m, p[i].M);
         min_k = std::min(min_k, p[i].K);
+    }
+    // As long as there is at most one 16-column tile per compute unit: 6 jobs x 16 rows, 1024 -> 1024 (384), 16 / 64 columns 7.6 / 7.9 us, 12
+    // jobs (768) 12.7 / 10.9.
+    if (columns_16 <= kFullGrid) {
+        auto launch_narrow = [&](int, const GroupArgs &a, uint32_t tiles) {
+            hipLaunchKernelGGL(grouped_dense_f32_narrow, dim3(tiles), dim3(kGemmThreads), 0, stream, a);
+        };
+        return launch_groups(p, n, 16, 0, 0, launch_narrow, launches, 1);
     }
     const bool one_32 = min_k > 512 && max_m > 16 && max_m <= 32 && tiles_16 > kFullGrid && tiles_32 <= kFullGrid && tiles_16 * 4 > tiles_32 * 7;
     const uint64_t rounds_64 = (tiles_64 + kFullGrid - 1) / kFullGrid;

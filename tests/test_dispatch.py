@@ -219,3 +219,10 @@ def test_columns_spread_evenly_up_to_32_rows(record):
         ([8] * 64, 4096, 1024, "<1, false, true>"), ([32] * 64, 1000, 3080, "<2, false, true>"), ([8] * 24, 8000, 1160, "<1, false, true>"),
         ([8] * 40, 4096, 1024, "<1, false, true>"),
     )])
+
+
+def test_narrow_float_tiles(record):
+    """16 columns while that is at most one tile per compute unit."""
+    check(record, [(case(rows, K, N, "f32"), ["grouped_dense_f32" + kernel]) for rows, K, N, kernel in (
+        ([1], 4, 4, "_narrow"), ([16] * 4, 1024, 1024, "_narrow"), ([16] * 4, 1024, 1028, "<1>"), ([128], 60, 512, "_narrow"), ([129], 60, 512, "<1>"),
+    )])

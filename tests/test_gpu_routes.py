@@ -154,6 +154,19 @@ def test_evenly_spread_columns_up_to_32_rows(jobs, dims, strip):
         assert np.array_equal(o.view(np.uint32), f.view(np.uint32)), j
 
 
+@pytest.mark.parametrize("jobs, dims, M", [
+    (1, (4, 4), 1), (2, (132, 68, 20), 17), (3, (1028, 1004, 12), 16), (1, (60, 260, 36), 128), (4, (516, 1024, 1028), 16),
+])
+def test_narrow_float_tiles(jobs, dims, M):
+    """Widths that end inside a tile, depths of less than a k-step per wavefront; the depth-fused launch gives the same bits."""
+    specs = [dict(M=max(1, M - 5 * (i % 3)), dims=dims, acts=([GELU, RELU] * 2)[:len(dims) - 2] + [NONE]) for i in range(jobs)]
+    outs, refs, _ = run_jobs(specs, salus.F32)
+    fused, _, _ = run_jobs(specs, salus.F32, fuse=True)
+    for o, r, f, j in zip(outs, refs, fused, specs):
+        assert np.isfinite(o).all() and norm_rel_err(o, r) < TOL_F32, (j, norm_rel_err(o, r))
+        assert np.array_equal(o.view(np.uint32), f.view(np.uint32)), j
+
+
 def test_rows_of_infinities_stay_in_their_rows_of_a_narrow_tile():
     """K ends inside a k-step: what follows a row of X and the last row of W does not reach the sums."""
     M, K, N = 3, 40, 24
