@@ -465,17 +465,13 @@ static int32_t forward_impl(salus_pool_t *pool, const salus_gemm_desc *descs, ui
             }
         }
         // one grouped launch per layer depth over all jobs that have that layer
-        uint64_t weights = 0;
-        for (uint32_t i = 0; i < n; ++i)
-            for (uint32_t l = 0; l < descs[i].n_layers; ++l)
-                weights += (uint64_t)descs[i].layers[l].K * descs[i].layers[l].N * (descs[i].dtype == SALUS_BF16 ? 2 : 4);
         for (uint32_t l = 0; l < depth; ++l) {
             probs.clear();
             for (uint32_t i = 0; i < n; ++i)
                 if (descs[i].dtype == dt && l < descs[i].n_layers) probs.push_back(problem(i, l));
             if (probs.empty()) continue;
             hipError_t e = dt == SALUS_BF16
-                               ? launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), false, weights <= kCachedBytes, s, &pool->gemm_launches)
+                               ? launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), false, pool->core->resident_bytes() <= kCachedBytes, s, &pool->gemm_launches)
                                : launch_grouped_f32(probs.data(), (uint32_t)probs.size(), s, &pool->gemm_launches);
             if (e != hipSuccess) return set_error(pool, SALUS_EHIP, hipGetErrorString(e));
         }
@@ -618,10 +614,7 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
     uint64_t *count = &pool->gemm_launches;
     // forward, one launch per layer depth
     std::vector<Problem> probs;
-    uint64_t weights = 0;      // master and working copies
-    for (uint32_t i = 0; i < n; ++i)
-        for (uint32_t l = 0; l < descs[i].n_layers; ++l) weights += (uint64_t)descs[i].layers[l].K * descs[i].layers[l].N * 6;
-    const bool cached = weights <= kCachedBytes;
+    const bool cached = pool->core->resident_bytes() <= kCachedBytes;
     for (uint32_t l = 0; l < depth && e == hipSuccess; ++l) {
         probs.clear();
         for (uint32_t i = 0; i < n; ++i) {

@@ -149,9 +149,10 @@ constexpr uint32_t kDeepK = 1024;
 // Tile width (in 16 columns) with which the busiest compute unit streams least, its weights and the activations beside them; 0: 128
 // columns through registers.  A width that is no whole lines, where the rows of the weights are, costs a fifth (80) or a
 // third (96) more: 8 jobs, 3072 -> 2688, 96 columns 1.3 of 128.  Weights that come from HBM leave less to gain: whole lines
-// stream faster through registers (20 jobs x 1 - 32 rows, 2048 -> 2048 -> 2048 -> 2048, strips: 102 us, 64 columns 111), others are worth
-// the change only where the load falls by a tenth (registers / this, 40 jobs, 776 wide, nine layers 156 / 140 us, 16 jobs,
-// 3080 -> 1496 -> 3080 -> 1496 101 / 88; without: 24 jobs, 1160 wide, 107 / 122).  Where they come from the cache (256 MB), also with one
+// stream faster through registers (20 jobs x 1 - 32 rows, 2048 -> 2048 -> 2048 -> 2048, strips: 102 us, 64 columns 111) unless 64
+// columns nearly halve the load (45 jobs, 2560 -> 320: 18.2 / 14.9; at 0.8 of the load 12 jobs, 1792 -> 1536, 80 columns 1.09 of
+// registers), others are worth the change only where the load falls by a tenth (registers / this, 40 jobs, 776 wide, nine layers
+// 156 / 140 us, 16 jobs, 3080 -> 1496 -> 3080 -> 1496 101 / 88; without: 24 jobs, 1160 wide, 107 / 122).  Where they come from the cache (256 MB), also with one
 // tile of 128 per compute unit, but for whole lines in shallow layers (40 jobs, 768 wide, three layers 30 / 32): 15 jobs, 2136 -> 1144 23.1 / 13.3, 20 jobs x 32 rows, 2048 -> 2048 39.7 / 29.1, 33 jobs,
 // 2832 -> 928 45 / 28, 12 jobs, 512 -> 1792 -> 2816, strips, 34 / 27.
 static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
@@ -164,10 +165,11 @@ static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
         lines = lines && ((q.flags & kStripW) || q.N % 64 == 0);
         wide_tiles += (q.N + 127) / 128;
     }
-    if (lines && (!cached || (!deep && wide_tiles <= kFullGrid))) return 0;
+    const bool one_each = wide_tiles <= kFullGrid;
+    if (lines && cached && !deep && one_each) return 0;
     const uint64_t x = two * 2 > p.size() ? 20 : two ? 15 : 10;      // tenths of what 16 columns of weights are
     auto cost = [&](uint64_t tiles, uint32_t nb) { return (tiles + kFullGrid - 1) / kFullGrid * (10 * nb + x) * (lines && nb == 5 ? 24 : lines && nb == 6 ? 27 : 20); };
-    uint64_t least = cached && wide_tiles <= kFullGrid ? ~0ull : cost(wide_tiles, 8) * 9 / 10;
+    uint64_t least = cached && one_each ? ~0ull : cost(wide_tiles, 8) * (lines && !cached ? 6 : 9) / 10;
     uint32_t best = 0;
     for (const uint32_t nb : {8u, 4u, 5u, 6u}) {
         uint64_t tiles = 0;

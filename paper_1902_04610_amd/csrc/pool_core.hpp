@@ -87,6 +87,7 @@ public:
     const std::vector<Lane> &lanes() const { return lanes_; }
     uint64_t capacity() const { return C_; }
     uint64_t floor() const { return C_ - sumL_; }
+    uint64_t resident_bytes() const { return sumP_; }      // persistent bytes of the resident jobs
     uint64_t queued() const { return queue_.size(); }
 
     salus_stats stats{};

@@ -26,17 +26,29 @@ def pool(capacity, **kw):
 def forward(case):
     dt = salus.F32 if case["dtype"] == "f32" else salus.BF16
     esz = 4 if dt == salus.F32 else 2
-    K, N = max(case["K"]), case["N"]
+    widths = case["N"] if isinstance(case["N"], list) else [case["N"]]
     up = lambda v: (v + 255) // 256 * 256
-    top = max(case["rows"])
-    P, y = up(K * N * esz), up(top * K * esz)
-    E = y + up(top * N * 4)
-    p = pool(len(case["rows"]) * (P + E))
+    top, layers = max(case["rows"]), []
+    for k, strip in zip(case["K"], case["strip"]):
+        dims, at, mine = [k] + widths, 0, []
+        for l, (a, b) in enumerate(zip(dims, widths)):
+            mine.append((a, b, at, salus.ACT_NONE, salus.LAYOUT_STRIP128 if strip else salus.LAYOUT_ROWMAJOR))
+            at += up(a * b * esz)
+        layers.append((at, mine))
+    P, y = max(size for size, _ in layers), up(top * max(case["K"]) * esz)
+    h = y + up(top * widths[-1] * 4)
+    E = h + max(salus.forward_work_bytes(top, [t[:4] for t in mine], dt) for _, mine in layers)
+    p = pool(len(case["rows"]) * (P + E) + sum(v + 256 for v in case["idle"]))
+    for v in case["idle"]:
+        st, other = p.lane_alloc(v, 256, 0, 0)
+        assert st == salus.OK
     items = []
-    for M, k in zip(case["rows"], case["K"]):
+    for M, (_, mine) in zip(case["rows"], layers):
         st, job = p.lane_alloc(P, E, 0, 1)
         assert st == salus.OK
-        items.append(dict(job=job, M=M, dtype=dt, layers=[(k, N, 0, salus.ACT_NONE)], x_off=0, y_off=y, h_off=E))
+        items.append(dict(job=job, M=M, dtype=dt, layers=mine, x_off=0, y_off=y, h_off=h))
+    if case["evicted"]:
+        assert p.switch_out(other) == salus.OK
     descs, keep = salus.Pool.make_descs(items)
     take()
     assert p.grouped_forward(descs, stream=STREAM) == salus.OK, p.last_error()
@@ -107,9 +119,11 @@ def kernels(lines):
     return [line.rsplit(" ", 3)[0][len("launch "):] for line in lines if line.startswith("launch ")]
 
 
-def case(rows, K, N, dtype="bf16"):
-    """Jobs of one layer; K one for all or one for each."""
-    return dict(do="forward", rows=rows, K=K if isinstance(K, list) else [K] * len(rows), N=N, dtype=dtype)
+def case(rows, K, N, dtype="bf16", strip=False, idle=(), evicted=False):
+    """Jobs of one layer, or of as many as N has widths; K and strip one for all or one for each.  idle: bytes of jobs that the
+    pool holds besides; evicted: the last of them has been switched out."""
+    each = lambda v: v if isinstance(v, list) else [v] * len(rows)
+    return dict(do="forward", rows=rows, K=each(K), N=N, dtype=dtype, strip=each(strip), idle=list(idle), evicted=evicted)
 
 
 def check(record, expected):
@@ -226,3 +240,21 @@ def test_narrow_float_tiles(record):
     check(record, [(case(rows, K, N, "f32"), ["grouped_dense_f32" + kernel]) for rows, K, N, kernel in (
         ([1], 4, 4, "_narrow"), ([16] * 4, 1024, 1024, "_narrow"), ([16] * 4, 1024, 1028, "<1>"), ([128], 60, 512, "_narrow"), ([129], 60, 512, "<1>"),
     )])
+
+
+def test_columns_spread_evenly_while_all_that_is_resident_fits_the_cache(record):
+    """What decides is what the pool's jobs hold, not what this round reads; several layers, strips."""
+    even = "grouped_dense_bf16_even<1, %d>"
+    registers = "grouped_dense_bf16<1, false, true>"
+    small = ([8] * 30, 2048, 640)
+    check(record, [
+        (case(*small), [even % 5]), (case(*small, idle=[200 << 20]), [registers]),
+        (case(*small, idle=[200 << 20], evicted=True), [even % 5]), (case(*small, idle=[100 << 20, 100 << 20], evicted=True), [even % 5]),
+        # 3 layers of together 8.5 MB a job, every one of which would fit by itself
+        (case([8] * 28, 2048, [640, 2304, 640]), [registers] * 3), (case([8] * 27, 2048, [640, 2304, 640]), [even % 5, registers, even % 5]),
+        (case([8] * 30, 2048, 640, strip=True), [even % 5]), (case([8] * 30, 2048, 640, strip=True, idle=[200 << 20]), [registers]),
+        (case([8] * 36, 2048, 448), [even % 4]), (case([8] * 36, 2048, 448, idle=[200 << 20]), [even % 4]),       # almost half the load
+        # from further away: only rows that begin inside a line, and only where the load falls by a tenth
+        (case([8] * 48, 6160, 776), [even % 5]), (case([8] * 48, 1000, 776, idle=[400 << 20]), [even % 5]),
+        (case([8] * 23, 520, 1272), [even % 8]), (case([8] * 23, 520, 1272, idle=[400 << 20]), [registers]),
+    ])
