@@ -147,31 +147,37 @@ constexpr uint64_t kFullGrid = 256;      // one workgroup per compute unit
 constexpr uint32_t kDeepK = 1024;
 
 // Tile width (in 16 columns) with which the busiest compute unit streams least, its weights and the activations beside them; 0: 128
-// columns through registers.  A width that is no whole lines, where the rows of the weights are, costs a fifth (80) or a
-// third (96) more: 8 jobs, 3072 -> 2688, 96 columns 1.3 of 128.  Weights that come from HBM leave less to gain: whole lines
-// stream faster through registers (20 jobs x 1 - 32 rows, 2048 -> 2048 -> 2048 -> 2048, strips: 102 us, 64 columns 111) unless 64
-// columns nearly halve the load (45 jobs, 2560 -> 320: 18.2 / 14.9; at 0.8 of the load 12 jobs, 1792 -> 1536, 80 columns 1.09 of
-// registers), others are worth the change only where the load falls by a tenth (registers / this, 40 jobs, 776 wide, nine layers
-// 156 / 140 us, 16 jobs, 3080 -> 1496 -> 3080 -> 1496 101 / 88; without: 24 jobs, 1160 wide, 107 / 122).  Where they come from the cache (256 MB), also with one
-// tile of 128 per compute unit, but for whole lines in shallow layers (40 jobs, 768 wide, three layers 30 / 32): 15 jobs, 2136 -> 1144 23.1 / 13.3, 20 jobs x 32 rows, 2048 -> 2048 39.7 / 29.1, 33 jobs,
-// 2832 -> 928 45 / 28, 12 jobs, 512 -> 1792 -> 2816, strips, 34 / 27.
+// columns through registers.  What the change is worth depends on the rows of the weights and on where they come from.
+// Whole lines: 80 columns cost a fifth more and 96 a third (8 jobs, 3072 -> 2688, 96 columns 1.3 of 128), so those never pay.  From the
+// cache (256 MB) where the load falls by a tenth, but with one tile of 128 per compute unit not in shallow layers (40 jobs, 768
+// wide, three layers 30 / 32 us); 128 columns through LDS there only in layers deeper than 2048 or for jobs of 17 rows and more
+// (registers / LDS, up to 16 rows: 47 jobs, 1152 -> 512 9.9 / 10.9, 24 jobs, 1152 -> 1152 0.88, 9 jobs, 1536 -> 2688 0.94, 22 jobs, 2624 -> 1152 1.04, 23 jobs,
+// 3328 -> 1024 1.12; 32 rows: 20 jobs, 1664 -> 1408 1.03, 23 jobs, 2944 -> 1024 1.15).  From HBM only where 64 columns nearly halve
+// the load (45 jobs, 2560 -> 320: 18.2 / 14.9; at 0.8 of the load 12 jobs, 1792 -> 1536 0.92; 20 jobs x 1 - 32 rows, 2048 -> 2048 -> 2048 -> 2048, strips: 102 / 111).
+// Rows that begin inside a line, which cost registers extra: from HBM where the load falls by a tenth (40 jobs, 776 wide, nine layers
+// 156 / 140 us, 16 jobs, 3080 -> 1496 -> 3080 -> 1496 101 / 88; without: 24 jobs, 1160 wide, 107 / 122), from the cache also with one
+// tile of 128 per compute unit: 15 jobs, 2136 -> 1144 23.1 / 13.3, 33 jobs, 2832 -> 928 45 / 28.
 static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
 {
     uint64_t two = 0, wide_tiles = 0;
-    bool lines = true, deep = true;
+    uint32_t min_k = ~0u;
+    bool lines = true;
     for (const Problem &q : p) {
         two += q.M > 16;
-        deep = deep && q.K > kDeepK;
+        min_k = std::min(min_k, q.K);
         lines = lines && ((q.flags & kStripW) || q.N % 64 == 0);
         wide_tiles += (q.N + 127) / 128;
     }
     const bool one_each = wide_tiles <= kFullGrid;
-    if (lines && cached && !deep && one_each) return 0;
+    if (lines && cached && min_k <= kDeepK && one_each) return 0;
     const uint64_t x = two * 2 > p.size() ? 20 : two ? 15 : 10;      // tenths of what 16 columns of weights are
-    auto cost = [&](uint64_t tiles, uint32_t nb) { return (tiles + kFullGrid - 1) / kFullGrid * (10 * nb + x) * (lines && nb == 5 ? 24 : lines && nb == 6 ? 27 : 20); };
-    uint64_t least = cached && one_each ? ~0ull : cost(wide_tiles, 8) * (lines && !cached ? 6 : 9) / 10;
+    auto cost = [&](uint64_t tiles, uint32_t nb) { return (tiles + kFullGrid - 1) / kFullGrid * (10 * nb + x) * (lines && nb == 5 ? 12 : 10); };
+    // in tenths of what registers take
+    const uint32_t at_most = lines ? (!cached ? 6 : one_each ? 10 : 9) : cached && one_each ? 100 : 9;
+    uint64_t least = cost(wide_tiles, 8) * at_most / 10;
     uint32_t best = 0;
     for (const uint32_t nb : {8u, 4u, 5u, 6u}) {
+        if (lines && (nb == 6 || (nb == 8 && min_k <= 2 * kDeepK && !two))) continue;
         uint64_t tiles = 0;
         for (const Problem &q : p) tiles += (q.N + 16 * nb - 1) / (16 * nb);
         const uint64_t c = cost(tiles, nb);
