@@ -150,9 +150,10 @@ constexpr uint32_t kDeepK = 1024;
 // columns through registers.  What the change is worth depends on the rows of the weights and on where they come from.
 // Whole lines: 80 columns cost a fifth more and 96 a third (8 jobs, 3072 -> 2688, 96 columns 1.3 of 128), so those never pay.  From the
 // cache (256 MB) where the load falls by a tenth, but with one tile of 128 per compute unit not in shallow layers (40 jobs, 768
-// wide, three layers 30 / 32 us); 128 columns through LDS there only in layers deeper than 2048 or for jobs of 17 rows and more
-// (registers / LDS, up to 16 rows: 47 jobs, 1152 -> 512 9.9 / 10.9, 24 jobs, 1152 -> 1152 0.88, 9 jobs, 1536 -> 2688 0.94, 22 jobs, 2624 -> 1152 1.04, 23 jobs,
-// 3328 -> 1024 1.12; 32 rows: 20 jobs, 1664 -> 1408 1.03, 23 jobs, 2944 -> 1024 1.15).  From HBM only where 64 columns nearly halve
+// wide, three layers 30 / 32 us); 128 columns through LDS there only for jobs of 17 rows and more, in layers deeper than 2048 with at most three
+// tiles for four compute units and in those deeper than 3072 (registers / LDS, up to 16 rows: 47 jobs, 1152 -> 512 9.9 / 10.9, 24 jobs, 1152 -> 1152
+// 0.90, 9 jobs, 1536 -> 2688 0.94; 26 jobs, 2496 -> 832 (182 tiles) 1.12, 21 jobs, 2176 -> 960 (168) 1.08, 50 jobs, 2176 -> 640 (250) 0.96, 27 jobs, 2688 -> 1024
+// (216) 0.96; 42 jobs, 3136 -> 576 (210) 1.09, 23 jobs, 3328 -> 1024 1.07; 32 rows: 20 jobs, 1664 -> 1408 0.99, 23 jobs, 2944 -> 1024 1.14).  From HBM only where 64 columns nearly halve
 // the load (45 jobs, 2560 -> 320: 18.2 / 14.9; at 0.8 of the load 12 jobs, 1792 -> 1536 0.92; 20 jobs x 1 - 32 rows, 2048 -> 2048 -> 2048 -> 2048, strips: 102 / 111).
 // Rows that begin inside a line, which cost registers extra: from HBM where the load falls by a tenth (40 jobs, 776 wide, nine layers
 // 156 / 140 us, 16 jobs, 3080 -> 1496 -> 3080 -> 1496 101 / 88; without: 24 jobs, 1160 wide, 107 / 122), from the cache also with one
@@ -174,10 +175,11 @@ static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
     auto cost = [&](uint64_t tiles, uint32_t nb) { return (tiles + kFullGrid - 1) / kFullGrid * (10 * nb + x) * (lines && nb == 5 ? 12 : 10); };
     // in tenths of what registers take
     const uint32_t at_most = lines ? (!cached ? 6 : one_each ? 10 : 9) : cached && one_each ? 100 : 9;
+    const uint32_t lds_from = wide_tiles * 4 <= kFullGrid * 3 ? 2 * kDeepK : 3 * kDeepK;
     uint64_t least = cost(wide_tiles, 8) * at_most / 10;
     uint32_t best = 0;
     for (const uint32_t nb : {8u, 4u, 5u, 6u}) {
-        if (lines && (nb == 6 || (nb == 8 && min_k <= 2 * kDeepK && !two))) continue;
+        if (lines && (nb == 6 || (nb == 8 && min_k <= lds_from && !two))) continue;
         uint64_t tiles = 0;
         for (const Problem &q : p) tiles += (q.N + 16 * nb - 1) / (16 * nb);
         const uint64_t c = cost(tiles, nb);

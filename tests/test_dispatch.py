@@ -261,10 +261,11 @@ def test_columns_spread_evenly_while_all_that_is_resident_fits_the_cache(record)
 
 
 def test_whole_lines_one_tile_per_compute_unit(record):
-    """128 columns through LDS only in layers deeper than 2048 or for jobs of 17 rows and more; narrower ones that are still one per
-    compute unit from 1024; never 96."""
+    """128 columns through LDS only for jobs of 17 rows and more, in layers deeper than 2048 (up to 192 tiles) or 3072; narrower ones that are
+    still one per compute unit from 1024; never 96."""
     check(record, [(case(rows, K, N), ["grouped_dense_bf16" + kernel]) for rows, K, N, kernel in (
         ([8] * 47, 1152, 512, "<1, false, true>"), ([2] * 9, 1536, 2688, "<1, false, true>"), ([16] * 23, 2048, 1024, "<1, false, true>"),
         ([16] * 23, 2056, 1024, "_even<1, 8>"), ([17] + [8] * 19, 1664, 1408, "_even<2, 8>"), ([8] * 30, 1032, 640, "_even<1, 5>"),
-        ([8] * 30, 1024, 640, "<1, false, true>"),
+        ([8] * 30, 1024, 640, "<1, false, true>"), ([8] * 24, 2056, 1024, "_even<1, 8>"), ([8] * 25, 3072, 1024, "<1, false, true>"),
+        ([8] * 25, 3080, 1024, "_even<1, 8>"),
     )])
