@@ -155,17 +155,20 @@ constexpr uint32_t kDeepK = 1024;
 // 0.90, 9 jobs, 1536 -> 2688 0.94; 26 jobs, 2496 -> 832 (182 tiles) 1.12, 21 jobs, 2176 -> 960 (168) 1.08, 50 jobs, 2176 -> 640 (250) 0.96, 27 jobs, 2688 -> 1024
 // (216) 0.96; 42 jobs, 3136 -> 576 (210) 1.09, 23 jobs, 3328 -> 1024 1.07; 32 rows: 20 jobs, 1664 -> 1408 0.99, 23 jobs, 2944 -> 1024 1.14).  From HBM only where 64 columns nearly halve
 // the load (45 jobs, 2560 -> 320: 18.2 / 14.9; at 0.8 of the load 12 jobs, 1792 -> 1536 0.92; 20 jobs x 1 - 32 rows, 2048 -> 2048 -> 2048 -> 2048, strips: 102 / 111).
-// Rows that begin inside a line, which cost registers extra: from HBM where the load falls by a tenth (40 jobs, 776 wide, nine layers
-// 156 / 140 us, 16 jobs, 3080 -> 1496 -> 3080 -> 1496 101 / 88; without: 24 jobs, 1160 wide, 107 / 122), from the cache also with one
-// tile of 128 per compute unit: 15 jobs, 2136 -> 1144 23.1 / 13.3, 33 jobs, 2832 -> 928 45 / 28.
+// Rows that begin inside a line, which cost registers extra: from the cache always (17 jobs, 472 -> 1712, the same load either way 6.4 / 5.1, 64
+// jobs x 32 rows, 680 -> 1760, 1.16, 33 jobs, 2832 -> 928 45 / 28), in layers below 320 where the load falls by a fifth (28 jobs, 136 -> 928, 64 jobs,
+// 256 -> 424, the same load 0.90 and 0.92, 184 -> 1560, 0.83 of it 0.91, 30 jobs, 224 -> 1464, 0.78 of it 1.26).  From HBM where it falls by a tenth (40
+// jobs, 776 wide, nine layers 156 / 140 us, 16 jobs, 3080 -> 1496 -> 3080 -> 1496 101 / 88; without: 24 jobs, 1160 wide, 107 / 122), in layers below 512
+// by three tenths (21 jobs, 424 -> 3752, 0.89 of the load 15.0 / 16.3, 59 jobs, 296 -> 1096, 0.79 of it 13.3 / 14.8, 10 jobs, 384 -> 3304, 0.67 of it 1.08).
 static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
 {
     uint64_t two = 0, wide_tiles = 0;
-    uint32_t min_k = ~0u;
+    uint32_t min_k = ~0u, max_k = 0;
     bool lines = true;
     for (const Problem &q : p) {
         two += q.M > 16;
         min_k = std::min(min_k, q.K);
+        max_k = std::max(max_k, q.K);
         lines = lines && ((q.flags & kStripW) || q.N % 64 == 0);
         wide_tiles += (q.N + 127) / 128;
     }
@@ -174,7 +177,7 @@ static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
     const uint64_t x = two * 2 > p.size() ? 20 : two ? 15 : 10;      // tenths of what 16 columns of weights are
     auto cost = [&](uint64_t tiles, uint32_t nb) { return (tiles + kFullGrid - 1) / kFullGrid * (10 * nb + x) * (lines && nb == 5 ? 12 : 10); };
     // in tenths of what registers take
-    const uint32_t at_most = lines ? (!cached ? 6 : one_each ? 10 : 9) : cached && one_each ? 100 : 9;
+    const uint32_t at_most = lines ? (!cached ? 6 : one_each ? 10 : 9) : cached ? (max_k < 320 ? 8 : 100) : max_k < 512 ? 7 : 9;
     const uint32_t lds_from = wide_tiles * 4 <= kFullGrid * 3 ? 2 * kDeepK : 3 * kDeepK;
     uint64_t least = cost(wide_tiles, 8) * at_most / 10;
     uint32_t best = 0;

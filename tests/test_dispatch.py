@@ -269,3 +269,15 @@ def test_whole_lines_one_tile_per_compute_unit(record):
         ([8] * 30, 1024, 640, "<1, false, true>"), ([8] * 24, 2056, 1024, "_even<1, 8>"), ([8] * 25, 3072, 1024, "<1, false, true>"),
         ([8] * 25, 3080, 1024, "_even<1, 8>"),
     )])
+
+
+def test_rows_inside_lines_in_shallow_layers(record):
+    """From the cache LDS tiles always, in layers below 320 only where the load falls by a fifth; from further away where it falls by
+    a tenth, in layers below 512 by three tenths."""
+    far = dict(idle=[400 << 20])
+    check(record, [(case(rows, K, N, **kw), ["grouped_dense_bf16" + kernel]) for rows, K, N, kw, kernel in (
+        ([8] * 64, 256, 424, {}, "<1, false, true>"), ([1] * 64, 184, 1560, {}, "<1, false, true>"), ([8] * 30, 224, 1464, {}, "_even<1, 6>"),
+        ([8] * 64, 312, 424, {}, "<1, false, true>"), ([8] * 64, 320, 424, {}, "_even<1, 8>"), ([32] * 64, 680, 1752, {}, "_even<2, 8>"),
+        ([8] * 21, 424, 3752, far, "<1, false, true>"), ([8] * 64, 448, 696, far, "<1, false, true>"), ([8] * 10, 384, 3304, far, "_even<1, 5>"),
+        ([8] * 64, 512, 696, far, "_even<1, 6>"), ([8] * 64, 520, 424, far, "<1, false, true>"),
+    )])
