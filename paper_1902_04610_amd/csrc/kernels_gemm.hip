@@ -160,12 +160,13 @@ constexpr uint32_t kDeepK = 1024;
 // 256 -> 424, the same load 0.90 and 0.92, 184 -> 1560, 0.83 of it 0.91, 30 jobs, 224 -> 1464, 0.78 of it 1.26).  From HBM where it falls by a tenth (40
 // jobs, 776 wide, nine layers 156 / 140 us, 16 jobs, 3080 -> 1496 -> 3080 -> 1496 101 / 88; without: 24 jobs, 1160 wide, 107 / 122), in layers below 512
 // by three tenths (21 jobs, 424 -> 3752, 0.89 of the load 15.0 / 16.3, 59 jobs, 296 -> 1096, 0.79 of it 13.3 / 14.8, 10 jobs, 384 -> 3304, 0.67 of it 1.08).
-static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
+static uint32_t even_columns(const Problem *p, uint32_t n, bool cached)
 {
     uint64_t two = 0, wide_tiles = 0;
     uint32_t min_k = ~0u, max_k = 0;
     bool lines = true;
-    for (const Problem &q : p) {
+    for (uint32_t i = 0; i < n; ++i) {
+        const Problem &q = p[i];
         two += q.M > 16;
         min_k = std::min(min_k, q.K);
         max_k = std::max(max_k, q.K);
@@ -174,7 +175,7 @@ static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
     }
     const bool one_each = wide_tiles <= kFullGrid;
     if (lines && cached && min_k <= kDeepK && one_each) return 0;
-    const uint64_t x = two * 2 > p.size() ? 20 : two ? 15 : 10;      // tenths of what 16 columns of weights are
+    const uint64_t x = two * 2 > n ? 20 : two ? 15 : 10;      // tenths of what 16 columns of weights are
     auto cost = [&](uint64_t tiles, uint32_t nb) { return (tiles + kFullGrid - 1) / kFullGrid * (10 * nb + x) * (lines && nb == 5 ? 12 : 10); };
     // in tenths of what registers take
     const uint32_t at_most = lines ? (!cached ? 6 : one_each ? 10 : 9) : cached ? (max_k < 320 ? 8 : 100) : max_k < 512 ? 7 : 9;
@@ -184,7 +185,7 @@ static uint32_t even_columns(const std::vector<Problem> &p, bool cached)
     for (const uint32_t nb : {8u, 4u, 5u, 6u}) {
         if (lines && (nb == 6 || (nb == 8 && min_k <= lds_from && !two))) continue;
         uint64_t tiles = 0;
-        for (const Problem &q : p) tiles += (q.N + 16 * nb - 1) / (16 * nb);
+        for (uint32_t i = 0; i < n; ++i) tiles += (p[i].N + 16 * nb - 1) / (16 * nb);
         const uint64_t c = cost(tiles, nb);
         if (c > least || (c == least && best)) continue;
         least = c;
@@ -280,8 +281,6 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
         std::vector<Problem> rest;
         for (const Problem &q : small) (q.M > 16 && tiled_shape_fits(q) ? mid : rest).push_back(q);
         small.swap(rest);
-        small_tiles = 0;
-        for (const Problem &q : small) small_tiles += (q.N + 127) / 128;
     }
     auto launch_wide = [&](int mt, const GroupArgs &a, uint32_t tiles) {
         const dim3 grid(tiles), block(kGemmThreads);
@@ -296,21 +295,22 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
         else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16<1, true, true>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((grouped_dense_bf16<1, false, true>), grid, block, 0, stream, a);
     };
-    const bool narrow = small_tiles * 2 <= kFullGrid && (trans_w || std::all_of(small.begin(), small.end(), tiled_shape_fits));
-    if (!small.empty() && !trans_w && !narrow && std::all_of(small.begin(), small.end(), tiled_shape_fits)) {
-        if (const uint32_t nb = even_columns(small, cached)) {
-            auto launch_even = [&](int mt, const GroupArgs &a, uint32_t tiles) {
-                auto go = [&](auto one, auto two) { hipLaunchKernelGGL(mt == 2 ? two : one, dim3(tiles), dim3(kGemmThreads), 0, stream, a); };
-                if (nb == 4) go(grouped_dense_bf16_even<1, 4>, grouped_dense_bf16_even<2, 4>);
-                else if (nb == 5) go(grouped_dense_bf16_even<1, 5>, grouped_dense_bf16_even<2, 5>);
-                else if (nb == 6) go(grouped_dense_bf16_even<1, 6>, grouped_dense_bf16_even<2, 6>);
-                else go(grouped_dense_bf16_even<1, 8>, grouped_dense_bf16_even<2, 8>);
-            };
-            if (hipError_t e = launch_groups(small.data(), (uint32_t)small.size(), 16 * nb, 16, 32, launch_even, launches)) return e;
-            small.clear();
-        }
-    }
-    if (!small.empty()) {
+    // Every launch of up to kMaxProblems jobs for itself: what counts is how its own tiles spread over the compute units (100 jobs,
+    // 1024 -> 200, are launches of 128 and 72 tiles, not one of 200).
+    for (uint32_t at = 0; at < small.size(); at += kMaxProblems) {
+        const Problem *q = small.data() + at;
+        const uint32_t count = std::min(kMaxProblems, (uint32_t)small.size() - at);
+        uint64_t tiles_128 = 0;
+        for (uint32_t i = 0; i < count; ++i) tiles_128 += (q[i].N + 127) / 128;
+        const bool fits = std::all_of(q, q + count, tiled_shape_fits), narrow = tiles_128 * 2 <= kFullGrid && (trans_w || fits);
+        const uint32_t nb = trans_w || narrow || !fits ? 0 : even_columns(q, count, cached);
+        auto launch_even = [&](int mt, const GroupArgs &a, uint32_t tiles) {
+            auto go = [&](auto one, auto two) { hipLaunchKernelGGL(mt == 2 ? two : one, dim3(tiles), dim3(kGemmThreads), 0, stream, a); };
+            if (nb == 4) go(grouped_dense_bf16_even<1, 4>, grouped_dense_bf16_even<2, 4>);
+            else if (nb == 5) go(grouped_dense_bf16_even<1, 5>, grouped_dense_bf16_even<2, 5>);
+            else if (nb == 6) go(grouped_dense_bf16_even<1, 6>, grouped_dense_bf16_even<2, 6>);
+            else go(grouped_dense_bf16_even<1, 8>, grouped_dense_bf16_even<2, 8>);
+        };
         // As many workgroups as compute units, not more: a narrower tile streams less efficiently.  32 / 16 columns, one job x
         // 1 row: 2048 -> 1024 4.9 / 4.0 us (32 / 64 workgroups; 32 columns through registers 9.2), 1024 -> 1024 3.6 / 3.2, x 32 rows
         // 5.1 / 4.8, 4 jobs x 32 rows 5.3 / 5.0.  Transposed weights, 128 / 64 / 32 columns: 2048 -> 2048 of 4 jobs 20.3 /
@@ -335,12 +335,11 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
             else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, true, 2, 8>), grid, block, 0, stream, a);
             else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 2, 0>), grid, block, 0, stream, a);
         };
-        const Problem *q = small.data();
-        const uint32_t count = (uint32_t)small.size();
-        const hipError_t e = !narrow                                      ? launch_groups(q, count, 128, 16, 32, launch_wide, launches)
-                             : !trans_w && small_tiles * 8 <= kFullGrid   ? launch_groups(q, count, 16, 16, 32, launch_16, launches)
-                             : small_tiles * 4 <= kFullGrid               ? launch_groups(q, count, 32, 16, 32, launch_32, launches)
-                                                                          : launch_groups(q, count, 64, 16, 32, launch_64, launches);
+        const hipError_t e = nb                                         ? launch_groups(q, count, 16 * nb, 16, 32, launch_even, launches)
+                             : !narrow                                  ? launch_groups(q, count, 128, 16, 32, launch_wide, launches)
+                             : !trans_w && tiles_128 * 8 <= kFullGrid   ? launch_groups(q, count, 16, 16, 32, launch_16, launches)
+                             : tiles_128 * 4 <= kFullGrid               ? launch_groups(q, count, 32, 16, 32, launch_32, launches)
+                                                                        : launch_groups(q, count, 64, 16, 32, launch_64, launches);
         if (e != hipSuccess) return e;
     }
     if (!mid.empty() && !trans_w) {
@@ -405,24 +404,15 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
     // 64 rows, 1024 -> 1024 8.8 / 12.7 / 21.3; 12 jobs x 32 rows, 1204 -> 780 (312 16-row tiles) 16.9 / 15.3, 40 jobs, 256 -> 256 (320) 5.9 / 6.0; 12 jobs x 128
     // rows, 1536 -> 1536 88 / 80 / 89, 4 jobs 33 / 33 / 32; 40 jobs x 33 rows, 1536 -> 1536 (960 64-row tiles, 3.75 rounds), 32 / 64 rows:
     // 121 / 113; 40 jobs x 128 rows, 1024 -> 1024 -> 1024 (5 rounds) 213 / 202, 40 rows (2.5) 110 / 122.
-    uint64_t tiles_16 = 0, tiles_32 = 0, tiles_64 = 0, columns_16 = 0;
+    uint64_t tiles_16 = 0, tiles_32 = 0, tiles_64 = 0;
     uint32_t max_m = 0, min_k = ~0u;
     for (uint32_t i = 0; i < n; ++i) {
         const uint64_t cols = (p[i].N + 63) / 64;
         tiles_16 += (p[i].M + 15) / 16 * cols;
         tiles_32 += (p[i].M + 31) / 32 * cols;
         tiles_64 += (p[i].M + 63) / 64 * cols;
-        columns_16 += (uint64_t)((p[i].M + 15) / 16) * ((p[i].N + 15) / 16);
         max_m = std::max(max_m, p[i].M);
         min_k = std::min(min_k, p[i].K);
-    }
-    // As long as there is at most one 16-column tile per compute unit: 6 jobs x 16 rows, 1024 -> 1024 (384), 16 / 64 columns 7.6 / 7.9 us, 12
-    // jobs (768) 12.7 / 10.9.
-    if (columns_16 <= kFullGrid) {
-        auto launch_narrow = [&](int, const GroupArgs &a, uint32_t tiles) {
-            hipLaunchKernelGGL(grouped_dense_f32_narrow, dim3(tiles), dim3(kGemmThreads), 0, stream, a);
-        };
-        return launch_groups(p, n, 16, 0, 0, launch_narrow, launches, 1);
     }
     const bool one_32 = min_k > 512 && max_m > 16 && max_m <= 32 && tiles_16 > kFullGrid && tiles_32 <= kFullGrid && tiles_16 * 4 > tiles_32 * 7;
     const uint64_t rounds_64 = (tiles_64 + kFullGrid - 1) / kFullGrid;
@@ -432,7 +422,20 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
                    : max_m > 128 || tiles_64 <= kFullGrid          ? 0
                    : max_m > 32 && whole_64                        ? 4
                    : max_m > 16                                    ? 2 : 1;
-    return launch_groups(p, n, 64, 16, 32, launch, launches, mt);
+    // 16 columns as long as there is at most one such tile per compute unit, in every launch for itself: 6 jobs x 16 rows, 1024 -> 1024 (384), 16 / 64
+    // columns 7.6 / 7.9 us, 12 jobs (768) 12.7 / 10.9.
+    auto launch_narrow = [&](int, const GroupArgs &a, uint32_t tiles) {
+        hipLaunchKernelGGL(grouped_dense_f32_narrow, dim3(tiles), dim3(kGemmThreads), 0, stream, a);
+    };
+    for (uint32_t at = 0; at < n; at += kMaxProblems) {
+        const uint32_t count = std::min(kMaxProblems, n - at);
+        uint64_t columns_16 = 0;
+        for (uint32_t i = at; i < at + count; ++i) columns_16 += (uint64_t)((p[i].M + 15) / 16) * ((p[i].N + 15) / 16);
+        const hipError_t e = columns_16 <= kFullGrid ? launch_groups(p + at, count, 16, 0, 0, launch_narrow, launches, 1)
+                                                     : launch_groups(p + at, count, 64, 16, 32, launch, launches, mt);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace salus

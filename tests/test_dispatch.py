@@ -281,3 +281,14 @@ def test_rows_inside_lines_in_shallow_layers(record):
         ([8] * 21, 424, 3752, far, "<1, false, true>"), ([8] * 64, 448, 696, far, "<1, false, true>"), ([8] * 10, 384, 3304, far, "_even<1, 5>"),
         ([8] * 64, 512, 696, far, "_even<1, 6>"), ([8] * 64, 520, 424, far, "<1, false, true>"),
     )])
+
+
+def test_more_jobs_than_a_launch_holds(record):
+    """Every launch of 64 jobs takes the tiles that suit it, whatever the others hold."""
+    check(record, [
+        (case([8] * 100, 1024, 200), ["grouped_dense_bf16_narrow<1, false, 4, 0, true>"] * 2),
+        (case([8] * 65, 512, 1016), ["grouped_dense_bf16_even<1, 8>", "grouped_dense_bf16_narrow<1, false, 1, 0, true>"]),
+        (case([8] * 64 + [17] * 17, 1032, 1024), ["grouped_dense_bf16<1, false, true>", "grouped_dense_bf16_even<2, 5>"]),
+        (case([8] * 128, 512, 64, "f32"), ["grouped_dense_f32_narrow"] * 2),
+        (case([8] * 65, 512, 256, "f32"), ["grouped_dense_f32<1>", "grouped_dense_f32_narrow"]),
+    ])
