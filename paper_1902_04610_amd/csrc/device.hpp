@@ -88,8 +88,7 @@ bool tiled_shape_ok(const Problem &p);
 bool tiled_shape_ragged(const Problem &p);
 bool tiled_shape_shallow(const Problem &p);
 uint64_t tiled_tiles(const Problem &p);
-hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t stream,
-                                     uint64_t *launches);
+hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, bool cached, hipStream_t stream, uint64_t *launches);
 // Jobs of 33 .. 128 rows, and transposed weights above: 64-row tiles fed through an LDS ring (tiled_shape_fits).
 hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream,
                                       uint64_t *launches);

@@ -253,7 +253,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
         if (std::any_of(p, p + n, takes_tiled)) {
             std::vector<Problem> tiled, streamed;
             for (uint32_t i = 0; i < n; ++i) (takes_tiled(p[i]) ? tiled : streamed).push_back(p[i]);
-            hipError_t e = launch_grouped_bf16_tiled(tiled.data(), (uint32_t)tiled.size(), stream, launches);
+            hipError_t e = launch_grouped_bf16_tiled(tiled.data(), (uint32_t)tiled.size(), cached, stream, launches);
             if (e != hipSuccess || streamed.empty()) return e;
             return launch_grouped_bf16(streamed.data(), (uint32_t)streamed.size(), false, cached, stream, launches);
         }

@@ -293,7 +293,11 @@ hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStre
 // 0.6 of the time.  Two 128 x 256 tiles per compute unit also cover each other's waits for weights: where every weight
 // is used by one row tile (up to 128 rows) and most compute units have one, half (64 jobs x 100 rows, 1024 -> 1024: 28 us,
 // one per compute unit with twice the wavefronts 38; 24 jobs 20 / 18, so not there).  Over 528 launches of 33 - 4096 rows,
-// 512 - 4096 -> 512 - 4096, the choice is 1.0 % off the best kind on average; without that kind it was 2.4 % slower.  What the rule is
+// 512 - 4096 -> 512 - 4096, the choice is 1.0 % off the best kind on average; without that kind it was 2.4 % slower.  Weights from HBM cost
+// one round of 256 x 256 tiles, which ask for every weight once per 256 rows, less than what the others need more rounds for: 5 jobs x
+// 500 rows, 1280 -> 3968, 256 x 256 / 128 x 128 37.8 / 37.0 us from the cache, 38.3 / 47.6 from HBM; 18 jobs x 256 - 1024, 1024 -> 896, 30.4 / 29.1 and
+// 32.9 / 38.6.  7 % off its time then (any figure from there to 20 % gives the same choices but one): over 207 launches of 65 - 1024 rows with weights from
+// HBM the choice is 1.4 % off the best kind, 2.0 % without.  What the rule is
 // for: 4 jobs x 500 rows, 2048 -> 2048, 256 x 256 / 128 x 256 / 128 x 128 / two 128 x 256: 48 / 30 / 25 / 33 us; 32 jobs x
 // 300 - 1000 rows, 4096 -> 1024 207 / 200 / 222 / 195, 1024 -> 1024 70 / 69 / 61 / 55; 32 jobs x 500 rows, 1024 -> 4096 167 /
 // 190 / 222 / 181.
@@ -301,7 +305,7 @@ struct TileKind { uint32_t bm, bn, per_cu, slab_ns, rest_ns; };
 constexpr TileKind kTile256 = {256, 256, 1, 1640, 12000}, kTile128x256 = {128, 256, 1, 935, 8000}, kTile128 = {128, 128, 2, 1090, 6000},
                    kTilePair = {128, 256, 2, 1720, 12000};
 
-static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n)
+static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n, bool cached)
 {
     uint64_t tiles = 0, work = 0;
     bool weight_bound = true;
@@ -315,7 +319,8 @@ static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n)
     const uint64_t cus = resident_grid(), grid = cus * t.per_cu, last = tiles % grid;
     uint64_t tenths = tiles / grid * 10;       // of a round
     if (last) tenths += t.per_cu == 1 || last > cus ? 10 : &t == &kTilePair && weight_bound && last * 4 > cus * 3 ? 5 : 6;
-    return tenths * (work / tiles) / 10;
+    const uint64_t ns = tenths * (work / tiles) / 10;
+    return &t == &kTile256 && !cached && tiles <= cus ? ns * 93 / 100 : ns;
 }
 
 // Launches bound by the weight stream.  64 x 128 tiles, two workgroups per compute unit; 64 x 64, twice the workgroups,
@@ -344,20 +349,20 @@ hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w
 // epilogue, which only two tiles on a compute unit overlap: 128 x 128 (160 launches of 256 -> 1024 and 4096, 192 - 4096 rows:
 // 1 % off the best kind on average, 128 x 256 11 %, 256 x 256 28 %).
 struct TileChoice { const TileKind *kind; uint64_t ns; };
-static TileChoice choose_tile(const std::vector<Problem> &p, bool tall)
+static TileChoice choose_tile(const std::vector<Problem> &p, bool tall, bool cached)
 {
     TileChoice best{nullptr, ~0ull};
     if (p.empty()) return best;
     const bool shallow = std::all_of(p.begin(), p.end(), tiled_shape_shallow);
     for (const TileKind *t : {&kTile256, &kTile128x256, &kTile128, &kTilePair}) {
         if ((t == &kTile256 && !tall) || (t != &kTile128 && shallow)) continue;
-        const uint64_t ns = launch_ns(*t, p.data(), (uint32_t)p.size());
+        const uint64_t ns = launch_ns(*t, p.data(), (uint32_t)p.size(), cached);
         if (ns < best.ns) best = {t, ns};
     }
     return best;
 }
 
-hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
+hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, bool cached, hipStream_t stream, uint64_t *launches)
 {
     std::vector<Problem> big, small;
     bool ragged = false;
@@ -367,14 +372,14 @@ hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, hipStream_t s
     }
     big.reserve(n);
     for (uint32_t i = 0; i < n; ++i) (p[i].M >= kTiled256MinM ? big : small).push_back(p[i]);
-    TileChoice tall = choose_tile(big, true);
-    const TileChoice low = choose_tile(small, false);
+    TileChoice tall = choose_tile(big, true, cached);
+    const TileChoice low = choose_tile(small, false, cached);
     if (ragged && !big.empty() && !small.empty()) {
         // Jobs on either side of 192 rows, ragged ones among them (whose alternative, register tiles, is one launch): one
         // launch of 128-row tiles, unless two are quicker even though each ends with a round of its own.  16 jobs x
         // 129 - 260 rows, 2056 -> 520: 21 us, in two launches 42.
         const std::vector<Problem> all(p, p + n);
-        const TileChoice one = choose_tile(all, false);
+        const TileChoice one = choose_tile(all, false, cached);
         if (one.ns <= tall.ns + low.ns) {
             big = all;
             small.clear();

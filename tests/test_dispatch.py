@@ -292,3 +292,13 @@ def test_more_jobs_than_a_launch_holds(record):
         (case([8] * 128, 512, 64, "f32"), ["grouped_dense_f32_narrow"] * 2),
         (case([8] * 65, 512, 256, "f32"), ["grouped_dense_f32<1>", "grouped_dense_f32_narrow"]),
     ])
+
+
+def test_one_round_of_256_by_256_from_further_away_than_the_cache(record):
+    """It is not traded for a round and a bit of 128 x 128 tiles there; launches of several rounds choose alike."""
+    far = dict(idle=[400 << 20])
+    check(record, [(case(rows, K, N, **kw), ["grouped_dense_bf16_tiled" + kernel]) for rows, K, N, kw, kernel in (
+        ([500] * 5, 1280, 3968, {}, "<128, 128, 2, 2>"), ([500] * 5, 1280, 3968, far, "<256, 256, 2, 4>"),
+        ([500] * 5, 1280, 3968, dict(idle=[400 << 20], evicted=True), "<128, 128, 2, 2>"),
+        ([1000] * 29, 512, 768, {}, "<128, 256, 1, 4>"), ([1000] * 29, 512, 768, far, "<128, 256, 1, 4>"),
+    )])
