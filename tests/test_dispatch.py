@@ -9,6 +9,7 @@ import sys
 import pytest
 
 from paper_1902_04610_amd import build
+from test_gpu_routes import SMALL_TILES, small_tiles
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 STREAM = 0x50                        # any handle
@@ -26,17 +27,16 @@ def pool(capacity, **kw):
 def forward(case):
     dt = salus.F32 if case["dtype"] == "f32" else salus.BF16
     esz = 4 if dt == salus.F32 else 2
-    widths = case["N"] if isinstance(case["N"], list) else [case["N"]]
     up = lambda v: (v + 255) // 256 * 256
     top, layers = max(case["rows"]), []
-    for k, strip in zip(case["K"], case["strip"]):
-        dims, at, mine = [k] + widths, 0, []
-        for l, (a, b) in enumerate(zip(dims, widths)):
-            mine.append((a, b, at, salus.ACT_NONE, salus.LAYOUT_STRIP128 if strip else salus.LAYOUT_ROWMAJOR))
-            at += up(a * b * esz)
+    for dims, strip in zip(case["dims"], case["strip"]):
+        at, mine = 0, []
+        for k, n in zip(dims, dims[1:]):
+            mine.append((k, n, at, salus.ACT_NONE, salus.LAYOUT_STRIP128 if strip and n %% 128 == 0 else salus.LAYOUT_ROWMAJOR))
+            at += up(k * n * esz)
         layers.append((at, mine))
-    P, y = max(size for size, _ in layers), up(top * max(case["K"]) * esz)
-    h = y + up(top * widths[-1] * 4)
+    P, y = max(size for size, _ in layers), up(top * max(dims[0] for dims in case["dims"]) * esz)
+    h = y + up(top * max(dims[-1] for dims in case["dims"]) * 4)
     E = h + max(salus.forward_work_bytes(top, [t[:4] for t in mine], dt) for _, mine in layers)
     p = pool(len(case["rows"]) * (P + E) + sum(v + 256 for v in case["idle"]))
     for v in case["idle"]:
@@ -123,7 +123,8 @@ def case(rows, K, N, dtype="bf16", strip=False, idle=(), evicted=False):
     """Jobs of one layer, or of as many as N has widths; K and strip one for all or one for each.  idle: bytes of jobs that the
     pool holds besides; evicted: the last of them has been switched out."""
     each = lambda v: v if isinstance(v, list) else [v] * len(rows)
-    return dict(do="forward", rows=rows, K=each(K), N=N, dtype=dtype, strip=each(strip), idle=list(idle), evicted=evicted)
+    dims = [[k] + (N if isinstance(N, list) else [N]) for k in each(K)]
+    return dict(do="forward", rows=rows, dims=dims, dtype=dtype, strip=each(strip), idle=list(idle), evicted=evicted)
 
 
 def check(record, expected):
@@ -302,3 +303,10 @@ def test_one_round_of_256_by_256_from_further_away_than_the_cache(record):
         ([500] * 5, 1280, 3968, dict(idle=[400 << 20], evicted=True), "<128, 128, 2, 2>"),
         ([1000] * 29, 512, 768, {}, "<128, 256, 1, 4>"), ([1000] * 29, 512, 768, far, "<128, 256, 1, 4>"),
     )])
+
+
+def test_parity_tests_of_small_tiles_launch_what_they_are_named_after(record):
+    cases = [small_tiles(name) for name in SMALL_TILES]
+    check(record, [(dict(do="forward", rows=[j["M"] for j in specs], dims=[j["dims"] for j in specs], dtype="bf16",
+                         strip=[j["strip"] for j in specs], idle=[], evicted=False), ["grouped_dense_bf16_" + k for k in names])
+                   for specs, names in cases])

@@ -137,7 +137,7 @@ def test_narrow_tiles_up_to_32_rows(jobs, dims, strip):
 
 
 @pytest.mark.parametrize("jobs, dims, strip", [
-    (48, (40, 1016), False), (48, (8, 776, 1016), False),                            # 64 columns, 80
+    (48, (40, 1016), False), (48, (8, 776, 1016), False),                            # registers (shallow), 80 columns, 64
     (20, (264, 1000), False), (23, (520, 1272), False), (48, (136, 776), False),     # 96, 128, 80
     (64, (72, 640), True), (40, (136, 1024, 8), True),                               # strips: 80 columns, across their borders; 64
 ])
@@ -147,6 +147,43 @@ def test_evenly_spread_columns_up_to_32_rows(jobs, dims, strip):
     specs = [dict(M=[1, 16, 17, 32, 7][i % 5], dims=dims, acts=([GELU, RELU] * 2)[:len(dims) - 2] + [NONE], strip=strip) for i in range(jobs)]
     outs, refs, n = run_jobs(specs, salus.BF16)
     assert n == len(dims) - 1
+    fused, _, _ = run_jobs(specs, salus.BF16, fuse=True)
+    for o, r, f, j in zip(outs, refs, fused, specs):
+        assert np.isfinite(o).all(), j
+        assert norm_rel_err(o, r) < TOL_BF16_TIGHT, (j, norm_rel_err(o, r))
+        assert np.array_equal(o.view(np.uint32), f.view(np.uint32)), j
+
+
+# Tiles of up to 32 rows through LDS, one and two row tiles of each width: (jobs, widths, strips); ROWS has the rows that make
+# it one row tile or two.  Depths go round the ring more than once and end inside a k-step, widths end inside a tile.
+ROWS = {1: [1, 16, 7, 12, 3], 2: [1, 16, 17, 32, 7]}
+SMALL_TILES = {
+    "even<%d, 4>": (36, (1096, 448), False), "even<%d, 5>": (48, (1000, 776), False), "even<%d, 6>": (20, (520, 1000), False),
+    "even<%d, 8>": (23, (520, 1272), False),
+    "even<%d, 4>, strips": (40, (1064, 1024), True), "even<%d, 5>, strips": (30, (1064, 640), True), "even<%d, 8>, strips": (24, (2088, 1024), True),
+    "even<%d, 6>, strips beside rows": (20, (520, [1024, 1000]), True), "even<%d, 8>, strips beside rows": (23, (520, [1280, 1272]), True),
+    "even<%d, 4>, less than a ring": (37, (40, 800), False),
+    "narrow<%d, false, 1, 0, true>": (3, (4104, 24), False), "narrow<%d, false, 2, 0, true>": (5, (1064, 1032), False),
+    "narrow<%d, false, 4, 0, true>": (14, (1064, 1032), False), "narrow<%d, false, 4, 0, true>, strips": (14, (1064, 1024), True),
+    "narrow<%d, false, 4, 0, true>, two launches": (100, (264, 200), False),
+}
+SMALL_TILES = {n.replace("%d", str(mt)): (mt, *v) for n, v in SMALL_TILES.items() for mt in (1, 2)}
+
+
+def small_tiles(name):
+    """The jobs of one of them and the kernels that they launch."""
+    mt, jobs, (K, N), strip = SMALL_TILES[name]
+    N = N if isinstance(N, list) else [N]
+    return ([dict(M=ROWS[mt][i % 5], dims=(K, N[i % len(N)]), acts=[[GELU, RELU, NONE][i % 3]], strip=strip) for i in range(jobs)],
+            [name.split(">")[0] + ">"] * ((jobs + 63) // 64))
+
+
+@pytest.mark.parametrize("name", SMALL_TILES)
+def test_small_tiles_through_lds(name):
+    """Against the oracle, and bit for bit against the depth-fused launch, whose tiles sum in the same order."""
+    specs, kernels = small_tiles(name)
+    outs, refs, n = run_jobs(specs, salus.BF16)
+    assert n == len(kernels)
     fused, _, _ = run_jobs(specs, salus.BF16, fuse=True)
     for o, r, f, j in zip(outs, refs, fused, specs):
         assert np.isfinite(o).all(), j
