@@ -39,11 +39,11 @@ constexpr int kGemmThreads = 256;
 constexpr int kWaves = 4;
 
 // bf16 kernels: GELU(z) = z / 2 + |z| (1/2 - Q(|z|)) with the upper tail Q(x) = erfc(x / sqrt 2) / 2 = 2^p(x), p the
-// polynomial of degree 6 that minimizes the largest |x (2^p - Q)| over [0, 5.5] (fitted by linear programming: 9.4e-8),
+// polynomial of degree 6 that minimizes the largest |x (2^p - Q)| over [0, 5.5] (fitted by linear programming; 9.8e-8 with the coefficients in float),
 // evaluated up to 9, from where on Q is below 2^-62 and 1/2 - Q is 1/2.  Fourteen operations, counting the exponential
 // (v_exp_f32) as four: the epilogues of wide layers are bound by them, and where the power limit sets the clock they cost
 // what multiplies could use (16 jobs x 4096 rows, 1024 - 4096 - 1024 - 1024: 1186 us, 1264 with the rational
-// approximation of erfc before it).  In float arithmetic over [-40, 40]: |error| of the result below 3.8e-7 (7.6e-7).  The error is *absolute* in Q,
+// approximation of erfc before it).  In float arithmetic over [-40, 40]: |error| of the result below 4e-7 (7.6e-7).  The error is *absolute* in Q,
 // so for z < -3.5, where Q itself falls below 5e-4, the relative error of a single output grows; such outputs are below
 // 1e-3 in magnitude and only decide a comparison when a whole matrix consists of them.  Infinities give what the sum
 // of z / 2 and |z| / 2 gives, a NaN stays a NaN.

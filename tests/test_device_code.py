@@ -1,10 +1,13 @@
-"""What the compiler makes of the device code (CPU only: every kernel file is compiled for gfx950, nothing is run)."""
+"""What the compiler makes of the device code (CPU only: every kernel file is compiled for gfx950, nothing is run), and what its
+constants are good for."""
 import concurrent.futures
 import os
 import re
 import subprocess
 
+import numpy as np
 import pytest
+from scipy.special import erfc
 
 from paper_1902_04610_amd import build
 
@@ -119,3 +122,23 @@ def test_no_kernel_spills_vector_registers(assembly):
     spills = re.findall(r"VGPRs Spill: (\d+)", assembly["remarks"])
     assert len(names) == len(scratch) == len(spills) > 30
     assert not [t for t in zip(names, scratch, spills) if t[1:] != ("0", "0")]
+
+
+def test_gelu_polynomial_keeps_its_bounds():
+    """The exponent polynomial of the bf16 kernels' GELU, with the coefficients as they stand in the source: its largest
+    |x (2^p - Q)| where it is fitted, and the largest error of the result in float arithmetic (exponential correctly rounded)."""
+    with open(os.path.join(build.CSRC, "group.hpp")) as f:
+        body = re.search(r"float gelu_fast\(float z\)\n\{(.*?)\n\}", f.read(), re.S).group(1)
+    coef = [np.float32(v) for v in re.findall(r"(-?\d+\.\d+(?:e-\d+)?)f", body.split("float p =")[1].split("const float q")[0])]
+    assert len(coef) == 7
+    x = np.linspace(0, 5.5, 1 << 20)
+    exact = 0.5 * erfc(x / np.sqrt(2))
+    assert np.abs(x * (2.0 ** np.polyval(np.float64(coef), x) - exact)).max() < 1.0e-7
+    z = np.concatenate([np.linspace(-40, 40, 1 << 21), np.linspace(-9.5, 9.5, 1 << 21), [4.0205336]]).astype(np.float32)
+    x = np.abs(z).astype(np.float64)
+    c, p = np.clip(x, 0, 9), np.float64(coef[0])
+    for k in coef[1:]:
+        p = np.float64(np.float32(p * c + np.float64(k)))           # one rounding: the product of two floats is exact
+    q = np.exp2(p).astype(np.float32)
+    got = np.float32(x * np.float64(np.float32(0.5) - q) + np.float64(np.float32(0.5) * z))
+    assert np.abs(got - 0.5 * np.float64(z) * erfc(-np.float64(z) / np.sqrt(2))).max() < 4.0e-7
