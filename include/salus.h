@@ -240,10 +240,11 @@ int32_t salus_schedule_iteration(salus_pool_t *pool, salus_slot *out, uint32_t c
  * 32 rows (otherwise that dtype takes the per-depth launches): the workgroups
  * of layer l+1 wait on a device counter for the job's layer l, so a job's next
  * layer starts as soon as its own input is complete and no launch boundary
- * drains the GPU.  Outputs are bit-identical to the per-depth launches.  The
- * job's persistent state and iteration boundary are untouched: this is batching
- * inside one iteration (Section 3.2.2 rules out scheduling below it, not
- * this).  Fused calls of one pool must be ordered on the device (use one
+ * drains the GPU.  Outputs are bit-identical to those of the per-depth launches
+ * (finite weights: an infinity in the first 8 rows of a bf16 W may give NaN in one
+ * and an infinity in the other if K is no multiple of 32).  The job's persistent
+ * state and iteration boundary are untouched: this is batching inside one
+ * iteration (Section 3.2.2 rules out scheduling below it, not this).  Fused calls of one pool must be ordered on the device (use one
  * stream) and cannot be recorded in a HIP graph (SALUS_EINVAL while the stream
  * is capturing: consecutive launches alternate between two sets of counters);
  * the per-depth launches can, they are plain kernel launches with by-value

@@ -6,11 +6,12 @@
 //
 // Shape of the work: per job Y[M x N] = act(X[M x K] . W[K x N]) with M small
 // (1..32 rows, more where the round is small, 64 for deep layers; the others go to kernels_gemm_tiled.hip) and
-// W read straight out of the job's persistent block.  Every weight is used once per launch, so the kernel is a weight-streaming kernel:
-// W goes HBM -> registers with 16-byte loads (no LDS staging: nothing would be
-// reused), each wavefront keeps two k-steps of loads in flight, the 8x8 bf16
-// sub-blocks are transposed in registers into MFMA operand order, and the four
-// wavefronts of a workgroup split K and combine their partial tiles through LDS.
+// W read straight out of the job's persistent block.  Every weight is used once per launch, so these are weight-streaming kernels.
+// The four wavefronts of a workgroup split K and combine their partial tiles through LDS.  In launches that fill the chip
+// W goes HBM -> registers with 16-byte loads, each wavefront keeps two k-steps of loads in flight, and the 8x8 bf16
+// sub-blocks are transposed in registers into MFMA operand order.  Where a launch holds few tiles, or would load the compute units unevenly, the tiles
+// are narrower and their operands go straight into an LDS ring per wavefront, for bytes in flight and not for reuse, and are transposed on
+// the way out (narrow_tile.hpp).
 #include <algorithm>
 #include <vector>
 
@@ -36,7 +37,7 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16(GroupArgs a)
 // tile (NT) its operands go straight into LDS (narrow_tile.hpp).  Transposed weights, whose lanes load 16 bytes as it
 // is, and several row tiles above one another (4 jobs x 64 rows, 2048 -> 512: 7.6 us, through LDS 7.9; 16 jobs x 33 rows,
 // 128 -> 512 4.0 / 4.4) keep registers.  A wavefront's k-step is only CPL / 8 of 8 KB there: deep layers keep DEEP of them
-// in flight instead of two.
+// in flight instead of two (DEEP is 0 where there are no such registers).
 constexpr uint32_t kNarrowDeepK = 2048;
 template <int MT, bool TW, int CPL, int DEEP, bool NT = true>
 __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(GroupArgs a)

@@ -131,13 +131,12 @@ struct DenseWalk {
     }
 };
 
-// The workgroups are resident (one per compute unit, two of the 128 x 128 tile): workgroup b runs tiles b, b + grid, ...
-// Bound, deep layers: the power limit.  16 jobs x 4096 rows, 4096 -> 1024: 489 us (1.12 PFLOP/s; 529 us with operands staged
-// through registers and transposed on the way into LDS); 64 jobs: matrix pipes busy 64 % of the cycles at the 1.8 GHz that the
+// The workgroups are resident (one per compute unit, two of the 128 x 128 tile and of <128, 256, 1, 4>): workgroup b runs tiles b, b + grid, ...
+// Bound, deep layers: the power limit.  16 jobs x 4096 rows, 4096 -> 1024: 480 us (1.14 PFLOP/s; 529 us with operands staged
+// through registers and transposed on the way into LDS); 64 jobs: matrix pipes busy 65 % of the cycles at the 1.76 GHz that the
 // chip then holds, no bank conflicts.  Layers of 16 slabs: the epilogue, which the one workgroup of a compute unit does with
-// all its wavefronts at once, 128 outputs per lane (pipes 42 % at 1.95 GHz).  1024 -> 4096 -> 1024 -> 1024 with GELU, 16 jobs x
-// 4096 rows: 1270 - 1290 us (1421).
-// <128, 256, 1, 4>: the tile of two workgroups per compute unit.
+// all its wavefronts at once, 128 outputs per lane (pipes 42 - 48 % at 1.9 GHz); under two workgroups per compute unit one multiplies
+// meanwhile (32 jobs x 300 - 1000 rows, 1024 -> 4096: 46 % at 1.92 GHz).  1024 -> 4096 -> 1024 -> 1024 with GELU, 16 jobs x 4096 rows: 1180 - 1187 us (1421).
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled(GroupArgs a)
 {

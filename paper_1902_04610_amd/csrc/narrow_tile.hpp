@@ -11,8 +11,8 @@
 namespace salus {
 
 // What a launch of few workgroups lasts is how long one compute unit fetches one tile, and what bounds that is not bytes but
-// vector memory instructions: about 7 clocks for one whose lanes load 4 bytes each (a narrow tile's row of weights
-// gives them no more, if a lane is to hold a column), 16 for one of 16 bytes, four times as much.  So weights travel in
+// vector memory instructions: a lane that is to hold a column of a narrow tile loads 4 bytes of each row and no more, a quarter
+// of what the instruction can fetch.  So weights travel in
 // the order in which they lie in memory, a kilobyte an instruction, into an LDS ring that each wavefront has to itself (no
 // barrier in the loop), and ds_read_b64_tr_b16 hands each lane its column.  One job, one row,
 // 1024 -> 4096 -> 1024 -> 1024: 15.7 us, 24.0 with loads into registers; 2048 -> 1024 4.0 / 9.2; 3 jobs x 32 rows, 4096 -> 1024 14.8 / 22.
