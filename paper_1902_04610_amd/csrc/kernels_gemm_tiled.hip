@@ -146,6 +146,20 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled(Grou
     T::run(walk, smem);
 }
 
+// Two 128 x 256 tiles per compute unit for weights that come from HBM and that one row tile uses (jobs of up to 128 rows): bound by
+// HBM, and asked for non-temporally they displace neither activations nor each other in L2.  64 jobs x 33 - 128 rows,
+// 4096 -> 1024: 90 us (5.4 -> 6.0 TB/s of weights; 105 with plain requests), 1024 -> 4096 107 (115), the three layers of 1024 - 4096 -
+// 1024 - 1024 246 (257); 39 jobs x 91 - 128 rows, 1288 -> 3576, rows of weights that begin inside a line, 99 (114).  Weights that the
+// memory-side cache holds lose by it: 30 jobs x 65 - 128 rows, 1248 -> 2288: 45 plain, 58.
+template <int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled_once(GroupArgs a)
+{
+    using T = TilePair<BM, BN, WM, WN, true>;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
+    const DenseWalk<BM, BN, false> walk(a);
+    T::run(walk, smem);
+}
+
 template <int BM, int BN, int WM, int WN, int KS, bool TW, int D>
 __global__ __launch_bounds__(64 * WM * WN * KS, WM * WN * KS / 2) void grouped_dense_bf16_stream(GroupArgs a)
 {
@@ -296,7 +310,8 @@ hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStre
 // one round of 256 x 256 tiles, which ask for every weight once per 256 rows, less than what the others need more rounds for: 5 jobs x
 // 500 rows, 1280 -> 3968, 256 x 256 / 128 x 128 37.8 / 37.0 us from the cache, 38.3 / 47.6 from HBM; 18 jobs x 256 - 1024, 1024 -> 896, 30.4 / 29.1 and
 // 32.9 / 38.6.  7 % off its time then (any figure from there to 20 % gives the same choices but one): over 207 launches of 65 - 1024 rows with weights from
-// HBM the choice is 1.4 % off the best kind, 2.0 % without.  What the rule is
+// HBM the choice is 1.4 % off the best kind, 2.0 % without; and 7 % off that of two 128 x 256 tiles that ask for weights
+// non-temporally (grouped_dense_bf16_tiled_once, 3 - 12 % less than with plain requests).  What the rule is
 // for: 4 jobs x 500 rows, 2048 -> 2048, 256 x 256 / 128 x 256 / 128 x 128 / two 128 x 256: 48 / 30 / 25 / 33 us; 32 jobs x
 // 300 - 1000 rows, 4096 -> 1024 207 / 200 / 222 / 195, 1024 -> 1024 70 / 69 / 61 / 55; 32 jobs x 500 rows, 1024 -> 4096 167 /
 // 190 / 222 / 181.
@@ -319,7 +334,14 @@ static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n, bool 
     uint64_t tenths = tiles / grid * 10;       // of a round
     if (last) tenths += t.per_cu == 1 || last > cus ? 10 : &t == &kTilePair && weight_bound && last * 4 > cus * 3 ? 5 : 6;
     const uint64_t ns = tenths * (work / tiles) / 10;
-    return &t == &kTile256 && !cached && tiles <= cus ? ns * 93 / 100 : ns;
+    const bool less = &t == &kTile256 ? tiles <= cus : &t == &kTilePair && weight_bound;
+    return !cached && less ? ns * 93 / 100 : ns;
+}
+
+// What the launch of two 128 x 256 tiles per compute unit asks for non-temporally.
+static bool weights_once(const Problem *p, uint32_t n, bool cached)
+{
+    return !cached && std::all_of(p, p + n, [](const Problem &q) { return q.M <= 128; });
 }
 
 // Launches bound by the weight stream.  64 x 128 tiles, two workgroups per compute unit; 64 x 64, twice the workgroups,
@@ -391,7 +413,8 @@ hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, bool cached, 
         const uint32_t count = (uint32_t)group->size();
         const TileKind *kind = group == &big ? tall.kind : low.kind;
         const hipError_t e = kind == &kTile256       ? launch_tiled<256, 256, 1>(grouped_dense_bf16_tiled<256, 256, 2, 4>, 512, q, count, stream, launches)
-                             : kind == &kTilePair    ? launch_tiled<128, 256, 2>(grouped_dense_bf16_tiled<128, 256, 1, 4>, 256, q, count, stream, launches)
+                             : kind == &kTilePair    ? launch_tiled<128, 256, 2>(weights_once(q, count, cached) ? grouped_dense_bf16_tiled_once<128, 256, 1, 4> : grouped_dense_bf16_tiled<128, 256, 1, 4>,
+                                                                                 256, q, count, stream, launches)
                              : kind == &kTile128x256 ? launch_tiled<128, 256, 1>(grouped_dense_bf16_tiled<128, 256, 2, 4>, 512, q, count, stream, launches)
                                                      : launch_tiled<128, 128, 2>(grouped_dense_bf16_tiled<128, 128, 2, 2>, 256, q, count, stream, launches);
         if (e != hipSuccess) return e;

@@ -62,12 +62,15 @@ __device__ inline int fresh_lane()
 constexpr uint32_t kOutside = 0x80000000u;
 // m0 (the LDS address) is reserved: the compiler sets it where it needs it and keeps nothing there, but it may take two
 // equal settings for one unless it knows that the register changes in between.  It warns about any reserved register.
+// ONCE: non-temporal, for what no other workgroup will ask for.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
+template <bool ONCE = false>
 __device__ inline void dma16(uint32_t to, uint64_t base, uint32_t off)
 {
     const u32x4 buffer = {(uint32_t)base, (uint32_t)(base >> 32) & 0xffffu, kOutside, 0x00027000u};
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(buffer) : "m0", "memory");
+    if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(to), "v"(off), "s"(buffer) : "m0", "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(buffer) : "m0", "memory");
 }
 #pragma clang diagnostic pop
 
@@ -93,8 +96,8 @@ __device__ inline uint32_t tr_swizzle(uint32_t row) { return B >= 128 ? 4u * (ro
 // One operand's request stream: where it is in the walk and what this wavefront's share of it is, I instructions of
 // 1 KB per slab.  Requests are issued in k-steps 3, 0, 1, 2 (major: a slab, three slabs ahead) or 1, 2 and 3, 0 (tr: the
 // first and the second half of a slab, two slabs ahead) of the slab being multiplied.
-// UNIT: k-values of a stage (a major operand's is a whole slab, the 128 bytes of a line).
-template <int B, bool TR, int WAVES, int STAGES = TR ? 2 : 3, uint32_t UNIT = kSlab>
+// UNIT: k-values of a stage (a major operand's is a whole slab, the 128 bytes of a line).  ONCE: requests are non-temporal.
+template <int B, bool TR, int WAVES, int STAGES = TR ? 2 : 3, uint32_t UNIT = kSlab, bool ONCE = false>
 struct OperandStream {
     static constexpr int kBytes = B * (int)UNIT * 2, I = kBytes / 1024 / WAVES;
     static constexpr int kStages = STAGES, kRing = kStages * kBytes;
@@ -158,7 +161,7 @@ struct OperandStream {
         const uint32_t pc = piece(wave, i);
         const int left = (int)(depth - k) - (TR ? (int)(kRowsPer * pc) : 0);          // k-rows or k-values from here on
         const int mine = TR ? lane_k : (int)((uint32_t)lane_k ^ (32u * (pc & 1u)));
-        dma16(lds + at + pc * 1024u, base, mine < left ? off[i] : kOutside);
+        dma16<ONCE>(lds + at + pc * 1024u, base, mine < left ? off[i] : kOutside);
     }
     // the requests that belong to k-step q
     __device__ void request(int q, uint32_t lds, int wave) const
@@ -394,12 +397,13 @@ struct TileMfma {
 // slab two barriers, before k-steps 1 and 3.  After the first, the slab's first half of N has been read and its stage is
 // requested into (second half of the next slab); after the other, its second half and the M slab (first half and M slab two
 // ahead).  Requests have the three k-steps to the barrier that needs them.
-template <int BM, int BN, int WM, int WN>
+// ONCE: the N side is requested non-temporally (weights that one row tile uses and that come from HBM).
+template <int BM, int BN, int WM, int WN, bool ONCE = false>
 struct TilePair {
     static constexpr int kWavesT = WM * WN, kThreads = 64 * kWavesT;
     static constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
     using SM = OperandStream<BM, false, kWavesT, 2>;
-    using SN = OperandStream<BN, true, kWavesT, 3, kSlab / 2>;
+    using SN = OperandStream<BN, true, kWavesT, 3, kSlab / 2, ONCE>;
     static constexpr uint32_t kLds = SM::kRing + SN::kRing;
     static_assert(kLds <= 80 * 1024, "half the LDS of a compute unit");
     typedef f32x16 Acc[FN][FM];

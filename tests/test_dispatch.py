@@ -310,3 +310,13 @@ def test_parity_tests_of_small_tiles_launch_what_they_are_named_after(record):
     check(record, [(dict(do="forward", rows=[j["M"] for j in specs], dims=[j["dims"] for j in specs], dtype="bf16",
                          strip=[j["strip"] for j in specs], idle=[], evicted=False), ["grouped_dense_bf16_" + k for k in names])
                    for specs, names in cases])
+
+
+def test_weights_of_up_to_128_rows_from_further_away_are_asked_for_once(record):
+    far, once, plain = dict(idle=[240 << 20]), "_once<128, 256, 1, 4>", "<128, 256, 1, 4>"
+    check(record, [(case(rows, K, N, **kw), ["grouped_dense_bf16_tiled" + kernel]) for rows, K, N, kw, kernel in (
+        ([100] * 64, 1024, 1024, {}, plain), ([100] * 64, 1024, 1024, far, once), ([128] * 64, 1024, 1024, far, once),
+        ([1000] * 29, 512, 768, far, plain),
+    )])
+    from test_gpu_once_and_few import ONCE
+    check(record, [(dict(case([M] * min(jobs, 64), K, N, strip=strip, **far)), ["grouped_dense_bf16_tiled" + once]) for jobs, M, K, N, strip in ONCE])
