@@ -199,14 +199,19 @@ hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, hipStream_t str
 // the kernel is bound by the read-modify-write of the float master weights
 // (4 B read, 4 B + 2 B written per weight).
 //
-// One wavefront owns a 64 (k) x 64 (n) block of W; a workgroup is four such
-// blocks side by side.  Lane (c, g) loads the 8 x 4 blocks H[m0+8g ..][k0+4c ..]
-// and G[m0+8g ..][n0+4c ..] (8-byte loads), transposes them in registers into
-// four A and four B operands of v_mfma_f32_16x16x32_bf16; MFMA (i, j) yields
-// rows k0 + 4*rho + i, columns n0 + 4*c + j.  A lane ends up with 16 rows x 4
+// One wavefront owns a 32 (k) x 64 (n) block of W; a workgroup is four such
+// blocks side by side.  Lane (c, g) loads the 8 x 2 blocks H[m0+8g ..][k0+2c ..]
+// and 8 x 4 blocks G[m0+8g ..][n0+4c ..] (4- and 8-byte loads), transposes them in registers into
+// two A and four B operands of v_mfma_f32_16x16x32_bf16; MFMA (i, j) yields
+// rows k0 + 2*rho + i, columns n0 + 4*c + j.  A lane ends up with 8 rows x 4
 // consecutive columns, so master weights move as 16-byte vectors, 256
-// contiguous bytes per row across the 16 lanes.  The master-weight loads are
-// issued before the MFMA phase and complete underneath it.
+// contiguous bytes per row across the 16 lanes.
+// What a block waits for is requested at once, up to 128 rows of H and G and behind them its master weights, which arrive under
+// the multiplies: a block that asked for 32 rows at a time waited for HBM's queue with each of them.  The registers that
+// takes leave two workgroups per compute unit, which is no loss (three, with 64 rows at once, are slower).  Tiles of a row of
+// blocks are neighbours, so that what is under way at a time is whole rows of W.
+// 8 jobs x 64 rows, 2048 - 2048 - 2048 - 2048 - 1000 (1.17 GB): 191 us, in blocks of 64 x 64, 32 rows at a time and columns of blocks first,
+// 205; 8 rows 178 / 192.  The weights' traffic alone, in this order and without H and G, 182.
 // ---------------------------------------------------------------------------
 struct UpdateArgs {
     uint32_t n;
@@ -215,76 +220,100 @@ struct UpdateArgs {
     UpdateProblem p[kMaxProblems];
 };
 
-constexpr int kUpdK = 64, kUpdN = 256;      // workgroup tile
+constexpr int kUpdK = 32, kUpdN = 256;      // workgroup tile
+constexpr int kUpdSteps = 4;                // steps of 32 rows that are requested at once
 constexpr double kDwTiledRows = 192;
 constexpr int kDwTile = 128;                // tile of the many-row kernel
 
-// Tile t of one job's update.
-__device__ inline void dw_sgd_tile(const UpdateProblem &p, uint32_t t)
+__global__ __launch_bounds__(256, 2) void grouped_dw_sgd(UpdateArgs a)
 {
+    UpdateProblem p;
+    const uint32_t t = find_owner(a.first, a.p, blockIdx.x, p);
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t M = p.M, K = p.K, N = p.N, kt = (K + kUpdK - 1) / kUpdK;
-    const uint32_t k0 = (t % kt) * kUpdK;                  // neighbours share the G columns
-    const uint32_t n0 = (t / kt) * kUpdN + 64 * wave;
-    const uint32_t ncol = n0 + 4 * c;
+    const uint32_t M = p.M, K = p.K, N = p.N, nt = (N + kUpdN - 1) / kUpdN;
+    const uint32_t k0 = (t / nt) * kUpdK, n0 = (t % nt) * kUpdN + 64 * wave;
+    const uint32_t ncol = n0 + 4 * c, kcol = k0 + 2 * c;
     const bool col_ok = ncol < N;
-    const Global<uint16_t> *H = (const Global<uint16_t> *)p.H;
-    const Global<uint16_t> *G = (const Global<uint16_t> *)p.G;
+    // rows and columns outside the matrices: a valid address, and what comes of it is not stored
+    const Global<uint16_t> *H = (const Global<uint16_t> *)p.H + (kcol < K ? kcol : 0);
+    const Global<uint16_t> *G = (const Global<uint16_t> *)p.G + (col_ok ? ncol : 0);
     Global<float> *Wm = (Global<float> *)p.Wm;
     Global<uint16_t> *Wb = (Global<uint16_t> *)p.Wb;
 
-    // master weights of this lane: rows k0 + 16g + 4r + i, columns ncol .. ncol+3
-    f32x4 wm[16];
+    f32x4 acc[8];      // acc[i * 4 + j][r]
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t krow = k0 + 16 * g + 4 * r + i;
-            wm[r * 4 + i] = (krow < K && col_ok)
-                                ? __builtin_nontemporal_load((const Global<f32x4> *)(Wm + (size_t)krow * N + ncol))
-                                : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-
-    f32x4 acc[16];      // acc[i * 4 + j][r]
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint32_t kcol = k0 + 4 * c;
-    const bool kcol_ok = kcol < K;
-    for (uint32_t m0 = 0; m0 < M; m0 += 32) {
-        u32x2 h[8], d[8];
+    for (int i = 0; i < 8; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    uint32_t h[kUpdSteps][8];
+    u32x2 d[kUpdSteps][8];
+    auto load = [&](int s, uint32_t m0) {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
-            const uint32_t m = m0 + 8 * g + r;
-            h[r] = (m < M && kcol_ok) ? *(const Global<u32x2> *)(H + (size_t)m * K + kcol) : u32x2{0u, 0u};
-            d[r] = (m < M && col_ok) ? *(const Global<u32x2> *)(G + (size_t)m * N + ncol) : u32x2{0u, 0u};
+            const size_t m = min(m0 + 8 * g + r, M - 1);
+            h[s][r] = *(const Global<uint32_t> *)(H + m * K);
+            d[s][r] = *(const Global<u32x2> *)(G + m * N);
         }
-        u32x4 A[4], B[4];
+    };
+    auto multiply = [&](int s, uint32_t m0) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (m0 + 8 * g + r >= M) {
+                h[s][r] = 0u;
+                d[s][r] = u32x2{0u, 0u};
+            }
+        u32x4 A[2], B[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-                A[i][j] = __builtin_amdgcn_perm(h[2 * j + 1][i >> 1], h[2 * j][i >> 1], sel);
-                B[i][j] = __builtin_amdgcn_perm(d[2 * j + 1][i >> 1], d[2 * j][i >> 1], sel);
+                if (i < 2) A[i][j] = __builtin_amdgcn_perm(h[s][2 * j + 1], h[s][2 * j], sel);
+                B[i][j] = __builtin_amdgcn_perm(d[s][2 * j + 1][i >> 1], d[s][2 * j][i >> 1], sel);
             }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 acc[i * 4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                     __builtin_bit_cast(bf16x8, A[i]), __builtin_bit_cast(bf16x8, B[j]), acc[i * 4 + j],
                     0, 0, 0);
+    };
+#pragma unroll
+    for (int s = 0; s < kUpdSteps; ++s)
+        if (32u * s < M) load(s, 32u * s);
+    __builtin_amdgcn_sched_barrier(0);
+    // master weights of this lane: rows k0 + 8g + 2r + i, columns ncol .. ncol+3
+    f32x4 wm[8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t krow = k0 + 8 * g + 2 * r + i;
+            wm[r * 2 + i] = (krow < K && col_ok)
+                                ? __builtin_nontemporal_load((const Global<f32x4> *)(Wm + (size_t)krow * N + ncol))
+                                : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < kUpdSteps; ++s)
+        if (32u * s < M) multiply(s, 32u * s);
+    for (uint32_t m0 = 32 * kUpdSteps; m0 < M; m0 += 32 * kUpdSteps) {
+#pragma unroll
+        for (int s = 0; s < kUpdSteps; ++s)
+            if (m0 + 32u * s < M) load(s, m0 + 32u * s);
+#pragma unroll
+        for (int s = 0; s < kUpdSteps; ++s)
+            if (m0 + 32u * s < M) multiply(s, m0 + 32u * s);
     }
 
     const float lr = p.lr;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t krow = k0 + 16 * g + 4 * r + i;
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t krow = k0 + 8 * g + 2 * r + i;
             if (krow >= K || !col_ok) continue;
-            f32x4 w = wm[r * 4 + i];
+            f32x4 w = wm[r * 2 + i];
 #pragma unroll
             for (int j = 0; j < 4; ++j)      // one rounded multiply, one rounded subtract
                 w[j] = __fsub_rn(w[j], __fmul_rn(lr, acc[i * 4 + j][r]));
@@ -294,13 +323,6 @@ __device__ inline void dw_sgd_tile(const UpdateProblem &p, uint32_t t)
             b[1] = bf16_pack(w[2], w[3]);
             *(Global<u32x2> *)(Wb + (size_t)krow * N + ncol) = b;
         }
-}
-
-__global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
-{
-    UpdateProblem p;
-    const uint32_t t = find_owner(a.first, a.p, blockIdx.x, p);
-    dw_sgd_tile(p, t);
 }
 
 // Many rows per job (the contraction is long): the product goes through the LDS tiles of tile_mfma.hpp, both operands
