@@ -14,9 +14,10 @@ namespace salus {
 template <int ACT, bool BF16, bool PAST_L2, int FN, int FM, typename Landed>
 __device__ inline void store_dense(const Problem &p, uint32_t m, uint32_t n, const f32x16 (&acc)[FN][FM], int lane, Landed landed)
 {
-    constexpr int J = BF16 ? 2 : 1;              // blocks of a line
+    constexpr int J = BF16 && FN % 2 == 0 ? 2 : 1;       // blocks that are stored together
+    constexpr int kStores = BF16 ? 2 * J : 4, kRows = 32 / kStores;      // store instructions of them, rows of each
     const uint32_t N = p.N, esz = BF16 ? 2 : 4, pitch = N * esz;
-    const uint32_t column = BF16 ? line_column_bf16(lane) : line_column_f32(lane);
+    const uint32_t column = !BF16 ? line_column_f32(lane) : J == 2 ? line_column_bf16(lane) : half_line_column_bf16(lane);
     char *Y = (char *)p.Y + ((uint64_t)m * N + n) * esz;
     const char *aux = (const char *)p.aux + ((uint64_t)m * N + n) * 2;
     const bool mask = BF16 && (p.flags & kMaskPositive);
@@ -37,42 +38,34 @@ __device__ inline void store_dense(const Problem &p, uint32_t m, uint32_t n, con
             __builtin_amdgcn_sched_barrier(0);
             if (i == 0 && j == 0) landed();
             const uint32_t c = 32u * j + column;
-            if constexpr (BF16) {
-                u32x4 o[2][2];
-                to_lines_bf16(v, o);
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int b = 0; b < 2; ++b) {
-                        const uint32_t r_at = 32u * i + 16u * a + 8u * b + (lane & 7);
-                        if (!(r_at < rows && c < cols)) continue;
-                        const uint32_t at = r_at * pitch + c * 2u;
-                        u32x4 w = o[a][b];
-                        if (mask) {
-                            // ReLU derivative taken from the stored bf16 activation (sign bit clear, not zero)
-                            const u32x4 h = *(const u32x4 *)(aux + at);
-#pragma unroll
-                            for (int d = 0; d < 4; ++d) {
-                                const uint32_t lo = h[d] & 0xffffu, hi = h[d] >> 16;
-                                if ((lo & 0x8000u) || !lo) w[d] &= 0xffff0000u;
-                                if ((hi & 0x8000u) || !hi) w[d] &= 0x0000ffffu;
-                            }
-                        }
-                        *(u32x4 *)(Y + at) = w;
-                    }
+            u32x4 o[kStores];
+            if constexpr (BF16 && J == 1) {
+                to_half_lines_bf16(v[0], o);
             } else {
-                f32x4 o[2][2];
-                to_lines_f32(v[0], o);
+                std::conditional_t<BF16, u32x4, f32x4> lines[2][2];
+                if constexpr (BF16) to_lines_bf16(v, lines);
+                else to_lines_f32(v[0], lines);
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
+                for (int q = 0; q < 4; ++q) o[q] = __builtin_bit_cast(u32x4, lines[q >> 1][q & 1]);
+            }
 #pragma unroll
-                    for (int b = 0; b < 2; ++b) {
-                        const uint32_t r_at = 32u * i + 16u * a + 8u * b + (lane & 7);
-                        if (!(r_at < rows && c < cols)) continue;
-                        f32x4 *y = (f32x4 *)(Y + (r_at * pitch + c * 4u));
-                        if constexpr (PAST_L2) __builtin_nontemporal_store(o[a][b], y);
-                        else *y = o[a][b];
+            for (int q = 0; q < kStores; ++q) {
+                const uint32_t r_at = 32u * i + kRows * q + (lane & (kRows - 1));
+                if (!(r_at < rows && c < cols)) continue;
+                const uint32_t at = r_at * pitch + c * esz;
+                u32x4 w = o[q];
+                if (mask) {
+                    // ReLU derivative taken from the stored bf16 activation (sign bit clear, not zero)
+                    const u32x4 h = *(const u32x4 *)(aux + at);
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const uint32_t lo = h[d] & 0xffffu, hi = h[d] >> 16;
+                        if ((lo & 0x8000u) || !lo) w[d] &= 0xffff0000u;
+                        if ((hi & 0x8000u) || !hi) w[d] &= 0x0000ffffu;
                     }
+                }
+                if constexpr (PAST_L2) __builtin_nontemporal_store(w, (u32x4 *)(Y + at));
+                else *(u32x4 *)(Y + at) = w;
             }
         }
     }
@@ -160,10 +153,13 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled_once
     T::run(walk, smem);
 }
 
-template <int BM, int BN, int WM, int WN, int KS, bool TW, int D>
-__global__ __launch_bounds__(64 * WM * WN * KS, WM * WN * KS / 2) void grouped_dense_bf16_stream(GroupArgs a)
+// WN x NS wavefronts share the columns.  Every wavefront of a 64 x 64 tile multiplies a 32 x 32 block through all of K:
+// launches with at most one such tile per compute unit take 1.2 us less than with two wavefronts beside each other, the k-steps of a slab shared by
+// two such groups and their sums added through LDS (10 jobs x 68 rows, 144 -> 656, 4.5 / 5.7 us; 5 jobs x 60 rows, 2664 -> 2912, 15.9 / 17.0).
+template <int BM, int BN, int WM, int WN, int NS, bool TW, int D>
+__global__ __launch_bounds__(64 * WM * WN * NS, WM * WN * NS / 2) void grouped_dense_bf16_stream(GroupArgs a)
 {
-    using T = TileStream<BM, BN, WM, WN, KS, !TW, D>;
+    using T = TileStream<BM, BN, WM, WN * NS, !TW, D>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
     const DenseWalk<BM, BN, TW> walk(a);
     T::run(walk, smem);
@@ -347,10 +343,9 @@ static bool weights_once(const Problem *p, uint32_t n, bool cached)
 // Launches bound by the weight stream.  64 x 128 tiles, two workgroups per compute unit; 64 x 64, twice the workgroups,
 // while there is at most one of them per compute unit (transposed weights: while 64 x 128 would be fewer than one).  64 x
 // 128 / 64 x 64: 12 jobs x 64 rows, 2048 -> 1536 26 / 33 us, 20 jobs x 33 - 128 rows, 4096 -> 1024 47 / 56, 16 jobs x 33 -
-// 100 rows, 1536 -> 768 19 / 21, 8 jobs x 64 rows, 2048 -> 2048 with weights from memory 27 / 22.5.  The same launched over and over (weights
-// in L2): 15.4 us (registers-only kernel with K split over four wavefronts: 20.6; this tile without the split of the k-steps 17.5, with 64 x 128 tiles 19), input
-// gradients of the same layer 17 against 24; 8 jobs x 100 rows: 64 x 128 tiles, training step 386 us against 410 with 64
-// x 64.  Rings twice as deep with one workgroup per compute unit: 18.6.
+// 100 rows, 1536 -> 768 19 / 21, 8 jobs x 64 rows, 2048 -> 2048 with weights from memory 27 / 22.5; 8 jobs x 100 rows: 64 x 128 tiles, training
+// step 386 us against 410 with 64 x 64 (all of these with the k-steps of a 64 x 64 tile shared by two groups of wavefronts).  Rings of six and eight
+// slabs for one 64 x 64 tile per compute unit: step of 8 jobs x 64 rows 313 and 317 us, with four 301.
 hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream, uint64_t *launches)
 {
     uint64_t wide = 0, narrow = 0;

@@ -207,11 +207,6 @@ struct Fragments {
             for (uint32_t ks = 0; ks < 4; ++ks) at[ks] = r * 128u + (((2u * ks + (lane >> 5)) ^ ((r >> 1) & 7u)) << 4);
         }
     }
-    __device__ void skip(uint32_t ks)        // k-steps are counted from here on (ks 0 or 2)
-    {
-#pragma unroll
-        for (uint32_t &v : at) v = TR ? v + ks * 16u * (B * 2u) : v ^ (ks << 5);
-    }
     __device__ bf16x8 read(const unsigned char *base, int ks, int block) const
     {
         if (TR) {
@@ -546,15 +541,14 @@ struct TilePair {
 // The same tiles for launches that are bound by the weight stream (few rows per job): what counts is bytes in flight per
 // compute unit, so LDS is one ring of D whole slabs per operand, D - 1 of them on their way, and the walk across
 // tiles keeps it full through the epilogues.  One barrier per slab: after it slab s has landed for everyone
-// and everyone has left the stage of slab s - 1, which is requested into at once.  KS groups of wavefronts share the
-// k-steps of a slab (and the last one the sums, through LDS): with few tiles a slab's reads and multiplies are a chain.
-template <int BM, int BN, int WM, int WN, int KS, bool TRN, int D>
+// and everyone has left the stage of slab s - 1, which is requested into at once.
+template <int BM, int BN, int WM, int WN, bool TRN, int D>
 struct TileStream {
-    static constexpr int kWavesT = WM * WN * KS, kThreads = 64 * kWavesT;
+    static constexpr int kWavesT = WM * WN, kThreads = 64 * kWavesT;
     static constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
     using SM = OperandStream<BM, false, kWavesT, D>;
     using SN = OperandStream<BN, TRN, kWavesT, D>;
-    static constexpr uint32_t kRings = SM::kRing + SN::kRing, kLds = kRings + (KS - 1) * BM * BN * 4;
+    static constexpr uint32_t kLds = SM::kRing + SN::kRing;
     static constexpr int kBehind = (D - 2) * (SM::I + SN::I);
     static_assert(kLds <= 160 * 1024 && kBehind <= 63, "LDS of a compute unit, largest count of s_waitcnt");
     typedef f32x16 Acc[FN][FM];
@@ -564,14 +558,12 @@ struct TileStream {
     {
         const int lane = threadIdx.x & 63;
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const uint32_t kg = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+        const uint32_t wm = wave / WN, wn = wave % WN;
         const uint32_t lds_m = lds_address(smem), lds_n = lds_m + SM::kRing;
         Fragments<BM, false, FM> fm;
         Fragments<BN, TRN, FN> fn;
         fm.init(wm * (32u * FM), lane);
         fn.init(wn * (32u * FN), lane);
-        fm.skip(kg * (4 / KS));
-        fn.skip(kg * (4 / KS));
         const uint32_t tiles = walk.tiles();
         uint32_t id = blockIdx.x, cur_id = id;
         typename Walk::Place ahead = walk.place(id), cur = ahead;
@@ -622,9 +614,9 @@ struct TileStream {
             do {
                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kBehind) : "memory");
                 const unsigned char *base_m = smem + stage * SM::kBytes, *base_n = smem + SM::kRing + stage * SN::kBytes;
-                bf16x8 a[4 / KS][FN], b[4 / KS][FM];
+                bf16x8 a[4][FN], b[4][FM];
 #pragma unroll
-                for (int ks = 0; ks < 4 / KS; ++ks) {
+                for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
                     for (int i = 0; i < FM; ++i) b[ks][i] = fm.read(base_m, ks, i);
 #pragma unroll
@@ -635,7 +627,6 @@ struct TileStream {
                 for (int ks = 0; ks < 4; ++ks) {
                     request(ks);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (ks >= 4 / KS) continue;
 #pragma unroll
                     for (int j = 0; j < FN; ++j)
 #pragma unroll
@@ -645,30 +636,7 @@ struct TileStream {
                 }
                 stage = stage + 1 == (uint32_t)D ? 0u : stage + 1;
             } while (--left != 0);
-            if (KS > 1) {
-                // the first group of wavefronts collects the others' sums, in order
-                float *sums = (float *)(smem + kRings) + (size_t)(wave % (WM * WN)) * FM * FN * 16 * 64 + lane;
-                constexpr size_t kGroup = (size_t)BM * BN;
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int i = 0; i < FM; ++i)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            if (kg) sums[(kg - 1) * kGroup + ((j * FM + i) * 16 + r) * 64] = acc[j][i][r];
-                // clobbers memory, so that neither the stores above nor the loads below cross it
-                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-#pragma unroll
-                for (int g = 1; g < KS; ++g)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-#pragma unroll
-                        for (int i = 0; i < FM; ++i)
-#pragma unroll
-                            for (int r = 0; r < 16; ++r)
-                                if (!kg) acc[j][i][r] += sums[(g - 1) * kGroup + ((j * FM + i) * 16 + r) * 64];
-            }
-            if (kg == 0) walk.finish(cur, acc, typename Walk::Held{}, wm * (32u * FM), wn * (32u * FN), fresh_lane(), []() {});
+            walk.finish(cur, acc, typename Walk::Held{}, wm * (32u * FM), wn * (32u * FN), fresh_lane(), []() {});
             cur_id += gridDim.x;
             if (cur_id >= tiles) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may arrive in LDS after this workgroup
@@ -734,6 +702,26 @@ __device__ inline void to_lines_bf16(const float (&v)[2][16], u32x4 (&out)[2][2]
         for (int b = 0; b < 2; ++b) out[a][b] = u32x4{p[b][2 * a][0], p[b][2 * a][1], p[b][2 * a + 1][0], p[b][2 * a + 1][1]};
 }
 __device__ inline uint32_t line_column_bf16(int lane) { return 32u * ((lane >> 3) & 1u) + 16u * ((lane >> 4) & 1u) + 8u * (lane >> 5); }
+
+// One 32 x 32 block as bf16, half lines: out[a] is row 16 a + l % 16, columns half_line_column_bf16(l) .. + 7.
+__device__ inline void to_half_lines_bf16(const float (&v)[16], u32x4 (&out)[2])
+{
+    uint32_t p[4][2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int d = 0; d < 2; ++d) p[q][d] = bf16_pack(v[4 * q + 2 * d], v[4 * q + 2 * d + 1]);
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        swap_halves(p[0][d], p[1][d]);           // as the first two exchanges of to_lines_bf16
+        swap_halves(p[2][d], p[3][d]);
+        swap_rows(p[0][d], p[2][d]);
+        swap_rows(p[1][d], p[3][d]);
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a) out[a] = u32x4{p[2 * a][0], p[2 * a][1], p[2 * a + 1][0], p[2 * a + 1][1]};
+}
+__device__ inline uint32_t half_line_column_bf16(int lane) { return 16u * ((lane >> 4) & 1u) + 8u * (lane >> 5); }
 
 // One 32 x 32 block as float: out[a][b] is row 16 a + 8 b + l % 8, columns line_column_f32(l) .. + 3.
 __device__ inline void to_lines_f32(const float (&v)[16], f32x4 (&out)[2][2])

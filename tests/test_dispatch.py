@@ -320,3 +320,9 @@ def test_weights_of_up_to_128_rows_from_further_away_are_asked_for_once(record):
     )])
     from test_gpu_once_and_few import ONCE
     check(record, [(dict(case([M] * min(jobs, 64), K, N, strip=strip, **far)), ["grouped_dense_bf16_tiled" + once]) for jobs, M, K, N, strip in ONCE])
+
+
+def test_half_line_cases_take_64_by_64_tiles(record):
+    """The first layers of the GPU test of bf16 results in half lines."""
+    for jobs, K, N, M in ((24, 136, 520, 33), (20, 72, 536, 64), (12, 264, 1000, 65), (7, 200, 1064, 127)):
+        check(record, [(case([max(33, M - 5 * (i % 4)) for i in range(jobs)], K, N), ["grouped_dense_bf16_stream<64, 64, 2, 1, 2, false, 4>"])])
