@@ -195,6 +195,49 @@ static uint32_t even_columns(const Problem *p, uint32_t n, bool cached)
     return best;
 }
 
+static uint64_t count_tiles(const Problem *p, uint32_t n, uint32_t tm, uint32_t tn)
+{
+    uint64_t tiles = 0;
+    for (uint32_t i = 0; i < n; ++i) tiles += (uint64_t)((p[i].M + tm - 1) / tm) * ((p[i].N + tn - 1) / tn);
+    return tiles;
+}
+
+// Columns of 32-row register tiles, several above one another, of which there is at most one per compute unit: 32, 64 or 0.
+static uint32_t narrow_columns(const Problem *p, uint32_t n)
+{
+    return count_tiles(p, n, 32, 64) > kFullGrid ? 0 : count_tiles(p, n, 32, 32) <= kFullGrid ? 32 : 64;
+}
+
+static hipError_t launch_narrow_rows(const Problem *p, uint32_t n, uint32_t columns, hipStream_t stream, uint64_t *launches)
+{
+    auto launch = [&](int, const GroupArgs &a, uint32_t tiles) {
+        const dim3 grid(tiles), block(kGemmThreads);
+        if (columns == 32) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 8, false>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 4, 4, false>), grid, block, 0, stream, a);
+    };
+    return launch_groups(p, n, columns, 0, 0, launch, launches, 2);
+}
+
+// Jobs of 128 rows and more whose large tiles would leave most compute units idle, in layers deeper than five slabs: the smallest tile of which
+// there is at most one per compute unit, 32 x 32 and 32 x 64 through registers, 64 x 64 and 64 x 128 through the ring; and 64 x 128, two
+// per compute unit, where 128 x 128 tiles would be between one and two.  Before (128 x 128 or larger) / now: 1 job x 260 rows, 3200 -> 448, 28.3 / 10.1 us,
+// 1 job x 463 rows, 1024 -> 920, 12.4 / 6.8, 4 jobs x 129 rows, 1536 -> 1024, 16.8 / 9.6, 4 jobs x 429 rows, 1792 -> 1056, 19.8 /
+// 14.3, 6 jobs x 168 rows, 3392 -> 2944, 41.0 / 35.5.  Over 120 such launches, weights from the cache and from HBM, 0.57 of the time before on
+// average and 0.93 at most, within 3 % of the quickest of nine kinds of tiles in all but three.  Tiles beyond one per compute unit: 4 jobs x 619 rows,
+// 320 -> 576, 32 x 64 8.8 us, 64 x 64 6.1.  Shallower layers keep the large tiles that they are tested with (1 job x 256 rows, 320 -> 4096), and so do rounds that hold jobs of 128 rows among larger ones (a
+// launch for each tile height).
+static bool few_tiles(const Problem *p, uint32_t n)
+{
+    uint32_t of_128 = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        if (p[i].M < kTiledAlways || p[i].K < 384) return false;
+        of_128 += p[i].M == kTiledAlways;
+    }
+    if (of_128 != 0 && of_128 != n) return false;
+    const uint64_t tiles = count_tiles(p, n, 64, 128);
+    return tiles <= kFullGrid || (tiles <= 2 * kFullGrid && count_tiles(p, n, 128, 128) > kFullGrid);
+}
+
 hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool cached, hipStream_t stream,
                                uint64_t *launches)
 {
@@ -254,7 +297,12 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
         if (std::any_of(p, p + n, takes_tiled)) {
             std::vector<Problem> tiled, streamed;
             for (uint32_t i = 0; i < n; ++i) (takes_tiled(p[i]) ? tiled : streamed).push_back(p[i]);
-            hipError_t e = launch_grouped_bf16_tiled(tiled.data(), (uint32_t)tiled.size(), cached, stream, launches);
+            const uint32_t count = (uint32_t)tiled.size();
+            const bool few = few_tiles(tiled.data(), count);
+            const uint32_t columns = few ? narrow_columns(tiled.data(), count) : 0;
+            hipError_t e = columns ? launch_narrow_rows(tiled.data(), count, columns, stream, launches)
+                           : few   ? launch_grouped_bf16_stream(tiled.data(), count, false, stream, launches)
+                                   : launch_grouped_bf16_tiled(tiled.data(), count, cached, stream, launches);
             if (e != hipSuccess || streamed.empty()) return e;
             return launch_grouped_bf16(streamed.data(), (uint32_t)streamed.size(), false, cached, stream, launches);
         }
@@ -349,19 +397,8 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
         // (the 64 x 64 register tile that the ring replaced: 7.1), 4096 -> 1024 20.4 / 11.9 (16.5); 16 jobs x 33 rows,
         // 128 -> 512, 64 columns: 6.1 / 4.5 (5.7); 10 jobs x 33 rows, 1024 -> 512 9.0 / 7.3 (7.8); beyond one per compute unit,
         // 24 jobs x 65 rows, 1024 -> 512: 11.0 / 14.1.
-        uint64_t tiles_32 = 0, tiles_64 = 0;
-        for (const Problem &q : mid) {
-            tiles_32 += (uint64_t)((q.M + 31) / 32) * ((q.N + 31) / 32);
-            tiles_64 += (uint64_t)((q.M + 31) / 32) * ((q.N + 63) / 64);
-        }
-        if (tiles_64 <= kFullGrid) {
-            const bool narrowest = tiles_32 <= kFullGrid;
-            auto launch = [&](int, const GroupArgs &a, uint32_t tiles) {
-                const dim3 grid(tiles), block(kGemmThreads);
-                if (narrowest) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 8, false>), grid, block, 0, stream, a);
-                else hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 4, 4, false>), grid, block, 0, stream, a);
-            };
-            if (hipError_t e = launch_groups(mid.data(), (uint32_t)mid.size(), narrowest ? 32 : 64, 0, 0, launch, launches, 2)) return e;
+        if (const uint32_t columns = narrow_columns(mid.data(), (uint32_t)mid.size())) {
+            if (hipError_t e = launch_narrow_rows(mid.data(), (uint32_t)mid.size(), columns, stream, launches)) return e;
             mid.clear();
         }
     }

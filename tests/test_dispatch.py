@@ -326,3 +326,13 @@ def test_half_line_cases_take_64_by_64_tiles(record):
     """The first layers of the GPU test of bf16 results in half lines."""
     for jobs, K, N, M in ((24, 136, 520, 33), (20, 72, 536, 64), (12, 264, 1000, 65), (7, 200, 1064, 127)):
         check(record, [(case([max(33, M - 5 * (i % 4)) for i in range(jobs)], K, N), ["grouped_dense_bf16_stream<64, 64, 2, 1, 2, false, 4>"])])
+
+
+def test_jobs_of_128_rows_and_more_that_are_few(record):
+    """The smallest tile of which there is at most one per compute unit; 64 x 128, two per compute unit, where 128 x 128 tiles are more
+    than one; shallower layers, rounds with smaller jobs and more tiles as before."""
+    from test_gpu_few_tiles import FEW
+    check(record, [(case(rows, K, N, strip=strip), ["grouped_dense_bf16_" + kernel]) for rows, K, N, strip, kernel in FEW + [
+        ([256], 320, 4096, False, "tiled<128, 128, 2, 2>"), ([500] * 4, 2048, 2048, False, "tiled<128, 128, 2, 2>"),
+        ([200] * 24, 1024, 1024, False, "tiled<128, 256, 2, 4>"), ([128] * 33, 384, 1024, False, "tiled<128, 128, 2, 2>"),
+    ]])
