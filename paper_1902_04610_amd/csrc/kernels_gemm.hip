@@ -90,8 +90,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void grouped_dense_bf16_rows64(Gro
 }
 
 // Row tiles of 16 * MT rows; the last one of a job computes only as many 16-row blocks as it needs (the sums of a row do not
-// depend on how many there are).  A single block has little to multiply between its loads: four k-steps in flight instead of
-// two (12 jobs x 16 rows, 516 -> 1204: 7.9 / 8.6 us; six 8.5).
+// depend on how many there are).  A single block has little to multiply between its loads: three k-steps in flight instead of
+// two (12 jobs x 16 rows, 516 -> 1204, two / three / four / six: 8.6 / 6.0 / 6.3 / 6.6 us; 5 jobs x 16 rows, 900 -> 1500, three 7.7, four 8.1).
 template <int MT>
 __global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(GroupArgs a)
 {
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(GroupArgs a)
     Problem p;
     const Tile tile = find_tile<16 * MT, 64>(a, p);
     const uint32_t rows = p.M - tile.m0;
-    if (MT == 1 || rows <= 16) dense_f32_tile<1, 4>(p, tile, lds);
+    if (MT == 1 || rows <= 16) dense_f32_tile<1, 3>(p, tile, lds);
     else if (MT > 2 && rows <= 32) dense_f32_tile<2>(p, tile, lds);
     else dense_f32_tile<MT>(p, tile, lds);
 }
@@ -435,8 +435,10 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
             hipLaunchKernelGGL(grouped_dense_f32<4>, dim3(tiles), dim3(kGemmThreads), 0, stream, a);
     };
     // Float multiplies are what a 64-row tile takes long for (16 x 16 x 4 per instruction), so rows are spread over
-    // workgroups.  16-row tiles as long as two per compute unit hold them, except that jobs most of which have 17 .. 32 rows take one
-    // 32-row tile each, in layers deeper than 512, where compute units are left for all of them.  Else 64-row tiles while those leave compute units idle,
+    // workgroups.  16-row tiles as long as two per compute unit hold them, except that 32-row tiles take layers deeper than 256 of which there are more than one
+    // 16-row tile per compute unit and no more than one of those: two 16-row tiles on a compute unit read the weights twice (12 jobs x 1 - 77 rows, 1204 ->
+    // 780, 273 / 208 tiles: 17.3 / 13.8 us, with weights from HBM 24.0 / 18.1; 5 jobs x 86 rows, 1012 -> 936, 14.1 / 12.2 and 17.6 / 13.6; over 32 such
+    // layers 0.94 and 0.86 of the time; 4 jobs x 52 rows, 200 -> 976 5.1 / 5.2; more than one 32-row tile per compute unit: 8 jobs x 68 rows, 988 -> 760, 13.7 / 20.2).  Else 64-row tiles while those leave compute units idle,
     // or if they fill whole rounds of the chip and every job has the rows for them (a weight is then read half as often); else
     // 32-row tiles.  16 / 32 / 64 rows per tile: 12 jobs x 1 - 128 rows, 516 -> 1204 -> 780 -> 388: 50 / 50 / 70 us; one job x
     // 64 rows, 1024 -> 1024 8.8 / 12.7 / 21.3; 12 jobs x 32 rows, 1204 -> 780 (312 16-row tiles) 16.9 / 15.3, 40 jobs, 256 -> 256 (320) 5.9 / 6.0; 12 jobs x 128
@@ -452,7 +454,7 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
         max_m = std::max(max_m, p[i].M);
         min_k = std::min(min_k, p[i].K);
     }
-    const bool one_32 = min_k > 512 && max_m > 16 && max_m <= 32 && tiles_16 > kFullGrid && tiles_32 <= kFullGrid && tiles_16 * 4 > tiles_32 * 7;
+    const bool one_32 = min_k > 256 && tiles_16 > kFullGrid && tiles_32 <= kFullGrid;
     const uint64_t rounds_64 = (tiles_64 + kFullGrid - 1) / kFullGrid;
     const bool whole_64 = tiles_32 == 2 * tiles_64 && tiles_64 * 16 >= rounds_64 * kFullGrid * 15;
     const int mt = one_32                                          ? 2

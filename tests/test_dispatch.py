@@ -336,3 +336,12 @@ def test_jobs_of_128_rows_and_more_that_are_few(record):
         ([256], 320, 4096, False, "tiled<128, 128, 2, 2>"), ([500] * 4, 2048, 2048, False, "tiled<128, 128, 2, 2>"),
         ([200] * 24, 1024, 1024, False, "tiled<128, 256, 2, 4>"), ([128] * 33, 384, 1024, False, "tiled<128, 128, 2, 2>"),
     ]])
+
+
+def test_float_32_row_tiles_one_per_compute_unit(record):
+    """Layers deeper than 256 with more than one 16-row tile and at most one 32-row tile per compute unit."""
+    mixed = [1, 1, 2, 3, 4, 8, 9, 12, 14, 31, 76, 77]
+    check(record, [(case(rows, K, N, "f32"), ["grouped_dense_f32<%d>" % tile]) for rows, K, N, tile in (
+        (mixed, 1204, 780, 2), (mixed, 516, 1204, 1), (mixed, 780, 388, 1), ([86] * 5, 1012, 936, 2), ([125] * 2, 1484, 1136, 2),
+        ([95] * 5, 260, 696, 2), ([95] * 5, 256, 696, 1), ([68] * 8, 988, 760, 1), ([16] * 40, 516, 452, 1),
+    )])
