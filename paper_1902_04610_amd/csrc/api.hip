@@ -693,7 +693,7 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
         }
         if (!probs.empty()) e = launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), true, cached, stream, count);
     }
-    if (e == hipSuccess) e = launch_grouped_dw_sgd(ups.data(), (uint32_t)ups.size(), stream, count);
+    if (e == hipSuccess) e = launch_grouped_dw_sgd(ups.data(), (uint32_t)ups.size(), cached, stream, count);
     if (e != hipSuccess) return set_error(pool, SALUS_EHIP, hipGetErrorString(e));
     return SALUS_OK;
 }

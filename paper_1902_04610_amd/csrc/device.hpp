@@ -138,8 +138,8 @@ struct UpdateProblem {
     float lr;
 };
 hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, hipStream_t stream, uint64_t *launches);
-// Wm <- Wm - lr * (H^T . G), Wb <- bf16(Wm), all problems in one launch.
-hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, hipStream_t stream,
+// Wm <- Wm - lr * (H^T . G), Wb <- bf16(Wm), all problems in one launch.  cached: as for launch_grouped_bf16.
+hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, bool cached, hipStream_t stream,
                                  uint64_t *launches);
 
 }  // namespace salus

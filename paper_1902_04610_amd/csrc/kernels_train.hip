@@ -199,19 +199,13 @@ hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, hipStream_t str
 // the kernel is bound by the read-modify-write of the float master weights
 // (4 B read, 4 B + 2 B written per weight).
 //
-// One wavefront owns a 32 (k) x 64 (n) block of W; a workgroup is four such
-// blocks side by side.  Lane (c, g) loads the 8 x 2 blocks H[m0+8g ..][k0+2c ..]
-// and 8 x 4 blocks G[m0+8g ..][n0+4c ..] (4- and 8-byte loads), transposes them in registers into
-// two A and four B operands of v_mfma_f32_16x16x32_bf16; MFMA (i, j) yields
-// rows k0 + 2*rho + i, columns n0 + 4*c + j.  A lane ends up with 8 rows x 4
+// One wavefront owns a KB (k) x 64 (n) block of W, KB = 16 KI; a workgroup is four such
+// blocks side by side.  Lane (c, g) loads the 8 x KI blocks H[m0+8g ..][k0+KI*c ..]
+// and 8 x 4 blocks G[m0+8g ..][n0+4c ..], transposes them in registers into
+// KI A and four B operands of v_mfma_f32_16x16x32_bf16; MFMA (i, j) yields
+// rows k0 + KI*rho + i, columns n0 + 4*c + j.  A lane ends up with 4 KI rows x 4
 // consecutive columns, so master weights move as 16-byte vectors, 256
 // contiguous bytes per row across the 16 lanes.
-// What a block waits for is requested at once, up to 128 rows of H and G and behind them its master weights, which arrive under
-// the multiplies: a block that asked for 32 rows at a time waited for HBM's queue with each of them.  The registers that
-// takes leave two workgroups per compute unit, which is no loss (three, with 64 rows at once, are slower).  Tiles of a row of
-// blocks are neighbours, so that what is under way at a time is whole rows of W.
-// 8 jobs x 64 rows, 2048 - 2048 - 2048 - 2048 - 1000 (1.17 GB): 191 us, in blocks of 64 x 64, 32 rows at a time and columns of blocks first,
-// 205; 8 rows 178 / 192.  The weights' traffic alone, in this order and without H and G, 182.
 // ---------------------------------------------------------------------------
 struct UpdateArgs {
     uint32_t n;
@@ -220,37 +214,137 @@ struct UpdateArgs {
     UpdateProblem p[kMaxProblems];
 };
 
-constexpr int kUpdK = 32, kUpdN = 256;      // workgroup tile
-constexpr int kUpdSteps = 4;                // steps of 32 rows that are requested at once
+constexpr int kUpdK = 64, kUpdFewK = 32, kUpdN = 256;      // workgroup tiles
+constexpr int kUpdSteps = 4;                // steps of 32 rows that a tile of few rows requests at once
 constexpr double kDwTiledRows = 192;
 constexpr int kDwTile = 128;                // tile of the many-row kernel
 
-__global__ __launch_bounds__(256, 2) void grouped_dw_sgd(UpdateArgs a)
+// One step of 32 rows: a lane's blocks h and d into operands, and their products.
+template <int KI, typename HVec>
+__device__ inline void dw_multiply(const HVec (&h)[8], const u32x2 (&d)[8], f32x4 (&acc)[4 * KI])
+{
+    u32x4 A[KI], B[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
+            if (i < KI) A[i][j] = __builtin_amdgcn_perm(h[2 * j + 1][i >> 1], h[2 * j][i >> 1], sel);
+            B[i][j] = __builtin_amdgcn_perm(d[2 * j + 1][i >> 1], d[2 * j][i >> 1], sel);
+        }
+#pragma unroll
+    for (int i = 0; i < KI; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            acc[i * 4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, A[i]), __builtin_bit_cast(bf16x8, B[j]), acc[i * 4 + j],
+                0, 0, 0);
+}
+
+// Master weights of a lane: rows first + KI * r + i, columns ncol .. ncol+3.
+template <int KI>
+__device__ inline void dw_load(const UpdateProblem &p, uint32_t first, uint32_t ncol, f32x4 (&wm)[4 * KI])
+{
+    const Global<float> *Wm = (const Global<float> *)p.Wm;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < KI; ++i) {
+            const uint32_t krow = first + KI * r + i;
+            wm[r * KI + i] = (krow < p.K && ncol < p.N)
+                                 ? __builtin_nontemporal_load((const Global<f32x4> *)(Wm + (size_t)krow * p.N + ncol))
+                                 : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+}
+
+template <int KI>
+__device__ inline void dw_store(const UpdateProblem &p, uint32_t first, uint32_t ncol, const f32x4 (&wm)[4 * KI], const f32x4 (&acc)[4 * KI])
+{
+    Global<float> *Wm = (Global<float> *)p.Wm;
+    Global<uint16_t> *Wb = (Global<uint16_t> *)p.Wb;
+    const float lr = p.lr;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < KI; ++i) {
+            const uint32_t krow = first + KI * r + i;
+            if (krow >= p.K || ncol >= p.N) continue;
+            f32x4 w = wm[r * KI + i];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)      // one rounded multiply, one rounded subtract
+                w[j] = __fsub_rn(w[j], __fmul_rn(lr, acc[i * 4 + j][r]));
+            __builtin_nontemporal_store(w, (Global<f32x4> *)(Wm + (size_t)krow * p.N + ncol));
+            u32x2 b;
+            b[0] = bf16_pack(w[0], w[1]);
+            b[1] = bf16_pack(w[2], w[3]);
+            *(Global<u32x2> *)(Wb + (size_t)krow * p.N + ncol) = b;
+        }
+}
+
+// Blocks of 64 x 64.  The master-weight loads are issued before the MFMA phase and complete underneath it.
+__global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
+{
+    UpdateProblem p;
+    const uint32_t t = find_owner(a.first, a.p, blockIdx.x, p);
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t M = p.M, K = p.K, N = p.N, kt = (K + kUpdK - 1) / kUpdK;
+    const uint32_t k0 = (t % kt) * kUpdK;                  // neighbours share the G columns
+    const uint32_t n0 = (t / kt) * kUpdN + 64 * wave;
+    const uint32_t ncol = n0 + 4 * c;
+    const bool col_ok = ncol < N;
+    const Global<uint16_t> *H = (const Global<uint16_t> *)p.H;
+    const Global<uint16_t> *G = (const Global<uint16_t> *)p.G;
+    f32x4 wm[16], acc[16];      // acc[i * 4 + j][r]
+    dw_load<4>(p, k0 + 16 * g, ncol, wm);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint32_t kcol = k0 + 4 * c;
+    const bool kcol_ok = kcol < K;
+    for (uint32_t m0 = 0; m0 < M; m0 += 32) {
+        u32x2 h[8], d[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const uint32_t m = m0 + 8 * g + r;
+            h[r] = (m < M && kcol_ok) ? *(const Global<u32x2> *)(H + (size_t)m * K + kcol) : u32x2{0u, 0u};
+            d[r] = (m < M && col_ok) ? *(const Global<u32x2> *)(G + (size_t)m * N + ncol) : u32x2{0u, 0u};
+        }
+        dw_multiply<4>(h, d, acc);
+    }
+    dw_store<4>(p, k0 + 16 * g, ncol, wm, acc);
+}
+
+// Few rows: blocks of 32 x 64.  What a block waits for is requested at once, up to 128 rows of H and G and behind them its master weights, which
+// arrive under the multiplies: a block that asks for 32 rows at a time waits behind HBM's queue with each of them.  The registers that
+// takes leave two workgroups per compute unit, which is no loss (three, with 64 rows at once, are slower).  Tiles of a row of
+// blocks are neighbours, so that what is under way at a time is whole rows of W.  More rows, or weights from the cache, where blocks of 64 x 64
+// ask L2 for H and G two thirds as often, take those (launch_grouped_dw_sgd).
+// 8 jobs x 64 rows, 2048 - 2048 - 2048 - 2048 - 1000 (1.17 GB): 191 us, blocks of 64 x 64 205; 8 rows 178 / 192.
+// The weights' traffic alone, in this order and without H and G, 182.
+__global__ __launch_bounds__(256, 2) void grouped_dw_sgd_few_rows(UpdateArgs a)
 {
     UpdateProblem p;
     const uint32_t t = find_owner(a.first, a.p, blockIdx.x, p);
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t M = p.M, K = p.K, N = p.N, nt = (N + kUpdN - 1) / kUpdN;
-    const uint32_t k0 = (t / nt) * kUpdK, n0 = (t % nt) * kUpdN + 64 * wave;
+    const uint32_t k0 = (t / nt) * kUpdFewK, n0 = (t % nt) * kUpdN + 64 * wave;
     const uint32_t ncol = n0 + 4 * c, kcol = k0 + 2 * c;
     const bool col_ok = ncol < N;
     // rows and columns outside the matrices: a valid address, and what comes of it is not stored
     const Global<uint16_t> *H = (const Global<uint16_t> *)p.H + (kcol < K ? kcol : 0);
     const Global<uint16_t> *G = (const Global<uint16_t> *)p.G + (col_ok ? ncol : 0);
-    Global<float> *Wm = (Global<float> *)p.Wm;
-    Global<uint16_t> *Wb = (Global<uint16_t> *)p.Wb;
-
-    f32x4 acc[8];      // acc[i * 4 + j][r]
+    f32x4 acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    uint32_t h[kUpdSteps][8];
+    typedef unsigned int u32x1 __attribute__((ext_vector_type(1)));
+    u32x1 h[kUpdSteps][8];
     u32x2 d[kUpdSteps][8];
     auto load = [&](int s, uint32_t m0) {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const size_t m = min(m0 + 8 * g + r, M - 1);
-            h[s][r] = *(const Global<uint32_t> *)(H + m * K);
+            h[s][r] = *(const Global<u32x1> *)(H + m * K);
             d[s][r] = *(const Global<u32x2> *)(G + m * N);
         }
     };
@@ -258,41 +352,17 @@ __global__ __launch_bounds__(256, 2) void grouped_dw_sgd(UpdateArgs a)
 #pragma unroll
         for (int r = 0; r < 8; ++r)
             if (m0 + 8 * g + r >= M) {
-                h[s][r] = 0u;
+                h[s][r] = u32x1{0u};
                 d[s][r] = u32x2{0u, 0u};
             }
-        u32x4 A[2], B[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-                if (i < 2) A[i][j] = __builtin_amdgcn_perm(h[s][2 * j + 1], h[s][2 * j], sel);
-                B[i][j] = __builtin_amdgcn_perm(d[s][2 * j + 1][i >> 1], d[s][2 * j][i >> 1], sel);
-            }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                acc[i * 4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8, A[i]), __builtin_bit_cast(bf16x8, B[j]), acc[i * 4 + j],
-                    0, 0, 0);
+        dw_multiply<2>(h[s], d[s], acc);
     };
 #pragma unroll
     for (int s = 0; s < kUpdSteps; ++s)
         if (32u * s < M) load(s, 32u * s);
     __builtin_amdgcn_sched_barrier(0);
-    // master weights of this lane: rows k0 + 8g + 2r + i, columns ncol .. ncol+3
     f32x4 wm[8];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t krow = k0 + 8 * g + 2 * r + i;
-            wm[r * 2 + i] = (krow < K && col_ok)
-                                ? __builtin_nontemporal_load((const Global<f32x4> *)(Wm + (size_t)krow * N + ncol))
-                                : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+    dw_load<2>(p, k0 + 8 * g, ncol, wm);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < kUpdSteps; ++s)
@@ -305,24 +375,7 @@ __global__ __launch_bounds__(256, 2) void grouped_dw_sgd(UpdateArgs a)
         for (int s = 0; s < kUpdSteps; ++s)
             if (m0 + 32u * s < M) multiply(s, m0 + 32u * s);
     }
-
-    const float lr = p.lr;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t krow = k0 + 8 * g + 2 * r + i;
-            if (krow >= K || !col_ok) continue;
-            f32x4 w = wm[r * 2 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j)      // one rounded multiply, one rounded subtract
-                w[j] = __fsub_rn(w[j], __fmul_rn(lr, acc[i * 4 + j][r]));
-            __builtin_nontemporal_store(w, (Global<f32x4> *)(Wm + (size_t)krow * N + ncol));
-            u32x2 b;
-            b[0] = bf16_pack(w[0], w[1]);
-            b[1] = bf16_pack(w[2], w[3]);
-            *(Global<u32x2> *)(Wb + (size_t)krow * N + ncol) = b;
-        }
+    dw_store<2>(p, k0 + 8 * g, ncol, wm, acc);
 }
 
 // Many rows per job (the contraction is long): the product goes through the LDS tiles of tile_mfma.hpp, both operands
@@ -436,7 +489,7 @@ static hipError_t launch_dw_tiled(const UpdateProblem *p, uint32_t n, hipStream_
     return hipSuccess;
 }
 
-hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, hipStream_t stream,
+hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, bool cached, hipStream_t stream,
                                  uint64_t *launches)
 {
     // One kernel for all updates of a step (two would each ramp up and drain): the tiled one if a weight's rows, on
@@ -451,14 +504,19 @@ hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, hipStream_t
         fits = fits && p[i].K < kTiledMaxWidth && p[i].N < kTiledMaxWidth;
     }
     if (fits && rows >= kDwTiledRows * weights) return launch_dw_tiled(p, n, stream, launches);
+    // 32 x 64 blocks of few rows / 64 x 64, a step with weights from HBM: 6 jobs of 2048 - 2048 - 1000 at 16 / 72 / 104 / 128 / 150 rows 95 / 113 / 119 /
+    // 123 / 149 us, 103 / 122 / 127 / 128 / 146; from the cache: 8 jobs of 872 - 2032 - 872 - 528 - 128 at 16 / 48 / 72 / 96 / 128 rows 106 / 119 / 131 /
+    // 138 / 148, 108 / 121 / 133 / 135 / 142, 4 jobs of 1024 - 1536 - 776 at 48 / 72 / 96 53.6 / 58.4 / 59.4, 54.7 / 58.5 / 58.6.
+    const bool few_rows = rows <= (cached ? 64 : 128) * weights;
+    const uint32_t tile_k = few_rows ? kUpdFewK : kUpdK;
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         UpdateArgs a{};
-        const uint64_t tiles = fill_group(a, p + at, std::min(kMaxProblems, n - at), [](const UpdateProblem &q) {
-            return (uint64_t)((q.K + kUpdK - 1) / kUpdK) * ((q.N + kUpdN - 1) / kUpdN);
+        const uint64_t tiles = fill_group(a, p + at, std::min(kMaxProblems, n - at), [&](const UpdateProblem &q) {
+            return (uint64_t)((q.K + tile_k - 1) / tile_k) * ((q.N + kUpdN - 1) / kUpdN);
         });
         if (tiles == 0) continue;
         if (tiles > 0x7fffffffull) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(grouped_dw_sgd, dim3((uint32_t)tiles), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(few_rows ? grouped_dw_sgd_few_rows : grouped_dw_sgd, dim3((uint32_t)tiles), dim3(256), 0, stream, a);
         if (launches) *launches += 1;
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
