@@ -317,8 +317,8 @@ __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
 // Few rows: blocks of 32 x 64.  What a block waits for is requested at once, up to 128 rows of H and G and behind them its master weights, which
 // arrive under the multiplies: a block that asks for 32 rows at a time waits behind HBM's queue with each of them.  The registers that
 // takes leave two workgroups per compute unit, which is no loss (three, with 64 rows at once, are slower).  Tiles of a row of
-// blocks are neighbours, so that what is under way at a time is whole rows of W.  More rows, or weights from the cache, where blocks of 64 x 64
-// ask L2 for H and G two thirds as often, take those (launch_grouped_dw_sgd).
+// blocks are neighbours, so that what is under way at a time is whole rows of W.  More rows take blocks of 64 x 64, which
+// ask L2 for H and G two thirds as often (launch_grouped_dw_sgd).
 // 8 jobs x 64 rows, 2048 - 2048 - 2048 - 2048 - 1000 (1.17 GB): 191 us, blocks of 64 x 64 205; 8 rows 178 / 192.
 // The weights' traffic alone, in this order and without H and G, 182.
 __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_few_rows(UpdateArgs a)
@@ -505,9 +505,12 @@ hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, bool cached
     }
     if (fits && rows >= kDwTiledRows * weights) return launch_dw_tiled(p, n, stream, launches);
     // 32 x 64 blocks of few rows / 64 x 64, a step with weights from HBM: 6 jobs of 2048 - 2048 - 1000 at 16 / 72 / 104 / 128 / 150 rows 95 / 113 / 119 /
-    // 123 / 149 us, 103 / 122 / 127 / 128 / 146; from the cache: 8 jobs of 872 - 2032 - 872 - 528 - 128 at 16 / 48 / 72 / 96 / 128 rows 106 / 119 / 131 /
-    // 138 / 148, 108 / 121 / 133 / 135 / 142, 4 jobs of 1024 - 1536 - 776 at 48 / 72 / 96 53.6 / 58.4 / 59.4, 54.7 / 58.5 / 58.6.
-    const bool few_rows = rows <= (cached ? 64 : 128) * weights;
+    // 123 / 149 us, 103 / 122 / 127 / 128 / 146; from the cache: 8 jobs of 872 - 2032 - 872 - 528 - 128 at 16 / 48 / 72 / 96 / 128 rows 105 / 119 / 132 /
+    // 139 / 148, 108 / 122 / 133 / 135 / 143, 5 jobs of 712 - 1640 - 904 at 48 / 72 / 96 / 128 63 / 68 / 71 / 76, 67 / 72 / 72 / 75.  And not where 64 x 64 blocks
+    // are all under way at once: 2 jobs of 744 - 2040 - 600 - 840 - 136 at 48 / 72 / 96 66 / 69 / 71, 65 / 68 / 68.
+    uint64_t tall_tiles = 0;
+    for (uint32_t i = 0; i < n; ++i) tall_tiles += (uint64_t)((p[i].K + kUpdK - 1) / kUpdK) * ((p[i].N + kUpdN - 1) / kUpdN);
+    const bool few_rows = rows <= (cached ? 88 : 128) * weights && tall_tiles > 2 * resident_grid();
     const uint32_t tile_k = few_rows ? kUpdFewK : kUpdK;
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         UpdateArgs a{};

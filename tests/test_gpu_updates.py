@@ -8,18 +8,26 @@ from test_gpu_train import run
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M", [1, 32, 33, 64, 65, 96, 97, 128, 129, 191])
+@pytest.mark.parametrize("M", [1, 32, 33, 65, 191])
 @pytest.mark.parametrize("dims", [(72, 264, 8), (8, 40, 520)])
-def test_updates_of_up_to_191_rows(dims, M):
-    """Widths below a block, that end inside one and of several; blocks of 32 x 64 up to 64 rows, of 64 x 64 beyond."""
+def test_updates_of_few_blocks(dims, M):
+    """Blocks of 64 x 64: widths below a block, that end inside one and of several."""
     run([(dims, M, 0.05)], steps=1, seed=20 + M)
 
 
-@pytest.mark.parametrize("rows", [[65], [128], [97, 40, 33], [20, 17, 300]])
-def test_updates_with_weights_from_further_away(rows, monkeypatch):
-    """Blocks of 32 x 64 up to a mean of 128 rows, one job with more than are requested at once."""
+MANY = 12          # jobs of these widths have more blocks of 64 x 64 than are under way at once
+DIMS = (520, 1032, 264)
+
+
+@pytest.mark.parametrize("M", [1, 33, 64, 88, 89])
+def test_updates_of_few_rows(M):
+    """Blocks of 32 x 64 up to 88 rows, of 64 x 64 beyond."""
+    run([(DIMS, M, 0.05)] * MANY, steps=1, seed=40 + M)
+
+
+@pytest.mark.parametrize("rows", [[97], [128], [129], [100, 150]])
+def test_updates_of_few_rows_with_weights_from_further_away(rows, monkeypatch):
+    """Up to a mean of 128 rows; jobs with more rows than a tile requests at once."""
     monkeypatch.setattr(test_gpu_train, "DevicePool", FarPool)
-    dims = (136, 264, 72)
-    # 17 - 32, 33 - 128 and more rows take different launches of the forward layers and the input gradient
-    extra = {1: 0, 3: 0}[len(rows)] if 300 not in rows else 3
-    run([(dims, m, 0.05) for m in rows], steps=1, seed=31, extra_forward_launches=extra)
+    # rows on either side of 128 have two launches of each forward layer
+    run([(DIMS, rows[i % len(rows)], 0.05) for i in range(MANY)], steps=1, seed=31, extra_forward_launches=2 if len(rows) > 1 else 0)
