@@ -549,6 +549,7 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
         char *persist, *lane;
         std::vector<uint64_t> h_off;   // lane offset of H_l, l = 0 (= x) .. L-1
         std::vector<uint64_t> g_off;   // gradient buffer of backward step 0 .. L-1 (at least two)
+        uint32_t loss_step;            // backward step behind whose gradient the row losses fit into its buffer; n_layers: none
     };
     std::vector<Resolved> res(n);
     std::vector<int32_t> lanes_used;
@@ -606,8 +607,10 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
             }
             max_n = std::max<uint64_t>(max_n, d.layers[l].N);
         }
-        for (uint32_t b = 0; b < std::max<uint32_t>(d.n_layers, 2); ++b)
-            R.g_off.push_back(at + b * up256((uint64_t)d.M * max_n * 2));
+        const uint64_t g_bytes = up256((uint64_t)d.M * max_n * 2);
+        for (uint32_t b = 0; b < std::max<uint32_t>(d.n_layers, 2); ++b) R.g_off.push_back(at + b * g_bytes);
+        R.loss_step = 0;
+        while (R.loss_step < d.n_layers && g_bytes < (uint64_t)d.M * (d.layers[d.n_layers - 1 - R.loss_step].N * 2ull + 4)) ++R.loss_step;
         depth = std::max(depth, d.n_layers);
     }
     hipError_t e = hipSuccess;
@@ -633,7 +636,10 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
         }
         e = launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), false, cached, stream, count);
     }
-    // loss and its gradient
+    // Loss and its gradient.  The mean over the rows is left to the update launch if the row losses can lie untouched until then:
+    // behind the gradient of a layer that is narrower than the widest one (or whose buffer ends in enough padding).
+    bool mean_later = true;
+    for (uint32_t i = 0; i < n; ++i) mean_later = mean_later && (descs[i].M <= kLossRows || res[i].loss_step < descs[i].n_layers);
     if (e == hipSuccess) {
         std::vector<LossProblem> lp;
         for (uint32_t i = 0; i < n; ++i) {
@@ -646,9 +652,11 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
             p.row_loss = (float *)(res[i].lane + res[i].g_off[1]);   // a gradient buffer that is idle here
             p.M = d.M;
             p.N = d.layers[d.n_layers - 1].N;
+            if (mean_later && d.M > kLossRows)
+                p.row_loss = (float *)(res[i].lane + res[i].g_off[res[i].loss_step] + (uint64_t)d.M * d.layers[d.n_layers - 1 - res[i].loss_step].N * 2);
             lp.push_back(p);
         }
-        e = launch_softmax_xent(lp.data(), (uint32_t)lp.size(), stream, count);
+        e = launch_softmax_xent(lp.data(), (uint32_t)lp.size(), mean_later, stream, count);
     }
     // backward: layer `back` counted from each job's last layer, so that jobs of
     // different depth still share launches.  First the chain of input gradients
@@ -689,6 +697,7 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
             up.K = L.K;
             up.N = L.N;
             up.lr = d.lr;
+            if (mean_later && d.M > kLossRows && back == res[i].loss_step) up.loss = (float *)(res[i].lane + d.loss_off);
             ups.push_back(up);
         }
         if (!probs.empty()) e = launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), true, cached, stream, count);

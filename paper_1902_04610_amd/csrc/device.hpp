@@ -129,6 +129,7 @@ struct LossProblem {
     float *row_loss;         // scratch, M floats
     uint32_t M, N;
 };
+constexpr uint32_t kLossRows = 16;      // jobs of up to this many rows have their mean loss from launch_softmax_xent in any case
 struct UpdateProblem {
     const void *H;           // M x K bf16 (layer input)
     const void *G;           // M x N bf16 (gradient of the layer output)
@@ -136,8 +137,10 @@ struct UpdateProblem {
     void *Wb;                // K x N bf16 working copy, rewritten
     uint32_t M, K, N;
     float lr;
+    float *loss;             // if not null: becomes the mean of the M floats behind G
 };
-hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, hipStream_t stream, uint64_t *launches);
+// mean_later: the mean losses of jobs of more than kLossRows rows are left to launch_grouped_dw_sgd.
+hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, bool mean_later, hipStream_t stream, uint64_t *launches);
 // Wm <- Wm - lr * (H^T . G), Wb <- bf16(Wm), all problems in one launch.  cached: as for launch_grouped_bf16.
 hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, bool cached, hipStream_t stream,
                                  uint64_t *launches);

@@ -38,7 +38,8 @@ __device__ inline float wave_sum(float v)
 // 1024 classes are read once and kept in registers; wider rows are re-read from memory for each of the three
 // passes.  Row losses are added in row order, so the result does
 // not depend on how the rows were scheduled: inside the workgroup when it holds
-// the whole job, else by a second, tiny kernel over the scratch array.
+// the whole job, else over the scratch array, by the launch that updates the weights or, where the scratch
+// array cannot live that long, by a second, tiny kernel (5 us of a step).
 // ---------------------------------------------------------------------------
 struct LossArgs {
     uint32_t n;
@@ -47,7 +48,7 @@ struct LossArgs {
     LossProblem p[kMaxProblems];
 };
 
-constexpr int kLossRows = 16, kLossWaves = 16, kLossPerWave = kLossRows / kLossWaves, kLossRegs = 16;
+constexpr int kLossWaves = 16, kLossPerWave = kLossRows / kLossWaves, kLossRegs = 16;
 
 __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
 {
@@ -136,14 +137,14 @@ __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
         if (lane == 0) {
             const float loss = -(zlabel - zmax - logf(denom));
             row_loss[row - row0] = loss;
-            if (M > (uint32_t)kLossRows) row_losses[row] = loss;
+            if (M > kLossRows) row_losses[row] = loss;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0 && M <= (uint32_t)kLossRows) {      // this workgroup holds the whole job
+    if (threadIdx.x == 0 && M <= kLossRows) {      // this workgroup holds the whole job
         float sum = 0.0f;
 #pragma unroll
-        for (uint32_t r = 0; r < (uint32_t)kLossRows; ++r) {
+        for (uint32_t r = 0; r < kLossRows; ++r) {
             const float v = row_loss[r < M ? r : 0];
             if (r < M) sum += v;
         }
@@ -151,41 +152,46 @@ __global__ __launch_bounds__(64 * kLossWaves) void softmax_xent_rows(LossArgs a)
     }
 }
 
-// Jobs of more than 16 rows: add the row losses of each in row order: 512 of them are loaded at a time and added lane by
+// Jobs of more than 16 rows, one wavefront: add the row losses of one in row order: 512 of them are loaded at a time and added lane by
 // lane (500 rows: 5 us; a load per row took 23 us).
-__global__ __launch_bounds__(64) void loss_mean(LossArgs a)
+__device__ inline void mean_of_rows(const float *row_loss, uint32_t M, float *loss)
 {
-    const LossProblem &p = a.p[blockIdx.x];
-    if (p.M <= (uint32_t)kLossRows) return;
+    const uint32_t lane = threadIdx.x & 63;
     float sum = 0.0f;
-    for (uint32_t r0 = 0; r0 < p.M; r0 += 512) {
+    for (uint32_t r0 = 0; r0 < M; r0 += 512) {
         float v[8];
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const uint32_t r = r0 + 64u * c + threadIdx.x;
-            v[c] = r < p.M ? p.row_loss[r] : 0.0f;
+            const uint32_t r = r0 + 64u * c + lane;
+            v[c] = r < M ? ((const Global<float> *)row_loss)[r] : 0.0f;
         }
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            if (r0 + 64u * c >= p.M) break;
+            if (r0 + 64u * c >= M) break;
 #pragma unroll
             for (int i = 0; i < 64; ++i) sum += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[c]), i));
         }
     }
-    if (threadIdx.x == 0) *p.loss = sum / (float)p.M;
+    if (lane == 0) *(Global<float> *)loss = sum / (float)M;
 }
 
-hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
+__global__ __launch_bounds__(64) void loss_mean(LossArgs a)
+{
+    const LossProblem &p = a.p[blockIdx.x];
+    if (p.M > kLossRows) mean_of_rows(p.row_loss, p.M, p.loss);
+}
+
+hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, bool mean_later, hipStream_t stream, uint64_t *launches)
 {
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         LossArgs a{};
         const uint32_t count = std::min(kMaxProblems, n - at);
         const uint64_t blocks = fill_group(a, p + at, count, [](const LossProblem &q) { return (uint64_t)((q.M + kLossRows - 1) / kLossRows); });
-        const bool big = std::any_of(p + at, p + at + count, [](const LossProblem &q) { return q.M > (uint32_t)kLossRows; });
+        const bool big = std::any_of(p + at, p + at + count, [](const LossProblem &q) { return q.M > kLossRows; });
         if (blocks == 0) continue;
         if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
         hipLaunchKernelGGL(softmax_xent_rows, dim3((uint32_t)blocks), dim3(64 * kLossWaves), 0, stream, a);
-        if (big) hipLaunchKernelGGL(loss_mean, dim3(a.n), dim3(64), 0, stream, a);
+        if (big && !mean_later) hipLaunchKernelGGL(loss_mean, dim3(a.n), dim3(64), 0, stream, a);
         if (launches) *launches += 1;
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -213,11 +219,20 @@ struct UpdateArgs {
     uint32_t first[kMaxProblems];      // first tile of update i; kNoTile from n on
     UpdateProblem p[kMaxProblems];
 };
+static_assert(sizeof(UpdateArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
 constexpr int kUpdK = 64, kUpdFewK = 32, kUpdN = 256;      // workgroup tiles
 constexpr int kUpdSteps = 4;                // steps of 32 rows that a tile of few rows requests at once
 constexpr double kDwTiledRows = 192;
 constexpr int kDwTile = 128;                // tile of the many-row kernel
+
+// The mean loss that belongs to update `i` of the launch, if one does: its first wavefront's work in front of its tile.
+__device__ inline void dw_mean_loss(const UpdateArgs &a, uint32_t i)
+{
+    if (i >= a.n || threadIdx.x >= 64) return;
+    const UpdateProblem &p = a.p[i];
+    if (p.loss) mean_of_rows((const float *)((const uint16_t *)p.G + (size_t)p.M * p.N), p.M, p.loss);
+}
 
 // One step of 32 rows: a lane's blocks h and d into operands, and their products.
 template <int KI, typename HVec>
@@ -284,6 +299,7 @@ __device__ inline void dw_store(const UpdateProblem &p, uint32_t first, uint32_t
 // Blocks of 64 x 64.  The master-weight loads are issued before the MFMA phase and complete underneath it.
 __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
 {
+    dw_mean_loss(a, blockIdx.x);
     UpdateProblem p;
     const uint32_t t = find_owner(a.first, a.p, blockIdx.x, p);
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
@@ -323,6 +339,7 @@ __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
 // The weights' traffic alone, in this order and without H and G, 182.
 __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_few_rows(UpdateArgs a)
 {
+    dw_mean_loss(a, blockIdx.x);
     UpdateProblem p;
     const uint32_t t = find_owner(a.first, a.p, blockIdx.x, p);
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
@@ -468,6 +485,7 @@ __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_tiled(UpdateArgs a)
 {
     using T = TileMfma<kDwTile, kDwTile, 2, 2, true, true>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
+    dw_mean_loss(a, gridDim.x - 1 - blockIdx.x);      // the last workgroups have a tile less than the first
     const UpdateWalk walk(a);
     T::run(walk, smem);
 }
