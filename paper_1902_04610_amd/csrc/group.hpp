@@ -19,7 +19,16 @@ struct GroupArgs {
 constexpr uint32_t kNoTile = ~0u;
 static_assert(sizeof(GroupArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
-// Fills in a launch of at most kMaxProblems problems whose i-th has tiles(problem) tiles; returns how many there are in all.
+// The same for launches of few problems, whose time is the host's: a launch with 3.3 KB of arguments takes it 0.4 us longer than one with
+// 0.4 KB (3.7 us).  2 float jobs x 8 rows, 256 - 256 - 256, two launches: 9.2 us a round, 8.5 so.
+constexpr uint32_t kFewProblems = 8;
+struct FewArgs {
+    uint32_t n, tiles, past_l2, pad;
+    uint32_t first[kFewProblems];
+    Problem p[kFewProblems];
+};
+
+// Fills in a launch of at most as many problems as Args holds, whose i-th has tiles(problem) tiles; returns how many there are in all.
 template <typename Args, typename P, typename Tiles>
 inline uint64_t fill_group(Args &a, const P *p, uint32_t n, Tiles tiles)
 {
@@ -30,7 +39,7 @@ inline uint64_t fill_group(Args &a, const P *p, uint32_t n, Tiles tiles)
         a.first[i] = (uint32_t)total;
         total += tiles(p[i]);
     }
-    for (uint32_t i = n; i < kMaxProblems; ++i) a.first[i] = kNoTile;
+    for (uint32_t i = n; i < sizeof(a.first) / sizeof(a.first[0]); ++i) a.first[i] = kNoTile;
     a.tiles = (uint32_t)total;
     return total;
 }
@@ -106,15 +115,15 @@ __device__ inline uint32_t xcd_remap(uint32_t b, uint32_t total)
 // finds the last one that begins at or before `id`, and that lane is read out.  0.6 us from a workgroup's start; scanning
 // tile counts and then reading the problem by its number, three dependent trips, took 1.6: one request against a 1024 -
 // 4096 - 1024 - 1024 model, three launches, 26.1 / 24.1 us, 64 such models 174.5 / 172.5.
-template <typename P>
-__device__ inline uint32_t find_owner(const uint32_t (&first)[kMaxProblems], const P (&p)[kMaxProblems], uint32_t id, P &owner)
+template <typename P, uint32_t NP>
+__device__ inline uint32_t find_owner(const uint32_t (&first)[NP], const P (&p)[NP], uint32_t id, P &owner)
 {
     constexpr int kWords = sizeof(P) / 4;
     struct Words { uint32_t w[kWords]; };
-    const int lane = threadIdx.x & 63;
-    const uint32_t from = first[lane];
-    const Words mine = __builtin_bit_cast(Words, p[lane]);
-    const int g = __builtin_amdgcn_readfirstlane(wave_find_range(from, id, true));
+    const uint32_t lane = threadIdx.x & 63, at = NP == 64 ? lane : min(lane, NP - 1);
+    const uint32_t from = first[at];
+    const Words mine = __builtin_bit_cast(Words, p[at]);
+    const int g = __builtin_amdgcn_readfirstlane(wave_find_range(from, id, lane < NP));
     Words words;
 #pragma unroll
     for (int i = 0; i < kWords; ++i) words.w[i] = __builtin_amdgcn_readlane(mine.w[i], g);
@@ -127,8 +136,8 @@ struct Tile {
 };
 
 // Which (job, row tile, column tile) this workgroup owns, and that job's problem.
-template <int TM, int TN>
-__device__ inline Tile find_tile(const GroupArgs &a, Problem &p)
+template <int TM, int TN, typename Args>
+__device__ inline Tile find_tile(const Args &a, Problem &p)
 {
     const uint32_t t = find_owner(a.first, a.p, xcd_remap(blockIdx.x, a.tiles), p), rt = (p.M + TM - 1) / TM;
     return {(t % rt) * TM, (t / rt) * TN};      // row tiles of one column tile are neighbours: they share W

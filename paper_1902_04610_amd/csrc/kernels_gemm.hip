@@ -13,6 +13,7 @@
 // are narrower and their operands go straight into an LDS ring per wavefront, for bytes in flight and not for reuse, and are transposed on
 // the way out (narrow_tile.hpp).
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "narrow_tile.hpp"
@@ -39,8 +40,8 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16(GroupArgs a)
 // 128 -> 512 4.0 / 4.4) keep registers.  A wavefront's k-step is only CPL / 8 of 8 KB there: deep layers keep DEEP of them
 // in flight instead of two (DEEP is 0 where there are no such registers).
 constexpr uint32_t kNarrowDeepK = 2048;
-template <int MT, bool TW, int CPL, int DEEP, bool NT = true>
-__global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(GroupArgs a)
+template <int MT, bool TW, int CPL, int DEEP, bool NT, typename Args>
+__device__ inline void narrow_bf16(const Args &a)
 {
     Problem p;
     if constexpr (TW || !NT) {
@@ -62,6 +63,11 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(GroupA
         else NarrowTile<MT, CPL>::run(p, tile, smem);
     }
 }
+
+template <int MT, bool TW, int CPL, int DEEP, bool NT = true>
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(GroupArgs a) { narrow_bf16<MT, TW, CPL, DEEP, NT>(a); }
+template <int MT, bool TW, int CPL, int DEEP, bool NT = true>
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_bf16_narrow(FewArgs a) { narrow_bf16<MT, TW, CPL, DEEP, NT>(a); }
 
 // Tiles of 64, 80, 96 or 128 columns, operands through LDS, two workgroups per compute unit: for launches of too many jobs for narrow
 // tiles whose 128-column tiles would leave compute units unevenly loaded (even_columns).  48 jobs x 1 - 32 rows,
@@ -92,8 +98,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void grouped_dense_bf16_rows64(Gro
 // Row tiles of 16 * MT rows; the last one of a job computes only as many 16-row blocks as it needs (the sums of a row do not
 // depend on how many there are).  A single block has little to multiply between its loads: three k-steps in flight instead of
 // two (12 jobs x 16 rows, 516 -> 1204, two / three / four / six: 8.6 / 6.0 / 6.3 / 6.6 us; 5 jobs x 16 rows, 900 -> 1500, three 7.7, four 8.1).
-template <int MT>
-__global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(GroupArgs a)
+template <int MT, typename Args>
+__device__ inline void rows_f32(const Args &a)
 {
     __shared__ float lds[reduce_lds_floats<MT * 4>()];
     Problem p;
@@ -104,10 +110,16 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(GroupArgs a)
     else dense_f32_tile<MT>(p, tile, lds);
 }
 
+template <int MT>
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(GroupArgs a) { rows_f32<MT>(a); }
+template <int MT>
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(FewArgs a) { rows_f32<MT>(a); }
+
 // 16 columns and 16 rows per workgroup, for launches of few tiles: a launch lasts as long as one wavefront's chain of
 // multiplies and loads over its quarter of K, and this tile has a quarter of the multiplies.  16 columns / 64, 4 jobs x 16 rows, 1536 ->
 // 1000: 6.7 / 10.7 us, 1024 -> 1000 5.5 / 8.0, 384 -> 1000 4.1 / 5.2 on the device, 2 jobs x 8 rows, 256 -> 256 3.4 / 4.4.
-__global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32_narrow(GroupArgs a)
+template <typename Args>
+__device__ inline void narrow_f32(const Args &a)
 {
     __shared__ float lds[reduce_lds_floats<1>()];
     Problem p;
@@ -115,8 +127,11 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32_narrow(GroupAr
     dense_f32_tile<1, 4, 1>(p, tile, lds);
 }
 
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32_narrow(GroupArgs a) { narrow_f32(a); }
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32_narrow(FewArgs a) { narrow_f32(a); }
+
 // ---------------------------------------------------------------------------
-// force_mt != 0: row tiles of 16 * force_mt rows whatever the jobs' sizes
+// force_mt != 0: row tiles of 16 * force_mt rows whatever the jobs' sizes.  Launch: called with FewArgs where it takes them and they suffice.
 template <typename Launch>
 static hipError_t launch_groups(const Problem *p, uint32_t n, uint32_t tn, uint32_t m_small,
                                 uint32_t m_mid, Launch launch, uint64_t *launches, int force_mt = 0)
@@ -127,13 +142,17 @@ static hipError_t launch_groups(const Problem *p, uint32_t n, uint32_t tn, uint3
         for (uint32_t i = 0; i < count; ++i) max_m = std::max(max_m, p[at + i].M);
         const int mt = force_mt ? force_mt : max_m <= m_small ? 1 : max_m <= m_mid ? 2 : 4;
         const uint32_t tm = 16u * mt;
-        GroupArgs a{};
-        const uint64_t tiles = fill_group(a, p + at, count, [&](const Problem &q) { return (uint64_t)((q.M + tm - 1) / tm) * ((q.N + tn - 1) / tn); });
-        if (tiles == 0) continue;
-        if (tiles > 0x7fffffffull) return hipErrorInvalidValue;
-        launch(mt, a, (uint32_t)tiles);
-        if (launches) *launches += 1;
-        hipError_t e = hipGetLastError();
+        auto go = [&](auto &&a) {
+            const uint64_t tiles = fill_group(a, p + at, count, [&](const Problem &q) { return (uint64_t)((q.M + tm - 1) / tm) * ((q.N + tn - 1) / tn); });
+            if (tiles == 0) return hipSuccess;
+            if (tiles > 0x7fffffffull) return hipErrorInvalidValue;
+            launch(mt, a, (uint32_t)tiles);
+            if (launches) *launches += 1;
+            return hipGetLastError();
+        };
+        hipError_t e;
+        if constexpr (std::is_invocable_v<Launch, int, const FewArgs &, uint32_t>) e = count <= kFewProblems ? go(FewArgs{}) : go(GroupArgs{});
+        else e = go(GroupArgs{});
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -210,7 +229,7 @@ static uint32_t narrow_columns(const Problem *p, uint32_t n)
 
 static hipError_t launch_narrow_rows(const Problem *p, uint32_t n, uint32_t columns, hipStream_t stream, uint64_t *launches)
 {
-    auto launch = [&](int, const GroupArgs &a, uint32_t tiles) {
+    auto launch = [&](int, const auto &a, uint32_t tiles) {
         const dim3 grid(tiles), block(kGemmThreads);
         if (columns == 32) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 8, false>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 4, 4, false>), grid, block, 0, stream, a);
@@ -365,19 +384,19 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
         // 5.1 / 4.8, 4 jobs x 32 rows 5.3 / 5.0.  Transposed weights, 128 / 64 / 32 columns: 2048 -> 2048 of 4 jobs 20.3 /
         // 16.2 / 14.5, of 8 jobs 18.3 / 15.5 / 20.9, of 16 jobs 25.6 / 28.8 / 43.6.  (Widths from 2^22, which the direct-to-LDS
         // loads cannot address, keep 128.)
-        auto launch_16 = [&](int mt, const GroupArgs &a, uint32_t tiles) {
+        auto launch_16 = [&](int mt, const auto &a, uint32_t tiles) {
             const dim3 grid(tiles), block(kGemmThreads);
             if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 1, 0>), grid, block, 0, stream, a);
             else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 1, 0>), grid, block, 0, stream, a);
         };
-        auto launch_64 = [&](int mt, const GroupArgs &a, uint32_t tiles) {
+        auto launch_64 = [&](int mt, const auto &a, uint32_t tiles) {
             const dim3 grid(tiles), block(kGemmThreads);
             if (mt == 2 && trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, true, 4, 4>), grid, block, 0, stream, a);
             else if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 4, 0>), grid, block, 0, stream, a);
             else if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, true, 4, 4>), grid, block, 0, stream, a);
             else hipLaunchKernelGGL((grouped_dense_bf16_narrow<1, false, 4, 0>), grid, block, 0, stream, a);
         };
-        auto launch_32 = [&](int mt, const GroupArgs &a, uint32_t tiles) {
+        auto launch_32 = [&](int mt, const auto &a, uint32_t tiles) {
             const dim3 grid(tiles), block(kGemmThreads);
             if (mt == 2 && trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, true, 2, 8>), grid, block, 0, stream, a);
             else if (mt == 2) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 0>), grid, block, 0, stream, a);
@@ -426,7 +445,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
 
 hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
 {
-    auto launch = [&](int mt, const GroupArgs &a, uint32_t tiles) {
+    auto launch = [&](int mt, const auto &a, uint32_t tiles) {
         if (mt == 1)
             hipLaunchKernelGGL(grouped_dense_f32<1>, dim3(tiles), dim3(kGemmThreads), 0, stream, a);
         else if (mt == 2)
@@ -464,7 +483,7 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
                    : max_m > 16                                    ? 2 : 1;
     // 16 columns as long as there is at most one such tile per compute unit, in every launch for itself: 6 jobs x 16 rows, 1024 -> 1024 (384), 16 / 64
     // columns 7.6 / 7.9 us, 12 jobs (768) 12.7 / 10.9.
-    auto launch_narrow = [&](int, const GroupArgs &a, uint32_t tiles) {
+    auto launch_narrow = [&](int, const auto &a, uint32_t tiles) {
         hipLaunchKernelGGL(grouped_dense_f32_narrow, dim3(tiles), dim3(kGemmThreads), 0, stream, a);
     };
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
