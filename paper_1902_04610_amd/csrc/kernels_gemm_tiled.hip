@@ -345,8 +345,9 @@ static bool weights_once(const Problem *p, uint32_t n, bool cached)
 // 128 / 64 x 64: 12 jobs x 64 rows, 2048 -> 1536 26 / 33 us, 20 jobs x 33 - 128 rows, 4096 -> 1024 47 / 56, 16 jobs x 33 -
 // 100 rows, 1536 -> 768 19 / 21, 8 jobs x 64 rows, 2048 -> 2048 with weights from memory 27 / 22.5; 8 jobs x 100 rows: 64 x 128 tiles, training
 // step 386 us against 410 with 64 x 64 (all of these with the k-steps of a 64 x 64 tile shared by two groups of wavefronts).  While
-// there is at most one 64 x 128 tile per compute unit, eight wavefronts instead of four: 4 jobs x 200 rows, 4096 -> 1536, 25.7 / 28.3 us, 7 jobs x 234
-// rows, 1080 -> 728, 10.2 / 10.7; the same beyond.  Rings of six and eight
+// there is at most one 64 x 128 tile per compute unit, eight wavefronts instead of four for jobs of 128 rows and more: 4 jobs x 200 rows, 4096 -> 1536,
+// 25.7 / 28.3 us, 7 jobs x 234 rows, 1080 -> 728, 10.2 / 10.7; the same beyond, and not for one row tile whose weights come from HBM (10 jobs x 33 - 60
+// rows, 1992 -> 2536, 27.3 / 26.4).  Rings of six and eight
 // slabs for one 64 x 64 tile per compute unit: step of 8 jobs x 64 rows 313 and 317 us, with four 301.
 hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream, uint64_t *launches)
 {
@@ -360,7 +361,8 @@ hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w
     if (few && trans_w) return launch_tiled<64, 64, 2>(grouped_dense_bf16_stream<64, 64, 2, 1, 2, true, 4>, 256, p, n, stream, launches);
     if (few) return launch_tiled<64, 64, 2>(grouped_dense_bf16_stream<64, 64, 2, 1, 2, false, 4>, 256, p, n, stream, launches);
     if (trans_w) return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 1, true, 3>, 256, p, n, stream, launches);
-    if (wide <= resident_grid()) return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 2, false, 3>, 512, p, n, stream, launches);
+    if (wide <= resident_grid() && std::all_of(p, p + n, [](const Problem &q) { return q.M >= 128; }))
+        return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 2, false, 3>, 512, p, n, stream, launches);
     return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 1, false, 3>, 256, p, n, stream, launches);
 }
 
