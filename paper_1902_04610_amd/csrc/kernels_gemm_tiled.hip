@@ -307,7 +307,8 @@ hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStre
 // 500 rows, 1280 -> 3968, 256 x 256 / 128 x 128 37.8 / 37.0 us from the cache, 38.3 / 47.6 from HBM; 18 jobs x 256 - 1024, 1024 -> 896, 30.4 / 29.1 and
 // 32.9 / 38.6.  7 % off its time then (any figure from there to 20 % gives the same choices but one): over 207 launches of 65 - 1024 rows with weights from
 // HBM the choice is 1.4 % off the best kind, 2.0 % without; and 7 % off that of two 128 x 256 tiles that ask for weights
-// non-temporally (grouped_dense_bf16_tiled_once, 3 - 12 % less than with plain requests).  What the rule is
+// non-temporally (grouped_dense_bf16_tiled_once, 3 - 12 % less than with plain requests) where most compute units have one (10 jobs x 33 - 67 rows, 1792 -> 3456,
+// 140 tiles, 36.4 / 26.9 us of one per compute unit with twice the wavefronts).  What the rule is
 // for: 4 jobs x 500 rows, 2048 -> 2048, 256 x 256 / 128 x 256 / 128 x 128 / two 128 x 256: 48 / 30 / 25 / 33 us; 32 jobs x
 // 300 - 1000 rows, 4096 -> 1024 207 / 200 / 222 / 195, 1024 -> 1024 70 / 69 / 61 / 55; 32 jobs x 500 rows, 1024 -> 4096 167 /
 // 190 / 222 / 181.
@@ -330,7 +331,7 @@ static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n, bool 
     uint64_t tenths = tiles / grid * 10;       // of a round
     if (last) tenths += t.per_cu == 1 || last > cus ? 10 : &t == &kTilePair && weight_bound && last * 4 > cus * 3 ? 5 : 6;
     const uint64_t ns = tenths * (work / tiles) / 10;
-    const bool less = &t == &kTile256 ? tiles <= cus : &t == &kTilePair && weight_bound;
+    const bool less = &t == &kTile256 ? tiles <= cus : &t == &kTilePair && weight_bound && tiles * 4 > cus * 3;
     return !cached && less ? ns * 93 / 100 : ns;
 }
 

@@ -345,3 +345,9 @@ def test_float_32_row_tiles_one_per_compute_unit(record):
         (mixed, 1204, 780, 2), (mixed, 516, 1204, 1), (mixed, 780, 388, 1), ([86] * 5, 1012, 936, 2), ([125] * 2, 1484, 1136, 2),
         ([95] * 5, 260, 696, 2), ([95] * 5, 256, 696, 1), ([68] * 8, 988, 760, 1), ([16] * 40, 516, 452, 1),
     )])
+
+
+def test_half_a_round_of_128_by_256_from_further_away(record):
+    """Where two tiles per compute unit would leave most of them idle, weights from further away change nothing."""
+    for kw in ({}, dict(idle=[240 << 20])):
+        check(record, [(case([33, 67] * 5, 1792, 3456, strip=True, **kw), ["grouped_dense_bf16_tiled<128, 256, 2, 4>"])])
