@@ -227,11 +227,12 @@ static uint32_t narrow_columns(const Problem *p, uint32_t n)
     return count_tiles(p, n, 32, 64) > kFullGrid ? 0 : count_tiles(p, n, 32, 32) <= kFullGrid ? 32 : 64;
 }
 
-static hipError_t launch_narrow_rows(const Problem *p, uint32_t n, uint32_t columns, hipStream_t stream, uint64_t *launches)
+static hipError_t launch_narrow_rows(const Problem *p, uint32_t n, bool trans_w, uint32_t columns, hipStream_t stream, uint64_t *launches)
 {
     auto launch = [&](int, const auto &a, uint32_t tiles) {
         const dim3 grid(tiles), block(kGemmThreads);
-        if (columns == 32) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 8, false>), grid, block, 0, stream, a);
+        if (trans_w) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, true, 2, 8, false>), grid, block, 0, stream, a);
+        else if (columns == 32) hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 2, 8, false>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((grouped_dense_bf16_narrow<2, false, 4, 4, false>), grid, block, 0, stream, a);
     };
     return launch_groups(p, n, columns, 0, 0, launch, launches, 2);
@@ -319,7 +320,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
             const uint32_t count = (uint32_t)tiled.size();
             const bool few = few_tiles(tiled.data(), count);
             const uint32_t columns = few ? narrow_columns(tiled.data(), count) : 0;
-            hipError_t e = columns ? launch_narrow_rows(tiled.data(), count, columns, stream, launches)
+            hipError_t e = columns ? launch_narrow_rows(tiled.data(), count, false, columns, stream, launches)
                            : few   ? launch_grouped_bf16_stream(tiled.data(), count, false, stream, launches)
                                    : launch_grouped_bf16_tiled(tiled.data(), count, cached, stream, launches);
             if (e != hipSuccess || streamed.empty()) return e;
@@ -410,14 +411,17 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
                                                                         : launch_groups(q, count, 64, 16, 32, launch_64, launches);
         if (e != hipSuccess) return e;
     }
-    if (!mid.empty() && !trans_w) {
+    if (!mid.empty()) {
         // Too few for the ring, whose workgroup walks all of K in a row of slabs: narrow 32-row tiles as above, K split over
         // the wavefronts, as many workgroups as compute units.  Ring / narrow, one job x 33 rows, 1024 -> 64: 8.5 / 5.2 us
         // (the 64 x 64 register tile that the ring replaced: 7.1), 4096 -> 1024 20.4 / 11.9 (16.5); 16 jobs x 33 rows,
         // 128 -> 512, 64 columns: 6.1 / 4.5 (5.7); 10 jobs x 33 rows, 1024 -> 512 9.0 / 7.3 (7.8); beyond one per compute unit,
         // 24 jobs x 65 rows, 1024 -> 512: 11.0 / 14.1.
-        if (const uint32_t columns = narrow_columns(mid.data(), (uint32_t)mid.size())) {
-            if (hipError_t e = launch_narrow_rows(mid.data(), (uint32_t)mid.size(), columns, stream, launches)) return e;
+        // Input gradients take those of 32 columns only: steps of 2 jobs x 43 rows of 544 - 632 - 856 - 1704 - 240 58.5 us with them and 63.4 through the
+        // ring, 1 job x 147 rows of 1616 - 856 - 536 - 1192 - 128 69.6 / 73.9; with 64 columns too 1 job x 344 rows of 672 - 1384 - 856 - 832 - 896 77.2 / 75.0.
+        const uint32_t columns = narrow_columns(mid.data(), (uint32_t)mid.size());
+        if (columns == 32 || (columns && !trans_w)) {
+            if (hipError_t e = launch_narrow_rows(mid.data(), (uint32_t)mid.size(), trans_w, columns, stream, launches)) return e;
             mid.clear();
         }
     }
