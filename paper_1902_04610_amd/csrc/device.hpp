@@ -89,8 +89,9 @@ bool tiled_shape_ragged(const Problem &p);
 bool tiled_shape_shallow(const Problem &p);
 uint64_t tiled_tiles(const Problem &p);
 hipError_t launch_grouped_bf16_tiled(const Problem *p, uint32_t n, bool cached, hipStream_t stream, uint64_t *launches);
-// Jobs of 33 .. 128 rows, and transposed weights above: 64-row tiles fed through an LDS ring (tiled_shape_fits).
-hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream,
+// Jobs of 33 .. 128 rows, and transposed weights above: 64-row tiles fed through an LDS ring (tiled_shape_fits).  in_order: 64 x 64
+// tiles add in order of k, as the large tiles do.
+hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, bool in_order, hipStream_t stream,
                                       uint64_t *launches);
 // Calibration: the tiled kernel's multiply without its memory traffic (see kernels_gemm_tiled.hip).
 hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStream_t stream, uint64_t *flop);

@@ -18,6 +18,7 @@ struct GroupArgs {
 };
 constexpr uint32_t kNoTile = ~0u;
 static_assert(sizeof(GroupArgs) <= 4096, "kernel arguments are limited to 4 KB");
+struct InOrderArgs : GroupArgs {};      // names the variant of a kernel that adds every output's products in order of k
 
 // The same for launches of few problems, whose time is the host's: a launch with 3.3 KB of arguments takes it 0.4 us longer than one with
 // 0.4 KB (3.7 us).  2 float jobs x 8 rows, 256 - 256 - 256, two launches: 9.2 us a round, 8.5 so.

@@ -321,7 +321,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
             const bool few = few_tiles(tiled.data(), count);
             const uint32_t columns = few ? narrow_columns(tiled.data(), count) : 0;
             hipError_t e = columns ? launch_narrow_rows(tiled.data(), count, false, columns, stream, launches)
-                           : few   ? launch_grouped_bf16_stream(tiled.data(), count, false, stream, launches)
+                           : few   ? launch_grouped_bf16_stream(tiled.data(), count, false, true, stream, launches)
                                    : launch_grouped_bf16_tiled(tiled.data(), count, cached, stream, launches);
             if (e != hipSuccess || streamed.empty()) return e;
             return launch_grouped_bf16(streamed.data(), (uint32_t)streamed.size(), false, cached, stream, launches);
@@ -438,7 +438,7 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
             for (const Problem &q : mid) (q.K >= kDeepK ? deep : ring).push_back(q);
         else ring.swap(mid);
         if (!ring.empty())
-            if (hipError_t e = launch_grouped_bf16_stream(ring.data(), (uint32_t)ring.size(), trans_w, stream, launches)) return e;
+            if (hipError_t e = launch_grouped_bf16_stream(ring.data(), (uint32_t)ring.size(), trans_w, false, stream, launches)) return e;
         if (!deep.empty())
             if (hipError_t e = launch_groups(deep.data(), (uint32_t)deep.size(), 128, 0, 0, launch_wide, launches, 4)) return e;
     }

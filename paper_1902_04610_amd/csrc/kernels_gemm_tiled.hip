@@ -156,13 +156,27 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_dense_bf16_tiled_once
 // WN x NS wavefronts share the columns.  Every wavefront of a 64 x 64 tile multiplies a 32 x 32 block through all of K:
 // launches with at most one such tile per compute unit take 1.2 us less than with two wavefronts beside each other, the k-steps of a slab shared by
 // two such groups and their sums added through LDS (10 jobs x 68 rows, 144 -> 656, 4.5 / 5.7 us; 5 jobs x 60 rows, 2664 -> 2912, 15.9 / 17.0).
-template <int BM, int BN, int WM, int WN, int NS, bool TW, int D>
-__global__ __launch_bounds__(64 * WM * WN * NS, WM * WN * NS / 2) void grouped_dense_bf16_stream(GroupArgs a)
+// The order of its sums is that of those groups all the same: a wavefront keeps two, of the first and of the second half of every slab, and adds
+// them at the end, half the length of a chain of roundings.  (InOrderArgs: one sum in order of k, as the 128 x 128 tiles that such launches
+// took the place of have it.)
+template <int BM, int BN, int WM, int WN, bool TW, int D, bool HALVES>
+__device__ inline void stream_bf16(const GroupArgs &a)
 {
-    using T = TileStream<BM, BN, WM, WN * NS, !TW, D>;
+    using T = TileStream<BM, BN, WM, WN, !TW, D, HALVES>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[T::kLds];
     const DenseWalk<BM, BN, TW> walk(a);
     T::run(walk, smem);
+}
+
+template <int BM, int BN, int WM, int WN, int NS, bool TW, int D>
+__global__ __launch_bounds__(64 * WM * WN * NS, WM * WN * NS / 2) void grouped_dense_bf16_stream(GroupArgs a)
+{
+    stream_bf16<BM, BN, WM, WN * NS, TW, D, BM * BN == 64 * 64>(a);
+}
+template <int BM, int BN, int WM, int WN, int NS, bool TW, int D>
+__global__ __launch_bounds__(64 * WM * WN * NS, WM * WN * NS / 2) void grouped_dense_bf16_stream(InOrderArgs a)
+{
+    stream_bf16<BM, BN, WM, WN * NS, TW, D, false>(a);
 }
 
 bool tiled_shape_ok(const Problem &p) { return tiled_shape_fits(p) && p.K % kSlab == 0; }
@@ -181,11 +195,11 @@ bool tiled_shape_fits(const Problem &p)
 
 uint64_t tiled_tiles(const Problem &p) { return (uint64_t)((p.M + 127) / 128) * ((p.N + 255) / 256); }
 
-template <int BM, int BN, int PER_CU, typename Kernel>
-static hipError_t launch_tiled(Kernel kernel, int threads, const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
+template <int BM, int BN, int PER_CU, typename Args = GroupArgs>
+static hipError_t launch_tiled(void (*kernel)(Args), int threads, const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
 {
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
-        GroupArgs a{};
+        Args a{};
         const uint64_t tiles = fill_group(a, p + at, std::min(kMaxProblems, n - at),
                                           [](const Problem &q) { return (uint64_t)((q.M + BM - 1) / BM) * ((q.N + BN - 1) / BN); });
         if (tiles == 0) continue;
@@ -350,7 +364,7 @@ static bool weights_once(const Problem *p, uint32_t n, bool cached)
 // 25.7 / 28.3 us, 7 jobs x 234 rows, 1080 -> 728, 10.2 / 10.7; the same beyond, and not for one row tile whose weights come from HBM (10 jobs x 33 - 60
 // rows, 1992 -> 2536, 27.3 / 26.4).  Rings of six and eight
 // slabs for one 64 x 64 tile per compute unit: step of 8 jobs x 64 rows 313 and 317 us, with four 301.
-hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, hipStream_t stream, uint64_t *launches)
+hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, bool in_order, hipStream_t stream, uint64_t *launches)
 {
     uint64_t wide = 0, narrow = 0;
     for (uint32_t i = 0; i < n; ++i) {
@@ -360,6 +374,7 @@ hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w
     }
     const bool few = trans_w ? wide < resident_grid() : narrow <= resident_grid();
     if (few && trans_w) return launch_tiled<64, 64, 2>(grouped_dense_bf16_stream<64, 64, 2, 1, 2, true, 4>, 256, p, n, stream, launches);
+    if (few && in_order) return launch_tiled<64, 64, 2, InOrderArgs>(grouped_dense_bf16_stream<64, 64, 2, 1, 2, false, 4>, 256, p, n, stream, launches);
     if (few) return launch_tiled<64, 64, 2>(grouped_dense_bf16_stream<64, 64, 2, 1, 2, false, 4>, 256, p, n, stream, launches);
     if (trans_w) return launch_tiled<64, 128, 2>(grouped_dense_bf16_stream<64, 128, 2, 2, 1, true, 3>, 256, p, n, stream, launches);
     if (wide <= resident_grid() && std::all_of(p, p + n, [](const Problem &q) { return q.M >= 128; }))

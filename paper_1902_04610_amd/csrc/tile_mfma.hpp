@@ -541,8 +541,9 @@ struct TilePair {
 // The same tiles for launches that are bound by the weight stream (few rows per job): what counts is bytes in flight per
 // compute unit, so LDS is one ring of D whole slabs per operand, D - 1 of them on their way, and the walk across
 // tiles keeps it full through the epilogues.  One barrier per slab: after it slab s has landed for everyone
-// and everyone has left the stage of slab s - 1, which is requested into at once.
-template <int BM, int BN, int WM, int WN, bool TRN, int D>
+// and everyone has left the stage of slab s - 1, which is requested into at once.  HALVES: two sums per output, over the first and
+// over the second two k-steps of every slab, added at the end of a tile.
+template <int BM, int BN, int WM, int WN, bool TRN, int D, bool HALVES = false>
 struct TileStream {
     static constexpr int kWavesT = WM * WN, kThreads = 64 * kWavesT;
     static constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
@@ -600,15 +601,18 @@ struct TileStream {
 #pragma unroll
             for (int part = 0; part < 4; ++part) request(part);
 
-        Acc acc;
+        constexpr int kSums = HALVES ? 2 : 1;
+        Acc acc[kSums];
         uint32_t stage = 0;
         for (;;) {
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
+            for (int c = 0; c < kSums; ++c)
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
+                for (int j = 0; j < FN; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[c][j][i][r] = 0.f;
             uint32_t left = __builtin_amdgcn_readfirstlane(max((cur.depth + kSlab - 1) / kSlab, kMinSlabs));
 #pragma clang loop unroll(disable)
             do {
@@ -631,12 +635,18 @@ struct TileStream {
                     for (int j = 0; j < FN; ++j)
 #pragma unroll
                         for (int i = 0; i < FM; ++i)
-                            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][j], b[ks][i], acc[j][i], 0, 0, 0);
+                            acc[ks * kSums / 4][j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][j], b[ks][i], acc[ks * kSums / 4][j][i], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 stage = stage + 1 == (uint32_t)D ? 0u : stage + 1;
             } while (--left != 0);
-            walk.finish(cur, acc, typename Walk::Held{}, wm * (32u * FM), wn * (32u * FN), fresh_lane(), []() {});
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int r = 0; HALVES && r < 16; ++r) acc[0][j][i][r] += acc[kSums - 1][j][i][r];
+            walk.finish(cur, acc[0], typename Walk::Held{}, wm * (32u * FM), wn * (32u * FN), fresh_lane(), []() {});
             cur_id += gridDim.x;
             if (cur_id >= tiles) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may arrive in LDS after this workgroup
