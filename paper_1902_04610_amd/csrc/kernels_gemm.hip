@@ -468,34 +468,33 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
     // rows, 1536 -> 1536 88 / 80 / 89, 4 jobs 33 / 33 / 32; 40 jobs x 33 rows, 1536 -> 1536 (960 64-row tiles, 3.75 rounds), 32 / 64 rows:
     // 121 / 113; 40 jobs x 128 rows, 1024 -> 1024 -> 1024 (5 rounds) 213 / 202, 40 rows (2.5) 110 / 122.
     uint64_t tiles_16 = 0, tiles_32 = 0, tiles_64 = 0;
-    uint32_t max_m = 0, min_k = ~0u;
+    uint32_t max_m = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const uint64_t cols = (p[i].N + 63) / 64;
         tiles_16 += (p[i].M + 15) / 16 * cols;
         tiles_32 += (p[i].M + 31) / 32 * cols;
         tiles_64 += (p[i].M + 63) / 64 * cols;
         max_m = std::max(max_m, p[i].M);
-        min_k = std::min(min_k, p[i].K);
     }
-    const bool one_32 = min_k > 256 && tiles_16 > kFullGrid && tiles_32 <= kFullGrid;
     const uint64_t rounds_64 = (tiles_64 + kFullGrid - 1) / kFullGrid;
     const bool whole_64 = tiles_32 == 2 * tiles_64 && tiles_64 * 16 >= rounds_64 * kFullGrid * 15;
-    const int mt = one_32                                          ? 2
-                   : tiles_16 <= 2 * kFullGrid                     ? 1
+    const int mt = tiles_16 <= 2 * kFullGrid                       ? 1
                    : max_m > 128 || tiles_64 <= kFullGrid          ? 0
                    : max_m > 32 && whole_64                        ? 4
                    : max_m > 16                                    ? 2 : 1;
-    // 16 columns as long as there is at most one such tile per compute unit, in every launch for itself: 6 jobs x 16 rows, 1024 -> 1024 (384), 16 / 64
+    // One 32-row tile per compute unit, and 16 columns as long as there is at most one such tile per compute unit, in every launch for itself: 90 jobs x
+    // 48 rows, 900 -> 64, are launches of 192 and 78 16-row tiles, not one of 270 (15.0 us, with 32 rows 22.7); 6 jobs x 16 rows, 1024 -> 1024 (384), 16 / 64
     // columns 7.6 / 7.9 us, 12 jobs (768) 12.7 / 10.9.
     auto launch_narrow = [&](int, const auto &a, uint32_t tiles) {
         hipLaunchKernelGGL(grouped_dense_f32_narrow, dim3(tiles), dim3(kGemmThreads), 0, stream, a);
     };
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         const uint32_t count = std::min(kMaxProblems, n - at);
-        uint64_t columns_16 = 0;
-        for (uint32_t i = at; i < at + count; ++i) columns_16 += (uint64_t)((p[i].M + 15) / 16) * ((p[i].N + 15) / 16);
-        const hipError_t e = columns_16 <= kFullGrid ? launch_groups(p + at, count, 16, 0, 0, launch_narrow, launches, 1)
-                                                     : launch_groups(p + at, count, 64, 16, 32, launch, launches, mt);
+        const Problem *q = p + at;
+        const bool deep = std::all_of(q, q + count, [](const Problem &r) { return r.K > 256; });
+        const bool one_32 = deep && count_tiles(q, count, 16, 64) > kFullGrid && count_tiles(q, count, 32, 64) <= kFullGrid;
+        const hipError_t e = count_tiles(q, count, 16, 16) <= kFullGrid ? launch_groups(q, count, 16, 0, 0, launch_narrow, launches, 1)
+                                                                        : launch_groups(q, count, 64, 16, 32, launch, launches, one_32 ? 2 : mt);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

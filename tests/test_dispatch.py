@@ -351,3 +351,10 @@ def test_half_a_round_of_128_by_256_from_further_away(record):
     """Where two tiles per compute unit would leave most of them idle, weights from further away change nothing."""
     for kw in ({}, dict(idle=[240 << 20])):
         check(record, [(case([33, 67] * 5, 1792, 3456, strip=True, **kw), ["grouped_dense_bf16_tiled<128, 256, 2, 4>"])])
+
+
+def test_float_row_tiles_of_every_launch(record):
+    """One 32-row tile per compute unit is a matter of the launch, not of all jobs of the round."""
+    check(record, [(case([M] * jobs, K, N, "f32"), ["grouped_dense_f32" + k for k in names]) for jobs, M, K, N, names in (
+        (90, 48, 900, 64, ["<1>", "<1>"]), (65, 60, 1204, 68, ["<2>", "_narrow"]), (128, 48, 388, 128, ["<2>", "<2>"]), (64, 48, 900, 64, ["<1>"]),
+    )])
