@@ -322,7 +322,11 @@ hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStre
 // 32.9 / 38.6.  7 % off its time then (any figure from there to 20 % gives the same choices but one): over 207 launches of 65 - 1024 rows with weights from
 // HBM the choice is 1.4 % off the best kind, 2.0 % without; and 7 % off that of two 128 x 256 tiles that ask for weights
 // non-temporally (grouped_dense_bf16_tiled_once, 3 - 12 % less than with plain requests) where most compute units have one (10 jobs x 33 - 67 rows, 1792 -> 3456,
-// 140 tiles, 36.4 / 26.9 us of one per compute unit with twice the wavefronts).  What the rule is
+// 140 tiles, 36.4 / 26.9 us of one per compute unit with twice the wavefronts) and rows of an operand begin inside a line, which 128 x 128 tiles
+// ask for more pieces of: of 19 such launches whose choice that changes, 128 x 128 / once, 46 jobs x 49 - 110 rows, 2344 -> 3072, 181 / 152 us, 63 jobs x 72 -
+// 113, 1616 -> 1168, 76.8 / 70.8, 0.94 on average and never more than 1.00.  Whole lines keep the times as they are: 55 jobs x 96 - 126, 1024 -> 1280, 44.9 / 47.3,
+// 23 jobs x 93 - 128, 768 -> 3072, 36.7 / 39.4, 57 jobs x 53 - 101, 2944 -> 1280, 99.2 / 102.4, 1.007 on average over 25; what stays slower for it: 52 jobs x 38 -
+// 71, 2432 -> 3072, 150.7 / 146.7, 46 jobs x 75, 1536 -> 3328, 98.0 / 96.4.  What the rule is
 // for: 4 jobs x 500 rows, 2048 -> 2048, 256 x 256 / 128 x 256 / 128 x 128 / two 128 x 256: 48 / 30 / 25 / 33 us; 32 jobs x
 // 300 - 1000 rows, 4096 -> 1024 207 / 200 / 222 / 195, 1024 -> 1024 70 / 69 / 61 / 55; 32 jobs x 500 rows, 1024 -> 4096 167 /
 // 190 / 222 / 181.
@@ -333,19 +337,20 @@ constexpr TileKind kTile256 = {256, 256, 1, 1640, 12000}, kTile128x256 = {128, 2
 static uint64_t launch_ns(const TileKind &t, const Problem *p, uint32_t n, bool cached)
 {
     uint64_t tiles = 0, work = 0;
-    bool weight_bound = true;
+    bool weight_bound = true, lines = true;
     for (uint32_t i = 0; i < n; ++i) {
         const uint64_t count = (uint64_t)((p[i].M + t.bm - 1) / t.bm) * ((p[i].N + t.bn - 1) / t.bn);
         tiles += count;
         work += count * (((uint64_t)p[i].K + kSlab - 1) / kSlab * t.slab_ns + t.rest_ns);
         weight_bound = weight_bound && p[i].M <= 128;
+        lines = lines && p[i].K % 64 == 0 && ((p[i].flags & kStripW) || p[i].N % 64 == 0);
     }
     if (tiles == 0) return 0;
     const uint64_t cus = resident_grid(), grid = cus * t.per_cu, last = tiles % grid;
     uint64_t tenths = tiles / grid * 10;       // of a round
     if (last) tenths += t.per_cu == 1 || last > cus ? 10 : &t == &kTilePair && weight_bound && last * 4 > cus * 3 ? 5 : 6;
     const uint64_t ns = tenths * (work / tiles) / 10;
-    const bool less = &t == &kTile256 ? tiles <= cus : &t == &kTilePair && weight_bound && tiles * 4 > cus * 3;
+    const bool less = &t == &kTile256 ? tiles <= cus : &t == &kTilePair && weight_bound && !lines && tiles * 4 > cus * 3;
     return !cached && less ? ns * 93 / 100 : ns;
 }
 

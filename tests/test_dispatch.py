@@ -358,3 +358,13 @@ def test_float_row_tiles_of_every_launch(record):
     check(record, [(case([M] * jobs, K, N, "f32"), ["grouped_dense_f32" + k for k in names]) for jobs, M, K, N, names in (
         (90, 48, 900, 64, ["<1>", "<1>"]), (65, 60, 1204, 68, ["<2>", "_narrow"]), (128, 48, 388, 128, ["<2>", "<2>"]), (64, 48, 900, 64, ["<1>"]),
     )])
+
+
+def test_whole_lines_from_further_away_take_the_tiles_that_the_cache_gives(record):
+    """128 x 256 tiles that ask for weights once are preferred beyond their time only where rows of an operand begin inside a line."""
+    far = dict(idle=[400 << 20])
+    check(record, [(case([M] * jobs, K, N, strip=strip, **far), ["grouped_dense_bf16_tiled" + kernel]) for jobs, M, K, N, strip, kernel in (
+        (55, 110, 1024, 1280, True, "<128, 128, 2, 2>"), (23, 100, 768, 3072, False, "<128, 128, 2, 2>"), (26, 100, 1536, 2688, True, "<128, 128, 2, 2>"),
+        (63, 90, 1616, 1168, False, "_once<128, 256, 1, 4>"), (46, 80, 2344, 3072, False, "_once<128, 256, 1, 4>"),
+        (56, 110, 2048, 1528, False, "_once<128, 256, 1, 4>"),
+    )])
