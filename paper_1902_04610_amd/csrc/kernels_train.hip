@@ -335,8 +335,8 @@ __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
 // takes leave two workgroups per compute unit, which is no loss (three, with 64 rows at once, are slower).  Tiles of a row of
 // blocks are neighbours, so that what is under way at a time is whole rows of W.  More rows take blocks of 64 x 64, which
 // ask L2 for H and G two thirds as often (launch_grouped_dw_sgd).
-// 8 jobs x 64 rows, 2048 - 2048 - 2048 - 2048 - 1000 (1.17 GB): 191 us, blocks of 64 x 64 205; 8 rows 178 / 192.
-// The weights' traffic alone, in this order and without H and G, 182.
+// 8 jobs x 64 rows, 2048 - 2048 - 2048 - 2048 - 1000 (1.17 GB), kernel trace of twenty steps: 200 - 205 us, blocks of 64 x 64 210 - 212; 8 rows 172 / 184.
+// (55 steps of bench.py: 195 on average, 189 - 203.)
 __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_few_rows(UpdateArgs a)
 {
     dw_mean_loss(a, blockIdx.x);
@@ -345,7 +345,11 @@ __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_few_rows(UpdateArgs a)
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t M = p.M, K = p.K, N = p.N, nt = (N + kUpdN - 1) / kUpdN;
-    const uint32_t k0 = (t / nt) * kUpdFewK, n0 = (t % nt) * kUpdN + 64 * wave;
+    // Workgroups go round-robin to 8 XCDs.  Where a row of blocks ends with a partial one, which would recur on the same XCDs (8 blocks: always on the last),
+    // rows are turned: steps of 4 jobs x 64 rows of 1192 - 1832 - 824 - 1840 - 360 121.6 us (125.2), of 784 - 1592 - 312 48.4 (50.4).  Not where it is nearly
+    // whole: a column of blocks that keeps to its XCD finds its part of G in that L2 (8 jobs, 2048 wide: 323.8 us turned, 316.5).
+    const uint32_t row = t / nt, turn = N % kUpdN - 1u < 192u ? row * min(nt & -nt, 8u) / 8 : 0u;
+    const uint32_t k0 = row * kUpdFewK, n0 = (t + turn) % nt * kUpdN + 64 * wave;
     const uint32_t ncol = n0 + 4 * c, kcol = k0 + 2 * c;
     const bool col_ok = ncol < N;
     // rows and columns outside the matrices: a valid address, and what comes of it is not stored
@@ -522,10 +526,12 @@ hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, bool cached
         fits = fits && p[i].K < kTiledMaxWidth && p[i].N < kTiledMaxWidth;
     }
     if (fits && rows >= kDwTiledRows * weights) return launch_dw_tiled(p, n, stream, launches);
-    // 32 x 64 blocks of few rows / 64 x 64, a step with weights from HBM: 6 jobs of 2048 - 2048 - 1000 at 16 / 72 / 104 / 128 / 150 rows 95 / 113 / 119 /
-    // 123 / 149 us, 103 / 122 / 127 / 128 / 146; from the cache: 8 jobs of 872 - 2032 - 872 - 528 - 128 at 16 / 48 / 72 / 96 / 128 rows 105 / 119 / 132 /
-    // 139 / 148, 108 / 122 / 133 / 135 / 143, 5 jobs of 712 - 1640 - 904 at 48 / 72 / 96 / 128 63 / 68 / 71 / 76, 67 / 72 / 72 / 75.  And not where 64 x 64 blocks
-    // are all under way at once: 2 jobs of 744 - 2040 - 600 - 840 - 136 at 48 / 72 / 96 66 / 69 / 71, 65 / 68 / 68.
+    // 32 x 64 blocks of few rows against 64 x 64, steps of 16 sets of jobs (4 - 8 jobs of two to five layers of 128 - 2048): weights from HBM at 64 / 88 / 104 / 128
+    // rows 0.970 / 0.968 / 0.960 / 0.985 of the time on average, at 150 and 180 rows slower in four sets of five; from the cache at 48 / 64 / 88 rows 0.956 / 0.974 /
+    // 0.972, at 128 slower in two of four.  The mean decides also where rows differ: 7 jobs x 8 rows and one x 500, 1824 - 1480 - 152, 118 / 130 us.
+    // Slower within these limits and known: 8 jobs of 872 - 2032 - 872 - 528 - 128, whose second layer is two whole rounds of 64 x 64 blocks, at 64 and 88 rows from the
+    // cache 124 / 122 and 134 / 131, at 128 rows from HBM 162 / 157; 4 jobs of 680 - 1888 - 1336 - 1952 - 784, by up to 1 %.
+    // And not where 64 x 64 blocks are all under way at once: 2 jobs of 744 - 2040 - 600 - 840 - 136 at 48 / 72 / 96 rows 66 / 69 / 71, 65 / 68 / 68.
     uint64_t tall_tiles = 0;
     for (uint32_t i = 0; i < n; ++i) tall_tiles += (uint64_t)((p[i].K + kUpdK - 1) / kUpdK) * ((p[i].N + kUpdN - 1) / kUpdN);
     const bool few_rows = rows <= (cached ? 88 : 128) * weights && tall_tiles > 2 * resident_grid();

@@ -31,3 +31,9 @@ def test_updates_of_few_rows_with_weights_from_further_away(rows, monkeypatch):
     monkeypatch.setattr(test_gpu_train, "DevicePool", FarPool)
     # rows on either side of 128 have two launches of each forward layer
     run([(DIMS, rows[i % len(rows)], 0.05) for i in range(MANY)], steps=1, seed=31, extra_forward_launches=2 if len(rows) > 1 else 0)
+
+
+@pytest.mark.parametrize("dims, M", [((520, 1800, 776), 33), ((1320, 1288, 392), 80), ((72, 2016, 1024), 64)])
+def test_rows_of_blocks_that_end_with_a_partial_one(dims, M):
+    """8, 4, 6, 2 blocks of 32 x 64 x 4 side by side, the last one a few columns wide or nearly whole."""
+    run([(dims, M, 0.05)] * 4, steps=1, seed=70)
