@@ -123,6 +123,10 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
         u32x4 x[MT];
 #pragma unroll
         for (int t = 0; t < MT; ++t) x[t] = k_ok ? xr[t] : zero;
+        // Narrow tiles drop the weights of k-groups >= K as well (a selector of 0x0c is a zero byte): an infinite one, which a lane reads again there, times
+        // zero would be a NaN.  LDS tiles, whose jobs these take when they are few, fetch zeros for both.
+        const bool drop = !TW && CPL < 8 && !k_ok;
+        const uint32_t even = drop ? 0x0c0c0c0cu : 0x05040100u, odd = drop ? 0x0c0c0c0cu : 0x07060302u;
 #pragma unroll
         for (int i = 0; i < CPL; ++i) {
             // column i of the 8 x CPL block: dword j = (row 2j, row 2j+1)
@@ -132,8 +136,7 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    b[j] = __builtin_amdgcn_perm(w[2 * j + 1][i >> 1], w[2 * j][i >> 1],
-                                                 (i & 1) ? 0x07060302u : 0x05040100u);
+                    b[j] = __builtin_amdgcn_perm(w[2 * j + 1][i >> 1], w[2 * j][i >> 1], (i & 1) ? odd : even);
             }
 #pragma unroll
             for (int t = 0; t < MT; ++t)
