@@ -56,6 +56,33 @@ def forward(case):
     p.close()
     return out
 
+def train(case):
+    up = lambda v: (v + 255) // 256 * 256
+    jobs = []
+    for M, dims in zip(case["rows"], case["dims"]):
+        layers, at = [], 0
+        for k, n in zip(dims, dims[1:]):
+            layers.append((k, n, at, at + up(k * n * 2)))
+            at += up(k * n * 2) + up(k * n * 4)
+        lab = up(M * dims[0] * 2)
+        logits = lab + up(M * 4)
+        loss = logits + up(M * dims[-1] * 4)
+        jobs.append((M, layers, at, lab, logits, loss, loss + 256 + salus.train_work_bytes(M, layers)))
+    p = pool(sum(j[2] + j[6] for j in jobs) + sum(v + 256 for v in case["idle"]) + 4096)
+    for v in case["idle"]:
+        assert p.lane_alloc(v, 256, 0, 0)[0] == salus.OK
+    items = []
+    for M, layers, P, lab, logits, loss, E in jobs:
+        st, job = p.lane_alloc(P, E, 0, 1)
+        assert st == salus.OK
+        items.append(dict(job=job, M=M, lr=0.1, layers=layers, x_off=0, labels_off=lab, logits_off=logits, loss_off=loss, work_off=loss + 256))
+    descs, keep = salus.Pool.make_train_descs(items)
+    take()
+    assert p.grouped_train_step(descs, stream=STREAM) == salus.OK, p.last_error()
+    out = take().decode()
+    p.close()
+    return out
+
 def compaction(case):
     # two blocks above a hole smaller than either: one in-place move; then the same again above the next hole
     p = pool(1 << 30, max_lanes=1)
@@ -97,20 +124,20 @@ print(json.dumps([globals()[c["do"]](c) for c in CASES]))
 
 @pytest.fixture(scope="module")
 def record(tmp_path_factory):
-    """Runs cases in a child process; a list of lines for each, kernel names demangled and without arguments."""
+    """Runs cases in a child process; a list of lines for each, kernel names demangled and, unless asked for, without arguments."""
     if not os.path.exists(build.LIB):
         build.build()
     so = str(tmp_path_factory.mktemp("recorder") / "librecorder.so")
     subprocess.check_call(["gcc", "-O1", "-fPIC", "-shared", "-Wall", "-o", so, os.path.join(HERE, "launch_recorder.c")])
 
-    def run(cases):
+    def run(cases, arguments=False):
         env = dict(os.environ, LD_PRELOAD=":".join(filter(None, [so, os.environ.get("LD_PRELOAD")])), PYTHONPATH=build.ROOT)
         r = subprocess.run([sys.executable, "-c", CHILD], input=json.dumps(cases), cwd=build.ROOT, env=env, stdout=subprocess.PIPE,
                            stderr=subprocess.PIPE, text=True)
         assert r.returncode == 0, r.stderr[-3000:]
         logs = json.loads(r.stdout.splitlines()[-1])
         plain = subprocess.run(["c++filt"], input="----\n".join(logs), stdout=subprocess.PIPE, text=True, check=True).stdout
-        return [re.sub(r"(?:void )?salus::|\(.*?\)", "", p).split("\n") for p in plain.split("----\n")]
+        return [re.sub(r"(?:void )?salus::" + ("" if arguments else r"|\(.*?\)"), "", p).split("\n") for p in plain.split("----\n")]
 
     return run
 
@@ -368,3 +395,58 @@ def test_whole_lines_from_further_away_take_the_tiles_that_the_cache_gives(recor
         (63, 90, 1616, 1168, False, "_once<128, 256, 1, 4>"), (46, 80, 2344, 3072, False, "_once<128, 256, 1, 4>"),
         (56, 110, 2048, 1528, False, "_once<128, 256, 1, 4>"),
     )])
+
+
+def training(rows, dims, far=False):
+    """One training step; rows and dims of every job, dims one for all or one for each."""
+    return dict(do="train", rows=rows, dims=[list(d) for d in (dims if isinstance(dims, list) else [dims] * len(rows))], idle=[240 << 20] if far else [])
+
+
+def test_parity_tests_of_tails_and_of_the_ring_launch_what_they_are_named_after(record):
+    from test_gpu_tiles import RING_GRADIENTS, TAILS
+    check(record, [(case([M - i % 3 for i in range(jobs)], K, N, strip=strip), ["grouped_dense_bf16_tiled<128, 128, 2, 2>"]) for jobs, M, K, N, strip in TAILS])
+    for (jobs, dims, M, columns), log in zip(RING_GRADIENTS, record([training([M] * jobs, dims) for jobs, dims, M, _ in RING_GRADIENTS])):
+        assert kernels(log)[3:-1] == ["grouped_dense_bf16_stream<64, 64, 2, 1, 2, true, 4>" if columns == 64 else
+                                      "grouped_dense_bf16_stream<64, 128, 2, 2, 1, true, 3>"], (dims, M, kernels(log))
+
+
+def test_input_gradients_in_narrow_tiles(record):
+    """32 x 32 register tiles of at most one per compute unit (256 and 260 of them)."""
+    for (rows, dims, kernel), log in zip(*(lambda cs: (cs, record([training(r, d) for r, d, _ in cs])))([
+        ([127], (72, 2048, 264), "narrow<2, true, 2, 8, false>"), ([127], (72, 2056, 264), "stream<64, 64, 2, 1, 2, true, 4>"),
+        ([128] * 4, (40, 512, 72), "narrow<2, true, 2, 8, false>"), ([128] * 4, (40, 520, 72), "stream<64, 64, 2, 1, 2, true, 4>"),
+    ])):
+        assert kernels(log)[3:-1] == ["grouped_dense_bf16_" + kernel], (rows, dims, kernels(log))
+
+
+def test_updates(record):
+    """Blocks of 32 x 64 up to a mean of 88 rows (128 from further away) where more of 64 x 64 are there than run at once, LDS tiles from 192."""
+    from test_gpu_updates import DIMS, MANY
+    few, tall, lds = ("grouped_dw_sgd" + k for k in ("_few_rows", "", "_tiled"))
+    expected = [([m] * MANY, DIMS, far, kernel) for m, far, kernel in (
+        (1, False, few), (88, False, few), (89, False, tall), (191, False, tall), (192, False, lds), (89, True, few), (128, True, few), (129, True, tall))]
+    expected += [([100, 150] * 6, DIMS, True, few), ([100, 158] * 6, DIMS, True, tall), ([8] * 11 + [900], DIMS, False, few),
+                 ([64] * 6, DIMS, False, tall), ([64] * 7, DIMS, False, few),          # 474 and 553 blocks of 64 x 64
+                 ([64] * 4, (1024, 2048), False, tall), ([64] * 4, (1032, 2048), False, few)]      # 512 and 544
+    for (rows, dims, far, kernel), log in zip(expected, record([training(r, d, f) for r, d, f, _ in expected])):
+        assert kernels(log)[-1] == kernel, (rows, dims, far, kernels(log))
+
+
+def test_mean_losses(record):
+    """In the update's launch where every job has a place for its row losses, else by a launch of their own."""
+    expected = [([64], [(40, 64, 64)], True), ([65], [(40, 64)], True), ([17], [(40, 72)], False), ([17], [(72, 72, 72)], False), ([16], [(40, 64, 64)], False),
+                ([64, 16, 17], [(40, 64, 72), (72, 40), (40, 8)], False), ([64, 40], [(40, 64, 64), (40, 64, 72)], True)]
+    for (rows, dims, own), log in zip(expected, record([training(r, d) for r, d, _ in expected])):
+        assert kernels(log).count("loss_mean") == int(own), (rows, dims, kernels(log))
+
+
+def test_arguments_of_eight_and_nine_problems(record):
+    """The kernels of the GPU test, and the shorter arguments up to eight problems where a kernel has them."""
+    from test_gpu_few_problems import EDGE
+    for jobs in (8, 9):
+        cases = [case([M - (i % 3 if M > 3 else 0) for i in range(jobs)], dims[0], list(dims[1:]), dtype) for dtype, M, dims, _ in EDGE]
+        for (dtype, M, dims, names), log in zip(EDGE, record(cases, arguments=True)):
+            found = kernels(log)
+            assert [k.split("(")[0] for k in found] == ["grouped_dense_" + k for k in names], (jobs, dtype, M, dims, found)
+            for k in found:
+                assert ("FewArgs" in k) == (jobs == 8 and "stream" not in k), (jobs, k)

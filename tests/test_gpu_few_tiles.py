@@ -15,7 +15,7 @@ FEW = [
     ([130, 300], 576, 1000, False, "narrow<2, false, 4, 4, false>"),
     ([129, 193], 448, 2056, False, "stream<64, 64, 2, 1, 2, false, 4>"), ([256] * 4, 384, 1024, True, "stream<64, 64, 2, 1, 2, false, 4>"),
     ([200] * 5, 448, 1096, False, "stream<64, 128, 2, 2, 2, false, 3>"), ([512] * 2, 384, 2048, True, "stream<64, 128, 2, 2, 2, false, 3>"),
-    ([268] * 5, 512, 2392, False, "stream<64, 128, 2, 2, 1, false, 3>"),
+    ([268] * 5, 512, 2392, False, "stream<64, 128, 2, 2, 1, false, 3>"), ([200] * 5, 2120, 1288, False, "stream<64, 128, 2, 2, 2, false, 3>"),
 ]
 
 

@@ -144,3 +144,29 @@ def test_float_row_tiles(jobs, M):
     outs, refs, _ = run_jobs(specs, salus.F32)
     for o, r, j in zip(outs, refs, specs):
         assert np.isfinite(o).all() and norm_rel_err(o, r) < TOL_F32, (j, norm_rel_err(o, r))
+
+
+# jobs, rows, K, N, strips; every tile of 128 x 128
+TAILS = [(12, 257, 448, 1032, False), (9, 385, 1096, 520, False), (5, 500, 448, 1288, False), (3, 513, 448, 2688, True)]
+
+
+@pytest.mark.parametrize("jobs, M, K, N, strip", TAILS)
+def test_tails_of_128_by_128_tiles(jobs, M, K, N, strip):
+    """Deeper than the ring, rows and columns that end inside a tile, one or two tiles per compute unit."""
+    specs = [dict(M=M - (i % 3), dims=(K, N), acts=[[GELU, RELU, NONE][i % 3]], strip=strip) for i in range(jobs)]
+    outs, refs, _ = run_jobs(specs, salus.BF16)
+    for o, r, j in zip(outs, refs, specs):
+        assert np.isfinite(o).all() and norm_rel_err(o, r) < TOL_BF16_TIGHT, (j, norm_rel_err(o, r))
+
+
+# jobs, layers, rows, columns of the ring's tiles
+RING_GRADIENTS = [
+    (17, (72, 520, 264), 33, 64), (4, (264, 1032, 136), 70, 64), (4, (136, 1544, 264), 129, 64), (2, (40, 1032, 1000), 300, 64),
+    (30, (72, 1032, 264), 50, 128), (7, (72, 1032, 72), 257, 128),
+]
+
+
+@pytest.mark.parametrize("jobs, dims, M, columns", RING_GRADIENTS)
+def test_input_gradients_of_many_tiles_through_the_ring(jobs, dims, M, columns):
+    """64 x 64 tiles, whose wavefronts store masked half lines, and 64 x 128; depths and widths that end inside a slab, a line and a tile."""
+    run_training([(dims, M, 0.05)] * jobs, steps=1, seed=14)
