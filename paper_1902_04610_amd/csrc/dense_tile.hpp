@@ -132,7 +132,7 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
             // column i of the 8 x CPL block: dword j = (row 2j, row 2j+1)
             u32x4 b;
             if constexpr (TW) {
-                b = w[i];
+                b = NT || k_ok ? w[i] : zero;      // several row tiles: dropped too (the ring, which has such jobs when they are more, fetches zeros)
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
