@@ -242,10 +242,12 @@ static hipError_t launch_narrow_rows(const Problem *p, uint32_t n, bool trans_w,
 // there is at most one per compute unit, 32 x 32 and 32 x 64 through registers, 64 x 64 and 64 x 128 through the ring; and 64 x 128, two
 // per compute unit, where 128 x 128 tiles would be between one and two.  Before (128 x 128 or larger) / now: 1 job x 260 rows, 3200 -> 448, 28.3 / 10.1 us,
 // 1 job x 463 rows, 1024 -> 920, 12.4 / 6.8, 4 jobs x 129 rows, 1536 -> 1024, 16.8 / 9.6, 4 jobs x 429 rows, 1792 -> 1056, 19.8 /
-// 14.3, 6 jobs x 168 rows, 3392 -> 2944, 41.0 / 35.5.  Over 120 such launches, weights from the cache and from HBM, 0.57 of the time before on
-// average and 0.93 at most, within 3 % of the quickest of nine kinds of tiles in all but three.  Tiles beyond one per compute unit: 4 jobs x 619 rows,
-// 320 -> 576, 32 x 64 8.8 us, 64 x 64 6.1.  Shallower layers keep the large tiles that they are tested with (1 job x 256 rows, 320 -> 4096), and so do rounds that hold jobs of 128 rows among larger ones (a
-// launch for each tile height).
+// 14.3, 6 jobs x 168 rows, 3392 -> 2944, 41.0 / 35.5.  Over 95 such launches with weights from the cache 0.57 of the time before on
+// average and 0.93 at most, within 3 % of the quickest of seven kinds of tiles in all but two; over 40 drawn ones 0.58, and 0.63 (0.95 at most) with
+// weights from HBM.  Tiles beyond one per compute unit: 4 jobs x 619 rows, 320 -> 576, 32 x 64 8.8 us, 64 x 64 6.1.
+// Two limits do not lie where the times cross.  Layers of 320 and rounds that hold jobs of 128 rows among larger ones (a launch of large tiles for each height) keep
+// what they had and would gain too, large / these tiles: 1 job x 256 rows, 320 -> 4096, 8.1 / 5.4 us, 5 jobs x 268, 320 -> 2392, 11.2 / 9.2; one job x 128 rows and one
+// x 256, 1024 -> 1024, 25.2 / 6.9, 128, 333 and 600 rows, 512 -> 320, 17.5 / 5.0.
 static bool few_tiles(const Problem *p, uint32_t n)
 {
     uint32_t of_128 = 0;
@@ -463,10 +465,10 @@ hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, 
     // 780, 273 / 208 tiles: 17.3 / 13.8 us, with weights from HBM 24.0 / 18.1; 5 jobs x 86 rows, 1012 -> 936, 14.1 / 12.2 and 17.6 / 13.6; over 32 such
     // layers 0.94 and 0.86 of the time; 4 jobs x 52 rows, 200 -> 976 5.1 / 5.2; more than one 32-row tile per compute unit: 8 jobs x 68 rows, 988 -> 760, 13.7 / 20.2).  Else 64-row tiles while those leave compute units idle,
     // or if they fill whole rounds of the chip and every job has the rows for them (a weight is then read half as often); else
-    // 32-row tiles.  16 / 32 / 64 rows per tile: 12 jobs x 1 - 128 rows, 516 -> 1204 -> 780 -> 388: 50 / 50 / 70 us; one job x
-    // 64 rows, 1024 -> 1024 8.8 / 12.7 / 21.3; 12 jobs x 32 rows, 1204 -> 780 (312 16-row tiles) 16.9 / 15.3, 40 jobs, 256 -> 256 (320) 5.9 / 6.0; 12 jobs x 128
-    // rows, 1536 -> 1536 88 / 80 / 89, 4 jobs 33 / 33 / 32; 40 jobs x 33 rows, 1536 -> 1536 (960 64-row tiles, 3.75 rounds), 32 / 64 rows:
-    // 121 / 113; 40 jobs x 128 rows, 1024 -> 1024 -> 1024 (5 rounds) 213 / 202, 40 rows (2.5) 110 / 122.
+    // 32-row tiles.  16 / 32 / 64 rows per tile: the layers of 12 jobs x 1 - 128 rows, 516 -> 1204 -> 780 -> 388: 10.9 / 15.1 / 19.8,
+    // 17.2 / 15.6 / 26.4 and 6.8 / 10.3 / 17.3 us; one job x 64 rows, 1024 -> 1024 8.0 / 11.9 / 20.4; 12 jobs x 32 rows, 1204 -> 780 (312 16-row tiles) 16.6 / 15.1, 40 jobs, 256 -> 256
+    // (320) 5.6 / 5.6; 12 jobs x 128 rows, 1536 -> 1536 81 / 73 / 86, 4 jobs 27 / 30 / 29 (from HBM 32 / 32 / 30); 40 jobs x 33 rows, 1536 -> 1536 (960 64-row tiles, 3.75
+    // rounds), 32 / 64 rows: 122 / 111; 40 jobs x 128 rows, 1024 -> 1024 (5 rounds) 92 / 93, 40 rows (2.5) 53 / 57.
     uint64_t tiles_16 = 0, tiles_32 = 0, tiles_64 = 0;
     uint32_t max_m = 0;
     for (uint32_t i = 0; i < n; ++i) {

@@ -365,9 +365,11 @@ static bool weights_once(const Problem *p, uint32_t n, bool cached)
 // 128 / 64 x 64: 12 jobs x 64 rows, 2048 -> 1536 26 / 33 us, 20 jobs x 33 - 128 rows, 4096 -> 1024 47 / 56, 16 jobs x 33 -
 // 100 rows, 1536 -> 768 19 / 21, 8 jobs x 64 rows, 2048 -> 2048 with weights from memory 27 / 22.5; 8 jobs x 100 rows: 64 x 128 tiles, training
 // step 386 us against 410 with 64 x 64 (all of these with the k-steps of a 64 x 64 tile shared by two groups of wavefronts).  While
-// there is at most one 64 x 128 tile per compute unit, eight wavefronts instead of four for jobs of 128 rows and more: 4 jobs x 200 rows, 4096 -> 1536,
-// 25.7 / 28.3 us, 7 jobs x 234 rows, 1080 -> 728, 10.2 / 10.7; the same beyond, and not for one row tile whose weights come from HBM (10 jobs x 33 - 60
-// rows, 1992 -> 2536, 27.3 / 26.4).  Rings of six and eight
+// there is at most one 64 x 128 tile per compute unit, eight wavefronts instead of four for jobs of 128 rows and more, four / eight: 3 jobs x 300 rows, 2048 -> 1536,
+// 16.4 / 15.1 us, 4 jobs x 200, 4096 -> 1536, 29.7 / 28.1, 7 jobs x 234, 1088 -> 728, 10.5 / 9.9, 5 jobs x 200, 2120 -> 1288, 17.9 / 17.3; from HBM the same within 3 %
+// (16 jobs x 128 rows, 1024 -> 1024, 15.6 / 16.0), and beyond one tile as well.  Not for one row tile whose weights come from HBM (10 jobs x 33 - 60 rows, 1992 -> 2536, 26.4 / 27.3).
+// Jobs of 65 - 127 rows, which have two row tiles too, keep four: eight are 3 - 8 % quicker there from the cache (nine launches; 7 jobs x 127 rows, 1536 -> 2048, 14.2 /
+// 13.2) and as quick from HBM, so the line could lie at 65.  Rings of six and eight
 // slabs for one 64 x 64 tile per compute unit: step of 8 jobs x 64 rows 313 and 317 us, with four 301.
 hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w, bool in_order, hipStream_t stream, uint64_t *launches)
 {

@@ -335,8 +335,8 @@ __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
 // takes leave two workgroups per compute unit, which is no loss (three, with 64 rows at once, are slower).  Tiles of a row of
 // blocks are neighbours, so that what is under way at a time is whole rows of W.  More rows take blocks of 64 x 64, which
 // ask L2 for H and G two thirds as often (launch_grouped_dw_sgd).
-// 8 jobs x 64 rows, 2048 - 2048 - 2048 - 2048 - 1000 (1.17 GB), kernel trace of twenty steps: 200 - 205 us, blocks of 64 x 64 210 - 212; 8 rows 172 / 184.
-// (55 steps of bench.py: 195 on average, 189 - 203.)
+// 8 jobs x 64 rows, 2048 - 2048 - 2048 - 2048 - 1000 (1.17 GB), kernel trace of twenty steps: 196 us (192 - 201), blocks of 64 x 64 205 (199 - 210), on
+// another card 200 - 205 and 210 - 212; 8 rows 172 / 184.  (55 steps of bench.py: 194 on average, 188 - 203.)
 __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_few_rows(UpdateArgs a)
 {
     dw_mean_loss(a, blockIdx.x);
