@@ -188,7 +188,7 @@ __device__ inline void dense_bf16_tile(const Problem &p, const Tile tile, float 
         for (; i + 2 * D <= mine; i += D) {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                compute(w[d], x[d], ok[d]);
+                compute(w[d], x[d], !NT || ok[d]);      // the last step of a wavefront, the only one that can end past K, is peeled
                 __builtin_amdgcn_sched_barrier(0);
                 load(step(i + d + D), w[d], x[d], ok[d]);
                 __builtin_amdgcn_sched_barrier(0);

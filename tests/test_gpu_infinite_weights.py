@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     [(129, 448, 264), (140, 392, 264)],          # 32 x 32 register tiles: the second job takes what the first one takes
     [(257, 384, 1032), (129, 424, 1032)],        # 32 x 64
     [(33, 40, 136)], [(48, 72, 520)] * 9,        # both, up to 128 rows
+    [(40, 2504, 320)], [(60, 1064, 776)] * 4,    # deep enough for steps in front of the last ones, which drop nothing
 ])
 def test_infinite_weight(shapes):
     """Lanes past the last k-row read the first ones again, times zero."""
@@ -33,7 +34,7 @@ def test_infinite_weight(shapes):
         assert norm_rel_err(Y[:, rest], dense.dense_bf16(X, W, NONE)[:, rest]) < TOL_BF16_TIGHT
 
 
-@pytest.mark.parametrize("dims, M, lr", [((40, 64, 72), 33, 0.5), ((72, 256, 40), 129, 0.25)])
+@pytest.mark.parametrize("dims, M, lr", [((40, 64, 72), 33, 0.5), ((72, 256, 40), 129, 0.25), ((40, 64, 2504), 33, 0.5)])
 def test_infinite_weight_of_the_label(dims, M, lr):
     """Input gradients through 32 x 32 register tiles: an infinite loss whose gradient is an infinity and no NaN."""
     rng = np.random.default_rng(M)
