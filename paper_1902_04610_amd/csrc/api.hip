@@ -470,9 +470,10 @@ static int32_t forward_impl(salus_pool_t *pool, const salus_gemm_desc *descs, ui
             for (uint32_t i = 0; i < n; ++i)
                 if (descs[i].dtype == dt && l < descs[i].n_layers) probs.push_back(problem(i, l));
             if (probs.empty()) continue;
+            const bool cached = pool->core->resident_bytes() <= kCachedBytes;
             hipError_t e = dt == SALUS_BF16
-                               ? launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), false, pool->core->resident_bytes() <= kCachedBytes, s, &pool->gemm_launches)
-                               : launch_grouped_f32(probs.data(), (uint32_t)probs.size(), s, &pool->gemm_launches);
+                               ? launch_grouped_bf16(probs.data(), (uint32_t)probs.size(), false, cached, s, &pool->gemm_launches)
+                               : launch_grouped_f32(probs.data(), (uint32_t)probs.size(), cached, s, &pool->gemm_launches);
             if (e != hipSuccess) return set_error(pool, SALUS_EHIP, hipGetErrorString(e));
         }
     }

@@ -95,7 +95,7 @@ hipError_t launch_grouped_bf16_stream(const Problem *p, uint32_t n, bool trans_w
                                       uint64_t *launches);
 // Calibration: the tiled kernel's multiply without its memory traffic (see kernels_gemm_tiled.hip).
 hipError_t launch_mfma_rate(uint64_t *dev_out, uint32_t slabs, bool lds, hipStream_t stream, uint64_t *flop);
-hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches);
+hipError_t launch_grouped_f32(const Problem *p, uint32_t n, bool cached, hipStream_t stream, uint64_t *launches);
 
 // ---- depth-fused forward ------------------------------------------------------
 // One launch for all layer depths of a round; a tile of depth l waits on a

@@ -115,6 +115,27 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(GroupArgs a) {
 template <int MT>
 __global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(FewArgs a) { rows_f32<MT>(a); }
 
+// The same for 16-row tiles, four k-steps in flight: for wavefronts of five or eight steps, or twelve more, which end with a batch of two where three are in flight, and, if weights come
+// from HBM, of four.  Four / three, from the cache and from HBM: 82 jobs x 2 rows, 276 -> 944, 19.8 / 24.5 and 20.3 / 25.6 us, 30 jobs x 16 rows, 320 -> 1024, 9.1 / 11.6 and 9.6 / 11.9.  Over
+// seven sets of jobs, by steps: 5 0.99 and 0.95 of the time, 8 0.99 and 0.96, 17 1.00 and 0.985, 20 1.00 and 0.98, 4 1.02 and 0.97; 2, 3, 6, 7, 10, 11, 15, 18, 19 1.02 - 1.07 and
+// 1.02 - 1.07, the others 1.00 - 1.02 and 0.99 - 1.01.
+template <typename Args>
+struct FourInFlight : Args {};      // names this variant of the kernel
+template <int MT, typename Args>
+__device__ inline void four_in_flight_f32(const Args &a)
+{
+    static_assert(MT == 1, "16-row tiles");
+    __shared__ float lds[reduce_lds_floats<4>()];
+    Problem p;
+    const Tile tile = find_tile<16, 64>(a, p);
+    dense_f32_tile<1, 4>(p, tile, lds);
+}
+
+template <int MT>
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(FourInFlight<GroupArgs> a) { four_in_flight_f32<MT>(a); }
+template <int MT>
+__global__ __launch_bounds__(kGemmThreads) void grouped_dense_f32(FourInFlight<FewArgs> a) { four_in_flight_f32<MT>(a); }
+
 // 16 columns and 16 rows per workgroup, for launches of few tiles: a launch lasts as long as one wavefront's chain of
 // multiplies and loads over its quarter of K, and this tile has a quarter of the multiplies.  16 columns / 64, 4 jobs x 16 rows, 1536 ->
 // 1000: 6.7 / 10.7 us, 1024 -> 1000 5.5 / 8.0, 384 -> 1000 4.1 / 5.2 on the device, 2 jobs x 8 rows, 256 -> 256 3.4 / 4.4.
@@ -449,10 +470,16 @@ hipError_t launch_grouped_bf16(const Problem *p, uint32_t n, bool trans_w, bool 
     return hipSuccess;
 }
 
-hipError_t launch_grouped_f32(const Problem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
+hipError_t launch_grouped_f32(const Problem *p, uint32_t n, bool cached, hipStream_t stream, uint64_t *launches)
 {
     auto launch = [&](int mt, const auto &a, uint32_t tiles) {
-        if (mt == 1)
+        const bool four = std::all_of(a.p, a.p + a.n, [&](const Problem &q) {
+            const uint32_t steps = (q.K + 63) / 64;      // of 16 k-rows, a wavefront's share of them
+            return steps % 12 == 5 || steps % 12 == 8 || (steps == 4 && !cached);
+        });
+        if (mt == 1 && four)
+            hipLaunchKernelGGL(grouped_dense_f32<1>, dim3(tiles), dim3(kGemmThreads), 0, stream, FourInFlight<std::decay_t<decltype(a)>>{a});
+        else if (mt == 1)
             hipLaunchKernelGGL(grouped_dense_f32<1>, dim3(tiles), dim3(kGemmThreads), 0, stream, a);
         else if (mt == 2)
             hipLaunchKernelGGL(grouped_dense_f32<2>, dim3(tiles), dim3(kGemmThreads), 0, stream, a);

@@ -387,6 +387,19 @@ def test_float_row_tiles_of_every_launch(record):
     )])
 
 
+def test_float_layers_with_four_steps_in_flight(record):
+    """16-row tiles of layers 257 - 320, 449 - 512 and 768 more deep, from further away 193 - 256 too, in every launch for itself."""
+    far = [240 << 20]
+    expected = [(12, 16, 256, 1204, [], 0), (12, 16, 260, 1204, [], 1), (12, 16, 320, 1204, [], 1), (12, 16, 324, 1204, [], 0), (12, 16, 448, 1204, [], 0),
+                (12, 16, 452, 1204, [], 1), (12, 16, 512, 1204, [], 1), (12, 16, 516, 1204, [], 0), (12, 16, 192, 1204, far, 0), (12, 16, 196, 1204, far, 1),
+                (12, 16, 256, 1204, far, 1), (12, 16, 196, 1204, [], 0), (12, 16, 384, 1204, far, 0), (82, 2, 276, 944, [], 2), (5, 16, 276, 1500, [], 1),
+                (12, 30, 276, 780, [], 0), (12, 16, 1024, 1204, [], 0), (12, 16, 1028, 1204, [], 1), (12, 16, 1280, 1204, [], 1), (12, 16, 1284, 1204, far, 0)]
+    logs = record([case([M] * jobs, K, N, "f32", idle=idle) for jobs, M, K, N, idle, _ in expected], arguments=True)
+    for (jobs, M, K, N, idle, count), log in zip(expected, logs):
+        found = kernels(log)
+        assert sum("FourInFlight" in k for k in found) == count and len(found) == max(count, 1), (jobs, M, K, N, found)
+
+
 def test_whole_lines_from_further_away_take_the_tiles_that_the_cache_gives(record):
     """128 x 256 tiles that ask for weights once are preferred beyond their time only where rows of an operand begin inside a line."""
     far = dict(idle=[400 << 20])

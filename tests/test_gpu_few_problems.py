@@ -16,7 +16,7 @@ EDGE = [
     ("bf16", 36, (264, 136, 1032), ["bf16_narrow<2, false, 2, 8, false>", "bf16_stream<64, 64, 2, 1, 2, false, 4>"]),
     ("bf16", 140, (448, 136), ["bf16_narrow<2, false, 2, 8, false>"]), ("bf16", 64, (264, 776), ["bf16_narrow<2, false, 4, 4, false>"]),
     ("f32", 8, (260, 132), ["f32_narrow"]), ("f32", 30, (132, 900), ["f32<1>"]), ("f32", 60, (516, 516), ["f32<2>"]),
-    ("f32", 129, (132, 1028), ["f32<4>"]),
+    ("f32", 129, (132, 1028), ["f32<4>"]), ("f32", 12, (276, 1204), ["f32<1>"]),
 ]
 
 

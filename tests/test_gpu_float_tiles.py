@@ -19,3 +19,13 @@ def test_float_rows_on_both_sides(rows, dims):
     for o, r, f, j in zip(outs, refs, fused, specs):
         assert np.isfinite(o).all() and norm_rel_err(o, r) < TOL_F32, (j, norm_rel_err(o, r))
         assert np.array_equal(o.view(np.uint32), f.view(np.uint32)), j
+
+
+@pytest.mark.parametrize("rows, dims", [([16] * 12, (260, 1204)), ([1, 15, 16, 17] * 5, (320, 700)), ([2] * 82, (276, 944)), ([7, 16] * 6, (300, 1204, 512, 12)), ([9] * 30, (452, 516)), ([5] * 16, (1068, 1380, 8))])
+def test_float_layers_with_four_steps_in_flight(rows, dims):
+    specs = [dict(M=m, dims=dims, acts=[GELU] * (len(dims) - 2) + [NONE]) for m in rows]
+    outs, refs, _ = run_jobs(specs, salus.F32)
+    fused, _, _ = run_jobs(specs, salus.F32, fuse=True)
+    for o, r, f, j in zip(outs, refs, fused, specs):
+        assert np.isfinite(o).all() and norm_rel_err(o, r) < TOL_F32, (j, norm_rel_err(o, r))
+        assert np.array_equal(o.view(np.uint32), f.view(np.uint32)), j
