@@ -668,7 +668,7 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
     // second stream, or in the same launch, beside the next input gradient - under
     // the update's HBM stream the latency-bound input gradient takes 3 - 4 times as
     // long as alone and the launch waits for it.)
-    std::vector<UpdateProblem> ups;
+    std::vector<UpdateWithLoss> ups;
     for (uint32_t back = 0; back < depth && e == hipSuccess; ++back) {
         probs.clear();
         for (uint32_t i = 0; i < n; ++i) {
@@ -689,7 +689,7 @@ int32_t salus_grouped_train_step(salus_pool_t *pool, const salus_train_desc *des
                 pr.flags = kOutBf16 | kMaskPositive;
                 probs.push_back(pr);
             }
-            UpdateProblem up{};
+            UpdateWithLoss up{};
             up.H = res[i].lane + res[i].h_off[l];
             up.G = g_cur;
             up.Wm = (float *)(res[i].persist + L.wm_off);

@@ -138,12 +138,14 @@ struct UpdateProblem {
     void *Wb;                // K x N bf16 working copy, rewritten
     uint32_t M, K, N;
     float lr;
+};
+struct UpdateWithLoss : UpdateProblem {
     float *loss;             // if not null: becomes the mean of the M floats behind G
 };
 // mean_later: the mean losses of jobs of more than kLossRows rows are left to launch_grouped_dw_sgd.
 hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, bool mean_later, hipStream_t stream, uint64_t *launches);
 // Wm <- Wm - lr * (H^T . G), Wb <- bf16(Wm), all problems in one launch.  cached: as for launch_grouped_bf16.
-hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, bool cached, hipStream_t stream,
+hipError_t launch_grouped_dw_sgd(const UpdateWithLoss *p, uint32_t n, bool cached, hipStream_t stream,
                                  uint64_t *launches);
 
 }  // namespace salus

@@ -216,8 +216,10 @@ hipError_t launch_softmax_xent(const LossProblem *p, uint32_t n, bool mean_later
 struct UpdateArgs {
     uint32_t n;
     uint32_t tiles;      // all tiles of the launch
+    uint32_t losses;     // n if a mean loss is to be taken, else 0
     uint32_t first[kMaxProblems];      // first tile of update i; kNoTile from n on
     UpdateProblem p[kMaxProblems];
+    float *loss[kMaxProblems];
 };
 static_assert(sizeof(UpdateArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
@@ -226,12 +228,23 @@ constexpr int kUpdSteps = 4;                // steps of 32 rows that a tile of f
 constexpr double kDwTiledRows = 192;
 constexpr int kDwTile = 128;                // tile of the many-row kernel
 
-// The mean loss that belongs to update `i` of the launch, if one does: its first wavefront's work in front of its tile.
+// The mean loss that belongs to update `i` of the launch, if one does: a workgroup's first wavefront's work beside its tile.  Behind it, if that is the only
+// one: in front the look for a loss alone was 0.25 us of a launch of few blocks (6.1 us), also where no job has one.
 __device__ inline void dw_mean_loss(const UpdateArgs &a, uint32_t i)
 {
-    if (i >= a.n || threadIdx.x >= 64) return;
+    if (i >= a.losses || threadIdx.x >= 64) return;
     const UpdateProblem &p = a.p[i];
-    if (p.loss) mean_of_rows((const float *)((const uint16_t *)p.G + (size_t)p.M * p.N), p.M, p.loss);
+    if (a.loss[i]) mean_of_rows((const float *)((const uint16_t *)p.G + (size_t)p.M * p.N), p.M, a.loss[i]);
+}
+
+template <typename Tiles>
+static uint64_t fill_updates(UpdateArgs &a, const UpdateWithLoss *p, uint32_t n, Tiles tiles)
+{
+    for (uint32_t i = 0; i < n; ++i) {
+        a.loss[i] = p[i].loss;
+        if (p[i].loss) a.losses = n;
+    }
+    return fill_group(a, p, n, tiles);
 }
 
 // One step of 32 rows: a lane's blocks h and d into operands, and their products.
@@ -299,7 +312,6 @@ __device__ inline void dw_store(const UpdateProblem &p, uint32_t first, uint32_t
 // Blocks of 64 x 64.  The master-weight loads are issued before the MFMA phase and complete underneath it.
 __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
 {
-    dw_mean_loss(a, blockIdx.x);
     UpdateProblem p;
     const uint32_t t = find_owner(a.first, a.p, blockIdx.x, p);
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
@@ -328,6 +340,7 @@ __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
         dw_multiply<4>(h, d, acc);
     }
     dw_store<4>(p, k0 + 16 * g, ncol, wm, acc);
+    dw_mean_loss(a, blockIdx.x);
 }
 
 // Few rows: blocks of 32 x 64.  What a block waits for is requested at once, up to 128 rows of H and G and behind them its master weights, which
@@ -339,7 +352,6 @@ __global__ __launch_bounds__(256) void grouped_dw_sgd(UpdateArgs a)
 // another card 200 - 205 and 210 - 212; 8 rows 172 / 184.  (55 steps of bench.py: 194 on average, 188 - 203.)
 __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_few_rows(UpdateArgs a)
 {
-    dw_mean_loss(a, blockIdx.x);
     UpdateProblem p;
     const uint32_t t = find_owner(a.first, a.p, blockIdx.x, p);
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
@@ -397,6 +409,7 @@ __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_few_rows(UpdateArgs a)
             if (m0 + 32u * s < M) multiply(s, m0 + 32u * s);
     }
     dw_store<2>(p, k0 + 8 * g, ncol, wm, acc);
+    dw_mean_loss(a, blockIdx.x);
 }
 
 // Many rows per job (the contraction is long): the product goes through the LDS tiles of tile_mfma.hpp, both operands
@@ -494,11 +507,11 @@ __global__ __launch_bounds__(256, 2) void grouped_dw_sgd_tiled(UpdateArgs a)
     T::run(walk, smem);
 }
 
-static hipError_t launch_dw_tiled(const UpdateProblem *p, uint32_t n, hipStream_t stream, uint64_t *launches)
+static hipError_t launch_dw_tiled(const UpdateWithLoss *p, uint32_t n, hipStream_t stream, uint64_t *launches)
 {
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         UpdateArgs a{};
-        const uint64_t tiles = fill_group(a, p + at, std::min(kMaxProblems, n - at), [](const UpdateProblem &q) {
+        const uint64_t tiles = fill_updates(a, p + at, std::min(kMaxProblems, n - at), [](const UpdateProblem &q) {
             return (uint64_t)((q.K + kDwTile - 1) / kDwTile) * ((q.N + kDwTile - 1) / kDwTile);
         });
         if (tiles == 0) continue;
@@ -511,7 +524,7 @@ static hipError_t launch_dw_tiled(const UpdateProblem *p, uint32_t n, hipStream_
     return hipSuccess;
 }
 
-hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, bool cached, hipStream_t stream,
+hipError_t launch_grouped_dw_sgd(const UpdateWithLoss *p, uint32_t n, bool cached, hipStream_t stream,
                                  uint64_t *launches)
 {
     // One kernel for all updates of a step (two would each ramp up and drain): the tiled one if a weight's rows, on
@@ -538,7 +551,7 @@ hipError_t launch_grouped_dw_sgd(const UpdateProblem *p, uint32_t n, bool cached
     const uint32_t tile_k = few_rows ? kUpdFewK : kUpdK;
     for (uint32_t at = 0; at < n; at += kMaxProblems) {
         UpdateArgs a{};
-        const uint64_t tiles = fill_group(a, p + at, std::min(kMaxProblems, n - at), [&](const UpdateProblem &q) {
+        const uint64_t tiles = fill_updates(a, p + at, std::min(kMaxProblems, n - at), [&](const UpdateProblem &q) {
             return (uint64_t)((q.K + tile_k - 1) / tile_k) * ((q.N + kUpdN - 1) / kUpdN);
         });
         if (tiles == 0) continue;
